@@ -400,12 +400,11 @@ __global__ __launch_bounds__(NT) void k_mid(MidArgs a) {
 // Forward "hi" pass + main stage, worker side (Alg. 3: R = RHT(x) finished; clamp to [-M, M];
 // stochastic quantization onto the table's values (Sec. 4.1); Z = T^-1[Y] (Alg. 2); bit-pack).
 //
-// Per coordinate, in binary32:  v = h * c;  x' = med(v, -M, M);  y16 = (x' + M) * (scale * 2^16);
-// k = floor(y16 / 2^16);  (lo, wd, z0) = LUT[k];  t16 = y16 - lo * 2^16;
-// up iff (half + 1/2) * wd < t16  (one fused multiply-add, then compare);  z = z0 + up.
-// The top table entry carries wd = 255 so that it can never round up.  When 1/sqrt(B) is a power of
-// two (even log2 B) the multiplication by c is folded into M and the scale: that only moves exponents,
-// so every rounding stays where it was.
+// Per coordinate, in binary32:  v = h * c;  x' = med(v, m, M);  y = (x' - m) * scale;  k = floor(y);
+// (lo, wd, z0) = LUT[k];  t = y - lo;  up iff u * wd < t with u = (half + 1/2) / 2^16;  z = z0 + up.
+// Everything is carried scaled by 2^24, which moves exponents only: the cell is then the top byte of the converted
+// integer, and the conversion saturates, so the clamp itself costs nothing (see quantize8).  When 1/sqrt(B) is a power
+// of two (even log2 B) the multiplication by c is folded into m and the scale: again only exponents move.
 // ---------------------------------------------------------------------------------------------
 struct QuantArgs {
   const float* x;          // half-rotated vectors, d floats per worker of the launch (grid.y = worker)
@@ -423,28 +422,46 @@ struct QuantArgs {
 };
 
 struct QuantScalars {
-  float M, lo, sc16, c;  // range [lo, M]; for even log2 B they and sc16 are pre-scaled by c, and c is unused
+  float M, lo, sc, c;    // range [lo, M]; fast form: scale * 2^24, and lo, M and the scale folded with c where it is a power of two
 };
 
-// WIDE = false: the fast form, on the grid position scaled by 2^16 (sc16 = scale * 2^16, range optionally folded
-// with 1/sqrt(B)).  WIDE = true: ranges so narrow that scale * 2^16 would overflow binary32: the operations exactly
-// as listed above (sc16 then holds the plain scale, the range is not folded), and the comparison scales t instead.
+constexpr float GRID_SCALE = 0x1p24f;
+
+// float -> uint32, towards zero; below 0 gives 0 and above 2^32 - 1 gives 2^32 - 1 (a C++ cast leaves those undefined)
+__device__ __forceinline__ uint32_t cvt_u32_sat(float y) {
+  uint32_t k;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(k) : "v"(y));
+  return k;
+}
+
+// CAREFUL = false: no clamp.  Below m the position is negative, converts to cell 0 and never rounds up.  Above M it lies
+// in or beyond the last cell: there quant_scalars has made sure that M itself, hence everything above it, ends in the
+// top index for every draw.  Saves one of eleven instructions per coordinate: the kernels that end in the quantizer are
+// bound by vector issue.
+// CAREFUL = true: the operations exactly as listed above, unscaled; for ranges so narrow that the scaled form would
+// leave binary32, or so fine (g above 127) that a clamped coordinate may round down from the last cell.
 // Both forms take the same decisions: multiplying by a power of two commutes with every rounding involved.
-template <bool CFOLD, bool WIDE = false>
+template <bool MULC, bool CAREFUL = false>
 __device__ __forceinline__ void quantize8(const float (&hv)[8], const uint4 rnd, const QuantScalars s,
                                           const uint4* lut, uint32_t (&z)[8]) {
   const uint32_t rw[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const float v = (CFOLD && !WIDE) ? hv[e] : hv[e] * s.c;
-    const float xc = __builtin_amdgcn_fmed3f(v, s.lo, s.M);
-    const float y16 = (xc - s.lo) * s.sc16;          // WIDE: the grid position y itself
-    const uint32_t ki = (uint32_t)y16;
-    const uint4 ent = lut[(WIDE ? ki : ki >> 16) & 255u];
-    const float t16 = WIDE ? (y16 - __uint_as_float(ent.x) * 0x1p-16f) * 65536.0f : y16 - __uint_as_float(ent.x);
+    const float v = MULC ? hv[e] * s.c : hv[e];
+    float y;
+    uint4 ent;
+    if constexpr (CAREFUL) {
+      const float yu = (__builtin_amdgcn_fmed3f(v, s.lo, s.M) - s.lo) * s.sc;
+      ent = lut[cvt_u32_sat(yu) & 255u];
+      y = (yu - __uint_as_float(ent.x) * (1.0f / GRID_SCALE)) * GRID_SCALE;
+    } else {
+      y = (v - s.lo) * s.sc;
+      ent = lut[cvt_u32_sat(y) >> 24];
+      y -= __uint_as_float(ent.x);
+    }
     const float hf = (float)((e & 1) ? (rw[e >> 1] >> 16) : (rw[e >> 1] & 0xFFFFu));
     const float prod = __builtin_fmaf(hf, __uint_as_float(ent.y), __uint_as_float(ent.z));
-    z[e] = ent.w + (prod < t16 ? 1u : 0u);
+    z[e] = ent.w + (prod < y ? 1u : 0u);
   }
 }
 
@@ -473,11 +490,14 @@ __device__ __forceinline__ void store_packed8(uint8_t* packed, uint64_t j, uint3
   }
 }
 
-// LDS entry of grid cell k: {lo * 2^16, wd, wd / 2 (all binary32, exact), z0}
+// LDS entry of grid cell k: {lo * 2^24, wd * 2^8, wd * 2^7 (all binary32, exact), z0}; the comparison is
+// (half + 1/2) * wd * 2^8 < y - lo * 2^24.  The top value (wd = 255 in the argument) never rounds up.
 __device__ __forceinline__ uint4 quant_lut_entry(uint32_t ent) {
-  const float wd = (float)((ent >> 8) & 255u);
-  return make_uint4(__float_as_uint((float)(ent & 255u) * 65536.0f), __float_as_uint(wd), __float_as_uint(0.5f * wd),
-                    ent >> 16);
+  const uint32_t wd = (ent >> 8) & 255u;
+  const float w = wd == 255u && (ent & 255u) ? 0.f : (float)wd;
+  const float half = wd == 255u && (ent & 255u) ? __builtin_inff() : 0.5f * (float)wd;
+  return make_uint4(__float_as_uint((float)(ent & 255u) * GRID_SCALE), __float_as_uint(w * 256.0f),
+                    __float_as_uint(half * 256.0f), ent >> 16);
 }
 
 template <class A>
@@ -492,17 +512,21 @@ __device__ __forceinline__ float scale_of(float M, float m, uint32_t g) {
   return sc <= 3.4028234663852886e38f ? sc : 0.f;     // also false for NaN
 }
 
-// scale * 2^16 (and the fold with 1/sqrt(B)) stay finite below this
-constexpr float WIDE_SCALE = 0x1p110f;
+// scale * 2^24 (and the fold with 1/sqrt(B)) stay finite below this
+constexpr float WIDE_SCALE = 0x1p102f;
 
-// Per-block constants of the quantizer: the fast form whenever scale * 2^16 is representable.
-__device__ __forceinline__ QuantScalars quant_scalars(float M, float m, uint32_t g, float c, bool cfold, bool& wide) {
+// Per-block constants of the quantizer and which form it takes.  `last`: the table's last cell, lut[g - 1].
+__device__ __forceinline__ QuantScalars quant_scalars(float M, float m, uint32_t g, uint32_t last, float c, bool cfold,
+                                                      bool& careful) {
   const float sc = scale_of(M, m, g);
-  wide = sc >= WIDE_SCALE;
-  if (wide) return QuantScalars{M, m, sc, c};
-  const float sc16 = sc * 65536.0f;
-  if (cfold) return QuantScalars{M * (1.0f / c), m * (1.0f / c), sc16 * c, c};
-  return QuantScalars{M, m, sc16, c};
+  QuantScalars q{M, m, sc * GRID_SCALE, c};
+  if (cfold) q = QuantScalars{M * (1.0f / c), m * (1.0f / c), sc * GRID_SCALE * c, c};
+  // what a clamped coordinate comes to, and whether the largest draw still lets it reach the top index
+  const float top = (q.M - q.lo) * q.sc, wd = (float)((last >> 8) & 255u) * 256.0f;
+  const bool ends = top >= (float)g * GRID_SCALE ||
+                    __builtin_fmaf(65535.0f, wd, 0.5f * wd) < top - (float)(last & 255u) * GRID_SCALE;
+  careful = sc >= WIDE_SCALE || !ends;
+  return careful ? QuantScalars{M, m, sc, c} : q;
 }
 
 __device__ __forceinline__ float lower_of(const float* range_m, uint64_t blk, float M) {
@@ -513,7 +537,7 @@ struct alignas(16) SmemQuant {
   float lds[TILE];
   uint32_t lut[256][4];   // uint4 entries
   float sQ[8][4];         // QuantScalars
-  int sWide[8];
+  int sCare[8];           // the block takes the careful form
 };
 
 // One tile of the pass: tile index `tile` of the launch's vector `wk`, whose half-rotated image starts at xw.
@@ -523,7 +547,7 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
   float* const lds = sm.lds;
   uint4* const lut = reinterpret_cast<uint4*>(sm.lut);
   QuantScalars* const sQ = reinterpret_cast<QuantScalars*>(sm.sQ);
-  int* const sWide = sm.sWide;
+  int* const sCare = sm.sCare;
 
   const int t = threadIdx.x;
   uint8_t* const packed = static_cast<uint8_t*>(const_cast<void*>(a.packed.p[wk]));
@@ -537,9 +561,9 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
     if (t == 0) {                               // the whole tile lies in one block
       const uint64_t blk = g.base >> a.L;
       const float M = a.range_M[blk], m = lower_of(a.range_m, blk, M);
-      bool wide;
-      sQ[0] = quant_scalars(M, m, a.g, a.c, CFOLD, wide);
-      sWide[0] = wide;
+      bool careful;
+      sQ[0] = quant_scalars(M, m, a.g, a.lut[a.g - 1], a.c, CFOLD, careful);
+      sCare[0] = careful;
     }
     hi_r0_to_lds<R>(x, lds, t);
     hi_round1<R>(lds, t);
@@ -547,7 +571,7 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
     float v[2][8];
     hi_back<R>(lds, t, idx, v);
     const QuantScalars s = sQ[0];
-    const bool wide = sWide[0] != 0;            // uniform over the workgroup
+    const bool careful = __builtin_amdgcn_readfirstlane(sCare[0]) != 0;   // uniform over the workgroup
     const uint64_t q0 = (a.j0 + g.base) >> 3;   // tiles start on multiples of 64 coordinates
     uint8_t* const pk0 = packed + (g.base >> 3) * a.b;
 #pragma unroll
@@ -556,8 +580,8 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
       const uint64_t q = q0 + (o >> 3);
       const uint4 rnd = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, stream, a.k0, a.k1);
       uint32_t z[8];
-      if (!wide) quantize8<CFOLD>(v[h], rnd, s, lut, z);
-      else quantize8<CFOLD, true>(v[h], rnd, s, lut, z);
+      if (!careful) quantize8<!CFOLD>(v[h], rnd, s, lut, z);
+      else quantize8<true, true>(v[h], rnd, s, lut, z);
       store_packed8(pk0, o, a.b, z);
     }
   } else {
@@ -569,9 +593,9 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
       const uint64_t blk = (g.base >> a.L) + t;
       float M = 0.f, m = 0.f;
       if (blk < (a.d >> a.L)) { M = a.range_M[blk]; m = lower_of(a.range_m, blk, M); }
-      bool wide;
-      sQ[t] = quant_scalars(M, m, a.g, a.c, false, wide);
-      sWide[t] = wide;
+      bool careful;
+      sQ[t] = quant_scalars(M, m, a.g, a.lut[a.g - 1], a.c, false, careful);
+      sCare[t] = careful;
     }
     hi_load_to_lds<R>(xw, g, a.d, lds, t);
     lds_stages<LOG_TILE - R, LOG_TILE, false, PLAIN>(lds, t, [](int, int, float) {});
@@ -589,8 +613,8 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
       const uint64_t q = (a.j0 + j) >> 3;
       const uint4 rnd = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, stream, a.k0, a.k1);
       uint32_t z[8];
-      if (!sWide[bt]) quantize8<false>(hv, rnd, s, lut, z);
-      else quantize8<false, true>(hv, rnd, s, lut, z);
+      if (!sCare[bt]) quantize8<true>(hv, rnd, s, lut, z);
+      else quantize8<true, true>(hv, rnd, s, lut, z);
       store_packed8(packed, j, a.b, z);
     }
   }

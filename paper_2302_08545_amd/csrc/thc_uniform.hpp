@@ -207,7 +207,7 @@ template <bool BF16>
 __global__ __launch_bounds__(NT) void k_uniform_quant(const UQuantArgs a) {
   __shared__ uint4 lut[256];
   __shared__ QuantScalars sQ[8];
-  __shared__ int sWide[8];
+  __shared__ int sCare[8];
   __shared__ float sStep[8];
   const int t = threadIdx.x;
   const uint64_t off = (uint64_t)xcd_tile(blockIdx.x, gridDim.x) << LOG_TILE;
@@ -219,9 +219,9 @@ __global__ __launch_bounds__(NT) void k_uniform_quant(const UQuantArgs a) {
     const uint64_t blk = (off >> a.L) + t;
     float M = 0.f, m = 0.f;
     if (blk < (a.d >> a.L)) { M = a.range_M[blk]; m = lower_of(a.range_m, blk, M); }
-    bool wide;
-    sQ[t] = quant_scalars(M, m, a.g, 1.0f, false, wide);
-    sWide[t] = wide;
+    bool careful;
+    sQ[t] = quant_scalars(M, m, a.g, a.lut[a.g - 1], 1.0f, false, careful);
+    sCare[t] = careful;
     sStep[t] = (float)(((double)M - (double)m) / (double)a.g);
   }
   __syncthreads();
@@ -250,8 +250,8 @@ __global__ __launch_bounds__(NT) void k_uniform_quant(const UQuantArgs a) {
     const uint64_t q = (a.j0 + j) >> 3;
     const uint4 rnd = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, a.worker, a.k0, a.k1);
     uint32_t z[8];
-    if (!sWide[bt]) quantize8<true>(hv, rnd, s, lut, z);   // no scaling: the values are final (c = 1)
-    else quantize8<true, true>(hv, rnd, s, lut, z);
+    if (!sCare[bt]) quantize8<false>(hv, rnd, s, lut, z);   // no scaling: the values are final (c = 1)
+    else quantize8<false, true>(hv, rnd, s, lut, z);
     store_packed8(a.packed, j, a.b, z);
     if (a.ef_update) {
       const float step = sStep[bt], lo = s.lo;
