@@ -243,9 +243,9 @@ void launch_fwd_lo(const Plan& pl, const FwdLoArgs& a, bool bf16, bool ef, bool 
   }
 }
 
-void launch_range(const Plan& pl, const RangeArgs& r, hipStream_t s) {
-  const uint64_t K = r.d >> pl.L;
-  if (pl.L - pl.L1 <= 3) k_range_small<<<dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s>>>(r);
+void launch_range(const RangeArgs& r, hipStream_t s) {
+  const uint64_t K = r.d >> r.L;
+  if (r.L - r.L1 <= 3) k_range_small<<<dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s>>>(r);
   else k_range<<<dim3((unsigned)K), dim3(RANGE_NT), 0, s>>>(r);
 }
 
@@ -262,6 +262,89 @@ void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t 
   }
 }
 
+// ---- passes on tiles of 2^15 coordinates (thc_big.hpp) ------------------------------------------------------------
+// Blocks of 2^23 to 2^25: always (two passes instead of three: 1.16x at one block of one vector, 1.5x at 16 of them).
+// 2^22: both tile sizes take two passes, and the larger one pays once its few large tiles fill the chip many times over
+// (rounds of 256 to 3072 tiles: 0.91x to 1.05x; of 16384: 1.12x).
+constexpr uint64_t BIG_MIN_TILES_22 = 8192;
+
+bool use_big(const Plan& pl, uint64_t d, uint32_t W) {   // W vectors of d coordinates in the call
+  if (pl.L == 22) return W * (d >> LOG_BIG) >= BIG_MIN_TILES_22;
+  return pl.L > 22 && pl.L <= LOG_BIG + 10;
+}
+
+template <template <int> class Launcher, class... A>
+void dispatch_big(int r, A&&... args) {
+  switch (r) {
+    case 7: Launcher<7>::run(args...); break;
+    case 8: Launcher<8>::run(args...); break;
+    case 9: Launcher<9>::run(args...); break;
+    default: Launcher<10>::run(args...); break;
+  }
+}
+
+template <bool BF16, bool EF>
+void launch_big_lo_k(const BigLoArgs& a, bool split, bool norm_only, dim3 grid, hipStream_t s) {
+  if (norm_only) {
+    if (split) k_big_lo<BF16, EF, true, true><<<grid, dim3(NT), 0, s>>>(a);
+    else k_big_lo<BF16, EF, false, true><<<grid, dim3(NT), 0, s>>>(a);
+  } else {
+    if (split) k_big_lo<BF16, EF, true, false><<<grid, dim3(NT), 0, s>>>(a);
+    else k_big_lo<BF16, EF, false, false><<<grid, dim3(NT), 0, s>>>(a);
+  }
+}
+
+void launch_big_lo(const Plan& pl, const BigLoArgs& a, bool bf16, bool ef, bool norm_only, uint32_t W, hipStream_t s) {
+  const dim3 grid((unsigned)(a.d >> LOG_BIG), W);
+  if (bf16) {
+    if (ef) launch_big_lo_k<true, true>(a, pl.split, norm_only, grid, s);
+    else launch_big_lo_k<true, false>(a, pl.split, norm_only, grid, s);
+  } else {
+    if (ef) launch_big_lo_k<false, true>(a, pl.split, norm_only, grid, s);
+    else launch_big_lo_k<false, false>(a, pl.split, norm_only, grid, s);
+  }
+}
+
+template <int R> struct LaunchBigQuant {
+  static void run(const BigQuantArgs& a, bool split, uint32_t W, hipStream_t s) {
+    const dim3 grid((unsigned)(a.d >> LOG_BIG), W);
+    if (split) k_big_quant<R, true><<<grid, dim3(NT), 0, s>>>(a);
+    else k_big_quant<R, false><<<grid, dim3(NT), 0, s>>>(a);
+  }
+};
+
+template <int R> struct LaunchBigInvHi {
+  template <bool XO>
+  static void go(const BigInvHiArgs& a, int mode, dim3 grid, hipStream_t s) {
+    if (mode == 0) k_big_inv_hi<R, XO, 0><<<grid, dim3(NT), 0, s>>>(a);
+    else if (mode == 1) k_big_inv_hi<R, XO, 1><<<grid, dim3(NT), 0, s>>>(a);
+    else k_big_inv_hi<R, XO, 2><<<grid, dim3(NT), 0, s>>>(a);
+  }
+  static void run(const BigInvHiArgs& a, bool split, int mode, uint32_t W, hipStream_t s) {
+    const dim3 grid((unsigned)(a.d >> LOG_BIG), W);
+    if (split) go<true>(a, mode, grid, s);
+    else go<false>(a, mode, grid, s);
+  }
+};
+
+template <int SB, bool TABLE>
+void launch_big_inv_lo_k(const BigInvLoArgs& a, bool split, dim3 grid, hipStream_t s) {
+  if (split) k_big_inv_lo<SB, TABLE, true><<<grid, dim3(NT), 0, s>>>(a);
+  else k_big_inv_lo<SB, TABLE, false><<<grid, dim3(NT), 0, s>>>(a);
+}
+
+void launch_big_inv_lo(const Plan& pl, const BigInvLoArgs& a, uint32_t W, hipStream_t s) {
+  const dim3 grid((unsigned)(a.d >> LOG_BIG), W);
+  if (a.use_table) {
+    if (a.src_bits == 4) launch_big_inv_lo_k<4, true>(a, pl.split, grid, s);
+    else launch_big_inv_lo_k<0, true>(a, pl.split, grid, s);
+  } else {
+    if (a.src_bits == 8) launch_big_inv_lo_k<8, false>(a, pl.split, grid, s);
+    else if (a.src_bits == 16) launch_big_inv_lo_k<16, false>(a, pl.split, grid, s);
+    else launch_big_inv_lo_k<0, false>(a, pl.split, grid, s);
+  }
+}
+
 // middle passes of W vectors of `d` coordinates each, in place
 void run_mids(const Plan& pl, float* x, uint64_t d, uint32_t W, hipStream_t s) {
   for (int m = 0; m < pl.nmid; ++m) {
@@ -273,6 +356,15 @@ void run_mids(const Plan& pl, float* x, uint64_t d, uint32_t W, hipStream_t s) {
 // inverse transform of W vectors of `len` coordinates that k_inv_lo is about to produce in `wsx`
 void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, InvHiArgs hi, uint64_t len, uint32_t W,
                  hipStream_t s) {
+  if (use_big(pl, p->d, W)) {
+    BigInvLoArgs a{lo.src, lo.range_M, lo.range_m, wsx, len, lo.L, lo.src_bits, lo.use_table, lo.divisor, {}};
+    std::memcpy(a.table, lo.table, 256);
+    launch_big_inv_lo(pl, a, W, s);
+    const BigInvHiArgs h{wsx, hi.out, hi.grad, len, hi.j0, hi.round, hi.k0, hi.k1,
+                         (float)(1.0 / std::sqrt((double)p->block))};
+    dispatch_big<LaunchBigInvHi>(pl.L - LOG_BIG, h, pl.split, hi.mode == 0 ? 0 : hi.bf16 ? 2 : 1, W, s);
+    return;
+  }
   lo.tm = lo_tilemap(pl, len);
   lo.ws_x = wsx;
   lo.d = len;
@@ -396,6 +488,7 @@ void run_forward(const Forward& f) {
   float* const slot = wl.ring;
   double* const partials = wl.partials;
   const float* const range = f.range_out ? f.range_out : f.range_in;
+  const bool big = use_big(pl, p->d, f.W);
 
   QuantArgs q{};
   q.tm = pl.hi;
@@ -437,25 +530,37 @@ void run_forward(const Forward& f) {
       }
     }
     a.ws_x = slot;
-    a.partials = f.range_out ? partials + (x0 >> pl.L1) : nullptr;
-    a.pstride = p->d >> pl.L1;
+    const uint32_t L1 = big ? LOG_BIG : (uint32_t)pl.L1;
+    a.partials = f.range_out ? partials + (x0 >> L1) : nullptr;
+    a.pstride = p->d >> L1;
     a.d = len;
     a.j0 = base_coord(p) + x0;
     a.round = (uint32_t)f.round;
     a.k0 = q.k0;
     a.k1 = q.k1;
-    a.tm = lo_tilemap(pl, len);
-    launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, tiles, f.W, f.s);
-    if (f.range_out) {
-      RangeArgs r{a.partials, f.range_out + x0 / p->block, a.pstride, len, f.W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p};
-      launch_range(pl, r, f.s);
-    }
-    run_mids(pl, slot, len, f.W, f.s);
-    q.x = slot;
     q.range_M = range + x0 / p->block;
-    q.d = len;
     q.j0 = a.j0;
-    dispatch_0_9<LaunchQuant>(pl.R, q, (pl.L & 1) == 0, tiles, f.W, f.s);
+    if (big) {
+      const BigLoArgs bl{a.grads, a.efs, slot, a.partials, a.pstride, len, a.j0, a.round, a.k0, a.k1};
+      launch_big_lo(pl, bl, bf16, f.efs != nullptr, false, f.W, f.s);
+    } else {
+      a.tm = lo_tilemap(pl, len);
+      launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, tiles, f.W, f.s);
+    }
+    if (f.range_out) {
+      RangeArgs r{a.partials, f.range_out + x0 / p->block, a.pstride, len, f.W, (uint32_t)pl.L, L1, p->t_p};
+      launch_range(r, f.s);
+    }
+    if (big) {
+      BigQuantArgs bq{slot, q.range_M, nullptr, q.packed, len, q.j0, q.b, q.g, q.round, q.worker, q.k0, q.k1, q.c, {}};
+      std::memcpy(bq.lut, q.lut, sizeof q.lut);
+      dispatch_big<LaunchBigQuant>(pl.L - LOG_BIG, bq, pl.split, f.W, f.s);
+    } else {
+      run_mids(pl, slot, len, f.W, f.s);
+      q.x = slot;
+      q.d = len;
+      dispatch_0_9<LaunchQuant>(pl.R, q, (pl.L & 1) == 0, tiles, f.W, f.s);
+    }
     if (f.efs) {
       // e <- (grad + e) - RHT^-1(X_i): the group's slot is free again and takes the inverse's intermediate
       ilo.range_M = q.range_M;
@@ -565,18 +670,25 @@ int thc_prepare_range(const thc_params* p, const void* const* grads, const float
   // give the same M bit for bit.
   const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
   double* const partials = ws_layout(ws, p, pl, false).partials;
+  const bool big = use_big(pl, p->d, p->n);
+  const uint32_t L1 = big ? LOG_BIG : (uint32_t)pl.L1;
   FwdLoArgs a{};
   for (uint32_t i = 0; i < p->n; ++i) {
     a.grads.p[i] = grads[i];
     if (ef) a.efs.p[i] = ef[i];
   }
-  a.partials = partials;
-  a.pstride = p->d >> pl.L1;
-  a.d = p->d;
-  a.tm = lo_tilemap(pl, p->d);
-  launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(p->d), p->n, s);
-  RangeArgs r{partials, range_M, p->d >> pl.L1, p->d, p->n, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p};
-  launch_range(pl, r, s);
+  if (big) {
+    BigLoArgs bl{a.grads, a.efs, nullptr, partials, p->d >> LOG_BIG, p->d, 0, 0, 0, 0};
+    launch_big_lo(pl, bl, bf16, ef != nullptr, true, p->n, s);
+  } else {
+    a.partials = partials;
+    a.pstride = p->d >> pl.L1;
+    a.d = p->d;
+    a.tm = lo_tilemap(pl, p->d);
+    launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(p->d), p->n, s);
+  }
+  RangeArgs r{partials, range_M, p->d >> L1, p->d, p->n, (uint32_t)pl.L, L1, p->t_p};
+  launch_range(r, s);
   return check_launch();
 }
 

@@ -1,0 +1,710 @@
+// Transform passes on tiles of 2^15 coordinates, 64 values per thread: blocks of 2^22 (large calls) to 2^25.
+//
+// What bounds it: bytes.  Every pass over a block reads and writes (or reads) each value once at what HBM takes, 5 to
+// 6 TB/s here, so fewer passes is the gain: 15 + 10 stages make two passes of a 2^25-point block, where tiles of 8192
+// (13 + 6 + 6) make three; and blocks of 2^22 get rows of 256 columns (1 KB) in the last pass instead of 16 (64 bytes,
+// which over-fetches).  Measured, ResNet-50-shaped round (2^25, n = 8, error feedback): 3050 us with 8192-coordinate
+// tiles, 2160 us with these; the EF chain of GPT-2-shaped blocks (2^22, n = 32): 15.1 ms and 13.5 ms.
+//
+// Why this shape.  64 values x 512 threads is what two workgroups per compute unit can keep in registers (128 each);
+// the tile goes through LDS in two independent halves of 64 KB.  Four waves per SIMD are enough here because a wave
+// has 32 to 64 loads in flight.  Blocks up to 2^21 are as fast or faster with the smaller tiles (first pass 740 us
+// against 740 to 780 us at 64 blocks of 2^20 x 8 vectors), and small calls keep more compute units busy with them.
+#pragma once
+
+#include "thc_inverse.hpp"
+
+namespace thc {
+
+constexpr int LOG_BIG = 15;
+constexpr int BIG = 1 << LOG_BIG;
+
+// ---------------------------------------------------------------------------------------------
+// Coordinates of a block, as the big tiles see them.  The first pass does the first 15 bits of the stage order
+// (processing bits p0..p14), the last pass the remaining R = L - 15 (row bits q0..).
+//   ascending: p = coordinate bits 0..14,                    q = 15, 16, ...
+//   split:     p = coordinate bits 0..9, 13, 14, 15, 10, 11, q = 12, 16, 17, ...
+// ---------------------------------------------------------------------------------------------
+template <bool XO>
+__host__ __device__ constexpr uint32_t big_p(uint32_t p) {   // processing index inside a first-pass tile -> offset
+  return XO ? (p & 1023u) | (((p >> 10) & 7u) << 13) | (((p >> 13) & 3u) << 10) : p;
+}
+template <bool XO>
+__host__ __device__ constexpr uint32_t big_u(uint32_t u) {   // the same 15 bits in address order -> offset
+  return XO ? (u & 4095u) | ((u >> 12) << 13) : u;
+}
+template <bool XO>
+__host__ __device__ constexpr uint32_t big_q(uint32_t q) {   // row index of the last pass -> offset
+  return XO ? ((q & 1u) << 12) | ((q >> 1) << 16) : q << 15;
+}
+template <bool XO>
+__device__ __forceinline__ uint64_t big_lo_base(uint32_t tile) {
+  return XO ? ((uint64_t)(tile & 1u) << 12) | ((uint64_t)(tile >> 1) << 16) : (uint64_t)tile << 15;
+}
+
+// ---------------------------------------------------------------------------------------------
+// First pass.  A thread holds 64 values; the 15 stages run as 4 + 5 + 5 + 1: bits p0..p3 on the 16 consecutive
+// values a thread loads, p4..p8 and p9..p13 after one exchange through LDS each, p14 between the two halves of the
+// registers.  Both exchanges keep p14, so the tile goes through LDS in two halves of 64 KB and two workgroups share a
+// compute unit.  LDS slots are padded so that every access is free of bank conflicts and the 32 addresses of a
+// thread are one base plus constants.
+// ---------------------------------------------------------------------------------------------
+__host__ __device__ constexpr int bphys(int i) { return i + 4 * (i >> 6) + 16 * (i >> 10); }
+constexpr int BIG_LDS = bphys(1 << 14);
+constexpr int BIG_SIGN_WORDS = BIG / 32;
+
+// fill(h, x): x[y][0..15] = values p = lane << 4 | wave << 10 | y << 13 | h << 14 + (0..15), before any stage;
+// out(k, v): v belongs to processing index t | k << 9 (t = thread, k < 64, a constant).
+template <class Fill, class Out>
+__device__ __forceinline__ void big_lo_stages(float* lds, int t, Fill&& fill, Out&& out) {
+  const int lane = t & 63, wave = t >> 6;
+  float* const wp = lds + bphys(lane << 4 | wave << 10);
+  float* const r1 = lds + bphys((lane & 15) | (lane >> 4) << 9 | wave << 11);
+  const float* const r2 = lds + bphys(t);
+  float u[2][32];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float x[2][16];
+    fill(h, x);
+#pragma unroll
+    for (int y = 0; y < 2; ++y) bfly<4>(x[y]);
+    if (h) __syncthreads();                        // the first half has been read
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int e = 0; e < 16; e += 4)
+        *reinterpret_cast<float4*>(wp + bphys(y << 13) + e) = make_float4(x[y][e], x[y][e + 1], x[y][e + 2], x[y][e + 3]);
+    __syncthreads();
+    float v[32];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) v[e] = r1[bphys(e << 4)];
+    bfly<5>(v);
+#pragma unroll
+    for (int e = 0; e < 32; ++e) r1[bphys(e << 4)] = v[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 32; ++e) u[h][e] = r2[bphys(e << 9)];
+    bfly<5>(u[h]);
+  }
+#pragma unroll
+  for (int e = 0; e < 32; ++e) {
+    out(e, u[0][e] + u[1][e]);
+    out(e | 32, u[0][e] - u[1][e]);
+  }
+}
+
+struct alignas(16) SmemBigLo {
+  float lds[BIG_LDS];
+  uint32_t sgn[BIG_SIGN_WORDS];
+  double wsum[NT / 64];
+};
+
+struct BigLoArgs {
+  PtrArr grads;
+  PtrArr efs;          // unused without error feedback
+  float* ws_x;         // d floats per vector
+  double* partials;    // per vector `pstride` doubles, one per tile; or null
+  uint64_t pstride;
+  uint64_t d;
+  uint64_t j0;         // global coordinate of the vectors' first element
+  uint32_t round, k0, k1;
+};
+
+template <bool BF16>
+__device__ __forceinline__ void load_grad16(const void* g, uint64_t j, float (&v)[16]) {
+  if constexpr (BF16) {
+#pragma unroll
+    for (int e = 0; e < 16; e += 8) {
+      const uint4 r = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(g) + j + e);
+      const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        v[e + 2 * k] = __uint_as_float(w[k] << 16);
+        v[e + 2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; e += 4) {
+      const float4 r = *reinterpret_cast<const float4*>(static_cast<const float*>(g) + j + e);
+      v[e] = r.x; v[e + 1] = r.y; v[e + 2] = r.z; v[e + 3] = r.w;
+    }
+  }
+}
+
+// x with its sign bit flipped where bit k of `bits` is set: one shift and one three-input operation
+__device__ __forceinline__ float flip_bit(float x, uint32_t bits, int k) {
+  return __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(x), bits << (31 - k), 0x80000000u, 0x78));   // a ^ (b & c)
+}
+
+// grid = (tiles of a vector, vectors).  NORM_ONLY: stop after the partial sums of squares.
+template <bool BF16, bool EF, bool XO, bool NORM_ONLY>
+__global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
+  __shared__ SmemBigLo sm;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t off = big_lo_base<XO>(tile);
+  const char* const grad = static_cast<const char*>(a.grads.p[vec]) + off * (BF16 ? 2 : 4);
+  const float* const ef = EF ? static_cast<const float*>(a.efs.p[vec]) + off : nullptr;
+  const uint32_t tp = big_p<XO>(lane << 4 | wave << 10);
+
+  float v[4][16], e[2][16];
+  double acc[4];
+  auto load = [&](int h) {   // operands of one half of the tile
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      load_grad16<BF16>(grad, tp + big_p<XO>((2 * h + y) << 13), v[2 * h + y]);
+      if constexpr (EF) load_grad16<false>(ef, tp + big_p<XO>((2 * h + y) << 13), e[y]);
+    }
+  };
+  auto take = [&](int h) {   // x = grad + e and its squares in binary64 (a binary32 square is exact there)
+#pragma unroll
+    for (int s = 2 * h; s < 2 * h + 2; ++s) {
+      if constexpr (EF) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[s][k] += e[s & 1][k];
+      }
+      if (NORM_ONLY || a.partials) {
+        double c = (double)v[s][0] * (double)v[s][0];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) c = __builtin_fma((double)v[s][k], (double)v[s][k], c);
+        acc[s] = c;
+      }
+    }
+  };
+  auto reduce = [&] {
+    if (NORM_ONLY || a.partials) {
+      const double s = wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+      if (lane == 0) sm.wsum[wave] = s;
+      __syncthreads();
+      if (t == 0) {
+        double r = 0.0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) r += sm.wsum[w];
+        a.partials[(uint64_t)vec * a.pstride + tile] = r;
+      }
+    }
+  };
+
+  load(0);
+  if constexpr (NORM_ONLY) {
+    take(0);
+    load(1);
+    take(1);
+    reduce();
+    return;
+  }
+  if constexpr (!EF) load(1);
+  if (t < BIG / 128) {   // the tile's diagonal: one Philox call per 128 coordinates
+    const uint64_t q = (a.j0 + off + big_p<XO>(t << 7)) >> 7;
+    *reinterpret_cast<uint4*>(&sm.sgn[4 * t]) =
+        philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, SIGN_STREAM, a.k0, a.k1);
+  }
+  __syncthreads();   // diagonal bits visible
+  float* const dst = a.ws_x + (uint64_t)vec * a.d + off;
+  big_lo_stages(
+      sm.lds, t,
+      [&](int h, float (&x)[2][16]) {
+        take(h);
+        if constexpr (EF) {
+          if (h == 0) {      // the second half's operands travel while the first goes through its stages
+            __builtin_amdgcn_sched_barrier(0);
+            load(1);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const uint32_t bits = sm.sgn[lane >> 1 | wave << 5 | y << 8 | h << 9] >> ((lane & 1) << 4);
+#pragma unroll
+          for (int k = 0; k < 16; ++k) x[y][k] = flip_bit(v[2 * h + y][k], bits, k);
+        }
+      },
+      [&](int k, float r) { dst[big_p<XO>(k << 9) + t] = r; });
+  reduce();
+}
+
+// ---------------------------------------------------------------------------------------------
+// Last pass: tiles of 2^R rows (stage bits q), 7 <= R <= 10, by 2^C columns, C = 15 - R.  A thread holds 8 consecutive
+// columns (what one Philox call and one packed word cover) in eight slots.  Row bits q0..q2 start in the slot index,
+// q3 and q4 on lane bits 4 and 5, from where a lane swap brings them into the slot index (half an instruction per
+// value, no LDS, no barrier); q5..q7 take one exchange through LDS, in two halves of 64 KB, and q8 and q9 two more
+// swaps.
+// ---------------------------------------------------------------------------------------------
+// What the 3 slot bits and the 9 thread bits stand for: >= 0: row bit q; < 0: column bit -1 - c.
+struct BigLayout {
+  int slot[3];
+  int thr[9];
+};
+
+template <int R>
+struct BigHi {
+  static_assert(R >= 7 && R <= 10, "the last pass takes 7 to 10 row bits");
+  static constexpr int C = LOG_BIG - R;
+  static constexpr int E = R - 5;                // row bits that need LDS
+
+  // columns first, then the row bits that are still missing
+  static constexpr BigLayout first() {
+    BigLayout m{{0, 1, 2}, {}};
+    int c = 3, q = 5;
+    for (int i = 0; i < 9; ++i)
+      m.thr[i] = i == 4 ? 3 : i == 5 ? 4 : c < C ? -1 - c++ : q++;
+    return m;
+  }
+  static constexpr void swap(BigLayout& m, int slot, int thr) {
+    const int x = m.slot[slot];
+    m.slot[slot] = m.thr[thr];
+    m.thr[thr] = x;
+  }
+  static constexpr int pos(const BigLayout& m, int what) {   // thread bit that stands for `what`
+    for (int i = 0; i < 9; ++i)
+      if (m.thr[i] == what) return i;
+    return -1;
+  }
+  // after the lane swaps of q3 and q4
+  static constexpr BigLayout second() {
+    BigLayout m = first();
+    swap(m, 0, 4);
+    swap(m, 1, 5);
+    return m;
+  }
+  // after the LDS exchange: q5..q7 in the slots, q8 and q9 on lane bits 4 and 5
+  static constexpr BigLayout third() {
+    BigLayout m = second();
+    for (int i = 0; i < 3; ++i)
+      if (i < E) swap(m, i, pos(m, 5 + i));
+    for (int i = 3; i < E; ++i) {
+      const int a = 1 + i, b = pos(m, 5 + i);    // thread bits 4, 5
+      const int x = m.thr[a];
+      m.thr[a] = m.thr[b];
+      m.thr[b] = x;
+    }
+    return m;
+  }
+  static constexpr BigLayout last() {
+    BigLayout m = third();
+    if (E >= 4) swap(m, 0, 4);
+    if (E >= 5) swap(m, 1, 5);
+    return m;
+  }
+
+  template <bool XO>
+  static constexpr uint32_t what_off(int what) {
+    return what >= 0 ? big_q<XO>(1u << what) : big_u<XO>(1u << (-1 - what));
+  }
+  static constexpr int log2c(uint32_t v) { return v <= 1 ? 0 : 1 + log2c(v >> 1); }
+  template <bool XO, int B>
+  static __device__ __forceinline__ uint32_t thread_off(const BigLayout& m, int t) {
+    if constexpr (B == 9) return 0u;
+    else return (((uint32_t)t >> B) & 1u) << log2c(what_off<XO>(m.thr[B])) | thread_off<XO, B + 1>(m, t);
+  }
+  template <bool XO>
+  static constexpr uint32_t slot_off(const BigLayout& m, int k) {
+    return (k & 1 ? what_off<XO>(m.slot[0]) : 0u) | (k & 2 ? what_off<XO>(m.slot[1]) : 0u) |
+           (k & 4 ? what_off<XO>(m.slot[2]) : 0u);
+  }
+};
+
+// LDS slot (16-byte units) of thread t's half of slot k before the exchange
+__host__ __device__ constexpr int xphys(int k, int t) { return k * (NT + 4) + t; }
+constexpr int BIG_XLDS = 8 * (NT + 4);   // 16-byte units: 66 KB
+
+template <int BIT>
+__device__ __forceinline__ void slot_stage(float (&v)[8][8]) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (!(k & (1 << BIT))) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float a = v[k][e], b = v[k | (1 << BIT)][e];
+        v[k][e] = a + b;
+        v[k | (1 << BIT)][e] = a - b;
+      }
+    }
+}
+
+// exchanges slot bit BIT with lane bit 4 (LANE32 = false) or 5
+template <int BIT, bool LANE32>
+__device__ __forceinline__ void slot_swap(float (&v)[8][8]) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (!(k & (1 << BIT))) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t a = __float_as_uint(v[k][e]), b = __float_as_uint(v[k | (1 << BIT)][e]);
+        const auto r = LANE32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                              : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        v[k][e] = __uint_as_float(r[0]);
+        v[k | (1 << BIT)][e] = __uint_as_float(r[1]);
+      }
+    }
+}
+
+template <int R, bool XO>
+__device__ __forceinline__ void big_hi_load(const float* src, int t, float (&v)[8][8]) {
+  constexpr BigLayout m = BigHi<R>::first();
+  const float* const p = src + BigHi<R>::template thread_off<XO, 0>(m, t);
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+#pragma unroll
+    for (int e = 0; e < 8; e += 4) {
+      const float4 r = *reinterpret_cast<const float4*>(p + BigHi<R>::template slot_off<XO>(m, k) + e);
+      v[k][e] = r.x; v[k][e + 1] = r.y; v[k][e + 2] = r.z; v[k][e + 3] = r.w;
+    }
+}
+
+template <int R>
+__device__ __forceinline__ void big_hi_stages(float4* lds, int t, float (&v)[8][8]) {
+  using H = BigHi<R>;
+  slot_stage<0>(v);
+  slot_stage<1>(v);
+  slot_stage<2>(v);
+  slot_swap<0, false>(v);
+  slot_stage<0>(v);
+  slot_swap<1, true>(v);
+  slot_stage<1>(v);
+  {
+    constexpr BigLayout from = H::second(), to = H::third();
+    // where the new thread bits find their data: thread bit i of the reader stands for to.thr[i], which the writer
+    // had on a thread bit or in its slot index
+    uint32_t rt = 0, rk = 0;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      const uint32_t bit = ((uint32_t)t >> i) & 1u;
+      const int p = H::pos(from, to.thr[i]);
+      if (p >= 0) rt |= bit << p;
+      else
+        for (int s = 0; s < 3; ++s)
+          if (from.slot[s] == to.thr[i]) rk |= bit << s;
+    }
+    const int rbase = xphys((int)rk, (int)rt);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (h) __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        lds[xphys(k, t)] = make_float4(v[k][4 * h], v[k][4 * h + 1], v[k][4 * h + 2], v[k][4 * h + 3]);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        int o = 0;                              // where the writer had slot bits 0..2 of the reader
+        for (int s = 0; s < 3; ++s)
+          if (k & (1 << s)) {
+            const int p = H::pos(from, to.slot[s]);
+            if (p >= 0) o += 1 << p;
+            else
+              for (int z = 0; z < 3; ++z)
+                if (from.slot[z] == to.slot[s]) o += xphys(1 << z, 0);
+          }
+        const float4 r = lds[rbase + o];
+        v[k][4 * h] = r.x; v[k][4 * h + 1] = r.y; v[k][4 * h + 2] = r.z; v[k][4 * h + 3] = r.w;
+      }
+    }
+    slot_stage<0>(v);
+    slot_stage<1>(v);
+    if constexpr (H::E >= 3) slot_stage<2>(v);
+    if constexpr (H::E >= 4) { slot_swap<0, false>(v); slot_stage<0>(v); }
+    if constexpr (H::E >= 5) { slot_swap<1, true>(v); slot_stage<1>(v); }
+  }
+}
+
+// offset of a tile's first coordinate inside its vector
+template <int R, bool XO>
+__device__ __forceinline__ uint64_t big_hi_base(uint32_t tile) {
+  return ((uint64_t)(tile >> R) << (LOG_BIG + R)) | big_u<XO>((tile & ((1u << R) - 1u)) << (LOG_BIG - R));
+}
+
+template <bool V>
+struct Const { static constexpr bool value = V; };
+
+struct BigQuantArgs {
+  const float* x;          // half-rotated vectors, d floats per vector of the launch (grid.y)
+  const float* range_M;
+  const float* range_m;    // or null: m = -M
+  PtrArr packed;
+  uint64_t d;
+  uint64_t j0;
+  uint32_t b, g;
+  uint32_t round, worker, k0, k1;
+  float c;
+  uint32_t lut[256];
+};
+
+struct alignas(16) SmemBigHi {
+  float4 x[BIG_XLDS];
+  uint32_t lut[256][4];
+  float sQ[4];
+  int sCare;
+};
+
+template <int R, bool XO>
+__global__ __launch_bounds__(NT, 4) void k_big_quant(const BigQuantArgs a) {
+  constexpr bool CFOLD = ((LOG_BIG + R) & 1) == 0;
+  __shared__ SmemBigHi sm;
+  uint4* const lut = reinterpret_cast<uint4*>(sm.lut);
+  const int t = threadIdx.x;
+  const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t base = big_hi_base<R, XO>(tile);
+  float v[8][8];
+  big_hi_load<R, XO>(a.x + (uint64_t)vec * a.d + base, t, v);
+  build_quant_lut(a, lut, t);
+  if (t == 0) {
+    const uint32_t blk = tile >> R;
+    const float M = a.range_M[blk], m = lower_of(a.range_m, blk, M);
+    bool careful;
+    *reinterpret_cast<QuantScalars*>(sm.sQ) = quant_scalars(M, m, a.g, a.lut[a.g - 1], a.c, CFOLD, careful);
+    sm.sCare = careful;
+  }
+  __syncthreads();
+  big_hi_stages<R>(sm.x, t, v);
+  const QuantScalars s = *reinterpret_cast<const QuantScalars*>(sm.sQ);
+  const bool careful = __builtin_amdgcn_readfirstlane(sm.sCare) != 0;
+  constexpr BigLayout m = BigHi<R>::last();
+  const uint32_t to = BigHi<R>::template thread_off<XO, 0>(m, t);
+  // the tile's base has no bits in common with the offsets inside it: both counter words come from one OR
+  const uint64_t q0 = (a.j0 + base) >> 3;
+  const uint32_t qlo = (uint32_t)q0 | (to >> 3), qhi = (uint32_t)(q0 >> 32);
+  uint8_t* const packed = static_cast<uint8_t*>(const_cast<void*>(a.packed.p[vec])) + (base >> 3) * a.b;
+  const uint32_t stream = a.worker + vec;
+  auto step = [&](int k, auto mulc, auto care) {
+    const uint32_t so = BigHi<R>::template slot_off<XO>(m, k);
+    const uint4 rnd = philox4x32_10(qlo | (so >> 3), qhi, a.round, stream, a.k0, a.k1);
+    uint32_t z[8];
+    quantize8<mulc.value, care.value>(v[k], rnd, s, lut, z);
+    store_packed8(packed, to + so, a.b, z);
+    __builtin_amdgcn_sched_barrier(0);   // one step's draws at a time: interleaved steps would not fit the registers
+  };
+  if (!careful) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) step(k, Const<!CFOLD>{}, Const<false>{});
+  } else {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) step(k, Const<true>{}, Const<true>{});
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Inverse first pass.  SB: bits per code where that is known at compile time (4, 8, 16), else 0.
+// ---------------------------------------------------------------------------------------------
+struct BigInvLoArgs {
+  PtrArr src;
+  const float* range_M;
+  const float* range_m;    // or null: m = -M
+  float* ws_x;
+  uint64_t d;
+  uint32_t L, src_bits, use_table, divisor;
+  uint8_t table[256];
+};
+
+struct alignas(16) SmemBigInvLo {
+  float lds[BIG_LDS];
+  float tabf[256];
+  float lo, step;
+};
+
+// sixteen W-bit fields from bit 16 * `half` of `first` on, reading only the dwords that hold them
+template <int W>
+__device__ __forceinline__ void cut16_global(const uint32_t* first, bool half, uint32_t (&y)[16]) {
+  constexpr int NW = (16 * W + 31) / 32;
+  uint32_t d[NW + 1];
+#pragma unroll
+  for (int k = 0; k < NW; ++k) d[k] = first[k];
+  d[NW] = 0;
+  if (half) {
+#pragma unroll
+    for (int k = 0; k < NW; ++k) d[k] = __builtin_amdgcn_alignbit(d[k + 1], d[k], 16);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    constexpr uint32_t mask = (1u << W) - 1u;
+    const int k = (e * W) >> 5, sh = (e * W) & 31;
+    uint32_t v = d[k] >> sh;
+    if (sh + W > 32) v |= d[k + 1] << (32 - sh);
+    y[e] = v & mask;
+  }
+}
+
+// sixteen codes from coordinate j (a multiple of 16) on
+__device__ __forceinline__ void codes16(const uint8_t* src, uint32_t bits, uint64_t j, uint32_t (&y)[16]) {
+  if (codes_fast_width(bits)) {
+    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    codes_load(src, bits, j, w, y);
+    codes_decode(bits, true, w, y);
+    return;
+  }
+  const uint64_t bit = j * bits;
+  const uint32_t* const first = reinterpret_cast<const uint32_t*>(src) + (bit >> 5);
+  const bool half = (bit & 16u) != 0;
+  switch (bits) {
+#define THC_CUT(W) case W: cut16_global<W>(first, half, y); break;
+    THC_CUT(3) THC_CUT(5) THC_CUT(6) THC_CUT(7) THC_CUT(9) THC_CUT(10) THC_CUT(11) THC_CUT(12) THC_CUT(13)
+    THC_CUT(14) THC_CUT(15)
+#undef THC_CUT
+    default: break;
+  }
+}
+
+template <int SB, bool TABLE, bool XO>
+__global__ __launch_bounds__(NT, 4) void k_big_inv_lo(const BigInvLoArgs a) {
+  __shared__ SmemBigInvLo sm;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t off = big_lo_base<XO>(tile);
+  const uint32_t tp = big_p<XO>(lane << 4 | wave << 10);
+  const uint32_t bits = SB ? SB : a.src_bits;
+  const uint8_t* const src = static_cast<const uint8_t*>(a.src.p[vec]) + (off >> 3) * bits;
+  // fast widths: the raw words of all four runs are requested before anything waits
+  constexpr int NW = SB ? SB / 2 : 1;
+  uint32_t w[4][NW];
+  if constexpr (SB != 0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const uint32_t* const p = reinterpret_cast<const uint32_t*>(src + ((tp + big_p<XO>(s << 13)) >> 3) * SB);
+#pragma unroll
+      for (int k = 0; k < NW; ++k) w[s][k] = p[k];
+    }
+  }
+  const uint32_t blk = (uint32_t)(off >> a.L);
+  const float M = a.range_M[blk], lo = lower_of(a.range_m, blk, M);
+  const float step = (float)(((double)M - (double)lo) / (double)a.divisor);
+  if constexpr (TABLE) {
+    if (t < 256) sm.tabf[t] = (float)a.table[t] * step + lo;   // the table's values on the block's range
+    __syncthreads();
+  }
+  float* const dst = a.ws_x + (uint64_t)vec * a.d + off;
+  big_lo_stages(
+      sm.lds, t,
+      [&](int h, float (&x)[2][16]) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const int s = 2 * h + y;
+          uint32_t c[16];
+          if constexpr (SB != 0) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) c[e] = (w[s][e * SB / 32] >> (e * SB % 32)) & ((1u << SB) - 1u);
+          } else {
+            codes16(src, bits, tp + big_p<XO>(s << 13), c);
+          }
+#pragma unroll
+          for (int e = 0; e < 16; ++e) x[y][e] = TABLE ? sm.tabf[c[e]] : (float)c[e] * step + lo;
+        }
+      },
+      [&](int k, float r) { dst[big_p<XO>(k << 9) + t] = r; });
+}
+
+// ---------------------------------------------------------------------------------------------
+// Inverse last pass: finish H, scale, diagonal; EFM 0: out = result, 1 / 2: e <- (grad + e) - result with a binary32 /
+// bf16 gradient.
+// ---------------------------------------------------------------------------------------------
+struct BigInvHiArgs {
+  const float* x;
+  PtrArr out;
+  PtrArr grad;
+  uint64_t d;
+  uint64_t j0;
+  uint32_t round, k0, k1;
+  float c;
+};
+
+struct alignas(16) SmemBigInvHi {
+  float4 x[BIG_XLDS];
+  uint32_t sgn[BIG_SIGN_WORDS];   // bit (u & 31) of word (row << (C - 5)) + (column >> 5)
+};
+
+template <int EFM>
+__device__ __forceinline__ void load_grad8(const void* g, uint32_t j, float (&x)[8]) {
+  if constexpr (EFM == 2) {
+    const uint4 r = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(g) + j);
+    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      x[2 * k] = __uint_as_float(w[k] << 16);
+      x[2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
+    }
+  } else {
+    const float4 p = *reinterpret_cast<const float4*>(static_cast<const float*>(g) + j);
+    const float4 q = *reinterpret_cast<const float4*>(static_cast<const float*>(g) + j + 4);
+    x[0] = p.x; x[1] = p.y; x[2] = p.z; x[3] = p.w; x[4] = q.x; x[5] = q.y; x[6] = q.z; x[7] = q.w;
+  }
+}
+
+template <int R, bool XO, int EFM>
+__global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
+  using H = BigHi<R>;
+  __shared__ SmemBigInvHi sm;
+  const int t = threadIdx.x;
+  const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t base = big_hi_base<R, XO>(tile);
+  float v[8][8];
+  big_hi_load<R, XO>(a.x + (uint64_t)vec * a.d + base, t, v);
+  // the diagonal while the loads travel: one Philox call covers 128 coordinates, or what of them the tile holds
+  constexpr int PER = H::C >= 7 ? 4 : 1 << (H::C - 5);    // words of a call that belong to the tile
+  for (int i = t; i < BIG_SIGN_WORDS / PER; i += NT) {
+    const int word = i * PER, row = word >> (H::C - 5), col = (word & ((1 << (H::C - 5)) - 1)) << 5;
+    const uint64_t j = a.j0 + base + big_q<XO>(row) + big_u<XO>(col);
+    const uint4 r = philox4x32_10((uint32_t)(j >> 7), (uint32_t)(j >> 39), a.round, SIGN_STREAM, a.k0, a.k1);
+    if constexpr (PER == 4) {
+      *reinterpret_cast<uint4*>(&sm.sgn[word]) = r;
+    } else if constexpr (PER == 2) {
+      const bool up = (j >> 6) & 1u;
+      sm.sgn[word] = up ? r.z : r.x;
+      sm.sgn[word + 1] = up ? r.w : r.y;
+    } else {
+      const uint32_t sel = (uint32_t)(j >> 5) & 3u;
+      sm.sgn[word] = sel == 0 ? r.x : sel == 1 ? r.y : sel == 2 ? r.z : r.w;
+    }
+  }
+  __syncthreads();
+  big_hi_stages<R>(sm.x, t, v);
+  constexpr BigLayout m = H::last();
+  const uint32_t to = H::template thread_off<XO, 0>(m, t);
+  float* const out = static_cast<float*>(const_cast<void*>(a.out.p[vec])) + base;
+  const char* const grad = EFM ? static_cast<const char*>(a.grad.p[vec]) + base * (EFM == 2 ? 2 : 4) : nullptr;
+  // tile-local word and bit of the thread's eight columns
+  uint32_t tword = 0, tbit = 0;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    const uint32_t bit = ((uint32_t)t >> i) & 1u;
+    const int what = m.thr[i];
+    if (what >= 0) tword |= bit << (H::C - 5 + what);
+    else if (-1 - what >= 5) tword |= bit << (-1 - what - 5);
+    else tbit |= bit << (-1 - what);
+  }
+  // error feedback: the next eight values of the gradient and of the buffer are requested before this step's stores,
+  // which the compiler must not move them across
+  float g[8], e[8];
+  if constexpr (EFM != 0) {
+    load_grad8<EFM>(grad, to, g);
+    load_grad8<1>(out, to, e);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const uint32_t so = H::template slot_off<XO>(m, k);
+    float gn[8], en[8];
+    if constexpr (EFM != 0) {
+      if (k < 7) {
+        const uint32_t sn = H::template slot_off<XO>(m, k + 1);
+        load_grad8<EFM>(grad, to + sn, gn);
+        load_grad8<1>(out, to + sn, en);
+      }
+    }
+    uint32_t kw = 0;
+    for (int s = 0; s < 3; ++s)
+      if (k & (1 << s)) kw |= m.slot[s] >= 0 ? 1u << (H::C - 5 + m.slot[s]) : 1u << (-1 - m.slot[s] - 5);
+    const uint32_t bits = sm.sgn[tword | kw] >> tbit;
+    float r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      r[i] = flip_bit(v[k][i] * a.c, bits, i);
+      if constexpr (EFM != 0) r[i] = (g[i] + e[i]) - r[i];
+    }
+    *reinterpret_cast<float4*>(out + to + so) = make_float4(r[0], r[1], r[2], r[3]);
+    *reinterpret_cast<float4*>(out + to + so + 4) = make_float4(r[4], r[5], r[6], r[7]);
+    if constexpr (EFM != 0) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { g[i] = gn[i]; e[i] = en[i]; }
+    }
+  }
+}
+
+}  // namespace thc

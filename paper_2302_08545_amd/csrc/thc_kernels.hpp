@@ -2,7 +2,7 @@
 //
 // A Hadamard transform of a block of B = 2^L coordinates is split by index bits:
 //   "lo"  pass: bits [0, L1), L1 = min(L, 13): one workgroup owns 8192 consecutive coordinates
-//   "mid" pass: (only for L > 22) up to 7 more bits each, in place in the workspace
+//   "mid" pass: (only for L > 22, outside thc_big.hpp) up to 7 more bits each, in place in the workspace
 //   "hi"  pass: the remaining bits (at most 9): one workgroup owns 2^R rows, 8192 >> R consecutive
 //               coordinates wide
 // Which bits each pass takes, and in which order, is fixed by the stage order (thc_params.stage_order) and
@@ -14,6 +14,7 @@
 //   thc_uniform.hpp    k_minmax, k_minmax_final, k_fwd_hi_store, k_uniform_quant, k_uniform_dequant
 //   thc_aggregate.hpp  k_aggregate_b4w8, k_aggregate_b4w16, k_aggregate_b2w8, k_aggregate_generic
 //   thc_pipeline.hpp   k_pipe_forward: the forward passes of all blocks in one launch, block after block
+//   thc_big.hpp        the same passes on tiles of 2^15 coordinates: k_big_lo, k_big_quant, k_big_inv_lo, k_big_inv_hi
 #pragma once
 
 #include "thc_forward.hpp"
@@ -21,3 +22,4 @@
 #include "thc_uniform.hpp"
 #include "thc_aggregate.hpp"
 #include "thc_pipeline.hpp"
+#include "thc_big.hpp"

@@ -1,0 +1,82 @@
+"""Kernel variants and dispatch branches at the sizes where they can go wrong, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import thc_oracle as o
+
+from .test_gpu_parity import DEV, GpuRound, assert_indices_match, both_params, make_grads, rel_l2, to_np32
+
+pytestmark = pytest.mark.gpu
+
+
+def _round_against_oracle(P, L, R, grads, rnd, efs=None):
+    """compress_all, aggregate, decompress; the oracle works from the range the GPU computed."""
+    n, b = L.n, L.b
+    dg = [x.to(DEV) for x in grads]
+    gn = [to_np32(x) for x in grads]
+    R.compress_all(rnd, dg)
+    R.aggregate()
+    R.decompress(rnd)
+    M_ref, M = o.prepare_range(P, gn, efs), R.range_M.cpu().numpy()
+    assert np.all(np.abs(M - M_ref) <= np.abs(M_ref) * 2.0 ** -23)
+    pks = []
+    for i in range(n):
+        pk, ne = o.compress(P, i, rnd, gn[i], None if efs is None else efs[i], M)
+        assert_indices_match(R.packed[i].cpu().numpy(), pk, b, f"worker {i}")
+        if efs is not None:
+            assert rel_l2(R.efs[i].cpu().numpy(), ne) <= 1e-5, f"worker {i}"
+        pks.append(R.packed[i].cpu().numpy())
+    Y = o.aggregate(P, pks)
+    assert np.array_equal(R.agg_numpy(), Y)
+    assert rel_l2(R.out.cpu().numpy(), o.decompress(P, rnd, Y, M)) <= 1e-5
+
+
+@pytest.mark.parametrize("b,g", [(1, 1), (1, 255), (2, 8), (4, 30), (4, 100), (4, 128), (7, 200), (8, 255)])
+@pytest.mark.parametrize("log2_block", [10, 13])
+def test_clamped_coordinates_end_in_the_outer_indices(b, g, log2_block):
+    """Ranges far inside the data: a third of the coordinates lie outside.  The fast form of the quantizer has no clamp
+    and is taken per block only where the top index is certain for whatever lies above the range."""
+    block, K = 1 << log2_block, 24
+    T = o.solve_table(b, g, 1 / 32) if g < 100 else [round(i * g / ((1 << b) - 1)) for i in range(1 << b)]
+    P, L = both_params(block * K, block, 1, b=b, g=g, agg_bits=8, table=T)
+    x = make_grads(block * K, 1, seed=b * 256 + g)
+    M = (np.random.default_rng(g).uniform(0.5, 1.5, K) * 1e-3).astype(np.float32)
+    R = GpuRound(L)
+    R.compress_each(5, [x[0].to(DEV)], range_M=torch.from_numpy(M).to(DEV))
+    assert_indices_match(R.packed[0].cpu().numpy(), o.compress(P, 0, 5, to_np32(x[0]), None, M)[0], b)
+
+
+@pytest.mark.parametrize("log2_block,K,n,b,g,agg_bits,bf16,ef,order", [
+    (22, 64, 1, 4, 30, 8, False, False, 1),      # just enough tiles for the large ones
+    (23, 1, 2, 4, 30, 8, True, True, 0), (23, 1, 1, 3, 21, 5, False, False, 1),
+    (24, 1, 2, 4, 30, 16, False, True, 1), (24, 1, 1, 8, 255, 8, False, False, 0), (25, 1, 1, 2, 8, 9, True, True, 0)])
+def test_tiles_of_2_to_the_15(log2_block, K, n, b, g, agg_bits, bf16, ef, order):
+    block = 1 << log2_block
+    T = list(range(256)) if b == 8 else None
+    P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, bf16=bf16, order=order, table=T)
+    if K > 1:                                    # long: blocks 0 and K - 1 are compared
+        x = torch.randn(block * K, device=DEV, generator=torch.Generator(device=DEV).manual_seed(22)) * 1e-3
+        R = GpuRound(L)
+        R.compress_all(3, [x])
+        R.aggregate()
+        R.decompress(3)
+        M, pk, agg, out = (t.cpu().numpy() for t in (R.range_M, R.packed[0], R.agg, R.out))
+        for k in (0, K - 1):
+            Pk = o.Params(d=block, block=block, n=1, b=b, g=g, t_p=P.t_p, seed=P.seed, table=P.table,
+                          agg_bits=agg_bits, order=order)
+            gk = x[k * block:(k + 1) * block].cpu().numpy()
+            assert abs(M[k] - o.prepare_range(Pk, [gk])[0]) <= M[k] * 2.0 ** -23
+            ref = o.compress(Pk, 0, 3, gk, None, M[k:k + 1], j0=k * block)[0]
+            assert_indices_match(pk[k * block // 2:(k + 1) * block // 2], ref, b)
+            Y = o.aggregate(Pk, [pk[k * block // 2:(k + 1) * block // 2]])
+            assert np.array_equal(agg[k * block:(k + 1) * block], Y)
+            assert rel_l2(out[k * block:(k + 1) * block], o.decompress(Pk, 3, Y, M[k:k + 1], j0=k * block)) <= 1e-5
+        return
+    R = GpuRound(L, ef=ef)
+    efs = None
+    if ef:
+        for i, e in enumerate(R.efs):
+            e.copy_(make_grads(block, 1, 2e-4, seed=90 + i)[0])
+        efs = [e.cpu().numpy() for e in R.efs]
+    _round_against_oracle(P, L, R, make_grads(block, n, seed=log2_block, bf16=bf16), 3, efs)
