@@ -194,8 +194,13 @@ template <int R> struct LaunchMid {
 };
 template <int R> struct LaunchQuant {
   static void run(const QuantArgs& a, bool cfold, uint64_t tiles, uint32_t W, hipStream_t s) {
-    if (cfold && R >= 2) k_fwd_hi_quant<R, true><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
-    else k_fwd_hi_quant<R, false><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+    if (cfold && R >= 2) go<R >= 2>(a, tiles, W, s);
+    else go<false>(a, tiles, W, s);
+  }
+  template <bool CFOLD>
+  static void go(const QuantArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
+    if (a.partials) k_fwd_hi_quant<R, CFOLD, true><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+    else k_fwd_hi_quant<R, CFOLD, false><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
   }
 };
 template <int R> struct LaunchHiStore {
@@ -261,6 +266,12 @@ void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t 
       break;
   }
 }
+
+// The quantizer finds the range itself in calls of up to this many workgroups (and no middle pass: its blocks have too
+// many partial sums).  Small calls are bound by their launches, about 3 us each on the host and 6 on the device: rounds of
+// 2^15 and 2^20 coordinates with 4 workers went from 35.8 to 32.8 us.  Beyond it, the workgroups that do the same sums
+// over again would come to more than one launch.
+constexpr uint64_t FIND_RANGE_MAX_TILES = 2048;
 
 // ---- passes on tiles of 2^15 coordinates (thc_big.hpp) ------------------------------------------------------------
 // Blocks of 2^23 to 2^25: always (two passes instead of three: 1.16x at one block of one vector, 1.5x at 16 of them).
@@ -547,7 +558,8 @@ void run_forward(const Forward& f) {
       a.tm = lo_tilemap(pl, len);
       launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, tiles, f.W, f.s);
     }
-    if (f.range_out) {
+    const bool find = f.range_out && !big && pl.nmid == 0 && tiles * f.W <= FIND_RANGE_MAX_TILES;
+    if (f.range_out && !find) {
       RangeArgs r{a.partials, f.range_out + x0 / p->block, a.pstride, len, f.W, (uint32_t)pl.L, L1, p->t_p};
       launch_range(r, f.s);
     }
@@ -559,6 +571,12 @@ void run_forward(const Forward& f) {
       run_mids(pl, slot, len, f.W, f.s);
       q.x = slot;
       q.d = len;
+      q.partials = find ? a.partials : nullptr;
+      q.pstride = a.pstride;
+      q.range_out = find ? f.range_out + x0 / p->block : nullptr;
+      q.n = f.W;
+      q.L1 = L1;
+      q.t_p = p->t_p;
       dispatch_0_9<LaunchQuant>(pl.R, q, (pl.L & 1) == 0, tiles, f.W, f.s);
     }
     if (f.efs) {

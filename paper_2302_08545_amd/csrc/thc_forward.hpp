@@ -200,29 +200,71 @@ struct SmemRange {
   double wsum[MAXW][RANGE_NT / 64];
 };
 
+// largest sum over the lanes that hold one (NaN never wins, as in a loop of comparisons from 0)
+__device__ __forceinline__ double wave_largest(double s) {
+  double m = s > 0.0 ? s : 0.0;
+#pragma unroll
+  for (int k = 1; k < 64; k <<= 1) {
+    const double o = __shfl_xor(m, k, 64);
+    m = o > m ? o : m;
+  }
+  return m;
+}
+
+// The range of one block of at most 8 tiles by one wave, lane i on worker i: the same sums as k_range_small.
+__device__ __forceinline__ float small_block_range(const double* partials, uint64_t pstride, uint32_t n, uint32_t ppb,
+                                                   uint64_t k, float t_p, uint32_t L) {
+  const uint32_t lane = threadIdx.x & 63;
+  double s = 0.0;
+  if (lane < n) {
+    const double* const p = partials + (uint64_t)lane * pstride + k * ppb;
+    for (uint32_t j = 0; j < ppb; ++j) s += p[j];
+  }
+  return range_from_sum(wave_largest(s), t_p, L);
+}
+
 // Larger blocks: one workgroup of RANGE_NT threads per block k.  Sigma x^2 of every worker in a fixed summation
-// order (thread-strided partial sums, wave butterflies, then the wave totals in sequence), the maximum over workers,
-// and M, returned by thread 0 (other threads return 0).  `partials` points at this call's first partial sum.
+// order (partial sums strided by RANGE_NT, butterflies over each 64 of them, then those totals in sequence), the maximum
+// over workers, and M, returned by the first wave (other threads return 0).  `partials` points at this call's first
+// partial sum.  What bounds it is latency, so the (worker, 64 partial sums) pairs are dealt to the eight waves, four
+// loads in flight each, and one lane per worker adds the totals up.
 __device__ __forceinline__ float block_range(const double* partials, uint64_t pstride, uint32_t n, uint32_t ppb,
                                              uint64_t k, float t_p, uint32_t L, SmemRange& sm) {
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  for (uint32_t i = 0; i < n; ++i) {
-    const double* p = partials + (uint64_t)i * pstride + k * ppb;
-    double s = 0.0;
-    for (uint32_t j = t; j < ppb; j += RANGE_NT) s += p[j];
-    s = wave_sum(s);
-    if (lane == 0) sm.wsum[i][wave] = s;
+  const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t lc = ppb >= RANGE_NT ? 3 : ppb >= 256 ? 2 : ppb >= 128 ? 1 : 0;   // log2 of the totals per worker
+  const uint32_t items = n << lc;
+  for (uint32_t it = wave; it < items; it += 4 * (RANGE_NT / 64)) {
+    double s[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t item = it + u * (RANGE_NT / 64);
+      const uint32_t j = 64 * (item & ((1u << lc) - 1u)) + lane;
+      s[u] = item < items && j < ppb ? partials[(uint64_t)(item >> lc) * pstride + k * ppb + j] : 0.0;
+    }
+    if (ppb > RANGE_NT) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t item = it + u * (RANGE_NT / 64);
+        if (item >= items) break;
+        const double* const p = partials + (uint64_t)(item >> lc) * pstride + k * ppb;
+        for (uint32_t j = 64 * (item & 7u) + lane + RANGE_NT; j < ppb; j += RANGE_NT) s[u] += p[j];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t item = it + u * (RANGE_NT / 64);
+      if (item >= items) break;
+      s[u] = wave_sum(s[u]);
+      if (lane == 0) sm.wsum[item >> lc][item & ((1u << lc) - 1u)] = s[u];
+    }
   }
   __syncthreads();
   float M = 0.f;
-  if (t == 0) {
-    double smax = 0.0;
-    for (uint32_t i = 0; i < n; ++i) {
-      double s = 0.0;
-      for (int w = 0; w < RANGE_NT / 64; ++w) s += sm.wsum[i][w];
-      smax = s > smax ? s : smax;
-    }
-    M = range_from_sum(smax, t_p, L);
+  if (wave == 0) {
+    double s = 0.0;
+    if (lane < n)
+      for (uint32_t w = 0; w < (1u << lc); ++w) s += sm.wsum[lane][w];
+    M = range_from_sum(wave_largest(s), t_p, L);
   }
   return M;
 }
@@ -419,6 +461,12 @@ struct QuantArgs {
   uint32_t round, worker, k0, k1;   // worker: id of the launch's first worker (selects the rounding stream)
   float c;                 // 1/sqrt(B)
   uint32_t lut[256];       // per grid cell k: lo | wd << 8 | z0 << 16
+  // only where the pass finds the range itself (FIND): what k_range would be given, and where M goes
+  const double* partials;
+  uint64_t pstride;
+  float* range_out;
+  uint32_t n, L1;
+  float t_p;
 };
 
 struct QuantScalars {
@@ -541,9 +589,10 @@ struct alignas(16) SmemQuant {
 };
 
 // One tile of the pass: tile index `tile` of the launch's vector `wk`, whose half-rotated image starts at xw.
-template <int R, bool CFOLD, class A>
+// FIND: the range comes from the partial sums of squares, found again by every workgroup (see k_fwd_hi_quant).
+template <int R, bool CFOLD, bool FIND = false, class A>
 __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_t wk, const float* xw,
-                                              SmemQuant& sm) {
+                                              SmemQuant& sm, SmemRange* smr = nullptr) {
   float* const lds = sm.lds;
   uint4* const lut = reinterpret_cast<uint4*>(sm.lut);
   QuantScalars* const sQ = reinterpret_cast<QuantScalars*>(sm.sQ);
@@ -558,9 +607,16 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
     float4 x[4];
     hi_issue_loads<R>(xw, g, t, x);             // tile loads first: everything below overlaps their latency
     build_quant_lut(a, lut, t);
+    float found = 0.f;
+    if constexpr (FIND) {
+      const uint64_t blk = g.base >> a.L;
+      if constexpr (R > 3) found = block_range(a.partials, a.pstride, a.n, 1u << R, blk, a.t_p, a.L, *smr);
+      else if (t < 64) found = small_block_range(a.partials, a.pstride, a.n, 1u << R, blk, a.t_p, a.L);
+      if (t == 0 && wk == 0 && g.base == blk << a.L) a.range_out[blk] = found;
+    }
     if (t == 0) {                               // the whole tile lies in one block
       const uint64_t blk = g.base >> a.L;
-      const float M = a.range_M[blk], m = lower_of(a.range_m, blk, M);
+      const float M = FIND ? found : a.range_M[blk], m = FIND ? -M : lower_of(a.range_m, blk, M);
       bool careful;
       sQ[0] = quant_scalars(M, m, a.g, a.lut[a.g - 1], a.c, CFOLD, careful);
       sCare[0] = careful;
@@ -589,13 +645,26 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
     build_quant_lut(a, lut, t);
     // per-block scalars; a tile spans more than one block only when B < 8192 (then R == 0)
     const int nblk = a.L < LOG_TILE ? (TILE >> a.L) : 1;
-    if (t < nblk) {
-      const uint64_t blk = (g.base >> a.L) + t;
+    const int bt0 = FIND ? t >> 6 : t;          // FIND: a wave per block
+    if (bt0 < nblk) {
+      const uint64_t blk = (g.base >> a.L) + bt0;
       float M = 0.f, m = 0.f;
-      if (blk < (a.d >> a.L)) { M = a.range_M[blk]; m = lower_of(a.range_m, blk, M); }
+      if (blk < (a.d >> a.L)) {
+        if constexpr (FIND) {
+          M = small_block_range(a.partials, a.pstride, a.n, 1u << (a.L - a.L1), blk, a.t_p, a.L);
+          m = -M;
+          if ((t & 63) == 0 && wk == 0 && (a.L < LOG_TILE || g.base == blk << a.L)) a.range_out[blk] = M;
+        } else {
+          M = a.range_M[blk];
+          m = lower_of(a.range_m, blk, M);
+        }
+      }
       bool careful;
-      sQ[t] = quant_scalars(M, m, a.g, a.lut[a.g - 1], a.c, false, careful);
-      sCare[t] = careful;
+      const QuantScalars s = quant_scalars(M, m, a.g, a.lut[a.g - 1], a.c, false, careful);
+      if (!FIND || (t & 63) == 0) {
+        sQ[bt0] = s;
+        sCare[bt0] = careful;
+      }
     }
     hi_load_to_lds<R>(xw, g, a.d, lds, t);
     lds_stages<LOG_TILE - R, LOG_TILE, false, PLAIN>(lds, t, [](int, int, float) {});
@@ -620,10 +689,18 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
   }
 }
 
-template <int R, bool CFOLD>
-__global__ __launch_bounds__(NT, 8) void k_fwd_hi_quant(const QuantArgs a) {
+// FIND: the pass takes the place of the range kernel before it.  In a small call a launch of its own costs more than
+// the work: the workgroups of a block all add up the block's partial sums, which the cache holds.
+template <int R, bool CFOLD, bool FIND>
+__global__ __launch_bounds__(NT, FIND ? 4 : 8) void k_fwd_hi_quant(const QuantArgs a) {
   __shared__ SmemQuant sm;
-  hi_quant_tile<R, CFOLD>(a, blockIdx.x, blockIdx.y, a.x + (uint64_t)blockIdx.y * a.d, sm);
+  const float* const xw = a.x + (uint64_t)blockIdx.y * a.d;
+  if constexpr (FIND) {
+    __shared__ SmemRange smr;
+    hi_quant_tile<R, CFOLD, true>(a, blockIdx.x, blockIdx.y, xw, sm, &smr);
+  } else {
+    hi_quant_tile<R, CFOLD>(a, blockIdx.x, blockIdx.y, xw, sm);
+  }
 }
 
 }  // namespace thc

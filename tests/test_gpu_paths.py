@@ -80,3 +80,28 @@ def test_tiles_of_2_to_the_15(log2_block, K, n, b, g, agg_bits, bf16, ef, order)
             e.copy_(make_grads(block, 1, 2e-4, seed=90 + i)[0])
         efs = [e.cpu().numpy() for e in R.efs]
     _round_against_oracle(P, L, R, make_grads(block, n, seed=log2_block, bf16=bf16), 3, efs)
+
+
+@pytest.mark.parametrize("log2_block,K,n,b,g,order", [
+    (10, 1, 1, 3, 21, 0), (10, 13, 3, 4, 30, 0), (12, 7, 10, 3, 21, 0), (13, 5, 64, 2, 3, 0), (14, 3, 4, 4, 30, 0),
+    (15, 1, 5, 3, 31, 1), (16, 2, 33, 2, 3, 1), (17, 3, 2, 3, 21, 1), (19, 1, 7, 1, 1, 0), (20, 1, 10, 3, 21, 1),
+    (21, 1, 3, 4, 30, 0), (22, 1, 2, 3, 21, 1), (20, 16, 1, 4, 30, 1), (20, 17, 1, 4, 30, 1)])
+def test_range_found_by_the_last_pass(log2_block, K, n, b, g, order):
+    """Small calls: the quantizer adds the norms up itself.  The range is that of thc_prepare_range and the streams are
+    those of thc_compress, bit for bit (16 and 17 blocks of 2^20 lie on either side of the rule), and both are the oracle's."""
+    block = 1 << log2_block
+    agg_bits = 8 if g * n < 256 else 16
+    P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, order=order)
+    x = make_grads(block * K, n, seed=log2_block + K)
+    dg = [v.to(DEV) for v in x]
+    A, B = GpuRound(L), GpuRound(L)
+    A.compress_all(9, dg)
+    B.prepare(dg)
+    B.compress_each(9, dg)
+    assert torch.equal(A.range_M, B.range_M)
+    for p, q in zip(A.packed, B.packed):
+        assert torch.equal(p, q)
+    M, gn = A.range_M.cpu().numpy(), [to_np32(v) for v in x]
+    M_ref = o.prepare_range(P, gn)
+    assert np.all(np.abs(M - M_ref) <= np.abs(M_ref) * 2.0 ** -23)
+    assert_indices_match(A.packed[n - 1].cpu().numpy(), o.compress(P, n - 1, 9, gn[n - 1], None, M)[0], b)
