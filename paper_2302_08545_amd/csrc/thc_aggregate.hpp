@@ -6,74 +6,140 @@
 namespace thc {
 
 // ---------------------------------------------------------------------------------------------
-// Aggregation (Alg. 2: Y = sum_i T[Z_i]; the PS only looks up and adds).  Generic path: one thread
-// owns 16 consecutive coordinates of every stream; table in LDS.
+// Aggregation (Alg. 2: Y = sum_i T[Z_i]; the PS only looks up and adds).  Index widths without a kernel of their own
+// below, sums of any width.
+//
+// One thread owns 32 coordinates: exactly B dwords of every stream, whatever B, read as dwords and in batches of four
+// workers, because a small call has too few wavefronts to hide one load latency after another.  Up to 3 bits the table
+// is two registers and four indices are looked up per byte permute, byte-wise sums widened every `chunk` = floor(255 / g)
+// workers; wider tables sit in LDS.
 // ---------------------------------------------------------------------------------------------
 struct AggArgs {
   PtrArr packed;
-  void* out;
-  uint64_t d;
-  uint32_t n, b, agg_bits;
+  uint8_t* out;
+  uint64_t nvec;    // d / 32
+  uint32_t n, agg_bits, chunk;
+  uint32_t tb[2];   // table bytes 0..7, little endian (B <= 3)
   uint8_t table[256];
 };
 
-__global__ __launch_bounds__(256) void k_aggregate_generic(const AggArgs a) {
-  __shared__ uint32_t tab[256];
-  tab[threadIdx.x] = a.table[threadIdx.x];
-  __syncthreads();
-  const uint64_t j = ((uint64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-  if (j >= a.d) return;
-  uint32_t acc[16];
+// B bits at bit `pos` (a constant) of a thread's B dwords, with whatever follows them in the upper bits
+template <int B>
+__device__ __forceinline__ uint32_t bits_at(const uint32_t (&w)[B], int pos, int len) {
+  const int k = pos >> 5, sh = pos & 31;
+  return sh + len > 32 ? __builtin_amdgcn_alignbit(w[k + 1 < B ? k + 1 : k], w[k], sh) : w[k] >> sh;
+}
+
+// four consecutive fields of B <= 3 bits, one to a byte
+template <int B>
+__device__ __forceinline__ uint32_t spread4(uint32_t x) {
+  constexpr uint32_t pair = ((1u << (2 * B)) - 1u) * 0x00010001u, one = ((1u << B) - 1u) * 0x01010101u;
+  x &= (1u << (4 * B)) - 1u;
+  x = (x | x << (16 - 2 * B)) & pair;
+  return (x | x << (8 - B)) & one;
+}
+
+// Writes a thread's 32 sums, acc[m] = those of coordinates 2m (low half) and 2m + 1 (high half).  Widths other than 8
+// and 16 go through LDS, `stage` holding 256 * 16 dwords, so that the workgroup writes consecutive 16-byte vectors; all of its
+// threads take part, those with `own` false hold no coordinates.
+__device__ __forceinline__ void store_sums32(const uint32_t (&acc)[16], uint32_t bits, uint8_t* out, uint64_t v0,
+                                             uint64_t nvec, bool own, uint32_t* stage) {
+  const uint32_t t = threadIdx.x;
+  if (bits == 8 || bits == 16) {
+    if (!own) return;
+    uint4* const dst = reinterpret_cast<uint4*>(out + (v0 + t) * 4 * bits);
+    if (bits == 16) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0;
-  for (uint32_t i = 0; i < a.n; ++i) {
-    const uint8_t* s8 = static_cast<const uint8_t*>(a.packed.p[i]);
-    if (a.b == 4) {
-      const uint2 r = *reinterpret_cast<const uint2*>(s8 + (j >> 1));
-      const uint32_t w[2] = {r.x, r.y};
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] += tab[(w[e >> 3] >> (4 * (e & 7))) & 15u];
-    } else if (a.b == 2) {
-      const uint32_t w = *reinterpret_cast<const uint32_t*>(s8 + (j >> 2));
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] += tab[(w >> (2 * e)) & 3u];
-    } else if (a.b == 8) {
-      const uint4 r = *reinterpret_cast<const uint4*>(s8 + j);
-      const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] += tab[(w[e >> 2] >> (8 * (e & 3))) & 255u];
-    } else if (a.b == 1) {
-      const uint32_t w = *reinterpret_cast<const uint16_t*>(s8 + (j >> 3));
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] += tab[(w >> e) & 1u];
+      for (int k = 0; k < 4; ++k) dst[k] = make_uint4(acc[4 * k], acc[4 * k + 1], acc[4 * k + 2], acc[4 * k + 3]);
     } else {
-      uint32_t z0[8], z1[8];
-      load_fields8(s8 + (j >> 3) * a.b, a.b, z0);
-      load_fields8(s8 + ((j >> 3) + 1) * a.b, a.b, z1);
+      uint32_t o[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { acc[e] += tab[z0[e]]; acc[8 + e] += tab[z1[e]]; }
+      for (int k = 0; k < 8; ++k) o[k] = __builtin_amdgcn_perm(acc[2 * k + 1], acc[2 * k], 0x06040200u);
+      dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
+      dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
+    }
+    return;
+  }
+  uint64_t w = 0;
+  uint32_t fill = 0, k = 0;                 // uniform: the fields' places do not depend on the thread
+#pragma unroll
+  for (int e = 0; e < 32; ++e) {
+    const uint32_t f = (e & 1) ? acc[e >> 1] >> 16 : acc[e >> 1] & 0xFFFFu;
+    w |= (uint64_t)f << fill;
+    fill += bits;
+    if (fill >= 32) {
+      stage[t * bits + k] = (uint32_t)w;
+      w >>= 32;
+      fill -= 32;
+      ++k;
     }
   }
-  uint8_t* out = static_cast<uint8_t*>(a.out);
-  if (a.agg_bits == 8) {
-    uint32_t w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = acc[4 * k] | acc[4 * k + 1] << 8 | acc[4 * k + 2] << 16 | acc[4 * k + 3] << 24;
-    *reinterpret_cast<uint4*>(out + j) = make_uint4(w[0], w[1], w[2], w[3]);
-  } else if (a.agg_bits == 16) {
-    uint32_t w[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = acc[2 * k] | acc[2 * k + 1] << 16;
-    uint4* o = reinterpret_cast<uint4*>(out + 2 * j);
-    o[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    o[1] = make_uint4(w[4], w[5], w[6], w[7]);
-  } else {   // exact-width sums (Sec. 8.4: ceil(log2(g n + 1)) bits are enough)
-    uint32_t z0[8], z1[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { z0[e] = acc[e]; z1[e] = acc[8 + e]; }
-    store_fields8(out + (j >> 3) * a.agg_bits, z0, a.agg_bits);
-    store_fields8(out + ((j >> 3) + 1) * a.agg_bits, z1, a.agg_bits);
+  __syncthreads();
+  const uint64_t left = nvec - v0;
+  const uint32_t nvec4 = (uint32_t)(left < 256 ? left : 256) * bits / 4;   // whole: nvec is a multiple of 32
+  uint4* const dst = reinterpret_cast<uint4*>(out + v0 * 4 * bits);
+  for (uint32_t i = t; i < nvec4; i += 256) dst[i] = reinterpret_cast<const uint4*>(stage)[i];
+}
+
+template <int B>
+__global__ __launch_bounds__(256) void k_aggregate_any(const AggArgs a) {
+  __shared__ __align__(16) uint32_t stage[256 * 16];
+  __shared__ uint32_t tab[B > 3 ? 1 << B : 1];
+  const uint32_t t = threadIdx.x;
+  if constexpr (B > 3) {
+    if (t < (1u << B)) tab[t] = a.table[t];
+    __syncthreads();
   }
+  const uint64_t v0 = (uint64_t)blockIdx.x * 256, v = v0 + t;
+  const bool own = v < a.nvec;
+  uint32_t acc[16];
+#pragma unroll
+  for (int m = 0; m < 16; ++m) acc[m] = 0;
+  if (own) {
+    uint32_t by[8];                         // B <= 3: sums of four consecutive coordinates to a register
+    uint32_t run = 0;                       // workers in them
+#pragma unroll
+    for (int k = 0; k < 8; ++k) by[k] = 0;
+    auto widen = [&] {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        acc[2 * k] += __builtin_amdgcn_perm(0u, by[k], 0x0C010C00u);
+        acc[2 * k + 1] += __builtin_amdgcn_perm(0u, by[k], 0x0C030C02u);
+        by[k] = 0;
+      }
+      run = 0;
+    };
+    auto add = [&](const uint32_t (&w)[B]) {
+      if constexpr (B <= 3) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          by[k] += __builtin_amdgcn_perm(a.tb[1], a.tb[0], spread4<B>(bits_at<B>(w, 4 * B * k, 4 * B)));
+        if (++run == a.chunk) widen();
+      } else {
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+          const uint32_t lo = tab[bits_at<B>(w, 2 * B * m, B) & ((1u << B) - 1u)];
+          const uint32_t hi = tab[bits_at<B>(w, 2 * B * m + B, B) & ((1u << B) - 1u)];
+          acc[m] += lo | hi << 16;
+        }
+      }
+    };
+    for (uint32_t i0 = 0; i0 < a.n; i0 += 4) {
+      uint32_t w[4][B];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        const uint32_t i = i0 + u < a.n ? i0 + u : i0;          // past the end: a load that is not used
+        const uint32_t* const p = static_cast<const uint32_t*>(a.packed.p[i]) + v * B;
+#pragma unroll
+        for (int k = 0; k < B; ++k) w[u][k] = p[k];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u)
+        if (i0 + u < a.n) add(w[u]);
+    }
+    if constexpr (B <= 3) widen();
+  }
+  store_sums32(acc, a.agg_bits, a.out, v0, a.nvec, own, stage);
 }
 
 // 4-bit indices -> 8-bit sums, the paper's prototype widths (Sec. 3).  One thread owns 32 coordinates
@@ -101,15 +167,23 @@ __global__ __launch_bounds__(256) void k_aggregate_b4w8(const AggB4Args a) {
   if (v >= a.nvec) return;
   const uint32_t tb[4] = {a.tb[0], a.tb[1], a.tb[2], a.tb[3]};
   uint32_t ev[4] = {0, 0, 0, 0}, od[4] = {0, 0, 0, 0};
-  for (uint32_t i = 0; i < a.n; ++i) {
-    const uint4 r = reinterpret_cast<const uint4*>(a.packed.p[i])[v];
+  auto add = [&](const uint4 r) {
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       ev[k] += lut16x4(w[k] & 0x0F0F0F0Fu, tb);          // coordinates 8k + 0, 2, 4, 6
       od[k] += lut16x4((w[k] >> 4) & 0x0F0F0F0Fu, tb);   // coordinates 8k + 1, 3, 5, 7
     }
+  };
+  uint32_t i = 0;
+  for (; i + 4 <= a.n; i += 4) {           // four loads in flight: a small call has few wavefronts to hide them
+    uint4 r[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) r[u] = reinterpret_cast<const uint4*>(a.packed.p[i + u])[v];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) add(r[u]);
   }
+  for (; i < a.n; ++i) add(reinterpret_cast<const uint4*>(a.packed.p[i])[v]);
   uint32_t o[8];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {

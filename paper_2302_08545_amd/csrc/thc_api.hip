@@ -781,14 +781,20 @@ int thc_aggregate(const thc_params* p, const uint8_t* const* packed, void* agg_o
   } else {
     AggArgs a{};
     for (uint32_t i = 0; i < p->n; ++i) a.packed.p[i] = packed[i];
-    a.out = agg_out;
-    a.d = p->d;
+    a.out = static_cast<uint8_t*>(agg_out);
+    a.nvec = p->d / 32;
     a.n = p->n;
-    a.b = p->b;
     a.agg_bits = p->agg_bits;
+    a.chunk = 255u / p->g;              // g <= 255, so at least one worker per run
+    std::memcpy(a.tb, p->table, 8);
     std::memcpy(a.table, p->table, 256);
-    const uint64_t threads = p->d / 16;
-    k_aggregate_generic<<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s>>>(a);
+    const dim3 grid((unsigned)((a.nvec + 255) / 256)), blk(256);
+    switch (p->b) {
+#define THC_AGG_ANY(B) case B: k_aggregate_any<B><<<grid, blk, 0, s>>>(a); break;
+      THC_AGG_ANY(1) THC_AGG_ANY(2) THC_AGG_ANY(3) THC_AGG_ANY(5) THC_AGG_ANY(6) THC_AGG_ANY(7) THC_AGG_ANY(8)
+#undef THC_AGG_ANY
+      default: return THC_EINVAL;       // 4-bit indices have kernels of their own
+    }
   }
   return check_launch();
 }

@@ -471,7 +471,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_quant(const BigQuantArgs a) {
     const uint4 rnd = philox4x32_10(qlo | (so >> 3), qhi, a.round, stream, a.k0, a.k1);
     uint32_t z[8];
     quantize8<mulc.value, care.value>(v[k], rnd, s, lut, z);
-    store_packed8(packed, to + so, a.b, z);
+    store_packed8<false>(packed, to + so, a.b, z);
     __builtin_amdgcn_sched_barrier(0);   // one step's draws at a time: interleaved steps would not fit the registers
   };
   if (!careful) {

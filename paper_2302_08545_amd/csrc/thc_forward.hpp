@@ -522,6 +522,9 @@ __device__ __forceinline__ uint32_t pack8(const uint32_t (&z)[8]) {
   return w;
 }
 
+// QUAD: aligned groups of four lanes hold 32 consecutive coordinates, all of them or none active.  3-bit indices then
+// leave as dwords instead of bytes (the sweep's round of 2^20 coordinates, 10 workers, with k_aggregate_any: 63 to 46 us).
+template <bool QUAD = true>
 __device__ __forceinline__ void store_packed8(uint8_t* packed, uint64_t j, uint32_t b, const uint32_t (&z)[8]) {
   if (b == 4) {
     *reinterpret_cast<uint32_t*>(packed + (j >> 1)) = pack8<4>(z);
@@ -533,6 +536,11 @@ __device__ __forceinline__ void store_packed8(uint8_t* packed, uint64_t j, uint3
     *reinterpret_cast<uint2*>(packed + j) = make_uint2(w0, w1);
   } else if (b == 1) {
     packed[j >> 3] = (uint8_t)pack8<1>(z);
+  } else if (QUAD && b == 3) {
+    // four lanes hold three dwords: lane q < 3 takes the rest of its own 24 bits and the start of the next lane's
+    const uint32_t w = pack8<3>(z), q = threadIdx.x & 3u;
+    const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x39, 0xF, 0xF, true);   // lanes 1, 2, 3, 0
+    if (q < 3) *reinterpret_cast<uint32_t*>(packed + (j >> 3) * 3 + q) = w >> (8 * q) | next << (24 - 8 * q);
   } else {
     store_fields8(packed + (j >> 3) * b, z, b);
   }
@@ -590,7 +598,8 @@ struct alignas(16) SmemQuant {
 
 // One tile of the pass: tile index `tile` of the launch's vector `wk`, whose half-rotated image starts at xw.
 // FIND: the range comes from the partial sums of squares, found again by every workgroup (see k_fwd_hi_quant).
-template <int R, bool CFOLD, bool FIND = false, class A>
+// QUAD: see store_packed8; off where its registers would spill.
+template <int R, bool CFOLD, bool FIND = false, bool QUAD = false, class A>
 __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_t wk, const float* xw,
                                               SmemQuant& sm, SmemRange* smr = nullptr) {
   float* const lds = sm.lds;
@@ -638,7 +647,7 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
       uint32_t z[8];
       if (!careful) quantize8<!CFOLD>(v[h], rnd, s, lut, z);
       else quantize8<true, true>(v[h], rnd, s, lut, z);
-      store_packed8(pk0, o, a.b, z);
+      store_packed8<QUAD && HiGeom<R>::W >= 32>(pk0, o, a.b, z);
     }
   } else {
     const HiGeom<R> g(tile, a.tm);
@@ -684,7 +693,7 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
       uint32_t z[8];
       if (!sCare[bt]) quantize8<true>(hv, rnd, s, lut, z);
       else quantize8<true, true>(hv, rnd, s, lut, z);
-      store_packed8(packed, j, a.b, z);
+      store_packed8<QUAD>(packed, j, a.b, z);
     }
   }
 }
@@ -697,9 +706,9 @@ __global__ __launch_bounds__(NT, FIND ? 4 : 8) void k_fwd_hi_quant(const QuantAr
   const float* const xw = a.x + (uint64_t)blockIdx.y * a.d;
   if constexpr (FIND) {
     __shared__ SmemRange smr;
-    hi_quant_tile<R, CFOLD, true>(a, blockIdx.x, blockIdx.y, xw, sm, &smr);
+    hi_quant_tile<R, CFOLD, true, true>(a, blockIdx.x, blockIdx.y, xw, sm, &smr);
   } else {
-    hi_quant_tile<R, CFOLD>(a, blockIdx.x, blockIdx.y, xw, sm);
+    hi_quant_tile<R, CFOLD, false, true>(a, blockIdx.x, blockIdx.y, xw, sm);
   }
 }
 

@@ -105,3 +105,22 @@ def test_range_found_by_the_last_pass(log2_block, K, n, b, g, order):
     M_ref = o.prepare_range(P, gn)
     assert np.all(np.abs(M - M_ref) <= np.abs(M_ref) * 2.0 ** -23)
     assert_indices_match(A.packed[n - 1].cpu().numpy(), o.compress(P, n - 1, 9, gn[n - 1], None, M)[0], b)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 8, 13])
+@pytest.mark.parametrize("b,g", [(1, 1), (1, 100), (2, 8), (2, 255), (3, 21), (3, 255), (4, 17), (5, 40), (6, 63),
+                                 (7, 127), (8, 255)])
+def test_sums_of_any_width(b, g, n):
+    """Exact width, 8 bits where they fit, and 16; 33 * 1024 coordinates leave the last workgroup mostly empty."""
+    block, K = 1 << 10, 33
+    T = [round(i * g / ((1 << b) - 1)) for i in range(1 << b)]
+    exact = (g * n).bit_length()
+    pk = np.random.default_rng(n * 256 + g).integers(0, 256, (n, block * K * b // 8), dtype=np.uint8)
+    pk[:, :64] = 255                              # sums of g * n
+    for agg_bits in sorted({exact, max(exact, 8), 16}):
+        P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, table=T)
+        R = GpuRound(L)
+        for i in range(n):
+            R.packed[i].copy_(torch.from_numpy(pk[i]))
+        R.aggregate()
+        assert np.array_equal(R.agg_numpy(), o.aggregate(P, list(pk)))
