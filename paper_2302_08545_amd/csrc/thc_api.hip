@@ -204,7 +204,9 @@ template <int R> struct LaunchQuant {
   }
 };
 template <int R> struct LaunchHiStore {
-  static void run(const HiStoreArgs& a, uint64_t tiles, hipStream_t s) { k_fwd_hi_store<R><<<dim3((unsigned)tiles), dim3(NT), 0, s>>>(a); }
+  static void run(const HiStoreArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
+    k_fwd_hi_store<R><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+  }
 };
 template <int R> struct LaunchInvHi {
   static void run(const InvHiArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
@@ -902,7 +904,6 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
   hipStream_t s = static_cast<hipStream_t>(stream);
   float* pmin = pmin_of(p, rotate, ws);
   float* pmax = pmin + partial_count(p, pl);
-  const size_t per_worker = (size_t)(p->d >> pl.L1);
   const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
   if (rotate) {
     // full forward RHT of every worker, kept in the workspace
@@ -920,12 +921,9 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.tm = lo_tilemap(pl, p->d);
     launch_fwd_lo(pl, a, bf16, ef != nullptr, false, tiles_of(p->d), p->n, s);
     run_mids(pl, static_cast<float*>(ws), p->d, p->n, s);
-    for (uint32_t i = 0; i < p->n; ++i) {
-      float* wsx = static_cast<float*>(ws) + (size_t)i * p->d;
-      HiStoreArgs h{wsx, pmin + i * per_worker, pmax + i * per_worker, p->d, pl.hi, (uint32_t)pl.L,
-                    (float)(1.0 / std::sqrt((double)p->block))};
-      dispatch_0_9<LaunchHiStore>(pl.R, h, tiles_of(p->d), s);
-    }
+    const HiStoreArgs h{static_cast<float*>(ws), pmin, pmax, p->d, p->d >> pl.L1, pl.hi, (uint32_t)pl.L,
+                        (float)(1.0 / std::sqrt((double)p->block))};
+    dispatch_0_9<LaunchHiStore>(pl.R, h, tiles_of(p->d), p->n, s);
   } else {
     MinMaxArgs a{};
     for (uint32_t i = 0; i < p->n; ++i) {

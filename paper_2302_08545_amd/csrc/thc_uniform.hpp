@@ -101,10 +101,10 @@ __global__ __launch_bounds__(64) void k_minmax_final(const MinMaxFinalArgs a) {
 // Last strided pass of a forward RHT that keeps the rotated vector: finishes the butterflies, scales by
 // 1/sqrt(B), writes the result back in place and records the tile's minimum and maximum.
 struct HiStoreArgs {
-  float* x;          // one worker's half-rotated vector, d floats, rotated in place
-  float* pmin;       // this worker's partial minima, d >> L1 floats
+  float* x;          // half-rotated vectors, d floats per worker of the launch (grid.y), rotated in place
+  float* pmin;       // partial minima, `pstride` = d >> L1 floats per worker
   float* pmax;
-  uint64_t d;
+  uint64_t d, pstride;
   TileMap tm;
   uint32_t L;
   float c;
@@ -116,8 +116,11 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
   __shared__ float smin[16], smax[16];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const HiGeom<R> g(blockIdx.x, a.tm);
+  float* const x = a.x + (uint64_t)blockIdx.y * a.d;
+  float* const pmin = a.pmin + (uint64_t)blockIdx.y * a.pstride;
+  float* const pmax = a.pmax + (uint64_t)blockIdx.y * a.pstride;
   if constexpr (R >= 2) {
-    hi_front<R>(a.x, g, lds, t);
+    hi_front<R>(x, g, lds, t);
     int idx[2];
     float v[2][8];
     hi_back<R>(lds, t, idx, v);
@@ -130,7 +133,7 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
         mn = __builtin_fminf(mn, v[h][e]);
         mx = __builtin_fmaxf(mx, v[h][e]);
       }
-      float* o = a.x + g.coord(idx[h]);
+      float* o = x + g.coord(idx[h]);
       *reinterpret_cast<float4*>(o) = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
       *reinterpret_cast<float4*>(o + 4) = make_float4(v[h][4], v[h][5], v[h][6], v[h][7]);
     }
@@ -140,11 +143,11 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
     __syncthreads();
     if (t == 0) {   // the whole tile lies in one block: one partial per tile
       for (int w = 1; w < 8; ++w) { mn = __builtin_fminf(mn, smin[w]); mx = __builtin_fmaxf(mx, smax[w]); }
-      a.pmin[blockIdx.x] = mn;
-      a.pmax[blockIdx.x] = mx;
+      pmin[blockIdx.x] = mn;
+      pmax[blockIdx.x] = mx;
     }
   } else {
-    hi_load_to_lds<R>(a.x, g, a.d, lds, t);
+    hi_load_to_lds<R>(x, g, a.d, lds, t);
     lds_stages<LOG_TILE - R, LOG_TILE, false, PLAIN>(lds, t, [](int, int, float) {});
     __syncthreads();
     // thread owns tile indices [8(t + 512h), +8): a wave covers 512 consecutive values per h
@@ -158,8 +161,8 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
         float4 p1 = *reinterpret_cast<const float4*>(&lds[idx + 4]);
         p0.x *= a.c; p0.y *= a.c; p0.z *= a.c; p0.w *= a.c;
         p1.x *= a.c; p1.y *= a.c; p1.z *= a.c; p1.w *= a.c;
-        *reinterpret_cast<float4*>(a.x + j) = p0;
-        *reinterpret_cast<float4*>(a.x + j + 4) = p1;
+        *reinterpret_cast<float4*>(x + j) = p0;
+        *reinterpret_cast<float4*>(x + j + 4) = p1;
         mn = __builtin_fminf(__builtin_fminf(__builtin_fminf(p0.x, p0.y), __builtin_fminf(p0.z, p0.w)),
                              __builtin_fminf(__builtin_fminf(p1.x, p1.y), __builtin_fminf(p1.z, p1.w)));
         mx = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(p0.x, p0.y), __builtin_fmaxf(p0.z, p0.w)),
@@ -180,7 +183,7 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
         mx = __builtin_fmaxf(mx, smax[t * cpb + c]);
       }
       const uint64_t pidx = ((uint64_t)blockIdx.x << (LOG_TILE - L1)) + t;
-      if (pidx < (a.d >> L1)) { a.pmin[pidx] = mn; a.pmax[pidx] = mx; }
+      if (pidx < (a.d >> L1)) { pmin[pidx] = mn; pmax[pidx] = mx; }
     }
   }
 }
