@@ -258,15 +258,8 @@ void launch_range(const RangeArgs& r, hipStream_t s) {
 
 void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)tiles, W), blk(NT);
-  switch (pl.L1) {
-    case 10: k_inv_lo<10, false><<<grid, blk, 0, s>>>(a); break;
-    case 11: k_inv_lo<11, false><<<grid, blk, 0, s>>>(a); break;
-    case 12: k_inv_lo<12, false><<<grid, blk, 0, s>>>(a); break;
-    default:
-      if (pl.split) k_inv_lo<13, true><<<grid, blk, 0, s>>>(a);
-      else k_inv_lo<13, false><<<grid, blk, 0, s>>>(a);
-      break;
-  }
+  if (pl.split) k_inv_lo<true><<<grid, blk, 0, s>>>(a);
+  else k_inv_lo<false><<<grid, blk, 0, s>>>(a);
 }
 
 // The quantizer finds the range itself in calls of up to this many workgroups (and no middle pass: its blocks have too
@@ -366,6 +359,32 @@ void run_mids(const Plan& pl, float* x, uint64_t d, uint32_t W, hipStream_t s) {
   }
 }
 
+// Blocks of up to 2^15 coordinates: the inverse transform in one launch.
+template <int L1>
+void launch_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_t s) {
+  const dim3 grid((unsigned)tiles_of(a.lo.d), W), blk(NT);
+  if (efm == 0) k_inv_whole<L1, 0><<<grid, blk, 0, s>>>(a);
+  else if (efm == 1) k_inv_whole<L1, 1><<<grid, blk, 0, s>>>(a);
+  else k_inv_whole<L1, 2><<<grid, blk, 0, s>>>(a);
+}
+
+template <int L>
+void launch_big_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_t s) {
+  const dim3 grid((unsigned)((a.lo.d + BIG - 1) >> LOG_BIG), W), blk(NT);
+  const uint32_t bits = a.lo.src_bits;
+  if (efm == 0) {
+    if (bits == 8) k_big_inv_whole<L, 8, 0><<<grid, blk, 0, s>>>(a);
+    else if (bits == 16) k_big_inv_whole<L, 16, 0><<<grid, blk, 0, s>>>(a);
+    else k_big_inv_whole<L, 0, 0><<<grid, blk, 0, s>>>(a);
+  } else if (efm == 1) {
+    if (bits == 4) k_big_inv_whole<L, 4, 1><<<grid, blk, 0, s>>>(a);
+    else k_big_inv_whole<L, 0, 1><<<grid, blk, 0, s>>>(a);
+  } else {
+    if (bits == 4) k_big_inv_whole<L, 4, 2><<<grid, blk, 0, s>>>(a);
+    else k_big_inv_whole<L, 0, 2><<<grid, blk, 0, s>>>(a);
+  }
+}
+
 // inverse transform of W vectors of `len` coordinates that k_inv_lo is about to produce in `wsx`
 void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, InvHiArgs hi, uint64_t len, uint32_t W,
                  hipStream_t s) {
@@ -381,13 +400,34 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
   lo.tm = lo_tilemap(pl, len);
   lo.ws_x = wsx;
   lo.d = len;
+  if (pl.L <= LOG_BIG) {
+    const InvWholeArgs a{lo, hi.out, hi.grad, hi.j0, hi.round, hi.k0, hi.k1, (float)(1.0 / std::sqrt((double)p->block))};
+    const int efm = hi.mode == 0 ? 0 : hi.bf16 ? 2 : 1;
+    switch (pl.L) {
+      case 10: launch_inv_whole<10>(a, efm, W, s); break;
+      case 11: launch_inv_whole<11>(a, efm, W, s); break;
+      case 12: launch_inv_whole<12>(a, efm, W, s); break;
+      case 13: launch_inv_whole<13>(a, efm, W, s); break;
+      case 14: launch_big_inv_whole<14>(a, efm, W, s); break;
+      default: launch_big_inv_whole<15>(a, efm, W, s); break;
+    }
+    return;
+  }
   launch_inv_lo(pl, lo, tiles_of(len), W, s);
   run_mids(pl, wsx, len, W, s);
   hi.x = wsx;
   hi.d = len;
   hi.tm = pl.hi;
   hi.c = (float)(1.0 / std::sqrt((double)p->block));
-  dispatch_0_9<LaunchInvHi>(pl.R, hi, tiles_of(len), W, s);
+  switch (pl.R) {   // blocks of 2^16 and more: 3 bits at least
+    case 3: LaunchInvHi<3>::run(hi, tiles_of(len), W, s); break;
+    case 4: LaunchInvHi<4>::run(hi, tiles_of(len), W, s); break;
+    case 5: LaunchInvHi<5>::run(hi, tiles_of(len), W, s); break;
+    case 6: LaunchInvHi<6>::run(hi, tiles_of(len), W, s); break;
+    case 7: LaunchInvHi<7>::run(hi, tiles_of(len), W, s); break;
+    case 8: LaunchInvHi<8>::run(hi, tiles_of(len), W, s); break;
+    default: LaunchInvHi<9>::run(hi, tiles_of(len), W, s); break;
+  }
 }
 
 // Worker side of one round (Alg. 3) for W co-resident vectors, group by group:

@@ -54,8 +54,8 @@ constexpr int BIG_LDS = bphys(1 << 14);
 constexpr int BIG_SIGN_WORDS = BIG / 32;
 
 // fill(h, x): x[y][0..15] = values p = lane << 4 | wave << 10 | y << 13 | h << 14 + (0..15), before any stage;
-// out(k, v): v belongs to processing index t | k << 9 (t = thread, k < 64, a constant).
-template <class Fill, class Out>
+// out(k, v): v belongs to processing index t | k << 9 (t = thread, k < 64, a constant).  P14 false: no stage p14.
+template <bool P14 = true, class Fill, class Out>
 __device__ __forceinline__ void big_lo_stages(float* lds, int t, Fill&& fill, Out&& out) {
   const int lane = t & 63, wave = t >> 6;
   float* const wp = lds + bphys(lane << 4 | wave << 10);
@@ -88,8 +88,8 @@ __device__ __forceinline__ void big_lo_stages(float* lds, int t, Fill&& fill, Ou
   }
 #pragma unroll
   for (int e = 0; e < 32; ++e) {
-    out(e, u[0][e] + u[1][e]);
-    out(e | 32, u[0][e] - u[1][e]);
+    out(e, P14 ? u[0][e] + u[1][e] : u[0][e]);
+    out(e | 32, P14 ? u[0][e] - u[1][e] : u[1][e]);
   }
 }
 
@@ -704,6 +704,85 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) { g[i] = gn[i]; e[i] = en[i]; }
     }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The whole inverse transform of blocks of 2^14 (two to a tile) or 2^15 in one launch; see k_inv_whole.
+// ---------------------------------------------------------------------------------------------
+struct alignas(16) SmemBigWhole {
+  float lds[BIG_LDS];
+  uint32_t sgn[BIG_SIGN_WORDS];
+  float tabf[2][256];
+};
+
+template <int L, int SB, int EFM>
+__global__ __launch_bounds__(NT, 4) void k_big_inv_whole(const InvWholeArgs a) {
+  static_assert(L == 14 || L == 15, "one or two blocks to a tile");
+  constexpr bool TABLE = EFM != 0;               // error feedback starts from indices, decompression from sums
+  __shared__ SmemBigWhole sm;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t off = (uint64_t)tile << LOG_BIG;
+  const uint32_t tp = lane << 4 | wave << 10;
+  const uint32_t bits = SB ? SB : a.lo.src_bits;
+  const bool two = L == 15 || a.lo.d - off >= BIG;      // false: an odd number of blocks, the last tile holds one
+  const uint8_t* const src = static_cast<const uint8_t*>(a.lo.src.p[vec]) + (off >> 3) * bits;
+  constexpr int NW = SB ? SB / 2 : 1;
+  uint32_t w[4][NW];
+  if constexpr (SB != 0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const uint32_t* const p = reinterpret_cast<const uint32_t*>(src + ((tp + (s << 13)) >> 3) * SB);
+#pragma unroll
+      for (int k = 0; k < NW; ++k) w[s][k] = s < 2 || two ? p[k] : 0u;
+    }
+  }
+  if (t < BIG / 128) {
+    const uint64_t q = (a.j0 + off + 128u * t) >> 7;
+    *reinterpret_cast<uint4*>(&sm.sgn[4 * t]) = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, SIGN_STREAM, a.k0, a.k1);
+  }
+  float lo[2], step[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint64_t blk = (off >> L) + (L == 14 && two ? h : 0);
+    const float M = a.lo.range_M[blk];
+    lo[h] = lower_of(a.lo.range_m, blk, M);
+    step[h] = (float)(((double)M - (double)lo[h]) / (double)a.lo.divisor);
+    if constexpr (TABLE) {
+      if (t < 256) sm.tabf[h][t] = (float)a.lo.table[t] * step[h] + lo[h];
+    }
+  }
+  __syncthreads();
+  float v[8][8];
+  big_lo_stages<L == 15>(
+      sm.lds, t,
+      [&](int h, float (&x)[2][16]) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const int s = 2 * h + y;
+          uint32_t c[16];
+          if constexpr (SB != 0) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) c[e] = (w[s][e * SB / 32] >> (e * SB % 32)) & ((1u << SB) - 1u);
+          } else if (h == 0 || two) {
+            codes16(src, bits, tp + (s << 13), c);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) c[e] = 0;
+          }
+#pragma unroll
+          for (int e = 0; e < 16; ++e) x[y][e] = TABLE ? sm.tabf[h][c[e]] : (float)c[e] * step[h] + lo[h];
+        }
+      },
+      [&](int k, float r) { v[k >> 3][k & 7] = r; });
+  float* const out = static_cast<float*>(const_cast<void*>(a.out.p[vec])) + off + t;
+  const char* const grad = EFM ? static_cast<const char*>(a.grad.p[vec]) + (off + t) * (EFM == 2 ? 2 : 4) : nullptr;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    if (k >= 4 && !two) break;
+    finish_values<EFM>(v[k], a.c, out, grad, [&](int i) { return (uint32_t)(8 * k + i) << 9; },
+                       [&](int i) { return (sm.sgn[(8 * k + i) << 4 | t >> 5] >> (t & 31)) & 1u; });
   }
 }
 

@@ -109,10 +109,10 @@ struct alignas(16) SmemInvLo {
   float tabf[256];
 };
 
-// One tile: tile index `tile` of the launch's vector `vec`; the results go to dst_vec[offset in the vector].
-template <int L1, bool XO, class A>
-__device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t vec, float* dst_vec,
-                                            SmemInvLo& sm) {
+// One tile: tile index `tile` of the launch's vector `vec`; put(o, value) takes each result, o its offset from the
+// tile's first coordinate.
+template <int L1, bool XO, class A, class Put>
+__device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_t vec, SmemInvLo& sm, Put&& put) {
   static_assert(!XO || L1 == LOG_TILE, "the row-split tile needs blocks of at least 2^16");
   constexpr bool GUARD = L1 < LOG_TILE;
   float* const lds = sm.lds;
@@ -196,17 +196,19 @@ __device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t 
   for (int e = 0; e < 16; e += 4)
     *reinterpret_cast<float4*>(&lds[swz(idx + e)]) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
 
-  float* dst = dst_vec + off;
-  const uint64_t left = a.d - off;
-  lds_stages<4, L1, true, SWZ>(lds, t, [&](int base, int eoff, float val) {
-    if (!GUARD || (uint64_t)(base + eoff) < left) dst[lo_map<XO>(base) + lo_map<XO>(eoff)] = val;
-  });
+  lds_stages<4, L1, true, SWZ>(lds, t, [&](int base, int eoff, float val) { put(lo_map<XO>(base) + lo_map<XO>(eoff), val); });
 }
 
-template <int L1, bool XO>
+template <bool XO, class A>
+__device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t vec, float* dst_vec, SmemInvLo& sm) {
+  float* const dst = dst_vec + tm_base(a.tm, tile);
+  inv_lo_stages<LOG_TILE, XO>(a, tile, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
+}
+
+template <bool XO>
 __global__ __launch_bounds__(NT) void k_inv_lo(const InvLoArgs a) {
   __shared__ SmemInvLo sm;
-  inv_lo_tile<L1, XO>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
+  inv_lo_tile<XO>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -240,17 +242,6 @@ __device__ __forceinline__ float4 inv_finish4(float4 v, uint32_t bits, const A& 
   return v;
 }
 
-template <class A>
-__device__ __forceinline__ float4 inv_finish4(float4 v, uint32_t bits, const A& a, const float* out,
-                                              const void* grad, uint64_t j) {
-  float4 x = make_float4(0.f, 0.f, 0.f, 0.f), e = x;
-  if (a.mode == 1) {
-    x = a.bf16 ? load_grad4<true>(grad, j) : load_grad4<false>(grad, j);
-    e = *reinterpret_cast<const float4*>(out + j);
-  }
-  return inv_finish4(v, bits, a, x, e);
-}
-
 struct alignas(16) SmemInvHi {
   float lds[TILE];
   uint32_t sgn[TILE / 32];
@@ -268,69 +259,53 @@ __device__ __forceinline__ void inv_hi_tile(const A& a, uint32_t tile, uint32_t 
   float* const out = static_cast<float*>(const_cast<void*>(a.out.p[vec]));
   const void* const grad = a.grad.p[vec];
 
-  if constexpr (R >= 2) {
-    float4 x[4];
-    hi_issue_loads<R>(xv, g, t, x);
-    // the diagonal's bits while the loads travel
-    // 32 consecutive tile indices are 32 consecutive coordinates, or, with 16-wide rows, two aligned halves
-    if (t < TILE / 32) {
-      if constexpr (HiGeom<R>::W >= 32) {
-        sgn[t] = sign_word(a.j0 + g.coord(32 * t), a.round, a.k0, a.k1);
-      } else {
-        const uint64_t j0 = a.j0 + g.coord(32 * t), j1 = a.j0 + g.coord(32 * t + 16);
-        const uint32_t lo = sign_word(j0 & ~31ull, a.round, a.k0, a.k1) >> (j0 & 31);
-        const uint32_t hi = sign_word(j1 & ~31ull, a.round, a.k0, a.k1) >> (j1 & 31);
-        sgn[t] = (lo & 0xFFFFu) | (hi << 16);
-      }
-    }
-    hi_r0_to_lds<R>(x, lds, t);
-    hi_round1<R>(lds, t);
-    int idx[2];
-    hi_back_index<R>(t, idx);
-    // error-feedback update: the gradient and the buffer's old contents are requested for both halves before
-    // anything is stored (the stores go to that same buffer), and while the tile's last stage runs
-    float4 gx[2][2], ex[2][2];
-    if (a.mode == 1) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint64_t j = g.coord(idx[h]);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          gx[h][k] = a.bf16 ? load_grad4<true>(grad, j + 4 * k) : load_grad4<false>(grad, j + 4 * k);
-          ex[h][k] = *reinterpret_cast<const float4*>(out + j + 4 * k);
-        }
-      }
+  float4 x[4];
+  hi_issue_loads<R>(xv, g, t, x);
+  // the diagonal's bits while the loads travel
+  // 32 consecutive tile indices are 32 consecutive coordinates, or, with 16-wide rows, two aligned halves
+  if (t < TILE / 32) {
+    if constexpr (HiGeom<R>::W >= 32) {
+      sgn[t] = sign_word(a.j0 + g.coord(32 * t), a.round, a.k0, a.k1);
     } else {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        for (int k = 0; k < 2; ++k) gx[h][k] = ex[h][k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      const uint64_t j0 = a.j0 + g.coord(32 * t), j1 = a.j0 + g.coord(32 * t + 16);
+      const uint32_t lo = sign_word(j0 & ~31ull, a.round, a.k0, a.k1) >> (j0 & 31);
+      const uint32_t hi = sign_word(j1 & ~31ull, a.round, a.k0, a.k1) >> (j1 & 31);
+      sgn[t] = (lo & 0xFFFFu) | (hi << 16);
     }
-    float v[2][8];
-    hi_back<R>(lds, t, idx, v);
-    __syncthreads();
+  }
+  hi_r0_to_lds<R>(x, lds, t);
+  hi_round1<R>(lds, t);
+  int idx[2];
+  hi_back_index<R>(t, idx);
+  // error-feedback update: the gradient and the buffer's old contents are requested for both halves before
+  // anything is stored (the stores go to that same buffer), and while the tile's last stage runs
+  float4 gx[2][2], ex[2][2];
+  if (a.mode == 1) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const uint64_t j = g.coord(idx[h]);
-      const uint32_t bits = sgn[idx[h] >> 5] >> (idx[h] & 31);
-      const float4 o0 = inv_finish4(make_float4(v[h][0], v[h][1], v[h][2], v[h][3]), bits, a, gx[h][0], ex[h][0]);
-      const float4 o1 = inv_finish4(make_float4(v[h][4], v[h][5], v[h][6], v[h][7]), bits >> 4, a, gx[h][1], ex[h][1]);
-      *reinterpret_cast<float4*>(out + j) = o0;
-      *reinterpret_cast<float4*>(out + j + 4) = o1;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        gx[h][k] = a.bf16 ? load_grad4<true>(grad, j + 4 * k) : load_grad4<false>(grad, j + 4 * k);
+        ex[h][k] = *reinterpret_cast<const float4*>(out + j + 4 * k);
+      }
     }
   } else {
-    if (t < TILE / 32) sgn[t] = sign_word(a.j0 + g.coord(32 * t), a.round, a.k0, a.k1);
-    hi_load_to_lds<R>(xv, g, a.d, lds, t);
-    lds_stages<LOG_TILE - R, LOG_TILE, false, PLAIN>(lds, t, [](int, int, float) {});
-    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = 4 * (i * NT + t);
-      const uint64_t j = g.coord(idx);
-      if (j >= a.d) continue;
-      const float4 v = *reinterpret_cast<const float4*>(&lds[idx]);
-      const uint32_t bits = sgn[idx >> 5] >> (idx & 31);
-      *reinterpret_cast<float4*>(out + j) = inv_finish4(v, bits, a, out, grad, j);
-    }
+    for (int h = 0; h < 2; ++h)
+      for (int k = 0; k < 2; ++k) gx[h][k] = ex[h][k] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  float v[2][8];
+  hi_back<R>(lds, t, idx, v);
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint64_t j = g.coord(idx[h]);
+    const uint32_t bits = sgn[idx[h] >> 5] >> (idx[h] & 31);
+    const float4 o0 = inv_finish4(make_float4(v[h][0], v[h][1], v[h][2], v[h][3]), bits, a, gx[h][0], ex[h][0]);
+    const float4 o1 = inv_finish4(make_float4(v[h][4], v[h][5], v[h][6], v[h][7]), bits >> 4, a, gx[h][1], ex[h][1]);
+    *reinterpret_cast<float4*>(out + j) = o0;
+    *reinterpret_cast<float4*>(out + j + 4) = o1;
   }
 }
 
@@ -338,6 +313,73 @@ template <int R>
 __global__ __launch_bounds__(NT) void k_inv_hi(const InvHiArgs a) {
   __shared__ SmemInvHi sm;
   inv_hi_tile<R>(a, blockIdx.x, blockIdx.y, a.x + (uint64_t)blockIdx.y * a.d, sm);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Blocks that fit one workgroup (2^10 to 2^13 here, 2^14 and 2^15 in thc_big.hpp): the whole inverse transform in one
+// launch.  What bounds the two passes is bytes and, in small calls, launches: the intermediate's 8 bytes per
+// coordinate and one launch go.  Rounds of 8 workers with error feedback: 4096 blocks of 2^13 2031 -> 1505 us, 512 blocks
+// of 2^15 999 -> 764 us; one block of 2^14 without it 36 -> 25 us.  No size was found where two passes are faster.
+// ---------------------------------------------------------------------------------------------
+// `N` results of a thread: scale, diagonal, and with EFM 1 / 2 (binary32 / bf16 gradient) e <- (grad + e) - that.  All
+// operands are requested before the first store, which goes to the buffer some of them come from.
+template <int EFM, int N, class Off, class Bit>
+__device__ __forceinline__ void finish_values(const float (&v)[N], float c, float* out, const void* grad, Off&& off,
+                                              Bit&& bit) {
+  float x[N], e[N];
+  if constexpr (EFM != 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      x[i] = EFM == 2 ? bf16_to_f32(static_cast<const uint16_t*>(grad)[off(i)]) : static_cast<const float*>(grad)[off(i)];
+      e[i] = out[off(i)];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    float r = flip(v[i] * c, bit(i));
+    if constexpr (EFM != 0) r = (x[i] + e[i]) - r;
+    out[off(i)] = r;
+  }
+}
+
+struct InvWholeArgs {
+  InvLoArgs lo;      // ws_x unused
+  PtrArr out;        // per vector: d floats
+  PtrArr grad;       // per vector, EFM only
+  uint64_t j0;
+  uint32_t round, k0, k1;
+  float c;
+};
+
+template <int L1, int EFM>
+__global__ __launch_bounds__(NT) void k_inv_whole(const InvWholeArgs a) {
+  __shared__ SmemInvLo sm;
+  __shared__ __align__(16) uint32_t sgn[TILE / 32];
+  const int t = threadIdx.x;
+  const uint32_t vec = blockIdx.y, tile = blockIdx.x;
+  const uint64_t off = tm_base(a.lo.tm, tile);
+  if (t < TILE / 128) {
+    const uint64_t q = (a.j0 + off + 128u * t) >> 7;
+    *reinterpret_cast<uint4*>(&sgn[4 * t]) = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, SIGN_STREAM, a.k0, a.k1);
+  }
+  float v[16];
+  uint32_t at[16];
+  int c = 0;
+  inv_lo_stages<L1, false>(a.lo, tile, vec, sm, [&](uint32_t o, float val) { v[c] = val; at[c] = o; ++c; });
+  float* const out = static_cast<float*>(const_cast<void*>(a.out.p[vec])) + off;
+  const char* const grad = EFM ? static_cast<const char*>(a.grad.p[vec]) + off * (EFM == 2 ? 2 : 4) : nullptr;
+  const uint64_t left = a.lo.d - off;
+  auto bit = [&](uint32_t o) { return (sgn[o >> 5] >> (o & 31)) & 1u; };
+  if (L1 == LOG_TILE || left >= TILE) {
+    finish_values<EFM>(v, a.c, out, grad, [&](int i) { return at[i]; }, [&](int i) { return bit(at[i]); });
+  } else {           // the last tile of a vector of short blocks
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (at[i] >= left) continue;
+      const float one[1] = {v[i]};
+      finish_values<EFM>(one, a.c, out, grad, [&](int) { return at[i]; }, [&](int) { return bit(at[i]); });
+    }
+  }
 }
 
 }  // namespace thc

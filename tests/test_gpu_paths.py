@@ -124,3 +124,22 @@ def test_sums_of_any_width(b, g, n):
             R.packed[i].copy_(torch.from_numpy(pk[i]))
         R.aggregate()
         assert np.array_equal(R.agg_numpy(), o.aggregate(P, list(pk)))
+
+
+@pytest.mark.parametrize("log2_block,K,n,b,g,agg_bits,bf16,ef", [
+    (10, 1, 1, 4, 30, 8, False, True), (10, 19, 2, 3, 21, 6, True, True), (11, 5, 2, 4, 30, 16, False, True),
+    (12, 3, 3, 8, 255, 10, True, True), (13, 2, 2, 4, 30, 8, True, True), (14, 1, 1, 4, 30, 5, False, True),
+    (14, 2, 2, 3, 21, 16, True, True), (14, 5, 2, 4, 30, 8, True, True), (15, 1, 2, 2, 8, 5, False, True),
+    (15, 3, 1, 4, 30, 16, True, True), (15, 2, 2, 4, 30, 8, False, False)])
+def test_whole_inverse_in_one_launch(log2_block, K, n, b, g, agg_bits, bf16, ef):
+    """Blocks of up to 2^15: odd numbers of blocks leave the last tile partly empty."""
+    block = 1 << log2_block
+    P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, bf16=bf16,
+                       table=list(range(256)) if b == 8 else None)
+    R = GpuRound(L, ef=ef)
+    efs = None
+    if ef:
+        for i, e in enumerate(R.efs):
+            e.copy_(make_grads(block * K, 1, 2e-4, seed=70 + i)[0])
+        efs = [e.cpu().numpy() for e in R.efs]
+    _round_against_oracle(P, L, R, make_grads(block * K, n, seed=log2_block, bf16=bf16), 6, efs)
