@@ -180,13 +180,13 @@ int thc_decompress_noalloc(const thc_params* p, uint64_t round, const void* agg,
  * thc_aggregate serves unchanged (with the identity table it sums the indices).  Same pointer, stream,
  * workspace and error conventions as above. */
 
-/* Workspace of the three calls below: min/max partials and, with rotation, the rotated vectors of all n workers
+/* Workspace of the three calls below: min/max partials and, with rotation, the half-rotated vectors of all n workers
  * (n * d binary32 values, kept from thc_uniform_prepare_range to thc_uniform_compress). */
 int thc_uniform_workspace_bytes(const thc_params* p, int rotate, size_t* bytes_out /* host */);
 
 /* Preliminary stage of Alg. 1: every worker's min / max, then the global ones.
  *   range_m, range_M   device, d/block floats each, written.
- * With rotate != 0 the fully rotated vectors of all workers are left in `ws` for thc_uniform_compress. */
+ * With rotate != 0 all workers' vectors, rotated up to the transform's last pass, are left in `ws` for thc_uniform_compress. */
 int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* const* grads /* host */,
                               const float* const* ef /* host or NULL */, int rotate, float* range_m,
                               float* range_M, void* ws, void* stream);

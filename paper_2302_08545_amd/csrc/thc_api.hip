@@ -203,9 +203,9 @@ template <int R> struct LaunchQuant {
     else k_fwd_hi_quant<R, CFOLD, false><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
   }
 };
-template <int R> struct LaunchHiStore {
-  static void run(const HiStoreArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
-    k_fwd_hi_store<R><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+template <int R> struct LaunchHiMinMax {
+  static void run(const HiMinMaxArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
+    k_fwd_hi_minmax<R><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
   }
 };
 template <int R> struct LaunchInvHi {
@@ -262,11 +262,14 @@ void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t 
   else k_inv_lo<false><<<grid, blk, 0, s>>>(a);
 }
 
-// The quantizer finds the range itself in calls of up to this many workgroups (and no middle pass: its blocks have too
-// many partial sums).  Small calls are bound by their launches, about 3 us each on the host and 6 on the device: rounds of
-// 2^15 and 2^20 coordinates with 4 workers went from 35.8 to 32.8 us.  Beyond it, the workgroups that do the same sums
-// over again would come to more than one launch.
-constexpr uint64_t FIND_RANGE_MAX_TILES = 2048;
+// Whether the quantizer finds the range itself.  Small calls are bound by their launches, about 3 us each on the host and
+// 6 on the device: rounds of 2^15 and 2^20 coordinates with 4 workers went from 35.8 to 32.8 us.  Against that, every
+// workgroup reads its block's partial sums over again, and its LDS lets three instead of four share a compute unit.
+// Blocks of 2^17 to 2^20: 1280 workgroups gain 4 %, 1536 and 1792 lose 1 to 3 %, 4096 lose 8 to 12 %.  Blocks of up to
+// 2^16, with at most 8 partial sums: 4096 gain 1 % (2^14) and 20 % (2^16, 32 workers).  Blocks of 2^22 lose 2 % at 1024.
+bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {
+  return pl.L <= 20 && tiles * W <= (pl.L <= 16 ? 4096u : 1280u);
+}
 
 // ---- passes on tiles of 2^15 coordinates (thc_big.hpp) ------------------------------------------------------------
 // Blocks of 2^23 to 2^25: always (two passes instead of three: 1.16x at one block of one vector, 1.5x at 16 of them).
@@ -600,7 +603,7 @@ void run_forward(const Forward& f) {
       a.tm = lo_tilemap(pl, len);
       launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, tiles, f.W, f.s);
     }
-    const bool find = f.range_out && !big && pl.nmid == 0 && tiles * f.W <= FIND_RANGE_MAX_TILES;
+    const bool find = f.range_out && !big && find_range(pl, tiles, f.W);
     if (f.range_out && !find) {
       RangeArgs r{a.partials, f.range_out + x0 / p->block, a.pstride, len, f.W, (uint32_t)pl.L, L1, p->t_p};
       launch_range(r, f.s);
@@ -912,7 +915,7 @@ int validate_uniform(const thc_params* p) {
   return THC_OK;
 }
 
-// Workspace of the uniform entry points: with rotation the fully rotated vectors of all n workers (n*d binary32
+// Workspace of the uniform entry points: with rotation the half-rotated vectors of all n workers (n*d binary32
 // values, kept from thc_uniform_prepare_range to thc_uniform_compress), then per-tile minima and maxima.
 size_t uni_x_bytes(const thc_params* p, int rotate) { return rotate ? (size_t)p->n * (size_t)p->d * sizeof(float) : 0; }
 
@@ -946,7 +949,7 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
   float* pmax = pmin + partial_count(p, pl);
   const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
   if (rotate) {
-    // full forward RHT of every worker, kept in the workspace
+    // every worker's forward RHT up to its last pass, kept in the workspace, and the range of what that pass gives
     FwdLoArgs a{};
     for (uint32_t i = 0; i < p->n; ++i) {
       a.grads.p[i] = grads[i];
@@ -961,9 +964,9 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.tm = lo_tilemap(pl, p->d);
     launch_fwd_lo(pl, a, bf16, ef != nullptr, false, tiles_of(p->d), p->n, s);
     run_mids(pl, static_cast<float*>(ws), p->d, p->n, s);
-    const HiStoreArgs h{static_cast<float*>(ws), pmin, pmax, p->d, p->d >> pl.L1, pl.hi, (uint32_t)pl.L,
+    const HiMinMaxArgs h{static_cast<float*>(ws), pmin, pmax, p->d, p->d >> pl.L1, pl.hi, (uint32_t)pl.L,
                         (float)(1.0 / std::sqrt((double)p->block))};
-    dispatch_0_9<LaunchHiStore>(pl.R, h, tiles_of(p->d), p->n, s);
+    dispatch_0_9<LaunchHiMinMax>(pl.R, h, tiles_of(p->d), p->n, s);
   } else {
     MinMaxArgs a{};
     for (uint32_t i = 0; i < p->n; ++i) {
@@ -995,27 +998,47 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
   const Plan pl = make_plan(p->block, p->stage_order);
   hipStream_t s = static_cast<hipStream_t>(stream);
   float* wsx = rotate ? static_cast<float*>(ws) + (size_t)worker_id * p->d : nullptr;
-  UQuantArgs q{};
-  q.x = wsx;
-  q.grad = grad;
-  q.ef = rotate ? nullptr : ef_inout;
-  q.range_M = range_M;
-  q.range_m = range_m;
-  q.packed = packed_out;
-  q.d = p->d;
-  q.L = (uint32_t)pl.L;
-  q.b = p->b;
-  q.g = p->g;
-  q.round = (uint32_t)round;
-  q.worker = worker_id;
-  q.k0 = (uint32_t)p->seed;
-  q.k1 = (uint32_t)(p->seed >> 32);
-  q.ef_update = (!rotate && ef_inout) ? 1u : 0u;
-  q.j0 = base_coord(p);
-  fill_lut(p, q.lut);
-  const dim3 grid((unsigned)tiles_of(p->d)), blk(NT);
-  if (p->in_dtype == THC_DTYPE_BF16) k_uniform_quant<true><<<grid, blk, 0, s>>>(q);
-  else k_uniform_quant<false><<<grid, blk, 0, s>>>(q);
+  const uint32_t k0 = (uint32_t)p->seed, k1 = (uint32_t)(p->seed >> 32);
+  if (rotate) {
+    QuantArgs q{};
+    q.x = wsx;
+    q.range_M = range_M;
+    q.range_m = range_m;
+    q.packed.p[0] = packed_out;
+    q.d = p->d;
+    q.j0 = base_coord(p);
+    q.tm = pl.hi;
+    q.L = (uint32_t)pl.L;
+    q.b = p->b;
+    q.g = p->g;
+    q.round = (uint32_t)round;
+    q.worker = worker_id;
+    q.k0 = k0;
+    q.k1 = k1;
+    q.c = (float)(1.0 / std::sqrt((double)p->block));
+    fill_lut(p, q.lut);
+    dispatch_0_9<LaunchQuant>(pl.R, q, (pl.L & 1) == 0, tiles_of(p->d), 1, s);
+  } else {
+    UQuantArgs q{};
+    q.grad = grad;
+    q.ef = ef_inout;
+    q.range_M = range_M;
+    q.range_m = range_m;
+    q.packed = packed_out;
+    q.d = p->d;
+    q.L = (uint32_t)pl.L;
+    q.b = p->b;
+    q.g = p->g;
+    q.round = (uint32_t)round;
+    q.worker = worker_id;
+    q.k0 = k0;
+    q.k1 = k1;
+    q.j0 = base_coord(p);
+    fill_lut(p, q.lut);
+    const dim3 grid((unsigned)tiles_of(p->d)), blk(NT);
+    if (p->in_dtype == THC_DTYPE_BF16) k_uniform_quant<true><<<grid, blk, 0, s>>>(q);
+    else k_uniform_quant<false><<<grid, blk, 0, s>>>(q);
+  }
   if (rotate && ef_inout) {
     // e <- (grad + e) - RHT^-1(X_i): rebuild X_i from the indices, inverse transform, subtract
     InvLoArgs lo{};
@@ -1033,8 +1056,8 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
     hi.out.p[0] = ef_inout;
     hi.grad.p[0] = grad;
     hi.round = (uint32_t)round;
-    hi.k0 = q.k0;
-    hi.k1 = q.k1;
+    hi.k0 = k0;
+    hi.k1 = k1;
     hi.mode = 1;
     hi.bf16 = p->in_dtype == THC_DTYPE_BF16;
     hi.j0 = base_coord(p);

@@ -11,7 +11,7 @@
 //   thc_device.hpp     building blocks: tiling, Philox, butterflies, LDS rounds, bit-stream codec
 //   thc_forward.hpp    k_fwd_lo, k_range, k_mid, k_fwd_hi_quant
 //   thc_inverse.hpp    k_inv_lo, k_inv_hi
-//   thc_uniform.hpp    k_minmax, k_minmax_final, k_fwd_hi_store, k_uniform_quant, k_uniform_dequant
+//   thc_uniform.hpp    k_minmax, k_minmax_final, k_fwd_hi_minmax, k_uniform_quant, k_uniform_dequant
 //   thc_aggregate.hpp  k_aggregate_b4w8, k_aggregate_b4w16, k_aggregate_b4wx, k_aggregate_b2w8, k_aggregate_any
 //   thc_pipeline.hpp   k_pipe_forward: the forward passes of all blocks in one launch, block after block
 //   thc_big.hpp        the same passes on tiles of 2^15 coordinates: k_big_lo, k_big_quant, k_big_inv_lo, k_big_inv_hi

@@ -98,10 +98,11 @@ __global__ __launch_bounds__(64) void k_minmax_final(const MinMaxFinalArgs a) {
   if (lane == 0) { a.range_m[k] = mn; a.range_M[k] = mx; }
 }
 
-// Last strided pass of a forward RHT that keeps the rotated vector: finishes the butterflies, scales by
-// 1/sqrt(B), writes the result back in place and records the tile's minimum and maximum.
-struct HiStoreArgs {
-  float* x;          // half-rotated vectors, d floats per worker of the launch (grid.y), rotated in place
+// Minimum and maximum of the rotated vectors: the last strided pass of the forward RHT, its results compared and
+// dropped.  The quantizer goes through that pass again (k_fwd_hi_quant): writing the rotated vector and reading it back
+// would cost twice the bytes of reading the half-rotated one a second time.
+struct HiMinMaxArgs {
+  const float* x;    // half-rotated vectors, d floats per worker of the launch (grid.y)
   float* pmin;       // partial minima, `pstride` = d >> L1 floats per worker
   float* pmax;
   uint64_t d, pstride;
@@ -111,12 +112,12 @@ struct HiStoreArgs {
 };
 
 template <int R>
-__global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
+__global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
   __shared__ __align__(16) float lds[TILE];
   __shared__ float smin[16], smax[16];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const HiGeom<R> g(blockIdx.x, a.tm);
-  float* const x = a.x + (uint64_t)blockIdx.y * a.d;
+  const float* const x = a.x + (uint64_t)blockIdx.y * a.d;
   float* const pmin = a.pmin + (uint64_t)blockIdx.y * a.pstride;
   float* const pmax = a.pmax + (uint64_t)blockIdx.y * a.pstride;
   if constexpr (R >= 2) {
@@ -133,9 +134,6 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
         mn = __builtin_fminf(mn, v[h][e]);
         mx = __builtin_fmaxf(mx, v[h][e]);
       }
-      float* o = x + g.coord(idx[h]);
-      *reinterpret_cast<float4*>(o) = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
-      *reinterpret_cast<float4*>(o + 4) = make_float4(v[h][4], v[h][5], v[h][6], v[h][7]);
     }
     mn = wave_min(mn);
     mx = wave_max(mx);
@@ -161,8 +159,6 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
         float4 p1 = *reinterpret_cast<const float4*>(&lds[idx + 4]);
         p0.x *= a.c; p0.y *= a.c; p0.z *= a.c; p0.w *= a.c;
         p1.x *= a.c; p1.y *= a.c; p1.z *= a.c; p1.w *= a.c;
-        *reinterpret_cast<float4*>(x + j) = p0;
-        *reinterpret_cast<float4*>(x + j + 4) = p1;
         mn = __builtin_fminf(__builtin_fminf(__builtin_fminf(p0.x, p0.y), __builtin_fminf(p0.z, p0.w)),
                              __builtin_fminf(__builtin_fminf(p1.x, p1.y), __builtin_fminf(p1.z, p1.w)));
         mx = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(p0.x, p0.y), __builtin_fmaxf(p0.z, p0.w)),
@@ -189,19 +185,16 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_store(const HiStoreArgs a) {
 }
 
 // Uniform stochastic quantization of one worker's vector: 8192 consecutive coordinates per workgroup.
-// Source: the rotated vector `x` when given, else grad (+ e).  Without rotation the error-feedback update
-// e <- x - (m + z (M-m)/g) is done here; with rotation it needs an inverse transform (separate passes).
+// Without rotation only, so that the error-feedback update e <- x - (m + z (M-m)/g) is done here.
 struct UQuantArgs {
-  const float* x;          // rotated vector or null
   const void* grad;
-  float* ef;               // error feedback, read (and written when ef_update) or null
+  float* ef;               // error feedback, read and written, or null
   const float* range_M;
   const float* range_m;
   uint8_t* packed;
   uint64_t d;
   uint32_t L, b, g;
   uint32_t round, worker, k0, k1;
-  uint32_t ef_update;
   uint64_t j0;             // global coordinate of the first element
   uint32_t lut[256];
 };
@@ -234,18 +227,13 @@ __global__ __launch_bounds__(NT) void k_uniform_quant(const UQuantArgs a) {
     const uint64_t j = off + idx;
     if (j >= a.d) continue;
     float4 p0, p1;
-    if (a.x) {
-      p0 = *reinterpret_cast<const float4*>(a.x + j);
-      p1 = *reinterpret_cast<const float4*>(a.x + j + 4);
-    } else {
-      p0 = load_grad4<BF16>(a.grad, j);
-      p1 = load_grad4<BF16>(a.grad, j + 4);
-      if (a.ef) {
-        const float4 e0 = *reinterpret_cast<const float4*>(a.ef + j);
-        const float4 e1 = *reinterpret_cast<const float4*>(a.ef + j + 4);
-        p0.x += e0.x; p0.y += e0.y; p0.z += e0.z; p0.w += e0.w;
-        p1.x += e1.x; p1.y += e1.y; p1.z += e1.z; p1.w += e1.w;
-      }
+    p0 = load_grad4<BF16>(a.grad, j);
+    p1 = load_grad4<BF16>(a.grad, j + 4);
+    if (a.ef) {
+      const float4 e0 = *reinterpret_cast<const float4*>(a.ef + j);
+      const float4 e1 = *reinterpret_cast<const float4*>(a.ef + j + 4);
+      p0.x += e0.x; p0.y += e0.y; p0.z += e0.z; p0.w += e0.w;
+      p1.x += e1.x; p1.y += e1.y; p1.z += e1.z; p1.w += e1.w;
     }
     const float hv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
     const int bt = a.L < LOG_TILE ? (idx >> a.L) : 0;
@@ -256,7 +244,7 @@ __global__ __launch_bounds__(NT) void k_uniform_quant(const UQuantArgs a) {
     if (!sCare[bt]) quantize8<false>(hv, rnd, s, lut, z);   // no scaling: the values are final (c = 1)
     else quantize8<false, true>(hv, rnd, s, lut, z);
     store_packed8(a.packed, j, a.b, z);
-    if (a.ef_update) {
+    if (a.ef) {
       const float step = sStep[bt], lo = s.lo;
       float e[8];
 #pragma unroll
