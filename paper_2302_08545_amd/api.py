@@ -98,6 +98,8 @@ def _ptr_array(ts):
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():   # the handle alone: a Stream object costs a small call more than its launches
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
