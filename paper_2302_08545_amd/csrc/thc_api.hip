@@ -293,24 +293,19 @@ void dispatch_big(int r, A&&... args) {
 }
 
 template <bool BF16, bool EF>
-void launch_big_lo_k(const BigLoArgs& a, bool split, bool norm_only, dim3 grid, hipStream_t s) {
-  if (norm_only) {
-    if (split) k_big_lo<BF16, EF, true, true><<<grid, dim3(NT), 0, s>>>(a);
-    else k_big_lo<BF16, EF, false, true><<<grid, dim3(NT), 0, s>>>(a);
-  } else {
-    if (split) k_big_lo<BF16, EF, true, false><<<grid, dim3(NT), 0, s>>>(a);
-    else k_big_lo<BF16, EF, false, false><<<grid, dim3(NT), 0, s>>>(a);
-  }
+void launch_big_lo_k(const BigLoArgs& a, bool split, dim3 grid, hipStream_t s) {
+  if (split) k_big_lo<BF16, EF, true><<<grid, dim3(NT), 0, s>>>(a);
+  else k_big_lo<BF16, EF, false><<<grid, dim3(NT), 0, s>>>(a);
 }
 
-void launch_big_lo(const Plan& pl, const BigLoArgs& a, bool bf16, bool ef, bool norm_only, uint32_t W, hipStream_t s) {
+void launch_big_lo(const Plan& pl, const BigLoArgs& a, bool bf16, bool ef, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)(a.d >> LOG_BIG), W);
   if (bf16) {
-    if (ef) launch_big_lo_k<true, true>(a, pl.split, norm_only, grid, s);
-    else launch_big_lo_k<true, false>(a, pl.split, norm_only, grid, s);
+    if (ef) launch_big_lo_k<true, true>(a, pl.split, grid, s);
+    else launch_big_lo_k<true, false>(a, pl.split, grid, s);
   } else {
-    if (ef) launch_big_lo_k<false, true>(a, pl.split, norm_only, grid, s);
-    else launch_big_lo_k<false, false>(a, pl.split, norm_only, grid, s);
+    if (ef) launch_big_lo_k<false, true>(a, pl.split, grid, s);
+    else launch_big_lo_k<false, false>(a, pl.split, grid, s);
   }
 }
 
@@ -586,9 +581,8 @@ void run_forward(const Forward& f) {
       }
     }
     a.ws_x = slot;
-    const uint32_t L1 = big ? LOG_BIG : (uint32_t)pl.L1;
-    a.partials = f.range_out ? partials + (x0 >> L1) : nullptr;
-    a.pstride = p->d >> L1;
+    a.partials = f.range_out ? partials + (x0 >> pl.L1) : nullptr;
+    a.pstride = p->d >> pl.L1;
     a.d = len;
     a.j0 = base_coord(p) + x0;
     a.round = (uint32_t)f.round;
@@ -598,14 +592,14 @@ void run_forward(const Forward& f) {
     q.j0 = a.j0;
     if (big) {
       const BigLoArgs bl{a.grads, a.efs, slot, a.partials, a.pstride, len, a.j0, a.round, a.k0, a.k1};
-      launch_big_lo(pl, bl, bf16, f.efs != nullptr, false, f.W, f.s);
+      launch_big_lo(pl, bl, bf16, f.efs != nullptr, f.W, f.s);
     } else {
       a.tm = lo_tilemap(pl, len);
       launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, tiles, f.W, f.s);
     }
     const bool find = f.range_out && !big && find_range(pl, tiles, f.W);
     if (f.range_out && !find) {
-      RangeArgs r{a.partials, f.range_out + x0 / p->block, a.pstride, len, f.W, (uint32_t)pl.L, L1, p->t_p};
+      RangeArgs r{a.partials, f.range_out + x0 / p->block, a.pstride, len, f.W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p};
       launch_range(r, f.s);
     }
     if (big) {
@@ -620,7 +614,7 @@ void run_forward(const Forward& f) {
       q.pstride = a.pstride;
       q.range_out = find ? f.range_out + x0 / p->block : nullptr;
       q.n = f.W;
-      q.L1 = L1;
+      q.L1 = (uint32_t)pl.L1;
       q.t_p = p->t_p;
       dispatch_0_9<LaunchQuant>(pl.R, q, (pl.L & 1) == 0, tiles, f.W, f.s);
     }
@@ -729,28 +723,21 @@ int thc_prepare_range(const thc_params* p, const void* const* grads, const float
   if (rv) return rv;
   const Plan pl = make_plan(p->block, p->stage_order);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // The same partial sums, in the same order, as the first pass of thc_compress_all takes them group by group: both
-  // give the same M bit for bit.
+  // The same partial sums, in the same order, as the first pass of thc_compress_all takes them group by group, on tiles
+  // of either size and in the single launch: all give the same M bit for bit.
   const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
   double* const partials = ws_layout(ws, p, pl, false).partials;
-  const bool big = use_big(pl, p->d, p->n);
-  const uint32_t L1 = big ? LOG_BIG : (uint32_t)pl.L1;
   FwdLoArgs a{};
   for (uint32_t i = 0; i < p->n; ++i) {
     a.grads.p[i] = grads[i];
     if (ef) a.efs.p[i] = ef[i];
   }
-  if (big) {
-    BigLoArgs bl{a.grads, a.efs, nullptr, partials, p->d >> LOG_BIG, p->d, 0, 0, 0, 0};
-    launch_big_lo(pl, bl, bf16, ef != nullptr, true, p->n, s);
-  } else {
-    a.partials = partials;
-    a.pstride = p->d >> pl.L1;
-    a.d = p->d;
-    a.tm = lo_tilemap(pl, p->d);
-    launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(p->d), p->n, s);
-  }
-  RangeArgs r{partials, range_M, p->d >> L1, p->d, p->n, (uint32_t)pl.L, L1, p->t_p};
+  a.partials = partials;
+  a.pstride = p->d >> pl.L1;
+  a.d = p->d;
+  a.tm = lo_tilemap(pl, p->d);
+  launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(p->d), p->n, s);
+  RangeArgs r{partials, range_M, p->d >> pl.L1, p->d, p->n, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p};
   launch_range(r, s);
   return check_launch();
 }

@@ -96,14 +96,14 @@ __device__ __forceinline__ void big_lo_stages(float* lds, int t, Fill&& fill, Ou
 struct alignas(16) SmemBigLo {
   float lds[BIG_LDS];
   uint32_t sgn[BIG_SIGN_WORDS];
-  double wsum[NT / 64];
+  double wsum[BIG / TILE][NT / 64];
 };
 
 struct BigLoArgs {
   PtrArr grads;
   PtrArr efs;          // unused without error feedback
   float* ws_x;         // d floats per vector
-  double* partials;    // per vector `pstride` doubles, one per tile; or null
+  double* partials;    // per vector `pstride` doubles, one per 8192 coordinates; or null
   uint64_t pstride;
   uint64_t d;
   uint64_t j0;         // global coordinate of the vectors' first element
@@ -137,8 +137,14 @@ __device__ __forceinline__ float flip_bit(float x, uint32_t bits, int k) {
   return __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(x), bits << (31 - k), 0x80000000u, 0x78));   // a ^ (b & c)
 }
 
-// grid = (tiles of a vector, vectors).  NORM_ONLY: stop after the partial sums of squares.
-template <bool BF16, bool EF, bool XO, bool NORM_ONLY>
+// grid = (tiles of a vector, vectors).
+//
+// The norms are added up exactly as fwd_lo_tile does, one partial sum per 8192 coordinates, so that M does not depend on
+// which tile a call takes: a run of 16 values per thread and value of (p13, p14) is one of its tiles, whose thread holds
+// four sums of four squares 2048 coordinates apart.  Those lie with other waves here and cross over through LDS, 32 KB a
+// half, before the half's first stages need the space.  Measured against sums of 16 values in a row and one partial sum a tile:
+// one block of 2^23 or 2^25 38 us (35) and 97 us (93) a call, eight vectors of eight blocks of 2^25 5250 us (5235).
+template <bool BF16, bool EF, bool XO>
 __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
   __shared__ SmemBigLo sm;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -149,7 +155,6 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
   const uint32_t tp = big_p<XO>(lane << 4 | wave << 10);
 
   float v[4][16], e[2][16];
-  double acc[4];
   auto load = [&](int h) {   // operands of one half of the tile
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
@@ -157,43 +162,41 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
       if constexpr (EF) load_grad16<false>(ef, tp + big_p<XO>((2 * h + y) << 13), e[y]);
     }
   };
+  double* const squares = reinterpret_cast<double*>(sm.lds);
   auto take = [&](int h) {   // x = grad + e and its squares in binary64 (a binary32 square is exact there)
+    if constexpr (EF) {
 #pragma unroll
-    for (int s = 2 * h; s < 2 * h + 2; ++s) {
-      if constexpr (EF) {
+      for (int y = 0; y < 2; ++y)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) v[s][k] += e[s & 1][k];
-      }
-      if (NORM_ONLY || a.partials) {
-        double c = (double)v[s][0] * (double)v[s][0];
+        for (int k = 0; k < 16; ++k) v[2 * h + y][k] += e[y][k];
+    }
+    if (!a.partials) return;
+    if (h) __syncthreads();  // the first half has been read
 #pragma unroll
-        for (int k = 1; k < 16; ++k) c = __builtin_fma((double)v[s][k], (double)v[s][k], c);
-        acc[s] = c;
+    for (int y = 0; y < 2; ++y) {
+      double2* const w = reinterpret_cast<double2*>(squares + (y << 11 | t << 2));
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        double c[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const float* const x = &v[2 * h + y][4 * (i + k)];
+          c[k] = sum_squares4(make_float4(x[0], x[1], x[2], x[3]));
+        }
+        w[i >> 1] = make_double2(c[0], c[1]);
       }
     }
-  };
-  auto reduce = [&] {
-    if (NORM_ONLY || a.partials) {
-      const double s = wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
-      if (lane == 0) sm.wsum[wave] = s;
-      __syncthreads();
-      if (t == 0) {
-        double r = 0.0;
+    __syncthreads();
 #pragma unroll
-        for (int w = 0; w < NT / 64; ++w) r += sm.wsum[w];
-        a.partials[(uint64_t)vec * a.pstride + tile] = r;
-      }
+    for (int y = 0; y < 2; ++y) {
+      const double* const r = squares + (y << 11 | t);
+      const double s = wave_sum((r[0] + r[NT]) + (r[2 * NT] + r[3 * NT]));
+      if (lane == 0) sm.wsum[2 * h + y][wave] = s;
     }
+    if (!h) __syncthreads();   // the second half has a barrier of its own before its first stages
   };
 
   load(0);
-  if constexpr (NORM_ONLY) {
-    take(0);
-    load(1);
-    take(1);
-    reduce();
-    return;
-  }
   if constexpr (!EF) load(1);
   if (t < BIG / 128) {   // the tile's diagonal: one Philox call per 128 coordinates
     const uint64_t q = (a.j0 + off + big_p<XO>(t << 7)) >> 7;
@@ -221,7 +224,13 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
         }
       },
       [&](int k, float r) { dst[big_p<XO>(k << 9) + t] = r; });
-  reduce();
+  // the stages' barriers have passed since the last wave sum; tiles 4 * tile + 0..3 of the smaller kind, in either stage order
+  if (a.partials && t < BIG / TILE) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) s += sm.wsum[t][w];
+    a.partials[(uint64_t)vec * a.pstride + (uint64_t)tile * (BIG / TILE) + t] = s;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -40,6 +40,12 @@ __device__ __forceinline__ float4 load_grad4(const void* g, uint64_t j) {
   }
 }
 
+// sum of squares in binary64 (a binary32 square is exact there)
+__device__ __forceinline__ double sum_squares4(const float4 x) {
+  const double p = (double)x.x, q = (double)x.y, r = (double)x.z, s = (double)x.w;
+  return __builtin_fma(s, s, __builtin_fma(r, r, __builtin_fma(q, q, p * p)));
+}
+
 struct alignas(16) SmemLo {
   float lds[TILE_PAD];
   uint32_t sgn[TILE / 32];
@@ -87,13 +93,9 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
 #pragma unroll
     for (int i = 0; i < 4; ++i) { x[i].x += e[i].x; x[i].y += e[i].y; x[i].z += e[i].z; x[i].w += e[i].w; }
   }
-  // sum of squares in binary64 (a binary32 square is exact there)
   double acc[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const double p = (double)x[i].x, q = (double)x[i].y, r = (double)x[i].z, s = (double)x[i].w;
-    acc[i] = __builtin_fma(s, s, __builtin_fma(r, r, __builtin_fma(q, q, p * p)));
-  }
+  for (int i = 0; i < 4; ++i) acc[i] = sum_squares4(x[i]);
   // a thread's four float4 sit 2048 coordinates apart: they share a block only if the block is that large
   if constexpr (L1 >= 13) {
     const double s = wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
@@ -241,14 +243,20 @@ __device__ __forceinline__ float block_range(const double* partials, uint64_t ps
       const uint32_t j = 64 * (item & ((1u << lc) - 1u)) + lane;
       s[u] = item < items && j < ppb ? partials[(uint64_t)(item >> lc) * pstride + k * ppb + j] : 0.0;
     }
-    if (ppb > RANGE_NT) {
+    // blocks of more than 512 tiles, a power of two of them: up to 28 loads in flight
+    for (uint32_t j0 = RANGE_NT; j0 < ppb; j0 += 7 * RANGE_NT) {
+      double x[4][7];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const uint32_t item = it + u * (RANGE_NT / 64);
-        if (item >= items) break;
+        const uint32_t item = it + u * (RANGE_NT / 64), j = 64 * (item & 7u) + lane + j0;
         const double* const p = partials + (uint64_t)(item >> lc) * pstride + k * ppb;
-        for (uint32_t j = 64 * (item & 7u) + lane + RANGE_NT; j < ppb; j += RANGE_NT) s[u] += p[j];
+#pragma unroll
+        for (uint32_t c = 0; c < 7; ++c) x[u][c] = item < items && j + c * RANGE_NT < ppb ? p[j + c * RANGE_NT] : 0.0;
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (uint32_t c = 0; c < 7; ++c) s[u] += x[u][c];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {

@@ -143,3 +143,36 @@ def test_whole_inverse_in_one_launch(log2_block, K, n, b, g, agg_bits, bf16, ef)
             e.copy_(make_grads(block * K, 1, 2e-4, seed=70 + i)[0])
         efs = [e.cpu().numpy() for e in R.efs]
     _round_against_oracle(P, L, R, make_grads(block * K, n, seed=log2_block, bf16=bf16), 6, efs)
+
+
+@pytest.mark.parametrize("order", [0, 1], ids=["ascending", "split"])
+@pytest.mark.parametrize("log2_block,K,n,bf16,ef,single_launch", [
+    (20, 1, 1, False, False, 0), (22, 1, 1, False, False, 0), (22, 1, 63, True, False, 0), (22, 1, 64, False, False, 0),
+    (22, 4, 16, True, False, 0), (22, 4, 16, False, False, 1), (22, 64, 1, False, True, 0), (24, 1, 1, False, True, 0),
+    (24, 1, 3, True, False, 0), (24, 1, 1, True, True, 0)])
+def test_norms_are_added_up_in_one_order_whatever_the_tile(log2_block, K, n, bf16, ef, single_launch, order):
+    """M must not depend on the call that forms it: n workers or one, a shard or the whole, tiles of 2^13 or 2^15 (from 64
+    blocks of 2^22 on), one launch or several.  The squares of the last block add up to 1 + 2^-23 + 2^-48, the square of
+    a tie between two binary32 numbers, and twelve times 2^-54.  Those are lost when added one by one to a sum of 1 or
+    more, and 3 * 2^-52, which settles the tie, when added up four to a thread first, as every call has to do."""
+    block = 1 << log2_block
+    x = torch.zeros(block * K, dtype=torch.bfloat16 if bf16 else torch.float32, device=DEV)
+    last = x[block * (K - 1):]
+    last[0] = 1.0
+    last[4:16] = 2.0 ** -27
+    last[torch.tensor([5, 9, 14], device=DEV) << 16] = torch.tensor([2.0 ** -12, 2.0 ** -12, 2.0 ** -24], device=DEV).to(x.dtype)
+    want = (1 + 2.0 ** -23) / 2.0 ** (log2_block // 2)
+    _, L = both_params(block * K, block, n, agg_bits=16, bf16=bf16, order=order, single_launch=single_launch)
+    L.t_p = 1.0
+    R = GpuRound(L, ef=ef)
+    if ef:                                       # half of every coordinate in the buffer
+        x = x * 0.5
+        for e in R.efs:
+            e.copy_(x.to(torch.float32))
+    R.prepare([x] * n)
+    assert R.range_M[K - 1].item() == want
+    R.range_M.zero_()
+    R.compress_all(2, [x] * n)
+    assert R.range_M[K - 1].item() == want
+    if single_launch:
+        assert R.status() == 0
