@@ -272,16 +272,6 @@ bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {
 }
 
 // ---- passes on tiles of 2^15 coordinates (thc_big.hpp) ------------------------------------------------------------
-// Blocks of 2^23 to 2^25: always (two passes instead of three: 1.16x at one block of one vector, 1.5x at 16 of them).
-// 2^22: both tile sizes take two passes, and the larger one pays once its few large tiles fill the chip many times over
-// (rounds of 256 to 3072 tiles: 0.91x to 1.05x; of 16384: 1.12x).
-constexpr uint64_t BIG_MIN_TILES_22 = 8192;
-
-bool use_big(const Plan& pl, uint64_t d, uint32_t W) {   // W vectors of d coordinates in the call
-  if (pl.L == 22) return W * (d >> LOG_BIG) >= BIG_MIN_TILES_22;
-  return pl.L > 22 && pl.L <= LOG_BIG + 10;
-}
-
 template <template <int> class Launcher, class... A>
 void dispatch_big(int r, A&&... args) {
   switch (r) {
@@ -383,10 +373,10 @@ void launch_big_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_
   }
 }
 
-// inverse transform of W vectors of `len` coordinates that k_inv_lo is about to produce in `wsx`
-void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, InvHiArgs hi, uint64_t len, uint32_t W,
-                 hipStream_t s) {
-  if (use_big(pl, p->d, W)) {
+// inverse transform of W vectors of `len` coordinates that the first pass is about to produce in `wsx`
+void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, InvHiArgs hi, uint64_t len, bool big,
+                 uint32_t W, hipStream_t s) {
+  if (big) {
     BigInvLoArgs a{lo.src, lo.range_M, lo.range_m, wsx, len, lo.L, lo.src_bits, lo.use_table, lo.divisor, {}};
     std::memcpy(a.table, lo.table, 256);
     launch_big_inv_lo(pl, a, W, s);
@@ -539,7 +529,6 @@ void run_forward(const Forward& f) {
   float* const slot = wl.ring;
   double* const partials = wl.partials;
   const float* const range = f.range_out ? f.range_out : f.range_in;
-  const bool big = use_big(pl, p->d, f.W);
 
   QuantArgs q{};
   q.tm = pl.hi;
@@ -566,8 +555,7 @@ void run_forward(const Forward& f) {
     ihi.mode = 1;
     ihi.bf16 = bf16;
   }
-  for (uint64_t x0 = 0; x0 < p->d; x0 += gc) {
-    const uint64_t len = p->d - x0 < gc ? p->d - x0 : gc;
+  for_groups(pl, p->d, gc, f.W, [&](uint64_t x0, uint64_t len, bool big, bool inv_big) {
     const uint64_t tiles = tiles_of(len);
     FwdLoArgs a{};
     for (uint32_t i = 0; i < f.W; ++i) {
@@ -622,9 +610,9 @@ void run_forward(const Forward& f) {
       // e <- (grad + e) - RHT^-1(X_i): the group's slot is free again and takes the inverse's intermediate
       ilo.range_M = q.range_M;
       ihi.j0 = a.j0;
-      run_inverse(p, pl, ilo, slot, ihi, len, f.W, f.s);
+      run_inverse(p, pl, ilo, slot, ihi, len, inv_big, f.W, f.s);
     }
-  }
+  });
 }
 
 // ---- scratch of the entry point that allocates nothing -------------------------------------------------------
@@ -846,14 +834,13 @@ void run_decompress(const thc_params* p, const Plan& pl, uint64_t round, const v
   hi.k0 = (uint32_t)p->seed;
   hi.k1 = (uint32_t)(p->seed >> 32);
   hi.mode = 0;
-  for (uint64_t x0 = 0; x0 < p->d; x0 += gc) {
-    const uint64_t len = p->d - x0 < gc ? p->d - x0 : gc;
+  for_groups(pl, p->d, gc, 1, [&](uint64_t x0, uint64_t len, bool, bool big) {
     lo.src.p[0] = static_cast<const uint8_t*>(agg) + x0 / 8 * p->agg_bits;
     lo.range_M = range_M + x0 / p->block;
     hi.out.p[0] = out + x0;
     hi.j0 = base_coord(p) + x0;
-    run_inverse(p, pl, lo, slot, hi, len, 1, s);
-  }
+    run_inverse(p, pl, lo, slot, hi, len, big, 1, s);
+  });
 }
 
 }  // namespace
@@ -1048,7 +1035,7 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
     hi.mode = 1;
     hi.bf16 = p->in_dtype == THC_DTYPE_BF16;
     hi.j0 = base_coord(p);
-    run_inverse(p, pl, lo, wsx, hi, p->d, 1, s);
+    run_inverse(p, pl, lo, wsx, hi, p->d, big_inverse(pl, p->d, p->d, 1), 1, s);
   }
   return check_launch();
 }
@@ -1085,7 +1072,7 @@ int thc_uniform_decompress(const thc_params* p, uint64_t round, const void* agg,
   hi.k1 = (uint32_t)(p->seed >> 32);
   hi.mode = 0;
   hi.j0 = base_coord(p);
-  run_inverse(p, pl, lo, wsx, hi, p->d, 1, s);
+  run_inverse(p, pl, lo, wsx, hi, p->d, big_inverse(pl, p->d, p->d, 1), 1, s);
   return check_launch();
 }
 

@@ -13,10 +13,10 @@
 #pragma once
 
 #include "thc_inverse.hpp"
+#include "thc_plan.hpp"
 
 namespace thc {
 
-constexpr int LOG_BIG = 15;
 constexpr int BIG = 1 << LOG_BIG;
 
 // ---------------------------------------------------------------------------------------------

@@ -136,4 +136,33 @@ inline TileMap lo_tilemap(const Plan& pl, uint64_t len) {
   return m.L ? m : pl.lo;
 }
 
+// Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of
+// 2^15 coordinates (thc_big.hpp).  Blocks of 2^23 to 2^25: all (two passes instead of three: 1.16x at one block of one
+// vector, 1.5x at 16 of them).  2^22: both tile sizes take two passes, and the larger one pays once its few large tiles
+// fill the chip many times over (rounds of 256 to 3072 tiles: 0.91x to 1.05x; of 16384: 1.12x).  The forward passes go by
+// the tiles of a launch (64 blocks of one vector, 512 tiles a launch: 707 us with the smaller tiles, 752 with the larger
+// ones), the inverse ones by those of the call (787 and 740 us) as long as a launch has a tile for each of the 512
+// workgroups the chip holds (thc_decompress_noalloc, 256 tiles a launch: 1030 and 1140 us, 995 and 1260 ascending).
+constexpr int LOG_BIG = 15;
+constexpr uint64_t BIG_MIN_TILES_22 = 8192, BIG_RESIDENT = 512;
+
+inline bool big_forward(const Plan& pl, uint64_t len, uint32_t W) {
+  if (pl.L == 22) return W * (len >> LOG_BIG) >= BIG_MIN_TILES_22;
+  return pl.L > 22 && pl.L <= LOG_BIG + 10;
+}
+
+inline bool big_inverse(const Plan& pl, uint64_t d, uint64_t len, uint32_t W) {
+  return big_forward(pl, d, W) && (pl.L > 22 || W * (len >> LOG_BIG) >= BIG_RESIDENT);
+}
+
+// The groups of whole blocks, `gc` coordinates of each of W vectors, in which a call walks its d coordinates:
+// group(first coordinate, coordinates, whether the forward and the inverse launches take the larger tiles).
+template <class Group>
+inline void for_groups(const Plan& pl, uint64_t d, uint64_t gc, uint32_t W, Group&& group) {
+  for (uint64_t x0 = 0; x0 < d; x0 += gc) {
+    const uint64_t len = d - x0 < gc ? d - x0 : gc;
+    group(x0, len, big_forward(pl, len, W), big_inverse(pl, d, len, W));
+  }
+}
+
 }  // namespace thc

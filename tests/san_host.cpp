@@ -42,8 +42,34 @@ static int check_cover(const TileMap& m, bool first_pass_rows) {
   return 0;
 }
 
+// a walk covers the vector in whole groups; forward passes pick the tile size by what one launch holds, inverse passes
+// by the call, but not where a launch is too short to fill the chip
+static int check_groups(uint64_t block, uint64_t d, uint64_t gc, uint32_t W, bool fwd_full, bool inv_full, bool fwd_last,
+                        bool inv_last) {
+  const Plan pl = make_plan(block, THC_ORDER_SPLIT);
+  uint64_t at = 0;
+  int bad = 0;
+  for_groups(pl, d, gc, W, [&](uint64_t x0, uint64_t len, bool fwd, bool inv) {
+    bad += x0 != at || len != (d - x0 < gc ? d - x0 : gc) || fwd != (len == gc ? fwd_full : fwd_last) ||
+           inv != (len == gc ? inv_full : inv_last);
+    at += len;
+  });
+  return bad + (at != d);
+}
+
 int main() {
   int bad = 0;
+  const uint64_t M22 = 1ull << 22;
+  bad += check_groups(M22, 64 * M22, 2 * M22, 1, false, false, false, false);   // thc_decompress_noalloc: 32 MB at a time
+  bad += check_groups(M22, 64 * M22, 4 * M22, 1, false, true, false, true);
+  bad += check_groups(M22, 66 * M22, 4 * M22, 1, false, true, false, false);     // the last group is too short
+  bad += check_groups(M22, 63 * M22, 63 * M22, 1, false, false, false, false);
+  bad += check_groups(M22, 64 * M22, 64 * M22, 1, true, true, true, true);
+  bad += check_groups(M22, 96 * M22, 64 * M22, 1, true, true, false, true);
+  bad += check_groups(M22, 16 * M22, 4 * M22, 32, true, true, true, true);
+  bad += check_groups(2 * M22, 3 * M22 * 2, 2 * M22, 1, true, true, true, true);
+  bad += check_groups(M22 / 2, 256 * M22, 128 * M22, 8, false, false, false, false);
+  bad += check_groups(16 * M22, 32 * M22, 16 * M22, 8, false, false, false, false);
   for (int L = 10; L <= 27; ++L)
     for (uint32_t order = 0; order <= 1; ++order) {
       const Plan pl = make_plan(1ull << L, order);

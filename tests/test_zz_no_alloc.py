@@ -43,3 +43,9 @@ def test_no_alloc_rejects_blocks_beyond_the_scratch_array():
     with pytest.raises(api.ThcError) as e:
         api.thc_decompress_noalloc(L, 0, z, z, z)
     assert e.value.status == -4
+
+
+@pytest.mark.parametrize("order", [0, 1], ids=["ascending", "split"])
+def test_no_alloc_decompress_equals_decompress_where_their_tiles_differ(order):
+    """64 blocks of 2^22 in one launch take tiles of 2^15 coordinates, two blocks at a time those of 2^13."""
+    _both(64 << 22, 1 << 22, 8, 8, order, 9, 4)
