@@ -262,15 +262,6 @@ void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t 
   else k_inv_lo<false><<<grid, blk, 0, s>>>(a);
 }
 
-// Whether the quantizer finds the range itself.  Small calls are bound by their launches, about 3 us each on the host and
-// 6 on the device: rounds of 2^15 and 2^20 coordinates with 4 workers went from 35.8 to 32.8 us.  Against that, every
-// workgroup reads its block's partial sums over again, and its LDS lets three instead of four share a compute unit.
-// Blocks of 2^17 to 2^20: 1280 workgroups gain 4 %, 1536 and 1792 lose 1 to 3 %, 4096 lose 8 to 12 %.  Blocks of up to
-// 2^16, with at most 8 partial sums: 4096 gain 1 % (2^14) and 20 % (2^16, 32 workers).  Blocks of 2^22 lose 2 % at 1024.
-bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {
-  return pl.L <= 20 && tiles * W <= (pl.L <= 16 ? 4096u : 1280u);
-}
-
 // ---- passes on tiles of 2^15 coordinates (thc_big.hpp) ------------------------------------------------------------
 template <template <int> class Launcher, class... A>
 void dispatch_big(int r, A&&... args) {

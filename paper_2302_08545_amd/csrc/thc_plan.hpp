@@ -136,6 +136,17 @@ inline TileMap lo_tilemap(const Plan& pl, uint64_t len) {
   return m.L ? m : pl.lo;
 }
 
+// Whether the quantizer finds the range itself.  Small calls are bound by their launches, about 3 us each on the host and
+// 6 on the device: rounds of 2^15 and 2^20 coordinates with 4 workers went from 35.8 to 32.8 us.  Against that, every
+// workgroup reads its block's partial sums over again, and its LDS lets three instead of four share a compute unit.
+// Blocks of 2^17 to 2^20: 1280 workgroups gain 4 %, 1536 and 1792 lose 1 to 3 %, 4096 lose 8 to 12 %.  Blocks of up to
+// 2^16, with at most 8 partial sums, which the launch of its own adds up one worker after another: 4096 workgroups gain 1
+// to 24 % with 16 or more workers, with 8 between -1 % (2^10) and 6 % (2^16); 4 workers gain up to 2 % at 3072 and lose
+// up to 3 % at 4096; 1 and 2 lose 0 to 3 % at 3072.  Blocks of 2^22 lose 2 % at 1024.
+inline bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {   // 8192-coordinate tiles of each of W vectors
+  return pl.L <= 20 && tiles * W <= (pl.L > 16 ? 1280u : W > 4 ? 4096u : W > 2 ? 3072u : 2048u);
+}
+
 // Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of
 // 2^15 coordinates (thc_big.hpp).  Blocks of 2^23 to 2^25: all (two passes instead of three: 1.16x at one block of one
 // vector, 1.5x at 16 of them).  2^22: both tile sizes take two passes, and the larger one pays once its few large tiles

@@ -70,6 +70,14 @@ int main() {
   bad += check_groups(2 * M22, 3 * M22 * 2, 2 * M22, 1, true, true, true, true);
   bad += check_groups(M22 / 2, 256 * M22, 128 * M22, 8, false, false, false, false);
   bad += check_groups(16 * M22, 32 * M22, 16 * M22, 8, false, false, false, false);
+  // largest number of workgroups at which the quantizer finds the range itself
+  const struct { int L; uint32_t W; uint64_t most; } find[] = {{10, 1, 2048}, {13, 2, 1024}, {14, 3, 1024}, {16, 4, 768},
+                                                              {16, 8, 512}, {10, 32, 128}, {17, 1, 1280}, {20, 4, 320}};
+  for (const auto& f : find) {
+    const Plan pl = make_plan(1ull << f.L, THC_ORDER_ASCENDING);
+    bad += !find_range(pl, f.most, f.W) || find_range(pl, f.most + 1, f.W);
+  }
+  bad += find_range(make_plan(1ull << 21, THC_ORDER_SPLIT), 256, 1);
   for (int L = 10; L <= 27; ++L)
     for (uint32_t order = 0; order <= 1; ++order) {
       const Plan pl = make_plan(1ull << L, order);

@@ -85,7 +85,8 @@ def test_tiles_of_2_to_the_15(log2_block, K, n, b, g, agg_bits, bf16, ef, order)
 @pytest.mark.parametrize("log2_block,K,n,b,g,order", [
     (10, 1, 1, 3, 21, 0), (10, 13, 3, 4, 30, 0), (12, 7, 10, 3, 21, 0), (13, 5, 64, 2, 3, 0), (14, 3, 4, 4, 30, 0),
     (15, 1, 5, 3, 31, 1), (16, 2, 33, 2, 3, 1), (17, 3, 2, 3, 21, 1), (19, 1, 7, 1, 1, 0), (20, 1, 10, 3, 21, 1),
-    (21, 1, 3, 4, 30, 0), (22, 1, 2, 3, 21, 1), (16, 16, 32, 4, 30, 1), (16, 17, 32, 4, 30, 1)])
+    (21, 1, 3, 4, 30, 0), (22, 1, 2, 3, 21, 1), (16, 16, 32, 4, 30, 1), (16, 17, 32, 4, 30, 1), (10, 16384, 1, 4, 30, 0),
+    (10, 16385, 1, 4, 30, 0), (13, 1024, 3, 4, 30, 0), (13, 1025, 3, 4, 30, 0)])
 def test_range_found_by_the_last_pass(log2_block, K, n, b, g, order):
     """Small calls: the quantizer adds the norms up itself.  The range is that of thc_prepare_range and the streams are
     those of thc_compress, bit for bit (16 and 17 blocks of 2^16, 32 workers, lie on either side of the rule), and both are the oracle's."""
