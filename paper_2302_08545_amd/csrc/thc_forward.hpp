@@ -2,6 +2,7 @@
 #pragma once
 
 #include "thc_device.hpp"
+#include "thc_quant.hpp"
 
 namespace thc {
 
@@ -477,12 +478,6 @@ struct QuantArgs {
   float t_p;
 };
 
-struct QuantScalars {
-  float M, lo, sc, c;    // range [lo, M]; fast form: scale * 2^24, and lo, M and the scale folded with c where it is a power of two
-};
-
-constexpr float GRID_SCALE = 0x1p24f;
-
 // float -> uint32, towards zero; below 0 gives 0 and above 2^32 - 1 gives 2^32 - 1 (a C++ cast leaves those undefined)
 __device__ __forceinline__ uint32_t cvt_u32_sat(float y) {
   uint32_t k;
@@ -495,7 +490,9 @@ __device__ __forceinline__ uint32_t cvt_u32_sat(float y) {
 // top index for every draw.  Saves one of eleven instructions per coordinate: the kernels that end in the quantizer are
 // bound by vector issue.
 // CAREFUL = true: the operations exactly as listed above, unscaled; for ranges so narrow that the scaled form would
-// leave binary32, or so fine (g above 127) that a clamped coordinate may round down from the last cell.
+// leave binary32, or grids so fine that a clamped coordinate may round down from the last cell: it takes three roundings
+// to place M, which may leave it 3 g 2^-24 of a cell short, and a last cell w wide needs less than w 2^-17 (g up to 42 w
+// never takes this form, g = 127 with w = 1 one time in six).
 // Both forms take the same decisions: multiplying by a power of two commutes with every rounding involved.
 template <bool MULC, bool CAREFUL = false>
 __device__ __forceinline__ void quantize8(const float (&hv)[8], const uint4 rnd, const QuantScalars s,
@@ -567,30 +564,6 @@ __device__ __forceinline__ uint4 quant_lut_entry(uint32_t ent) {
 template <class A>
 __device__ __forceinline__ void build_quant_lut(const A& a, uint4* lut, int t) {
   if (t < 256) lut[t] = quant_lut_entry(a.lut[t]);
-}
-
-// scale = g / (M - m): the width in binary64, the quotient rounded once to binary32.  Where that is not a finite
-// number (M = m, or a width so small that the quotient overflows binary32) the range is empty: scale 0, every index 0.
-__device__ __forceinline__ float scale_of(float M, float m, uint32_t g) {
-  const float sc = (float)((double)g / ((double)M - (double)m));
-  return sc <= 3.4028234663852886e38f ? sc : 0.f;     // also false for NaN
-}
-
-// scale * 2^24 (and the fold with 1/sqrt(B)) stay finite below this
-constexpr float WIDE_SCALE = 0x1p102f;
-
-// Per-block constants of the quantizer and which form it takes.  `last`: the table's last cell, lut[g - 1].
-__device__ __forceinline__ QuantScalars quant_scalars(float M, float m, uint32_t g, uint32_t last, float c, bool cfold,
-                                                      bool& careful) {
-  const float sc = scale_of(M, m, g);
-  QuantScalars q{M, m, sc * GRID_SCALE, c};
-  if (cfold) q = QuantScalars{M * (1.0f / c), m * (1.0f / c), sc * GRID_SCALE * c, c};
-  // what a clamped coordinate comes to, and whether the largest draw still lets it reach the top index
-  const float top = (q.M - q.lo) * q.sc, wd = (float)((last >> 8) & 255u) * 256.0f;
-  const bool ends = top >= (float)g * GRID_SCALE ||
-                    __builtin_fmaf(65535.0f, wd, 0.5f * wd) < top - (float)(last & 255u) * GRID_SCALE;
-  careful = sc >= WIDE_SCALE || !ends;
-  return careful ? QuantScalars{M, m, sc, c} : q;
 }
 
 __device__ __forceinline__ float lower_of(const float* range_m, uint64_t blk, float M) {

@@ -3,10 +3,12 @@
 // kernels derive from its tables.  Built and run by tests/test_host_sanitizers.py.
 #include <cstdio>
 #include <cstdlib>
+#include <cmath>
 #include <vector>
 
 #include "thc.h"
 #include "thc_plan.hpp"
+#include "thc_quant.hpp"
 
 using namespace thc;
 
@@ -57,8 +59,45 @@ static int check_groups(uint64_t block, uint64_t d, uint64_t gc, uint32_t W, boo
   return bad + (at != d);
 }
 
+// The index of a coordinate above the range, for the largest rounding draw: what the quantizer's fast form, which does
+// not clamp, makes of M itself.
+static bool fast_form_ends_at_the_top(const QuantScalars& q, uint32_t g, uint32_t wd) {
+  const float y = (q.M - q.lo) * q.sc;
+  if (y >= (float)g * GRID_SCALE) return true;
+  const float t = y - (float)(g - wd) * GRID_SCALE;               // in the last cell: up if the draw's product is below
+  return (65535.0f + 0.5f) * (float)wd * 256.0f < t;
+}
+
+static int check_quant_form() {
+  int bad = 0;
+  uint64_t seed = 12345;
+  auto uniform = [&] { seed = seed * 6364136223846793005ull + 1442695040888963407ull; return (float)(seed >> 40) * 0x1p-24f; };
+  auto form = [](float M, float m, uint32_t g, uint32_t wd, QuantScalars& q) {
+    bool careful = false;
+    q = quant_scalars(M, m, g, (g - wd) | wd << 8, 0x1p-10f, true, careful);
+    return careful;
+  };
+  QuantScalars q;
+  // empty blocks: every index is 0 in either form, so they take the short one
+  for (uint32_t g : {1u, 30u, 255u})
+    for (float M : {0.f, 1.f, -3.f, 1e-45f}) bad += form(M, M == 1e-45f ? -M : M, g, 1, q) || q.sc != 0.f;
+  bad += !form(1e-30f, -1e-30f, 30, 3, q);                          // scale beyond what the scaled form can hold
+  for (uint32_t wd : {1u, 2u, 5u})
+    for (uint32_t g = wd; g <= 255; ++g) {
+      int careful = 0;
+      for (int i = 0; i < 400; ++i) {
+        const float M = std::ldexp(0.5f + uniform(), (int)(uniform() * 40.f) - 30), m = i & 1 ? -M : -M * uniform();
+        if (form(M, m, g, wd, q)) ++careful;
+        else bad += !fast_form_ends_at_the_top(q, g, wd);
+      }
+      bad += g <= 42 * wd && careful;
+    }
+  return bad;
+}
+
 int main() {
   int bad = 0;
+  bad += check_quant_form();
   const uint64_t M22 = 1ull << 22;
   bad += check_groups(M22, 64 * M22, 2 * M22, 1, false, false, false, false);   // thc_decompress_noalloc: 32 MB at a time
   bad += check_groups(M22, 64 * M22, 4 * M22, 1, false, true, false, true);

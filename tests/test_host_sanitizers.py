@@ -1,5 +1,5 @@
-"""The library's host code (table solver, pass planner) built with gcc's AddressSanitizer and
-UndefinedBehaviorSanitizer and run on the CPU: no GPU involved."""
+"""The library's host code (table solver, pass planner, rules of the dispatch, form of the quantizer) built with gcc's
+AddressSanitizer and UndefinedBehaviorSanitizer and run on the CPU: no GPU involved."""
 import os
 import shutil
 import subprocess
@@ -15,7 +15,7 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
         pytest.skip("no g++")
     exe = tmp_path / "san_host"
     csrc = os.path.join(ROOT, "paper_2302_08545_amd", "csrc")
-    cmd = [gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+    cmd = [gxx, "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
            "-static-libasan", "-static-libubsan", "-Wall", "-Wextra", "-Werror",
            "-I", os.path.join(ROOT, "include"), "-I", csrc,
            os.path.join(ROOT, "tests", "san_host.cpp"), os.path.join(csrc, "thc_tables.cpp"), "-o", str(exe)]
