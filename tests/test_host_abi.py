@@ -233,3 +233,19 @@ def test_all_tables_the_paper_mentions_within_seconds():
         for b in (2, 3, 4):
             for g in range(2 ** b - 1, 26):
                 assert all_t[(b, 2 * g, p)][1] <= all_t[(b, g, p)][1] * (1 + 1e-12)
+
+
+@pytest.mark.parametrize("missing", [None, "_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_with_and_without_torchs_own_names(monkeypatch, missing):
+    import types
+
+    import torch
+    names = {"_cuda_getCurrentRawStream": lambda device: 1000 + device, "_cuda_getDevice": lambda: 3}
+    for name, f in names.items():
+        monkeypatch.setattr(torch._C, name, f, raising=False)
+    if missing:
+        monkeypatch.delattr(torch._C, missing)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=7))
+    assert api._stream(None) == (7 if missing else 1003)
+    assert api._stream(5) == 5 and api._stream(types.SimpleNamespace(cuda_stream=6)) == 6
