@@ -199,8 +199,13 @@ template <int R> struct LaunchQuant {
   }
   template <bool CFOLD>
   static void go(const QuantArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
-    if (a.partials) k_fwd_hi_quant<R, CFOLD, true><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
-    else k_fwd_hi_quant<R, CFOLD, false><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+    if constexpr (R <= 7) {                        // find_range: blocks of up to 2^20
+      if (a.partials) {
+        k_fwd_hi_quant<R, CFOLD, true><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+        return;
+      }
+    }
+    k_fwd_hi_quant<R, CFOLD, false><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
   }
 };
 template <int R> struct LaunchHiMinMax {
@@ -582,7 +587,7 @@ void run_forward(const Forward& f) {
       launch_range(r, f.s);
     }
     if (big) {
-      BigQuantArgs bq{slot, q.range_M, nullptr, q.packed, len, q.j0, q.b, q.g, q.round, q.worker, q.k0, q.k1, q.c, {}};
+      BigQuantArgs bq{slot, q.range_M, q.packed, len, q.j0, q.b, q.g, q.round, q.worker, q.k0, q.k1, q.c, {}};
       std::memcpy(bq.lut, q.lut, sizeof q.lut);
       dispatch_big<LaunchBigQuant>(pl.L - LOG_BIG, bq, pl.split, f.W, f.s);
     } else {

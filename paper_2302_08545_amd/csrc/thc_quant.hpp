@@ -2,13 +2,7 @@
 // checked on the host; to be compiled with -ffp-contract=off.
 #pragma once
 
-#include <stdint.h>
-
-#ifdef __HIPCC__
-#define THC_HOST_DEVICE __host__ __device__ __forceinline__
-#else
-#define THC_HOST_DEVICE inline
-#endif
+#include "thc_tilemap.hpp"
 
 namespace thc {
 

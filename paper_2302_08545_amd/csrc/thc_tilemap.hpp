@@ -3,6 +3,12 @@
 
 #include <stdint.h>
 
+#ifdef __HIPCC__
+#define THC_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define THC_HOST_DEVICE inline
+#endif
+
 namespace thc {
 
 constexpr int LOG_TILE = 13;
