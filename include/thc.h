@@ -204,7 +204,11 @@ int thc_uniform_decompress(const thc_params* p, uint64_t round, const void* agg,
 /* ---- host-side helpers (no GPU work) ------------------------------------------------------------- */
 
 /* Introspection for tests and tools: how the Hadamard transform of these parameters is cut into passes over
- * HBM and how every pass tiles a block.  Returns the number of passes (2 to 5), or a negative status; with
+ * HBM on tiles of 8192 coordinates, and how every pass tiles a block.  Blocks of 2^23 to 2^25, and of 2^22 in large
+ * calls, run on tiles of 2^15 coordinates instead (the first 15 bits, then the rest, in the same stage order), and the
+ * inverse transform of blocks of up to 2^15 in one pass; neither is described here, and neither changes a result, except
+ * that the rotated uniform variant's forward transform is always the one described.  Returns the number of passes
+ * (2 or 3), or a negative status; with
  * out != NULL it also writes one record of THC_PLAN_RECORD_WORDS 32-bit words per pass (cap_records must be at
  * least the number of passes).  Record layout (unused words are 0xFFFFFFFF):
  *   [0]      0 = first pass on 8192 consecutive coordinates, 3 = first pass on 8 rows of 1024 coordinates

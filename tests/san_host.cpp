@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "thc.h"
+#include "thc_bigmap.hpp"
 #include "thc_plan.hpp"
 #include "thc_quant.hpp"
 
@@ -42,6 +43,48 @@ static int check_cover(const TileMap& m, bool first_pass_rows) {
     }
   }
   return 0;
+}
+
+// Tiles of 2^15 coordinates: the tiles of either pass cover a block once, the first does the first 15 bits of the
+// stage order and the last pass the rest, each with the row bit it is meant for in the slot index when its turn comes.
+template <int R, bool XO>
+static int check_big() {
+  using H = BigHi<R>;
+  constexpr int L = LOG_BIG + R;
+  std::vector<uint32_t> order;                     // offset each stage pairs
+  if (XO) {
+    for (int b : {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 13, 14, 15, 10, 11, 12}) order.push_back(1u << b);
+    for (int b = 16; b < L; ++b) order.push_back(1u << b);
+  } else {
+    for (int b = 0; b < L; ++b) order.push_back(1u << b);
+  }
+  int bad = 0;
+  for (int i = 0; i < LOG_BIG; ++i) bad += big_p<XO>(1u << i) != order[i];
+  for (int i = 0; i < R; ++i) bad += big_q<XO>(1u << i) != order[LOG_BIG + i];
+  const BigLayout a = H::first(), b = H::second(), c = H::third(), e = H::last();
+  for (int i = 0; i < 3; ++i) bad += a.slot[i] != i || (i < H::E && c.slot[i] != 5 + i);
+  bad += b.slot[0] != 3 || b.slot[1] != 4;
+  bad += (H::E >= 4 && e.slot[0] != 8) || (H::E >= 5 && e.slot[1] != 9);
+  // every map takes bits to bits, so single bits show that the tiles' coordinates are disjoint and complete
+  uint64_t lo = 0, hi = 0, out = 0;
+  auto add = [&bad](uint64_t& seen, uint64_t bit) { bad += !bit || (bit & (bit - 1)) || (seen & bit); seen |= bit; };
+  for (int i = 0; i < LOG_BIG; ++i) add(lo, big_p<XO>(1u << i));
+  for (int i = 0; i < R; ++i) {
+    add(lo, big_lo_base<XO>(1u << i));
+    add(hi, big_hi_base<R, XO>(1u << i));
+    add(out, big_hi_base<R, XO>(1u << i));
+  }
+  for (int i = 0; i < 9; ++i) {
+    add(hi, H::template thread_off<XO, 0>(a, 1 << i));
+    add(out, H::template thread_off<XO, 0>(e, 1 << i));
+  }
+  for (int i = 0; i < 3; ++i) {
+    add(hi, H::template slot_off<XO>(a, 1 << i));
+    add(out, H::template slot_off<XO>(e, 1 << i));
+  }
+  const uint64_t most = (1ull << L) - 8;          // the low three bits are a thread's eight columns
+  bad += lo != most + 7 || hi != most || out != most;
+  return bad + (big_hi_base<R, XO>(3u << R | 1) != (3ull << L) + big_hi_base<R, XO>(1));
 }
 
 // a walk covers the vector in whole groups; forward passes pick the tile size by what one launch holds, inverse passes
@@ -98,6 +141,8 @@ static int check_quant_form() {
 int main() {
   int bad = 0;
   bad += check_quant_form();
+  bad += check_big<7, false>() + check_big<7, true>() + check_big<8, false>() + check_big<8, true>();
+  bad += check_big<9, false>() + check_big<9, true>() + check_big<10, false>() + check_big<10, true>();
   const uint64_t M22 = 1ull << 22;
   bad += check_groups(M22, 64 * M22, 2 * M22, 1, false, false, false, false);   // thc_decompress_noalloc: 32 MB at a time
   bad += check_groups(M22, 64 * M22, 4 * M22, 1, false, true, false, true);

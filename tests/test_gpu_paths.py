@@ -49,6 +49,7 @@ def test_clamped_coordinates_end_in_the_outer_indices(b, g, log2_block):
 
 @pytest.mark.parametrize("log2_block,K,n,b,g,agg_bits,bf16,ef,order", [
     (22, 64, 1, 4, 30, 8, False, False, 1),      # just enough tiles for the large ones
+    (22, 64, 1, 4, 30, 8, False, False, 0), (22, 64, 1, 4, 30, 16, False, True, 0), (22, 64, 1, 4, 30, 8, True, True, 1),
     (23, 1, 2, 4, 30, 8, True, True, 0), (23, 1, 1, 3, 21, 5, False, False, 1),
     (24, 1, 2, 4, 30, 16, False, True, 1), (24, 1, 1, 8, 255, 8, False, False, 0), (25, 1, 1, 2, 8, 9, True, True, 0)])
 def test_tiles_of_2_to_the_15(log2_block, K, n, b, g, agg_bits, bf16, ef, order):
@@ -56,18 +57,26 @@ def test_tiles_of_2_to_the_15(log2_block, K, n, b, g, agg_bits, bf16, ef, order)
     T = list(range(256)) if b == 8 else None
     P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, bf16=bf16, order=order, table=T)
     if K > 1:                                    # long: blocks 0 and K - 1 are compared
-        x = torch.randn(block * K, device=DEV, generator=torch.Generator(device=DEV).manual_seed(22)) * 1e-3
-        R = GpuRound(L)
+        gen = torch.Generator(device=DEV).manual_seed(22)
+        x = torch.randn(block * K, device=DEV, generator=gen) * 1e-3
+        x = x.to(torch.bfloat16) if bf16 else x
+        R = GpuRound(L, ef=ef)
+        e = {}
+        if ef:
+            R.efs[0].copy_(torch.randn(block * K, device=DEV, generator=gen) * 2e-4)
+            e = {k: R.efs[0][k * block:(k + 1) * block].cpu().numpy() for k in (0, K - 1)}
         R.compress_all(3, [x])
         R.aggregate()
         R.decompress(3)
-        M, pk, agg, out = (t.cpu().numpy() for t in (R.range_M, R.packed[0], R.agg, R.out))
+        M, pk, agg, out = R.range_M.cpu().numpy(), R.packed[0].cpu().numpy(), R.agg_numpy(), R.out.cpu().numpy()
         for k in (0, K - 1):
             Pk = o.Params(d=block, block=block, n=1, b=b, g=g, t_p=P.t_p, seed=P.seed, table=P.table,
                           agg_bits=agg_bits, order=order)
-            gk = x[k * block:(k + 1) * block].cpu().numpy()
-            assert abs(M[k] - o.prepare_range(Pk, [gk])[0]) <= M[k] * 2.0 ** -23
-            ref = o.compress(Pk, 0, 3, gk, None, M[k:k + 1], j0=k * block)[0]
+            gk = to_np32(x[k * block:(k + 1) * block])
+            assert abs(M[k] - o.prepare_range(Pk, [gk], [e[k]] if ef else None)[0]) <= M[k] * 2.0 ** -23
+            ref, ne = o.compress(Pk, 0, 3, gk, e.get(k), M[k:k + 1], j0=k * block)
+            if ef:
+                assert rel_l2(R.efs[0][k * block:(k + 1) * block].cpu().numpy(), ne) <= 1e-5
             assert_indices_match(pk[k * block // 2:(k + 1) * block // 2], ref, b)
             Y = o.aggregate(Pk, [pk[k * block // 2:(k + 1) * block // 2]])
             assert np.array_equal(agg[k * block:(k + 1) * block], Y)
@@ -88,8 +97,9 @@ def test_tiles_of_2_to_the_15(log2_block, K, n, b, g, agg_bits, bf16, ef, order)
     (21, 1, 3, 4, 30, 0), (22, 1, 2, 3, 21, 1), (16, 16, 32, 4, 30, 1), (16, 17, 32, 4, 30, 1), (10, 16384, 1, 4, 30, 0),
     (10, 16385, 1, 4, 30, 0), (13, 1024, 3, 4, 30, 0), (13, 1025, 3, 4, 30, 0)])
 def test_range_found_by_the_last_pass(log2_block, K, n, b, g, order):
-    """Small calls: the quantizer adds the norms up itself.  The range is that of thc_prepare_range and the streams are
-    those of thc_compress, bit for bit (16 and 17 blocks of 2^16, 32 workers, lie on either side of the rule), and both are the oracle's."""
+    """Small calls of blocks of up to 2^20: the quantizer adds the norms up itself.  The range is that of thc_prepare_range
+    and the streams are those of thc_compress, bit for bit, and both are the oracle's.  The pairs of rows that differ in one
+    block, 2^16, 2^10 and 2^13, lie on either side of the rule; 2^21 and 2^22 take the range kernel."""
     block = 1 << log2_block
     agg_bits = 8 if g * n < 256 else 16
     P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, order=order)

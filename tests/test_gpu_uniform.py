@@ -12,11 +12,11 @@ pytestmark = pytest.mark.gpu
 F32 = np.float32
 
 
-def uparams(d, block, n, b, agg_bits, bf16=False, first_block=0):
+def uparams(d, block, n, b, agg_bits, bf16=False, first_block=0, order=0):
     T = list(range(2 ** b))
-    P = o.Params(d=d, block=block, n=n, b=b, g=2 ** b - 1, t_p=1.0, seed=SEED, table=T, agg_bits=agg_bits)
+    P = o.Params(d=d, block=block, n=n, b=b, g=2 ** b - 1, t_p=1.0, seed=SEED, table=T, agg_bits=agg_bits, order=order)
     L = api.make_params(d, block, n, b, 2 ** b - 1, 1.0, SEED, T, agg_bits,
-                        api.THC_DTYPE_BF16 if bf16 else api.THC_DTYPE_F32, first_block=first_block)
+                        api.THC_DTYPE_BF16 if bf16 else api.THC_DTYPE_F32, stage_order=order, first_block=first_block)
     return P, L
 
 
@@ -26,9 +26,23 @@ def uparams(d, block, n, b, agg_bits, bf16=False, first_block=0):
     (1 << 16, 1, 2, 8, 9, True, 0), (1 << 20, 1, 3, 1, 2, False, 0), (1 << 21, 1, 2, 3, 4, True, 0),
     (1 << 12, 3, 2, 4, 8, True, (1 << 22) + 3)])
 def test_uniform_round(block, K, n, b, agg_bits, ef, first_block, rotate):
+    _uniform_round(block, K, n, b, agg_bits, ef, first_block, rotate)
+
+
+@pytest.mark.parametrize("log2_block,K,n,b,agg_bits,ef,order", [
+    (17, 3, 2, 4, 8, True, 1), (20, 2, 3, 4, 6, False, 1), (22, 1, 2, 4, 8, True, 1),
+    (23, 1, 2, 4, 8, True, 0), (23, 2, 2, 3, 4, True, 1), (24, 1, 1, 4, 16, True, 1), (25, 1, 1, 2, 2, True, 0),
+    (25, 1, 1, 8, 8, False, 1)])
+def test_uniform_round_on_large_rotated_blocks(log2_block, K, n, b, agg_bits, ef, order):
+    """Blocks of 2^23 to 2^25: a forward transform with a middle pass, an inverse one on tiles of 2^15 coordinates whose
+    range is not symmetric."""
+    _uniform_round(1 << log2_block, K, n, b, agg_bits, ef, 0, True, order)
+
+
+def _uniform_round(block, K, n, b, agg_bits, ef, first_block, rotate, order=0):
     d = block * K
     j0 = first_block * block            # the buffers hold a slice of a longer vector
-    P, L = uparams(d, block, n, b, agg_bits, first_block=first_block)
+    P, L = uparams(d, block, n, b, agg_bits, first_block=first_block, order=order)
     grads = make_grads(d, n, seed=block % 97 + b)
     for i, g in enumerate(grads):
         g += 0.002 * (i - 1)                                      # asymmetric ranges: m != -M
