@@ -27,10 +27,12 @@ def test_compulsory_bytes_per_coordinate(w, want):
 
 
 @pytest.mark.parametrize("w,want", [(wl.C3, 8 * 12.5 + 5 + 13), (wl.C4_B4, 16 * 12.5 + 10 + 14),
-                                    (wl.C2, 8 * (12 + 8 + 4.5 + 4.5 + 8 + 16) + 5 + (1 + 4 + 8 + 8))],
+                                    (wl.C2, 8 * (12 + 4.5 + 4.5 + 16) + 5 + 13),
+                                    (wl.replace(wl.C2, block=1 << 26, d=1 << 26),
+                                     8 * (12 + 8 + 4.5 + 4.5 + 8 + 16) + 5 + (1 + 4 + 8 + 8))],
                          ids=lambda x: getattr(x, "name", str(x)))
 def test_moved_bytes_per_coordinate_of_the_pass_structure(w, want):
-    # two passes (three for the 2^25 block), each reading and writing the vector once
+    # two passes (three above 2^25), each reading and writing the vector once
     assert wl.moved_bytes_per_coord(w) == want
 
 
