@@ -119,8 +119,9 @@ __device__ __forceinline__ float flip_bit(float x, uint32_t bits, int k) {
 // The norms are added up exactly as fwd_lo_tile does, one partial sum per 8192 coordinates, so that M does not depend on
 // which tile a call takes: a run of 16 values per thread and value of (p13, p14) is one of its tiles, whose thread holds
 // four sums of four squares 2048 coordinates apart.  Those lie with other waves here and cross over through LDS, 32 KB a
-// half, before the half's first stages need the space.  Measured against sums of 16 values in a row and one partial sum a tile:
-// one block of 2^23 or 2^25 38 us (35) and 97 us (93) a call, eight vectors of eight blocks of 2^25 5250 us (5235).
+// half, before the half's first stages need the space; the sums over a wave wait until the tile's stores are under way.
+// What that costs against sums of 16 values in a row and one partial sum a tile: one block of 2^23, 2^24 or 2^25 34.1 us
+// (32.5), 50.7 (49.3) and 92.6 (92.4) a call, eight vectors of 2^25 with error feedback 2041 us (2036).
 template <bool BF16, bool EF, bool XO>
 __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
   __shared__ SmemBigLo sm;
@@ -132,6 +133,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
   const uint32_t tp = big_p<XO>(lane << 4 | wave << 10);
 
   float v[4][16], e[2][16];
+  double acc[4];
   auto load = [&](int h) {   // operands of one half of the tile
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
@@ -167,8 +169,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
       const double* const r = squares + (y << 11 | t);
-      const double s = wave_sum((r[0] + r[NT]) + (r[2 * NT] + r[3 * NT]));
-      if (lane == 0) sm.wsum[2 * h + y][wave] = s;
+      acc[2 * h + y] = (r[0] + r[NT]) + (r[2 * NT] + r[3 * NT]);
     }
     if (!h) __syncthreads();   // the second half has a barrier of its own before its first stages
   };
@@ -201,12 +202,16 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
         }
       },
       [&](int k, float r) { dst[big_p<XO>(k << 9) + t] = r; });
-  // the stages' barriers have passed since the last wave sum; tiles 4 * tile + 0..3 of the smaller kind, in either stage order
-  if (a.partials && t < BIG / TILE) {
-    double s = 0.0;
+  if (a.partials) {          // the sums over a wave and over the waves, while the stores drain
+    const double s = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
+    if (lane < 4) sm.wsum[lane][wave] = s;
+    __syncthreads();
+    if (t < BIG / TILE) {    // tiles 4 * tile + 0..3 of the smaller kind, in either stage order
+      double r = 0.0;
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) s += sm.wsum[t][w];
-    a.partials[(uint64_t)vec * a.pstride + (uint64_t)tile * (BIG / TILE) + t] = s;
+      for (int w = 0; w < NT / 64; ++w) r += sm.wsum[t][w];
+      a.partials[(uint64_t)vec * a.pstride + (uint64_t)tile * (BIG / TILE) + t] = r;
+    }
   }
 }
 

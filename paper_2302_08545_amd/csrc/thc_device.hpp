@@ -179,6 +179,19 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// The same totals of four values, that of the i-th in lane i: a lane hands over what it does not keep, so three
+// exchanges take the place of eight (every sum has the same two operands as in wave_sum).
+__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d) {
+  const int lane = threadIdx.x & 63;
+  const bool odd = lane & 1, up = lane & 2;
+  const double p = (odd ? b : a) + __shfl_xor(odd ? a : b, 1, 64);
+  const double q = (odd ? d : c) + __shfl_xor(odd ? c : d, 1, 64);
+  double v = (up ? q : p) + __shfl_xor(up ? p : q, 2, 64);
+#pragma unroll
+  for (int m = 4; m < 64; m <<= 1) v += __shfl_xor(v, m, 64);
+  return v;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Bit streams of w-bit fields (w <= 16), least-significant bits first: eight consecutive fields occupy
 // exactly w consecutive bytes.  Generic (byte-wise) codec for the widths without a dedicated fast path.
