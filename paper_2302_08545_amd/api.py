@@ -98,11 +98,11 @@ def _ptr_array(ts):
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        # the handle alone: a Stream object costs a small call more than its launches.  Names of torch's own that a
-        # build may lack: then the public way.
-        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-        if raw and device and torch.cuda.is_initialized():
-            return raw(device())
+        if torch.cuda.is_initialized():   # the handle alone: a Stream object costs a small call more than its launches
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:        # names of torch's own that a build may lack: then the public way
+                pass
         stream = torch.cuda.current_stream()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
