@@ -97,7 +97,7 @@ typedef struct thc_params {
                           group_log2 = 0), blocks following each other through a ring of a few block-sized slots: a
                           sixteenth of the workspace at the same speed (within 2 %) without error feedback; with error
                           feedback and n * block beyond the 256 MB memory-side cache it is slower (n = 32, blocks of
-                          2^22: 81 against 46 ms).  Never a result.  See THC_SWEEP_OK below */
+                          2^22: 81 against 41 ms).  Never a result.  See THC_SWEEP_OK below */
 } thc_params;
 
 /* Library version (major*10000 + minor*100 + patch). */

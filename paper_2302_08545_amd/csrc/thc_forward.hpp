@@ -487,8 +487,8 @@ __device__ __forceinline__ uint32_t cvt_u32_sat(float y) {
 
 // CAREFUL = false: no clamp.  Below m the position is negative, converts to cell 0 and never rounds up.  Above M it lies
 // in or beyond the last cell: there quant_scalars has made sure that M itself, hence everything above it, ends in the
-// top index for every draw.  Saves one of eleven instructions per coordinate: the kernels that end in the quantizer are
-// bound by vector issue.
+// top index for every draw.  Saves one of eleven instructions per coordinate, 16 a wave, of which the choice between the
+// forms takes twelve back: 442 -> 438 a wave, and 472 -> 471 us for 64 blocks of 2^20 x 8 vectors.
 // CAREFUL = true: the operations exactly as listed above, unscaled; for ranges so narrow that the scaled form would
 // leave binary32, or grids so fine that a clamped coordinate may round down from the last cell: it takes three roundings
 // to place M, which may leave it 3 g 2^-24 of a cell short, and a last cell w wide needs less than w 2^-17 (g up to 42 w
