@@ -319,7 +319,9 @@ __global__ __launch_bounds__(NT) void k_inv_hi(const InvHiArgs a) {
 // Blocks that fit one workgroup (2^10 to 2^13 here, 2^14 and 2^15 in thc_big.hpp): the whole inverse transform in one
 // launch.  What bounds the two passes is bytes and, in small calls, launches: the intermediate's 8 bytes per
 // coordinate and one launch go.  Rounds of 8 workers with error feedback: 4096 blocks of 2^13 2031 -> 1505 us, 512 blocks
-// of 2^15 999 -> 764 us; one block of 2^14 without it 36 -> 25 us.  No size was found where two passes are faster.
+// of 2^15 999 -> 764 us; one block of 2^14 without it 36 -> 25 us.  Calls back to back are faster at every size.  A call
+// that is waited for is not with up to 16 blocks of 2^14 or 2^15, where one workgroup's chain is longer than two short
+// launches of several (2^15: 20.5 -> 21.0 us, with error feedback 32.3 -> 33.5); from 32 blocks on it is (22.6 -> 21.5).
 // ---------------------------------------------------------------------------------------------
 // `N` results of a thread: scale, diagonal, and with EFM 1 / 2 (binary32 / bf16 gradient) e <- (grad + e) - that.  All
 // operands are requested before the first store, which goes to the buffer some of them come from.
