@@ -339,7 +339,11 @@ void launch_big_inv_lo(const Plan& pl, const BigInvLoArgs& a, uint32_t W, hipStr
 void run_mids(const Plan& pl, float* x, uint64_t d, uint32_t W, hipStream_t s) {
   for (int m = 0; m < pl.nmid; ++m) {
     MidArgs a{x, d, pl.midmap[m]};
-    dispatch_0_7<LaunchMid>(pl.mid[m], a, tiles_of(d), W, s);
+    switch (pl.mid[m]) {   // blocks of 2^23 and more
+      case 5: LaunchMid<5>::run(a, tiles_of(d), W, s); break;
+      case 6: LaunchMid<6>::run(a, tiles_of(d), W, s); break;
+      default: LaunchMid<7>::run(a, tiles_of(d), W, s); break;
+    }
   }
 }
 

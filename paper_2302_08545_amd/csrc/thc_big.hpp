@@ -355,9 +355,12 @@ __global__ __launch_bounds__(NT, 4) void k_big_quant(const BigQuantArgs a) {
   const int t = threadIdx.x;
   const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
   const uint64_t base = big_hi_base<R, XO>(tile);
+  const uint32_t ent = a.lut[t & 255];   // requested before the tile, so that the table is made while that travels
   float v[8][8];
+  __builtin_amdgcn_sched_barrier(0);
   big_hi_load<R, XO>(a.x + (uint64_t)vec * a.d + base, t, v);
-  build_quant_lut(a, lut, t);
+  __builtin_amdgcn_sched_barrier(0);
+  build_quant_lut(ent, lut, t);
   if (t == 0) {
     const uint32_t blk = tile >> R;
     const float M = a.range_M[blk];

@@ -199,8 +199,9 @@ __global__ __launch_bounds__(256) void k_range_small(const RangeArgs a) {
   a.range_M[k] = range_from_sum(smax, a.t_p, a.L);
 }
 
+template <int TOTALS>     // totals of 64 partial sums a worker may have
 struct SmemRange {
-  double wsum[MAXW][RANGE_NT / 64];
+  double wsum[MAXW][TOTALS];
 };
 
 // largest sum over the lanes that hold one (NaN never wins, as in a loop of comparisons from 0)
@@ -214,35 +215,52 @@ __device__ __forceinline__ double wave_largest(double s) {
   return m;
 }
 
-// The range of one block of at most 8 tiles by one wave, lane i on worker i: the same sums as k_range_small.
-__device__ __forceinline__ float small_block_range(const double* partials, uint64_t pstride, uint32_t n, uint32_t ppb,
-                                                   uint64_t k, float t_p, uint32_t L) {
-  const uint32_t lane = threadIdx.x & 63;
-  double s = 0.0;
-  if (lane < n) {
-    const double* const p = partials + (uint64_t)lane * pstride + k * ppb;
-    for (uint32_t j = 0; j < ppb; ++j) s += p[j];
+// The range of one block of at most 8 tiles by one wave, lane i on worker i: the same sums as k_range_small.  In two
+// steps, so that a tile's loads can be requested between them and neither waits for the other.
+template <int PPB>
+struct SmallRange {
+  double p[PPB];
+  __device__ __forceinline__ void request(const double* partials, uint64_t pstride, uint32_t n, uint64_t k) {
+    const uint32_t lane = threadIdx.x & 63;
+    const double* const q = partials + (uint64_t)(lane < n ? lane : 0u) * pstride + k * PPB;
+#pragma unroll
+    for (int j = 0; j < PPB; ++j) p[j] = q[j];
   }
-  return range_from_sum(wave_largest(s), t_p, L);
-}
+  __device__ __forceinline__ float range(uint32_t n, float t_p, uint32_t L) const {
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < PPB; ++j) s += p[j];
+    return range_from_sum(wave_largest((threadIdx.x & 63) < n ? s : 0.0), t_p, L);
+  }
+};
 
 // Larger blocks: one workgroup of RANGE_NT threads per block k.  Sigma x^2 of every worker in a fixed summation
 // order (partial sums strided by RANGE_NT, butterflies over each 64 of them, then those totals in sequence), the maximum
 // over workers, and M, returned by the first wave (other threads return 0).  `partials` points at this call's first
 // partial sum.  What bounds it is latency, so the (worker, 64 partial sums) pairs are dealt to the eight waves, four
-// loads in flight each, and one lane per worker adds the totals up.
+// loads in flight each, and one lane per worker adds the totals up.  meanwhile() runs once in every wave, between the
+// first loads and what waits for them.
+template <int TOTALS, class Meanwhile>
 __device__ __forceinline__ float block_range(const double* partials, uint64_t pstride, uint32_t n, uint32_t ppb,
-                                             uint64_t k, float t_p, uint32_t L, SmemRange& sm) {
+                                             uint64_t k, float t_p, uint32_t L, SmemRange<TOTALS>& sm,
+                                             Meanwhile&& meanwhile) {
   const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const uint32_t lc = ppb >= RANGE_NT ? 3 : ppb >= 256 ? 2 : ppb >= 128 ? 1 : 0;   // log2 of the totals per worker
   const uint32_t items = n << lc;
-  for (uint32_t it = wave; it < items; it += 4 * (RANGE_NT / 64)) {
+  uint32_t it = wave;
+  do {
     double s[4];
 #pragma unroll
+    for (int u = 0; u < 4; ++u) {      // what does not exist is read from where something does, and not used
+      const uint32_t item = it + u * (RANGE_NT / 64), i = item < items ? item : 0u;
+      const uint32_t j = 64 * (i & ((1u << lc) - 1u)) + lane;
+      s[u] = partials[(uint64_t)(i >> lc) * pstride + k * ppb + (j < ppb ? j : 0u)];
+    }
+    if (it == wave) meanwhile();
+#pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const uint32_t item = it + u * (RANGE_NT / 64);
-      const uint32_t j = 64 * (item & ((1u << lc) - 1u)) + lane;
-      s[u] = item < items && j < ppb ? partials[(uint64_t)(item >> lc) * pstride + k * ppb + j] : 0.0;
+      const uint32_t item = it + u * (RANGE_NT / 64), j = 64 * (item & ((1u << lc) - 1u)) + lane;
+      if (item >= items || j >= ppb) s[u] = 0.0;
     }
     // blocks of more than 512 tiles, a power of two of them: up to 28 loads in flight
     for (uint32_t j0 = RANGE_NT; j0 < ppb; j0 += 7 * RANGE_NT) {
@@ -266,7 +284,8 @@ __device__ __forceinline__ float block_range(const double* partials, uint64_t ps
       s[u] = wave_sum(s[u]);
       if (lane == 0) sm.wsum[item >> lc][item & ((1u << lc) - 1u)] = s[u];
     }
-  }
+    it += 4 * (RANGE_NT / 64);
+  } while (it < items);
   __syncthreads();
   float M = 0.f;
   if (wave == 0) {
@@ -279,8 +298,8 @@ __device__ __forceinline__ float block_range(const double* partials, uint64_t ps
 }
 
 __global__ __launch_bounds__(RANGE_NT) void k_range(const RangeArgs a) {
-  __shared__ SmemRange sm;
-  const float M = block_range(a.partials, a.pstride, a.n, 1u << (a.L - a.L1), blockIdx.x, a.t_p, a.L, sm);
+  __shared__ SmemRange<RANGE_NT / 64> sm;
+  const float M = block_range(a.partials, a.pstride, a.n, 1u << (a.L - a.L1), blockIdx.x, a.t_p, a.L, sm, [] {});
   if (threadIdx.x == 0) a.range_M[blockIdx.x] = M;
 }
 
@@ -394,18 +413,43 @@ __device__ __forceinline__ void hi_back(const float* lds, int t, int (&idx)[2], 
   }
 }
 
-// generic (slow) front for R < 2 and partial tiles: whole transform part through LDS
+// R < 2: a thread's two groups of eight consecutive values (the two rows of the same columns where there are two) come
+// straight from memory.  Coordinates past the vector's end belong to blocks of their own, whose results nobody takes:
+// what is read for them does not matter, and loads that are requested in any case need not be waited for where an
+// earlier one is wanted.
 template <int R>
-__device__ __forceinline__ void hi_load_to_lds(const float* src, const HiGeom<R>& g, uint64_t d, float* lds, int t) {
-  float4 v[4];
+__device__ __forceinline__ void hi_direct_load(const float* src, const HiGeom<R>& g, uint64_t d, int t,
+                                               float4 (&x)[2][2]) {
+  static_assert(R < 2, "more rows go through LDS");
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint64_t j = g.coord(4 * (i * NT + t));
-    v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (j < d) v[i] = *reinterpret_cast<const float4*>(src + j);
+  for (int h = 0; h < 2; ++h) {
+    const uint64_t j = g.coord(8 * (t + NT * h));
+    const float4* const p = reinterpret_cast<const float4*>(src + (j < d ? j : 0));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const float4 r = p[k];
+      x[h][k] = make_float4(r.x, r.y, r.z, r.w);
+    }
   }
+}
+
+template <int R>
+__device__ __forceinline__ void hi_direct_stages(const float4 (&x)[2][2], float (&v)[2][8]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(&lds[4 * (i * NT + t)]) = v[i];
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      v[h][4 * k] = x[h][k].x; v[h][4 * k + 1] = x[h][k].y; v[h][4 * k + 2] = x[h][k].z; v[h][4 * k + 3] = x[h][k].w;
+    }
+  }
+  if constexpr (R == 1) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float a = v[0][e], b = v[1][e];
+      v[0][e] = a + b;
+      v[1][e] = a - b;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -423,27 +467,15 @@ __global__ __launch_bounds__(NT) void k_mid(MidArgs a) {
   const int t = threadIdx.x;
   const HiGeom<R> g(blockIdx.x, a.tm);
   a.x += (uint64_t)blockIdx.y * a.d;
-  if constexpr (R >= 2) {
-    hi_front<R>(a.x, g, lds, t);
-    int idx[2];
-    float v[2][8];
-    hi_back<R>(lds, t, idx, v);
+  hi_front<R>(a.x, g, lds, t);
+  int idx[2];
+  float v[2][8];
+  hi_back<R>(lds, t, idx, v);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float* o = a.x + g.coord(idx[h]);
-      *reinterpret_cast<float4*>(o) = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
-      *reinterpret_cast<float4*>(o + 4) = make_float4(v[h][4], v[h][5], v[h][6], v[h][7]);
-    }
-  } else {
-    hi_load_to_lds<R>(a.x, g, a.d, lds, t);
-    lds_stages<LOG_TILE - R, LOG_TILE, false, PLAIN>(lds, t, [](int, int, float) {});
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = 4 * (i * NT + t);
-      const uint64_t j = g.coord(idx);
-      if (j < a.d) *reinterpret_cast<float4*>(a.x + j) = *reinterpret_cast<const float4*>(&lds[idx]);
-    }
+  for (int h = 0; h < 2; ++h) {
+    float* o = a.x + g.coord(idx[h]);
+    *reinterpret_cast<float4*>(o) = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
+    *reinterpret_cast<float4*>(o + 4) = make_float4(v[h][4], v[h][5], v[h][6], v[h][7]);
   }
 }
 
@@ -561,29 +593,31 @@ __device__ __forceinline__ uint4 quant_lut_entry(uint32_t ent) {
                     __float_as_uint(half * 256.0f), ent >> 16);
 }
 
-template <class A>
-__device__ __forceinline__ void build_quant_lut(const A& a, uint4* lut, int t) {
-  if (t < 256) lut[t] = quant_lut_entry(a.lut[t]);
+__device__ __forceinline__ void build_quant_lut(uint32_t ent, uint4* lut, int t) {
+  if (t < 256) lut[t] = quant_lut_entry(ent);
 }
 
 __device__ __forceinline__ float lower_of(const float* range_m, uint64_t blk, float M) {
   return range_m ? range_m[blk] : -M;
 }
 
+template <int R>
 struct alignas(16) SmemQuant {
-  float lds[TILE];
+  float lds[R < 2 ? 4 : TILE];   // one or two rows need no exchange
   uint32_t lut[256][4];   // uint4 entries
   float sQ[8][4];         // QuantScalars
   int sCare[8];           // the block takes the careful form
 };
+
+// What FIND keeps of the partial sums: its blocks of up to 2^20 coordinates have at most 128 of them a worker.
+using FindSmem = SmemRange<2>;
 
 // One tile of the pass: tile index `tile` of the launch's vector `wk`, whose half-rotated image starts at xw.
 // FIND: the range comes from the partial sums of squares, found again by every workgroup (see k_fwd_hi_quant).
 // QUAD: see store_packed8; off where its registers would spill.
 template <int R, bool CFOLD, bool FIND = false, bool QUAD = false, class A>
 __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_t wk, const float* xw,
-                                              SmemQuant& sm, SmemRange* smr = nullptr) {
-  float* const lds = sm.lds;
+                                              SmemQuant<R>& sm, FindSmem* smr = nullptr) {
   uint4* const lut = reinterpret_cast<uint4*>(sm.lut);
   QuantScalars* const sQ = reinterpret_cast<QuantScalars*>(sm.sQ);
   int* const sCare = sm.sCare;
@@ -592,30 +626,47 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
   uint8_t* const packed = static_cast<uint8_t*>(const_cast<void*>(a.packed.p[wk]));
   const uint32_t stream = a.worker + wk;
 
+  // Loads come back in the order of their requests: what the tables and the range need goes first, so that both are made
+  // while the tile's own loads travel.
+  const uint32_t ent = a.lut[t & 255];
   if constexpr (R >= 2) {
     const HiGeom<R> g(tile, a.tm);
+    const uint64_t blk = g.base >> a.L;         // the whole tile lies in one block
     float4 x[4];
-    hi_issue_loads<R>(xw, g, t, x);             // tile loads first: everything below overlaps their latency
-    build_quant_lut(a, lut, t);
     float found = 0.f;
+    if constexpr (FIND && R > 3) {
+      found = block_range(a.partials, a.pstride, a.n, 1u << R, blk, a.t_p, a.L, *smr, [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        hi_issue_loads<R>(xw, g, t, x);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    } else if constexpr (FIND) {
+      SmallRange<1 << R> r;
+      if (t < 64) r.request(a.partials, a.pstride, a.n, blk);
+      __builtin_amdgcn_sched_barrier(0);
+      hi_issue_loads<R>(xw, g, t, x);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t < 64) found = r.range(a.n, a.t_p, a.L);
+    } else {
+      __builtin_amdgcn_sched_barrier(0);
+      hi_issue_loads<R>(xw, g, t, x);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if constexpr (FIND) {
-      const uint64_t blk = g.base >> a.L;
-      if constexpr (R > 3) found = block_range(a.partials, a.pstride, a.n, 1u << R, blk, a.t_p, a.L, *smr);
-      else if (t < 64) found = small_block_range(a.partials, a.pstride, a.n, 1u << R, blk, a.t_p, a.L);
       if (t == 0 && wk == 0 && g.base == blk << a.L) a.range_out[blk] = found;
     }
-    if (t == 0) {                               // the whole tile lies in one block
-      const uint64_t blk = g.base >> a.L;
+    if (t == 0) {
       const float M = FIND ? found : a.range_M[blk], m = FIND ? -M : lower_of(a.range_m, blk, M);
       bool careful;
       sQ[0] = quant_scalars(M, m, a.g, a.lut[a.g - 1], a.c, CFOLD, careful);
       sCare[0] = careful;
     }
-    hi_r0_to_lds<R>(x, lds, t);
-    hi_round1<R>(lds, t);
+    build_quant_lut(ent, lut, t);
+    hi_r0_to_lds<R>(x, sm.lds, t);
+    hi_round1<R>(sm.lds, t);
     int idx[2];
     float v[2][8];
-    hi_back<R>(lds, t, idx, v);
+    hi_back<R>(sm.lds, t, idx, v);
     const QuantScalars s = sQ[0];
     const bool careful = __builtin_amdgcn_readfirstlane(sCare[0]) != 0;   // uniform over the workgroup
     const uint64_t q0 = (a.j0 + g.base) >> 3;   // tiles start on multiples of 64 coordinates
@@ -632,16 +683,24 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
     }
   } else {
     const HiGeom<R> g(tile, a.tm);
-    build_quant_lut(a, lut, t);
     // per-block scalars; a tile spans more than one block only when B < 8192 (then R == 0)
     const int nblk = a.L < LOG_TILE ? (TILE >> a.L) : 1;
     const int bt0 = FIND ? t >> 6 : t;          // FIND: a wave per block
+    const uint64_t blk = (g.base >> a.L) + bt0;
+    const bool mine = bt0 < nblk && blk < (a.d >> a.L);
+    SmallRange<1 << R> r;                       // blocks of up to 2^13 have one partial sum a worker
+    if constexpr (FIND) {
+      if (mine) r.request(a.partials, a.pstride, a.n, blk);
+    }
+    float4 x[2][2];
+    __builtin_amdgcn_sched_barrier(0);
+    hi_direct_load<R>(xw, g, a.d, t, x);
+    __builtin_amdgcn_sched_barrier(0);
     if (bt0 < nblk) {
-      const uint64_t blk = (g.base >> a.L) + bt0;
       float M = 0.f, m = 0.f;
-      if (blk < (a.d >> a.L)) {
+      if (mine) {
         if constexpr (FIND) {
-          M = small_block_range(a.partials, a.pstride, a.n, 1u << (a.L - a.L1), blk, a.t_p, a.L);
+          M = r.range(a.n, a.t_p, a.L);
           m = -M;
           if ((t & 63) == 0 && wk == 0 && (a.L < LOG_TILE || g.base == blk << a.L)) a.range_out[blk] = M;
         } else {
@@ -656,9 +715,10 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
         sCare[bt0] = careful;
       }
     }
-    hi_load_to_lds<R>(xw, g, a.d, lds, t);
-    lds_stages<LOG_TILE - R, LOG_TILE, false, PLAIN>(lds, t, [](int, int, float) {});
+    build_quant_lut(ent, lut, t);
     __syncthreads();
+    float v[2][8];
+    hi_direct_stages<R>(x, v);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int idx = 8 * (t + NT * h);
@@ -666,27 +726,28 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
       if (j >= a.d) continue;
       const int bt = a.L < LOG_TILE ? (idx >> a.L) : 0;
       const QuantScalars s = sQ[bt];
-      const float4 p0 = *reinterpret_cast<const float4*>(&lds[idx]);
-      const float4 p1 = *reinterpret_cast<const float4*>(&lds[idx + 4]);
-      const float hv[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
       const uint64_t q = (a.j0 + j) >> 3;
       const uint4 rnd = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, stream, a.k0, a.k1);
       uint32_t z[8];
-      if (!sCare[bt]) quantize8<true>(hv, rnd, s, lut, z);
-      else quantize8<true, true>(hv, rnd, s, lut, z);
+      if (!sCare[bt]) quantize8<true>(v[h], rnd, s, lut, z);
+      else quantize8<true, true>(v[h], rnd, s, lut, z);
       store_packed8<QUAD>(packed, j, a.b, z);
     }
   }
 }
 
 // FIND: the pass takes the place of the range kernel before it.  In a small call a launch of its own costs more than
-// the work: the workgroups of a block all add up the block's partial sums, which the cache holds.
+// the work: the workgroups of a block all add up the block's partial sums, which the cache holds.  With the partial sums
+// requested before the tile, room in LDS for the totals that occur here only and 64 registers, so that four workgroups
+// share a compute unit as without it: 17.4 -> 15.4 us for one block of 2^20 x 10 vectors, 5.6 -> 4.9 us for two blocks of
+// 2^14 x 4, and 67.1 -> 58.2 us (without FIND 58.3 -> 53.0) for 512 blocks of 2^14 x 8, whose tiles of one or two rows
+// no longer go through LDS.
 template <int R, bool CFOLD, bool FIND>
-__global__ __launch_bounds__(NT, FIND ? 4 : 8) void k_fwd_hi_quant(const QuantArgs a) {
-  __shared__ SmemQuant sm;
+__global__ __launch_bounds__(NT, 8) void k_fwd_hi_quant(const QuantArgs a) {
+  __shared__ SmemQuant<R> sm;
   const float* const xw = a.x + (uint64_t)blockIdx.y * a.d;
   if constexpr (FIND) {
-    __shared__ SmemRange smr;
+    __shared__ FindSmem smr;
     hi_quant_tile<R, CFOLD, true, true>(a, blockIdx.x, blockIdx.y, xw, sm, &smr);
   } else {
     hi_quant_tile<R, CFOLD, false, true>(a, blockIdx.x, blockIdx.y, xw, sm);

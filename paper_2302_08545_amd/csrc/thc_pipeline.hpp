@@ -144,10 +144,10 @@ __device__ __forceinline__ void pipe_publish(uint32_t* unit_sync, uint32_t phase
 
 constexpr size_t pipe_smem_bytes() {
   size_t m = sizeof(SmemLo);
-  if (sizeof(SmemQuant) > m) m = sizeof(SmemQuant);
+  if (sizeof(SmemQuant<7>) > m) m = sizeof(SmemQuant<7>);
   if (sizeof(SmemInvLo) > m) m = sizeof(SmemInvLo);
   if (sizeof(SmemInvHi) > m) m = sizeof(SmemInvHi);
-  if (sizeof(SmemRange) > m) m = sizeof(SmemRange);
+  if (sizeof(SmemRange<8>) > m) m = sizeof(SmemRange<8>);
   return m;
 }
 
@@ -172,7 +172,8 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
     uint32_t* us = P.sync + (uint64_t)u * SYNC_PER_UNIT;
     if (!pipe_wait<true>(us + NXCD * SYNC_STRIDE, NXCD, P.status, &flag)) return;
     if (P.compute_range) {
-      const float M = block_range(P.partials, P.pstride, P.W, TB, u, P.t_p, P.L, *reinterpret_cast<SmemRange*>(raw));
+      const float M = block_range(P.partials, P.pstride, P.W, TB, u, P.t_p, P.L, *reinterpret_cast<SmemRange<8>*>(raw),
+                                  [] {});
       if (threadIdx.x == 0) {
         P.range_M[u] = M;
         __builtin_amdgcn_s_waitcnt(0);
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
     if (!pipe_wait<true>(us + SYNC_READY * SYNC_STRIDE, 1u, P.status, &flag)) return;
     const QuantView a{P.range_M, nullptr, P.packed, P.d, P.j0, P.hi_tm, P.L, P.b, P.g, P.round, P.worker0, P.k0, P.k1,
                       P.c, P.lut};
-    hi_quant_tile<R, CFOLD>(a, gt, w, vec, *reinterpret_cast<SmemQuant*>(raw));
+    hi_quant_tile<R, CFOLD>(a, gt, w, vec, *reinterpret_cast<SmemQuant<R>*>(raw));
     if constexpr (EF) {
       pipe_publish(us, 1, Tu >> 3);
     } else {

@@ -136,15 +136,21 @@ inline TileMap lo_tilemap(const Plan& pl, uint64_t len) {
   return m.L ? m : pl.lo;
 }
 
-// Whether the quantizer finds the range itself.  Small calls are bound by their launches, about 3 us each on the host and
-// 6 on the device: rounds of 2^15 and 2^20 coordinates with 4 workers went from 35.8 to 32.8 us.  Against that, every
-// workgroup reads its block's partial sums over again, and its LDS lets three instead of four share a compute unit.
-// Blocks of 2^17 to 2^20: 1280 workgroups gain 4 %, 1536 and 1792 lose 1 to 3 %, 4096 lose 8 to 12 %.  Blocks of up to
-// 2^16, with at most 8 partial sums, which the launch of its own adds up one worker after another: 4096 workgroups gain 1
-// to 24 % with 16 or more workers, with 8 between -1 % (2^10) and 6 % (2^16); 4 workers gain up to 2 % at 3072 and lose
-// up to 3 % at 4096; 1 and 2 lose 0 to 3 % at 3072.  Blocks of 2^22 lose 2 % at 1024.
+// Whether the quantizer finds the range itself.  Small calls are bound by their launches, about 2.4 us each on the host and
+// 3 on the device.  Against that, every workgroup reads its block's partial sums over again, while its tile's loads travel.
+// Measured, first pass and quantizer with the range found there against a launch of its own (time of the first over the
+// second), by the workgroups of the launch:
+//   blocks of 2^17 to 2^20, up to 128 partial sums a worker: 1 to 4 workers 0.94 to 0.97 at 1024, 0.96 to 1.00 at 1280,
+//     0.98 to 1.01 at 1536, 1.04 to 1.08 at 4096; 8 and 16 workers 0.94 to 0.99 at 512 and 1024, 1.00 to 1.05 at 1280 to
+//     1536; 32 workers 0.97 at 512, 1.03 at 1024.
+//   blocks of up to 2^16, at most 8 partial sums, which the launch of its own adds up one worker after another: 1 and 2
+//     workers 0.90 to 0.98 at up to 2048, 0.97 to 1.01 at 3072 and 4096; 4 and 8 workers 0.83 to 0.98 at up to 4096; 16
+//     and 32 workers 0.38 to 0.95 at up to 6144.
+// Blocks of 2^22 lose 2 % at 1024.
 inline bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {   // 8192-coordinate tiles of each of W vectors
-  return pl.L <= 20 && tiles * W <= (pl.L > 16 ? 1280u : W > 4 ? 4096u : W > 2 ? 3072u : 2048u);
+  if (pl.L > 20) return false;
+  if (pl.L > 16) return tiles * W <= (W > 16 ? 512u : W > 4 ? 1024u : 1280u);
+  return tiles * W <= (W > 8 ? 6144u : W > 2 ? 4096u : 2048u);
 }
 
 // Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of

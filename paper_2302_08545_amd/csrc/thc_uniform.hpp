@@ -113,7 +113,7 @@ struct HiMinMaxArgs {
 
 template <int R>
 __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
-  __shared__ __align__(16) float lds[TILE];
+  __shared__ __align__(16) float lds[R < 2 ? 4 : TILE];
   __shared__ float smin[16], smax[16];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const HiGeom<R> g(blockIdx.x, a.tm);
@@ -145,9 +145,10 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
       pmax[blockIdx.x] = mx;
     }
   } else {
-    hi_load_to_lds<R>(x, g, a.d, lds, t);
-    lds_stages<LOG_TILE - R, LOG_TILE, false, PLAIN>(lds, t, [](int, int, float) {});
-    __syncthreads();
+    float4 r[2][2];
+    float v[2][8];
+    hi_direct_load<R>(x, g, a.d, t, r);
+    hi_direct_stages<R>(r, v);
     // thread owns tile indices [8(t + 512h), +8): a wave covers 512 consecutive values per h
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -155,14 +156,12 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
       const uint64_t j = g.coord(idx);
       float mn = __builtin_inff(), mx = -__builtin_inff();
       if (j < a.d) {
-        float4 p0 = *reinterpret_cast<const float4*>(&lds[idx]);
-        float4 p1 = *reinterpret_cast<const float4*>(&lds[idx + 4]);
-        p0.x *= a.c; p0.y *= a.c; p0.z *= a.c; p0.w *= a.c;
-        p1.x *= a.c; p1.y *= a.c; p1.z *= a.c; p1.w *= a.c;
-        mn = __builtin_fminf(__builtin_fminf(__builtin_fminf(p0.x, p0.y), __builtin_fminf(p0.z, p0.w)),
-                             __builtin_fminf(__builtin_fminf(p1.x, p1.y), __builtin_fminf(p1.z, p1.w)));
-        mx = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(p0.x, p0.y), __builtin_fmaxf(p0.z, p0.w)),
-                             __builtin_fmaxf(__builtin_fmaxf(p1.x, p1.y), __builtin_fmaxf(p1.z, p1.w)));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float q = v[h][e] * a.c;
+          mn = __builtin_fminf(mn, q);
+          mx = __builtin_fmaxf(mx, q);
+        }
       }
       mn = wave_min(mn);
       mx = wave_max(mx);
