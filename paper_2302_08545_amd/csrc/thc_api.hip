@@ -261,10 +261,22 @@ void launch_range(const RangeArgs& r, hipStream_t s) {
   else k_range<<<dim3((unsigned)K), dim3(RANGE_NT), 0, s>>>(r);
 }
 
+template <int SB, int TB>
+void launch_inv_lo_k(const InvLoArgs& a, bool split, dim3 grid, hipStream_t s) {
+  if (split) k_inv_lo<true, SB, TB><<<grid, dim3(NT), 0, s>>>(a);
+  else k_inv_lo<false, SB, TB><<<grid, dim3(NT), 0, s>>>(a);
+}
+
 void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
-  const dim3 grid((unsigned)tiles, W), blk(NT);
-  if (pl.split) k_inv_lo<true><<<grid, blk, 0, s>>>(a);
-  else k_inv_lo<false><<<grid, blk, 0, s>>>(a);
+  const dim3 grid((unsigned)tiles, W);
+  if (a.use_table) {
+    if (a.src_bits == 4) launch_inv_lo_k<4, 1>(a, pl.split, grid, s);
+    else launch_inv_lo_k<0, 1>(a, pl.split, grid, s);
+  } else {
+    if (a.src_bits == 8) launch_inv_lo_k<8, 0>(a, pl.split, grid, s);
+    else if (a.src_bits == 16) launch_inv_lo_k<16, 0>(a, pl.split, grid, s);
+    else launch_inv_lo_k<0, 0>(a, pl.split, grid, s);
+  }
 }
 
 // ---- passes on tiles of 2^15 coordinates (thc_big.hpp) ------------------------------------------------------------
@@ -351,9 +363,17 @@ void run_mids(const Plan& pl, float* x, uint64_t d, uint32_t W, hipStream_t s) {
 template <int L1>
 void launch_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)tiles_of(a.lo.d), W), blk(NT);
-  if (efm == 0) k_inv_whole<L1, 0><<<grid, blk, 0, s>>>(a);
-  else if (efm == 1) k_inv_whole<L1, 1><<<grid, blk, 0, s>>>(a);
-  else k_inv_whole<L1, 2><<<grid, blk, 0, s>>>(a);
+  const uint32_t bits = a.lo.src_bits;
+  if (efm == 0) {
+    if (bits == 8) k_inv_whole<L1, 8, 0><<<grid, blk, 0, s>>>(a);
+    else k_inv_whole<L1, 0, 0><<<grid, blk, 0, s>>>(a);
+  } else if (efm == 1) {
+    if (bits == 4) k_inv_whole<L1, 4, 1><<<grid, blk, 0, s>>>(a);
+    else k_inv_whole<L1, 0, 1><<<grid, blk, 0, s>>>(a);
+  } else {
+    if (bits == 4) k_inv_whole<L1, 4, 2><<<grid, blk, 0, s>>>(a);
+    else k_inv_whole<L1, 0, 2><<<grid, blk, 0, s>>>(a);
+  }
 }
 
 template <int L>

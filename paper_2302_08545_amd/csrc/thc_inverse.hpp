@@ -110,8 +110,9 @@ struct alignas(16) SmemInvLo {
 };
 
 // One tile: tile index `tile` of the launch's vector `vec`; put(o, value) takes each result, o its offset from the
-// tile's first coordinate.
-template <int L1, bool XO, class A, class Put>
+// tile's first coordinate.  SB and TB are the width and the kind of the codes where the launch knows them (TB 1: table
+// indices, 0: sums, -1: a.use_table says); SB = 0: a.src_bits says.
+template <int L1, bool XO, int SB, int TB, class A, class Put>
 __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_t vec, SmemInvLo& sm, Put&& put) {
   static_assert(!XO || L1 == LOG_TILE, "the row-split tile needs blocks of at least 2^16");
   constexpr bool GUARD = L1 < LOG_TILE;
@@ -126,18 +127,22 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_
   const uint64_t j = off + lo_map<XO>(idx);
   const bool ok = !GUARD || j < a.d;
   const uint8_t* const src = static_cast<const uint8_t*>(a.src.p[vec]);
+  const uint32_t bits = SB ? SB : a.src_bits;
+  const bool use_table = TB < 0 ? a.use_table != 0 : TB != 0;
 
   // raw bits first, so the load is in flight while the block constants are prepared
+  uint32_t entry = 0;
+  if (use_table && t < 256) entry = a.table[t];
   uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   uint32_t y[16];
-  const bool staged = !codes_fast_width(a.src_bits);
+  const bool staged = !codes_fast_width(bits);
   if (!staged) {
-    if (ok) codes_load(src, a.src_bits, j, w, y);
+    if (ok) codes_load(src, bits, j, w, y);
   } else {
     // Any other width: the tile's eight runs of 1024 codes (128 * bits bytes each, dword aligned) are copied
     // into the still unused tile buffer with coalesced loads; every thread then cuts its sixteen fields out.
     uint32_t* stage = reinterpret_cast<uint32_t*>(lds);
-    const uint32_t per_row = 32u * a.src_bits;                       // dwords per 1024 codes: fewer than NT
+    const uint32_t per_row = 32u * bits;                             // dwords per 1024 codes: fewer than NT
     if ((uint32_t)t < per_row) {
       uint32_t val[8];
 #pragma unroll
@@ -145,32 +150,40 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_
         const uint64_t jr = off + lo_map<XO>(1024u * r);             // first coordinate of the run
         val[r] = 0;
         if (!GUARD || jr < a.d)                                      // runs exist whole or not at all: 1024 divides d
-          val[r] = reinterpret_cast<const uint32_t*>(src + (jr >> 3) * a.src_bits)[t];
+          val[r] = reinterpret_cast<const uint32_t*>(src + (jr >> 3) * bits)[t];
       }
 #pragma unroll
       for (uint32_t r = 0; r < 8; ++r) stage[r * per_row + t] = val[r];
     }
   }
 
+  // A tile inside one block looks up values on the block's range; one of several blocks, or whose kind is not known, looks
+  // up the table's own values.
+  constexpr bool SCALED = TB == 1 && L1 == LOG_TILE;
   const int nblk = a.L < LOG_TILE ? (TILE >> a.L) : 1;
-  if (t < nblk) {
-    const uint64_t blk = (off >> a.L) + t;
+  if (SCALED ? t < (SB ? 1 << SB : 256) : t < nblk) {
+    const uint64_t blk = (off >> a.L) + (SCALED ? 0 : t);
     float M = 0.f, m = 0.f;
     if (blk < (a.d >> a.L)) { M = a.range_M[blk]; m = lower_of(a.range_m, blk, M); }
-    sM[t] = m;                                                   // the affine map only needs the lower end
-    sStep[t] = (float)(((double)M - (double)m) / (double)a.divisor);
+    const float step = (float)(((double)M - (double)m) / (double)a.divisor);
+    if constexpr (SCALED) {
+      tabf[t] = (float)entry * step + m;
+    } else {
+      sM[t] = m;                                                     // the affine map only needs the lower end
+      sStep[t] = step;
+    }
   }
-  if (a.use_table && t < 256) tabf[t] = (float)a.table[t];
+  if (!SCALED && use_table && t < 256) tabf[t] = (float)entry;
   __syncthreads();
 
   if (!staged) {
-    codes_decode(a.src_bits, ok, w, y);
+    codes_decode(bits, ok, w, y);
   } else {
     // sixteen fields start at bit 16 * (field number / 16) * bits of the run: on a dword boundary or in its middle
     const uint32_t* stage = reinterpret_cast<const uint32_t*>(lds);
-    const uint32_t pos = (uint32_t)(idx & 1023) * a.src_bits;
-    const uint32_t* first = stage + (uint32_t)(idx >> 10) * 32u * a.src_bits + (pos >> 5);
-    switch (a.src_bits) {
+    const uint32_t pos = (uint32_t)(idx & 1023) * bits;
+    const uint32_t* first = stage + (uint32_t)(idx >> 10) * 32u * bits + (pos >> 5);
+    switch (bits) {
 #define THC_CUT(W) case W: cut16<W>(first, (pos & 16u) != 0, y); break;
       THC_CUT(3) THC_CUT(5) THC_CUT(6) THC_CUT(7) THC_CUT(9) THC_CUT(10) THC_CUT(11) THC_CUT(12) THC_CUT(13)
       THC_CUT(14) THC_CUT(15)
@@ -184,12 +197,13 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_
     __syncthreads();                                                 // every field is out before the tile is written
   }
   const int bt = a.L < LOG_TILE ? (idx >> a.L) : 0;
-  const float lo = sM[bt], step = sStep[bt];
+  float lo = 0.f, step = 0.f;
+  if constexpr (!SCALED) { lo = sM[bt]; step = sStep[bt]; }
   float v[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    const float f = a.use_table ? tabf[y[e]] : (float)y[e];
-    v[e] = ok ? f * step + lo : 0.f;
+    const float f = use_table ? tabf[y[e]] : (float)y[e];
+    v[e] = SCALED ? f : ok ? f * step + lo : 0.f;
   }
   bfly<4>(v);
 #pragma unroll
@@ -199,16 +213,20 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_
   lds_stages<4, L1, true, SWZ>(lds, t, [&](int base, int eoff, float val) { put(lo_map<XO>(base) + lo_map<XO>(eoff), val); });
 }
 
-template <bool XO, class A>
+template <bool XO, int SB, int TB, class A>
 __device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t vec, float* dst_vec, SmemInvLo& sm) {
   float* const dst = dst_vec + tm_base(a.tm, tile);
-  inv_lo_stages<LOG_TILE, XO>(a, tile, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
+  inv_lo_stages<LOG_TILE, XO, SB, TB>(a, tile, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
 }
 
-template <bool XO>
-__global__ __launch_bounds__(NT) void k_inv_lo(const InvLoArgs a) {
+// What bounds it: writing 4 bytes a coordinate (pure writes reach 5.7 TB/s here).  Decoding is a large part of its
+// instructions, so the widths and sources that rounds use have instantiations of their own: 2^28 coordinates from 8-bit
+// sums 251 -> 231 us, from 4-bit indices, whose values are looked up on the block's range, 268 -> 245 us; one block of
+// 2^20 from 4-bit indices 5.4 -> 4.3 us.
+template <bool XO, int SB, int TB>
+__global__ __launch_bounds__(NT, 8) void k_inv_lo(const InvLoArgs a) {
   __shared__ SmemInvLo sm;
-  inv_lo_tile<XO>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
+  inv_lo_tile<XO, SB, TB>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -353,8 +371,9 @@ struct InvWholeArgs {
   float c;
 };
 
-template <int L1, int EFM>
-__global__ __launch_bounds__(NT) void k_inv_whole(const InvWholeArgs a) {
+// SB as for k_inv_lo: 2^28 coordinates in blocks of 2^13 from 8-bit sums 285 -> 260 us.
+template <int L1, int SB, int EFM>
+__global__ __launch_bounds__(NT, EFM == 0 ? 8 : 4) void k_inv_whole(const InvWholeArgs a) {
   __shared__ SmemInvLo sm;
   __shared__ __align__(16) uint32_t sgn[TILE / 32];
   const int t = threadIdx.x;
@@ -367,7 +386,7 @@ __global__ __launch_bounds__(NT) void k_inv_whole(const InvWholeArgs a) {
   float v[16];
   uint32_t at[16];
   int c = 0;
-  inv_lo_stages<L1, false>(a.lo, tile, vec, sm, [&](uint32_t o, float val) { v[c] = val; at[c] = o; ++c; });
+  inv_lo_stages<L1, false, SB, EFM != 0>(a.lo, tile, vec, sm, [&](uint32_t o, float val) { v[c] = val; at[c] = o; ++c; });
   float* const out = static_cast<float*>(const_cast<void*>(a.out.p[vec])) + off;
   const char* const grad = EFM ? static_cast<const char*>(a.grad.p[vec]) + off * (EFM == 2 ? 2 : 4) : nullptr;
   const uint64_t left = a.lo.d - off;
