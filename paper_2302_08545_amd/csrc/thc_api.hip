@@ -1029,9 +1029,14 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
     q.k1 = k1;
     q.j0 = base_coord(p);
     fill_lut(p, q.lut);
-    const dim3 grid((unsigned)tiles_of(p->d)), blk(NT);
-    if (p->in_dtype == THC_DTYPE_BF16) k_uniform_quant<true><<<grid, blk, 0, s>>>(q);
-    else k_uniform_quant<false><<<grid, blk, 0, s>>>(q);
+    const dim3 grid((unsigned)((p->d + UTILE - 1) >> LOG_UTILE)), blk(NT);
+    if (p->in_dtype == THC_DTYPE_BF16) {
+      if (ef_inout) k_uniform_quant<true, true><<<grid, blk, 0, s>>>(q);
+      else k_uniform_quant<true, false><<<grid, blk, 0, s>>>(q);
+    } else {
+      if (ef_inout) k_uniform_quant<false, true><<<grid, blk, 0, s>>>(q);
+      else k_uniform_quant<false, false><<<grid, blk, 0, s>>>(q);
+    }
   }
   if (rotate && ef_inout) {
     // e <- (grad + e) - RHT^-1(X_i): rebuild X_i from the indices, inverse transform, subtract
