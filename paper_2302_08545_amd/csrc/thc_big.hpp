@@ -257,6 +257,16 @@ __device__ __forceinline__ void slot_swap(float (&v)[8][8]) {
     }
 }
 
+// Which tile bits select the XCD: 3 to 5, as for the first pass, but for two cases.  Tiles of 2^25-point blocks hold 128
+// bytes of each of their rows, and an XCD that takes 64 of them in a row fetches whole pages: 2^28 worker-coordinates with
+// error feedback 910 -> 867 us (ascending 928 -> 888), one vector 126 -> 117, the quantizer 287 -> 281.  The error-feedback
+// update of 2^22-point blocks in the split order: 2^29 worker-coordinates in bf16 1432 -> 1402 us, in binary32 729 -> 718.
+// Elsewhere no choice was better throughout (R = 9 gains 2 to 9 % with error feedback and loses 3 % without).
+template <int R, bool XO, bool EF>
+__device__ __forceinline__ uint32_t big_hi_tile() {
+  return xcd_tile<R == 10 ? 6 : R == 7 && XO && EF ? 4 : 3>(blockIdx.x, gridDim.x);
+}
+
 template <int R, bool XO>
 __device__ __forceinline__ void big_hi_load(const float* src, int t, float (&v)[8][8]) {
   constexpr BigLayout m = BigHi<R>::first();
@@ -353,7 +363,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_quant(const BigQuantArgs a) {
   __shared__ SmemBigHi sm;
   uint4* const lut = reinterpret_cast<uint4*>(sm.lut);
   const int t = threadIdx.x;
-  const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint32_t vec = blockIdx.y, tile = big_hi_tile<R, XO, false>();
   const uint64_t base = big_hi_base<R, XO>(tile);
   const uint32_t ent = a.lut[t & 255];   // requested before the tile, so that the table is made while that travels
   float v[8][8];
@@ -546,7 +556,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
   using H = BigHi<R>;
   __shared__ SmemBigInvHi sm;
   const int t = threadIdx.x;
-  const uint32_t vec = blockIdx.y, tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint32_t vec = blockIdx.y, tile = big_hi_tile<R, XO, EFM != 0>();
   const uint64_t base = big_hi_base<R, XO>(tile);
   float v[8][8];
   big_hi_load<R, XO>(a.x + (uint64_t)vec * a.d + base, t, v);
