@@ -143,14 +143,13 @@ inline TileMap lo_tilemap(const Plan& pl, uint64_t len) {
 //   blocks of 2^17 to 2^20, up to 128 partial sums a worker: 1 to 4 workers 0.94 to 0.97 at 1024, 0.96 to 1.00 at 1280,
 //     0.98 to 1.01 at 1536, 1.04 to 1.08 at 4096; 8 and 16 workers 0.94 to 0.99 at 512 and 1024, 1.00 to 1.05 at 1280 to
 //     1536; 32 workers 0.97 at 512, 1.03 at 1024.
-//   blocks of up to 2^16, at most 8 partial sums, which the launch of its own adds up one worker after another: 1 and 2
-//     workers 0.90 to 0.98 at up to 2048, 0.97 to 1.01 at 3072 and 4096; 4 and 8 workers 0.83 to 0.98 at up to 4096; 16
-//     and 32 workers 0.38 to 0.95 at up to 6144.
+//   blocks of up to 2^16, at most 8 partial sums a worker: 1 and 2 workers 0.90 to 0.98 at up to 2048, 0.97 to 1.01 at 3072
+//     and 4096; 4 workers 0.83 to 0.98 at up to 4096; 8 to 32 workers 0.38 to 0.98 at up to 4096.
 // Blocks of 2^22 lose 2 % at 1024.
 inline bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {   // 8192-coordinate tiles of each of W vectors
   if (pl.L > 20) return false;
   if (pl.L > 16) return tiles * W <= (W > 16 ? 512u : W > 4 ? 1024u : 1280u);
-  return tiles * W <= (W > 8 ? 6144u : W > 2 ? 4096u : 2048u);
+  return tiles * W <= (W > 4 ? 4096u : W > 2 ? 3072u : 2048u);
 }
 
 // Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of
