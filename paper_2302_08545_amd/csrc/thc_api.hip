@@ -257,7 +257,7 @@ void launch_fwd_lo(const Plan& pl, const FwdLoArgs& a, bool bf16, bool ef, bool 
 
 void launch_range(const RangeArgs& r, hipStream_t s) {
   const uint64_t K = r.d >> r.L;
-  if (r.L - r.L1 <= 3) k_range_small<<<dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s>>>(r);
+  if (r.L - r.L1 <= 3) k_range_small<<<dim3((unsigned)((K + RANGE_SMALL_BLOCKS - 1) / RANGE_SMALL_BLOCKS)), dim3(256), 0, s>>>(r);
   else k_range<<<dim3((unsigned)K), dim3(RANGE_NT), 0, s>>>(r);
 }
 
@@ -530,9 +530,81 @@ void run_forward_pipe(const Forward& f, const Plan& pl, const PipeShape& sh) {
   }
 }
 
+template <int L, bool BF16>
+void launch_whole_k(const WholeArgs& a, bool ef, bool find, dim3 grid, hipStream_t s) {
+  const dim3 blk(WholeTile<L>::N);
+  if (ef) k_whole<L, BF16, true, false><<<grid, blk, 0, s>>>(a);
+  else if (find) k_whole<L, BF16, false, true><<<grid, blk, 0, s>>>(a);
+  else k_whole<L, BF16, false, false><<<grid, blk, 0, s>>>(a);
+}
+
+template <int L>
+void launch_whole(const WholeArgs& a, bool bf16, bool ef, bool find, uint32_t W, hipStream_t s) {
+  const dim3 grid((unsigned)((a.d + (1ull << WholeTile<L>::LOG) - 1) >> WholeTile<L>::LOG), W);
+  if (bf16) launch_whole_k<L, true>(a, ef, find, grid, s);
+  else launch_whole_k<L, false>(a, ef, find, grid, s);
+}
+
+// the norms of W vectors and their range (Alg. 3's preliminary stage)
+void run_norms(const thc_params* p, const Plan& pl, const void* const* grads, const float* const* ef, uint32_t W,
+               float* range_M, double* partials, hipStream_t s) {
+  FwdLoArgs a{};
+  for (uint32_t i = 0; i < W; ++i) {
+    a.grads.p[i] = grads[i];
+    if (ef) a.efs.p[i] = ef[i];
+  }
+  a.partials = partials;
+  a.pstride = p->d >> pl.L1;
+  a.d = p->d;
+  a.tm = lo_tilemap(pl, p->d);
+  launch_fwd_lo(pl, a, p->in_dtype == THC_DTYPE_BF16, ef != nullptr, true, tiles_of(p->d), W, s);
+  launch_range(RangeArgs{partials, range_M, p->d >> pl.L1, p->d, W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p}, s);
+}
+
+// Blocks of up to 2^14, block by block: nothing of the vectors goes through the workspace.
+void run_forward_whole(const Forward& f, const Plan& pl, Whole route) {
+  const thc_params* p = f.p;
+  const bool bf16 = p->in_dtype == THC_DTYPE_BF16, ef = f.efs != nullptr, find = route == Whole::FIND;
+  if (route == Whole::NORMS)
+    run_norms(p, pl, f.grads, f.efs, f.W, f.range_out, ws_layout(f.ws, p, pl, ef).partials, f.s);
+  WholeArgs a{};
+  for (uint32_t i = 0; i < f.W; ++i) {
+    a.grads.p[i] = f.grads[i];
+    if (ef) a.efs.p[i] = f.efs[i];
+    a.packed.p[i] = f.packed[i];
+  }
+  a.range_M = f.range_out ? f.range_out : const_cast<float*>(f.range_in);
+  a.d = p->d;
+  a.j0 = base_coord(p);
+  a.L = (uint32_t)pl.L;
+  a.b = p->b;
+  a.g = p->g;
+  a.round = (uint32_t)f.round;
+  a.worker = f.worker0;
+  a.k0 = (uint32_t)p->seed;
+  a.k1 = (uint32_t)(p->seed >> 32);
+  a.n = f.W;
+  a.c = (float)(1.0 / std::sqrt((double)p->block));
+  a.t_p = p->t_p;
+  fill_lut(p, a.lut);
+  std::memcpy(a.table, p->table, 256);
+  switch (pl.L) {
+    case 10: launch_whole<10>(a, bf16, ef, find, f.W, f.s); break;
+    case 11: launch_whole<11>(a, bf16, ef, find, f.W, f.s); break;
+    case 12: launch_whole<12>(a, bf16, ef, find, f.W, f.s); break;
+    case 13: launch_whole<13>(a, bf16, ef, find, f.W, f.s); break;
+    default: launch_whole<14>(a, bf16, ef, find, f.W, f.s); break;
+  }
+}
+
 void run_forward(const Forward& f) {
   const thc_params* p = f.p;
   const Plan pl = make_plan(p->block, p->stage_order);
+  const Whole route = whole_route(pl, tiles_of(p->d), f.W, f.efs != nullptr, f.range_out == nullptr);
+  if (route != Whole::NO) {
+    run_forward_whole(f, pl, route);
+    return;
+  }
   {
     const PipeShape sh = pipe_shape(p, pl, f.W, f.efs != nullptr);
     const uint64_t Tu = (uint64_t)f.W << pl.R;
@@ -733,20 +805,7 @@ int thc_prepare_range(const thc_params* p, const void* const* grads, const float
   hipStream_t s = static_cast<hipStream_t>(stream);
   // The same partial sums, in the same order, as the first pass of thc_compress_all takes them group by group, on tiles
   // of either size and in the single launch: all give the same M bit for bit.
-  const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
-  double* const partials = ws_layout(ws, p, pl, false).partials;
-  FwdLoArgs a{};
-  for (uint32_t i = 0; i < p->n; ++i) {
-    a.grads.p[i] = grads[i];
-    if (ef) a.efs.p[i] = ef[i];
-  }
-  a.partials = partials;
-  a.pstride = p->d >> pl.L1;
-  a.d = p->d;
-  a.tm = lo_tilemap(pl, p->d);
-  launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(p->d), p->n, s);
-  RangeArgs r{partials, range_M, p->d >> pl.L1, p->d, p->n, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p};
-  launch_range(r, s);
+  run_norms(p, pl, grads, ef, p->n, range_M, ws_layout(ws, p, pl, false).partials, s);
   return check_launch();
 }
 

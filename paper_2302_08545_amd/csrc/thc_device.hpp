@@ -116,7 +116,8 @@ __device__ __forceinline__ void bfly_f4(float4& x) {   // strides 1 and 2 inside
 // All three keep four consecutive, 4-aligned values together as one 16-byte unit.
 // ---------------------------------------------------------------------------------------------
 enum Layout { PLAIN = 0, SWZ = 1, PAD = 2 };
-constexpr int TILE_PAD = TILE + 4 * (TILE / 64);
+constexpr int padded(int n) { return n + 4 * (n / 64); }
+constexpr int TILE_PAD = padded(TILE);
 
 __device__ __forceinline__ int swz(int i) { return i ^ (((i >> 6) & 7) << 2); }
 
@@ -130,7 +131,7 @@ __device__ __forceinline__ int phys(int i) {
 // One round: every thread gathers 16 values as (16 >> NB) groups of 2^NB values that differ in index
 // bits [P, P+NB), runs the butterflies, and hands each result to sink(base, e << P, value): the value's
 // tile index is base + (e << P), the two parts have no bits in common and the second is a constant.
-template <int P, int NB, Layout LY, class Sink>
+template <int P, int NB, Layout LY, int N, class Sink>
 __device__ __forceinline__ void lds_round(const float* lds, int t, Sink&& sink) {
   constexpr int E = 1 << NB;
   constexpr int G = 16 >> NB;
@@ -139,7 +140,7 @@ __device__ __forceinline__ void lds_round(const float* lds, int t, Sink&& sink) 
   static_assert(LY != PAD || P >= 6 || P + NB <= 6, "a padded gather must not straddle a 64-value group");
 #pragma unroll
   for (int gi = 0; gi < G; ++gi) {
-    const int vt = t + NT * gi;
+    const int vt = t + N * gi;
     const int base = (vt & ((1 << P) - 1)) | ((vt >> P) << (P + NB));
     const float* pb = lds + phys<LY>(base);
     float v[E];
@@ -151,20 +152,21 @@ __device__ __forceinline__ void lds_round(const float* lds, int t, Sink&& sink) 
   }
 }
 
-// Stages for index bits [P, HI) on a tile resident in LDS.  When FUSE is set the last round hands its
+// Stages for index bits [P, HI) on a tile resident in LDS, 16 values for each of the N threads.  When FUSE is set the last round hands its
 // results to `sink` (typically a global store) instead of writing them back to LDS.
-template <int P, int HI, bool FUSE, Layout LY, class Sink>
+template <int P, int HI, bool FUSE, Layout LY, int N = NT, class Sink>
 __device__ __forceinline__ void lds_stages(float* lds, int t, Sink&& sink) {
-  constexpr int NB = (HI - P) < 4 ? (HI - P) : 4;
+  constexpr int MAXB = LY == PAD && P < 6 ? (6 - P < 4 ? 6 - P : 4) : 4;   // a padded round stays inside 64 values or above
+  constexpr int NB = (HI - P) < MAXB ? (HI - P) : MAXB;
   constexpr bool LAST = (P + NB == HI);
   __syncthreads();
   if constexpr (LAST && FUSE) {
-    lds_round<P, NB, LY>(lds, t, sink);
+    lds_round<P, NB, LY, N>(lds, t, sink);
   } else {
     if constexpr (NB > 0) {
-      lds_round<P, NB, LY>(lds, t, [&](int base, int eoff, float v) { lds[phys<LY>(base + eoff)] = v; });
+      lds_round<P, NB, LY, N>(lds, t, [&](int base, int eoff, float v) { lds[phys<LY>(base + eoff)] = v; });
     }
-    if constexpr (!LAST) lds_stages<P + NB, HI, FUSE, LY>(lds, t, sink);
+    if constexpr (!LAST) lds_stages<P + NB, HI, FUSE, LY, N>(lds, t, sink);
   }
 }
 

@@ -182,21 +182,27 @@ __device__ __forceinline__ float range_from_sum(double smax, float t_p, uint32_t
   return (float)(((double)t_p * __builtin_sqrt(smax)) / __builtin_sqrt((double)(1ull << L)));
 }
 
-// Blocks of at most 8 tiles (up to 2^16 coordinates): one thread per block adds the block's partial sums of
-// every worker in index order.
+// Blocks of at most 8 tiles (up to 2^16 coordinates): eight lanes per block, each of which adds the block's partial sums of
+// every eighth worker in index order; they hold their largest up against each other.
+constexpr int RANGE_SMALL_BLOCKS = 256 / 8;      // of a workgroup
+
 __global__ __launch_bounds__(256) void k_range_small(const RangeArgs a) {
-  const uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (k >= (a.d >> a.L)) return;
+  const uint64_t k = (uint64_t)blockIdx.x * RANGE_SMALL_BLOCKS + (threadIdx.x >> 3);
+  if (k >= (a.d >> a.L)) return;                 // all eight lanes or none
   const uint32_t ppb = 1u << (a.L - a.L1);
-  const uint64_t per_worker = a.pstride;
   double smax = 0.0;
-  for (uint32_t i = 0; i < a.n; ++i) {
-    const double* p = a.partials + (uint64_t)i * per_worker + k * ppb;
+  for (uint32_t i = threadIdx.x & 7; i < a.n; i += 8) {
+    const double* p = a.partials + (uint64_t)i * a.pstride + k * ppb;
     double s = 0.0;
     for (uint32_t j = 0; j < ppb; ++j) s += p[j];
     smax = s > smax ? s : smax;
   }
-  a.range_M[k] = range_from_sum(smax, a.t_p, a.L);
+#pragma unroll
+  for (int m = 1; m < 8; m <<= 1) {
+    const double o = __shfl_xor(smax, m, 64);
+    smax = o > smax ? o : smax;
+  }
+  if ((threadIdx.x & 7) == 0) a.range_M[k] = range_from_sum(smax, a.t_p, a.L);
 }
 
 template <int TOTALS>     // totals of 64 partial sums a worker may have
@@ -215,7 +221,7 @@ __device__ __forceinline__ double wave_largest(double s) {
   return m;
 }
 
-// The range of one block of at most 8 tiles by one wave, lane i on worker i: the same sums as k_range_small.  In two
+// The range of one block of at most 8 tiles by one wave, lane i on worker i: the same sums as in k_range_small.  In two
 // steps, so that a tile's loads can be requested between them and neither waits for the other.
 template <int PPB>
 struct SmallRange {

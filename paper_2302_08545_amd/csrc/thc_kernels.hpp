@@ -25,3 +25,4 @@
 #include "thc_aggregate.hpp"
 #include "thc_pipeline.hpp"
 #include "thc_big.hpp"
+#include "thc_whole.hpp"

@@ -152,6 +152,39 @@ inline bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {   // 8192-c
   return tiles * W <= (W > 4 ? 4096u : W > 2 ? 3072u : 2048u);
 }
 
+// Blocks of up to 2^14: whether the worker side of W vectors goes block by block (thc_whole.hpp) instead of pass by pass,
+// and where the range comes from.
+//   GIVEN  range known (thc_compress): one launch instead of two, with error feedback three.  Faster at every size measured
+//          (2^15 to 2^28 worker-coordinates): 7.5 to 10.9 us -> 5.4 to 7.8 for small calls, 620 -> 290 for large ones.
+//   FIND   every workgroup adds up its block's squares of all workers: one launch, W times the reads.  One worker (no reads
+//          more): blocks of up to 2^13 8.1 to 52.7 us -> 6.5 to 45 at 4 to 3104 workgroups (of 8192 coordinates), 2^14
+//          11.8 -> 8.7 at 128, 18.3 -> 17.0 at 1024, 53.5 -> 57.5 at 3104.  2 and 4 workers 10.4 to 11.0 -> 7.6 to 9.4 at up
+//          to 128, 13.9 to 15.8 (NORMS) -> 11.7 to 13.6 at 512, 21 -> 26 at 1024 (8 workers: 10.4 to 12.5 -> 10.2 to 12.1 at
+//          up to 256, so no longer a gain); 2^14 with 4 workers 10.3 to 11.3 -> 11.1: a launch less, but not faster.
+//   NORMS  a pass that keeps the sums only, the range, the blocks: three launches instead of two or three, 8.5 bytes a
+//          coordinate instead of 12.5.  Up to 2^13: 11.5 to 12.5 -> 12.0 to 13.1 at 256, 18.5 to 20.0 -> 13.0 to 15.8 at
+//          512 (16 and 32 workers, whose range is found by the quantizer otherwise, 14.2 to 15.8 -> 14.1 to 16.5),
+//          19.1 to 20.9 -> 15.6 to 18.8 at 776, 622 -> 463 at 32768.  2^14, whose 1024 threads leave room for two
+//          workgroups a compute unit: 18.7 -> 13.7 at 512, 22.6 -> 18.4 at 1024, where they fill the chip evenly, 18.5 ->
+//          19.8 at 630, 19.2 -> 20.7 at 776, 53.5 -> 54.0 at 3104, 607 -> 477 at 32768.
+//          With error feedback (29 bytes -> 20.5) up to 2^13 always: 13.5 to 18.7 -> 12.6 to 16.9 at up to 256, 26 to 28 ->
+//          21 at 512, 45 -> 41 at 1024, 1459 -> 1019 at 32768; 2^14, one workgroup a compute unit: 21 to 33 -> 18 to 22 at
+//          up to 512, 36.1 -> 37.9 at 630, 47.6 -> 48.7 at 1024, 133.5 -> 132.8 at 3104, 1448 -> 1263 at 32768.
+enum class Whole { NO, GIVEN, FIND, NORMS };
+constexpr uint32_t WHOLE_FIND_WORKERS = 4;
+
+inline Whole whole_route(const Plan& pl, uint64_t tiles, uint32_t W, bool ef, bool range_given) {
+  if (pl.L > 14) return Whole::NO;
+  if (range_given) return Whole::GIVEN;
+  const uint64_t wg = tiles * W;
+  if (ef) return pl.L <= 13 || wg <= 512 || wg >= 4096 ? Whole::NORMS : Whole::NO;
+  if (W == 1 && (pl.L <= 13 || wg <= 1024)) return Whole::FIND;
+  if (W <= (pl.L <= 13 ? WHOLE_FIND_WORKERS : 2u) && wg <= 512) return Whole::FIND;
+  if (pl.L <= 13) return wg >= (W > 8 ? 640u : 512u) ? Whole::NORMS : Whole::NO;
+  const bool even = (wg > 448 && wg <= 512 && W <= 8) || (wg > 896 && wg <= 1024 && W <= 16);
+  return even || wg >= 4096 ? Whole::NORMS : Whole::NO;
+}
+
 // Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of
 // 2^15 coordinates (thc_big.hpp).  Blocks of 2^23 to 2^25: all (two passes instead of three: 1.16x at one block of one
 // vector, 1.5x at 16 of them).  2^22: both tile sizes take two passes, and the larger one pays once its few large tiles

@@ -190,3 +190,52 @@ def test_norms_are_added_up_in_one_order_whatever_the_tile(log2_block, K, n, bf1
     assert R.range_M[K - 1].item() == want
     if single_launch:
         assert R.status() == 0
+
+
+@pytest.mark.parametrize("log2_block,K,n,b,g,bf16,ef", [
+    (10, 1, 1, 4, 30, False, True), (10, 19, 2, 3, 21, True, True), (10, 9, 4, 4, 30, True, False),
+    (11, 5, 3, 1, 1, False, True), (11, 7, 4, 2, 8, False, False), (12, 3, 4, 8, 255, False, True),
+    (12, 7, 2, 2, 8, True, False), (13, 3, 2, 4, 30, False, True), (13, 1, 33, 4, 30, True, True),
+    (14, 1, 4, 4, 30, False, False), (14, 2, 4, 5, 40, True, False), (14, 3, 2, 4, 30, True, True), (14, 1, 1, 8, 128, False, True),
+    # either side of the limits of the rule, in workgroups of 8192 coordinates: found by every workgroup up to 512 (2^14 with
+    # one worker 1024), norms first from 512, 640 or where 2^14 fills the chip evenly, with error feedback in 2^14 up to 512
+    (13, 128, 4, 4, 30, False, False), (13, 129, 4, 4, 30, False, False), (13, 64, 8, 4, 30, False, False),
+    (13, 63, 8, 4, 30, False, False), (13, 40, 16, 2, 8, False, False), (13, 39, 16, 2, 8, False, False),
+    (10, 4097, 1, 4, 30, False, False), (14, 64, 4, 4, 30, False, False), (14, 65, 4, 4, 30, False, False),
+    (14, 32, 8, 4, 30, False, False), (14, 28, 8, 4, 30, False, False), (14, 64, 8, 2, 3, True, False),
+    (14, 512, 1, 4, 30, False, False), (14, 513, 1, 4, 30, False, False), (14, 64, 4, 4, 30, False, True),
+    (14, 65, 4, 4, 30, False, True)])
+def test_worker_side_block_by_block(log2_block, K, n, b, g, bf16, ef):
+    """Blocks of up to 2^14, whose worker side is one launch once the range is known: thc_compress_all gives what
+    thc_prepare_range and thc_compress give, bit for bit, whichever way its range comes about, and both are the oracle's."""
+    block = 1 << log2_block
+    agg_bits = 8 if g * n < 256 else 16
+    table = list(range(256)) if (b, g) == (8, 255) else [round(i * g / 255) for i in range(256)] if b == 8 else None
+    if b == 8 and g < 255:
+        b, table = 7, [round(i * g / 127) for i in range(128)]
+    P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, bf16=bf16, table=table)
+    x = make_grads(block * K, n, seed=log2_block + K, bf16=bf16)
+    dg = [v.to(DEV) for v in x]
+    A, B = GpuRound(L, ef=ef), GpuRound(L, ef=ef)
+    e = make_grads(block * K, n, 3e-4, seed=7 * K) if ef else None
+    for R in (A, B):
+        for i in range(n if ef else 0):
+            R.efs[i].copy_(e[i])
+    for rnd in (3, 4):                           # the second round starts from the first one's buffers
+        before = [v.cpu().numpy() for v in A.efs] if ef else None
+        A.compress_all(rnd, dg)
+        B.prepare(dg)
+        B.compress_each(rnd, dg)
+        assert torch.equal(A.range_M, B.range_M)
+        for p, q in zip(A.packed, B.packed):
+            assert torch.equal(p, q)
+        for p, q in zip(A.efs or [], B.efs or []):
+            assert torch.equal(p, q)
+    M, gn = A.range_M.cpu().numpy(), [to_np32(v) for v in x]
+    M_ref = o.prepare_range(P, gn, before)
+    assert np.all(np.abs(M - M_ref) <= np.abs(M_ref) * 2.0 ** -23)
+    i = n - 1
+    pk, ne = o.compress(P, i, 4, gn[i], before[i] if ef else None, M)
+    assert_indices_match(A.packed[i].cpu().numpy(), pk, b)
+    if ef:
+        assert rel_l2(A.efs[i].cpu().numpy(), ne) <= 1e-5
