@@ -145,14 +145,12 @@ uint64_t base_coord(const thc_params* p) { return (uint64_t)p->first_block * p->
 
 void fill_lut(const thc_params* p, uint32_t (&lut)[256]) {
   const uint32_t top = (1u << p->b) - 1;
-  for (uint32_t k = 0; k < 256; ++k) {
-    const uint32_t kk = k < p->g ? k : p->g;
-    uint32_t z0 = 0;
-    while (z0 < top && p->table[z0 + 1] <= kk) ++z0;
-    const uint32_t lo = p->table[z0];
-    const uint32_t wd = z0 < top ? (uint32_t)(p->table[z0 + 1] - lo) : 255u;   // 255: the top value never rounds up
-    lut[k] = lo | wd << 8 | z0 << 16;
+  uint32_t k = 0;
+  for (uint32_t z = 0; z < top; ++z) {
+    const uint32_t lo = p->table[z], next = p->table[z + 1], ent = lo | (next - lo) << 8 | z << 16;
+    for (; k < next; ++k) lut[k] = ent;
   }
+  for (; k < 256; ++k) lut[k] = p->g | 255u << 8 | top << 16;   // 255: the top value never rounds up
 }
 
 int check_launch() {
