@@ -357,21 +357,31 @@ void run_mids(const Plan& pl, float* x, uint64_t d, uint32_t W, hipStream_t s) {
   }
 }
 
+template <int L1>
+void launch_inv_whole_ef(const InvWholeArgs& a, int efm, dim3 grid, hipStream_t s) {
+  const dim3 blk(NT);
+  const bool b4 = a.lo.src_bits == 4;
+  if (efm == 1) {
+    if (b4) k_inv_whole<L1, 4, 1><<<grid, blk, 0, s>>>(a);
+    else k_inv_whole<L1, 0, 1><<<grid, blk, 0, s>>>(a);
+  } else {
+    if (b4) k_inv_whole<L1, 4, 2><<<grid, blk, 0, s>>>(a);
+    else k_inv_whole<L1, 0, 2><<<grid, blk, 0, s>>>(a);
+  }
+}
+
 // Blocks of up to 2^15 coordinates: the inverse transform in one launch.
 template <int L1>
 void launch_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_t s) {
-  const dim3 grid((unsigned)tiles_of(a.lo.d), W), blk(NT);
+  constexpr int N = inv_whole_threads(L1);
+  const dim3 grid((unsigned)((a.lo.d + 16 * N - 1) / (16 * N)), W), blk(N);
   const uint32_t bits = a.lo.src_bits;
   if (efm == 0) {
     if (bits == 8) k_inv_whole<L1, 8, 0><<<grid, blk, 0, s>>>(a);
     else k_inv_whole<L1, 0, 0><<<grid, blk, 0, s>>>(a);
-  } else if (efm == 1) {
-    if (bits == 4) k_inv_whole<L1, 4, 1><<<grid, blk, 0, s>>>(a);
-    else k_inv_whole<L1, 0, 1><<<grid, blk, 0, s>>>(a);
-  } else {
-    if (bits == 4) k_inv_whole<L1, 4, 2><<<grid, blk, 0, s>>>(a);
-    else k_inv_whole<L1, 0, 2><<<grid, blk, 0, s>>>(a);
+    return;
   }
+  if constexpr (L1 <= LOG_TILE) launch_inv_whole_ef<L1>(a, efm, grid, s);
 }
 
 template <int L>
@@ -414,7 +424,10 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
       case 11: launch_inv_whole<11>(a, efm, W, s); break;
       case 12: launch_inv_whole<12>(a, efm, W, s); break;
       case 13: launch_inv_whole<13>(a, efm, W, s); break;
-      case 14: launch_big_inv_whole<14>(a, efm, W, s); break;
+      case 14:
+        if (inv_whole_14(len, efm != 0, lo.src_bits)) launch_inv_whole<14>(a, efm, W, s);
+        else launch_big_inv_whole<14>(a, efm, W, s);
+        break;
       default: launch_big_inv_whole<15>(a, efm, W, s); break;
     }
     return;

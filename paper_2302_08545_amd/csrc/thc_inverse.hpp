@@ -103,26 +103,26 @@ struct InvLoArgs {
   uint8_t table[256];
 };
 
+template <int N = NT>          // threads, 16 values each
 struct alignas(16) SmemInvLo {
-  float lds[TILE];
+  float lds[16 * N];
   float sM[8], sStep[8];
   float tabf[256];
 };
 
-// One tile: tile index `tile` of the launch's vector `vec`; put(o, value) takes each result, o its offset from the
-// tile's first coordinate.  SB and TB are the width and the kind of the codes where the launch knows them (TB 1: table
+// One tile of N threads: the one at coordinate `off` of the launch's vector `vec`; put(o, value) takes each result, o its
+// offset from the tile's first coordinate.  SB and TB are the width and the kind of the codes where the launch knows them (TB 1: table
 // indices, 0: sums, -1: a.use_table says); SB = 0: a.src_bits says.
-template <int L1, bool XO, int SB, int TB, class A, class Put>
-__device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_t vec, SmemInvLo& sm, Put&& put) {
-  static_assert(!XO || L1 == LOG_TILE, "the row-split tile needs blocks of at least 2^16");
-  constexpr bool GUARD = L1 < LOG_TILE;
+template <int L1, bool XO, int SB, int TB, int N = NT, class A, class Put>
+__device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t vec, SmemInvLo<N>& sm, Put&& put) {
+  static_assert(!XO || (L1 == LOG_TILE && N == NT), "the row-split tile needs blocks of at least 2^16");
+  constexpr bool GUARD = (1 << L1) < 16 * N;
   float* const lds = sm.lds;
   float* const sM = sm.sM;
   float* const sStep = sm.sStep;
   float* const tabf = sm.tabf;
 
   const int t = threadIdx.x;
-  const uint64_t off = tm_base(a.tm, tile);
   const int idx = 16 * t;
   const uint64_t j = off + lo_map<XO>(idx);
   const bool ok = !GUARD || j < a.d;
@@ -139,28 +139,29 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_
   if (!staged) {
     if (ok) codes_load(src, bits, j, w, y);
   } else {
-    // Any other width: the tile's eight runs of 1024 codes (128 * bits bytes each, dword aligned) are copied
+    // Any other width: the tile's runs of 1024 codes (128 * bits bytes each, dword aligned) are copied
     // into the still unused tile buffer with coalesced loads; every thread then cuts its sixteen fields out.
     uint32_t* stage = reinterpret_cast<uint32_t*>(lds);
     const uint32_t per_row = 32u * bits;                             // dwords per 1024 codes: fewer than NT
     if ((uint32_t)t < per_row) {
-      uint32_t val[8];
+      constexpr uint32_t RUNS = 16 * N / 1024;
+      uint32_t val[RUNS];
 #pragma unroll
-      for (uint32_t r = 0; r < 8; ++r) {
+      for (uint32_t r = 0; r < RUNS; ++r) {
         const uint64_t jr = off + lo_map<XO>(1024u * r);             // first coordinate of the run
         val[r] = 0;
         if (!GUARD || jr < a.d)                                      // runs exist whole or not at all: 1024 divides d
           val[r] = reinterpret_cast<const uint32_t*>(src + (jr >> 3) * bits)[t];
       }
 #pragma unroll
-      for (uint32_t r = 0; r < 8; ++r) stage[r * per_row + t] = val[r];
+      for (uint32_t r = 0; r < RUNS; ++r) stage[r * per_row + t] = val[r];
     }
   }
 
   // A tile inside one block looks up values on the block's range; one of several blocks, or whose kind is not known, looks
   // up the table's own values.
-  constexpr bool SCALED = TB == 1 && L1 == LOG_TILE;
-  const int nblk = a.L < LOG_TILE ? (TILE >> a.L) : 1;
+  constexpr bool SCALED = TB == 1 && !GUARD;
+  const int nblk = GUARD ? (16 * N) >> a.L : 1;
   if (SCALED ? t < (SB ? 1 << SB : 256) : t < nblk) {
     const uint64_t blk = (off >> a.L) + (SCALED ? 0 : t);
     float M = 0.f, m = 0.f;
@@ -196,7 +197,7 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_
     }
     __syncthreads();                                                 // every field is out before the tile is written
   }
-  const int bt = a.L < LOG_TILE ? (idx >> a.L) : 0;
+  const int bt = GUARD ? (idx >> a.L) : 0;
   float lo = 0.f, step = 0.f;
   if constexpr (!SCALED) { lo = sM[bt]; step = sStep[bt]; }
   float v[16];
@@ -210,13 +211,14 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint32_t tile, uint32_
   for (int e = 0; e < 16; e += 4)
     *reinterpret_cast<float4*>(&lds[swz(idx + e)]) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
 
-  lds_stages<4, L1, true, SWZ>(lds, t, [&](int base, int eoff, float val) { put(lo_map<XO>(base) + lo_map<XO>(eoff), val); });
+  lds_stages<4, L1, true, SWZ, N>(lds, t, [&](int base, int eoff, float val) { put(lo_map<XO>(base) + lo_map<XO>(eoff), val); });
 }
 
 template <bool XO, int SB, int TB, class A>
-__device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t vec, float* dst_vec, SmemInvLo& sm) {
-  float* const dst = dst_vec + tm_base(a.tm, tile);
-  inv_lo_stages<LOG_TILE, XO, SB, TB>(a, tile, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
+__device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t vec, float* dst_vec, SmemInvLo<>& sm) {
+  const uint64_t off = tm_base(a.tm, tile);
+  float* const dst = dst_vec + off;
+  inv_lo_stages<LOG_TILE, XO, SB, TB>(a, off, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
 }
 
 // What bounds it: writing 4 bytes a coordinate (pure writes reach 5.7 TB/s here).  Decoding is a large part of its
@@ -225,7 +227,7 @@ __device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t 
 // 2^20 from 4-bit indices 5.4 -> 4.3 us.
 template <bool XO, int SB, int TB>
 __global__ __launch_bounds__(NT, 8) void k_inv_lo(const InvLoArgs a) {
-  __shared__ SmemInvLo sm;
+  __shared__ SmemInvLo<> sm;
   inv_lo_tile<XO, SB, TB>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
 }
 
@@ -371,27 +373,31 @@ struct InvWholeArgs {
   float c;
 };
 
+constexpr int inv_whole_threads(int L) { return L <= LOG_TILE ? NT : 1 << (L - 4); }
+
 // SB as for k_inv_lo: 2^28 coordinates in blocks of 2^13 from 8-bit sums 285 -> 260 us.
 template <int L1, int SB, int EFM>
-__global__ __launch_bounds__(NT, EFM == 0 ? 8 : 4) void k_inv_whole(const InvWholeArgs a) {
-  __shared__ SmemInvLo sm;
-  __shared__ __align__(16) uint32_t sgn[TILE / 32];
+__global__ __launch_bounds__(inv_whole_threads(L1), EFM == 0 ? 8 : 4) void k_inv_whole(const InvWholeArgs a) {
+  constexpr int N = inv_whole_threads(L1), T = 16 * N;
+  constexpr bool PART = (1 << L1) < T;     // several blocks to a tile: the vector's last one may be partly empty
+  __shared__ SmemInvLo<N> sm;
+  __shared__ __align__(16) uint32_t sgn[T / 32];
   const int t = threadIdx.x;
   const uint32_t vec = blockIdx.y, tile = blockIdx.x;
-  const uint64_t off = tm_base(a.lo.tm, tile);
-  if (t < TILE / 128) {
+  const uint64_t off = N == NT ? tm_base(a.lo.tm, tile) : (uint64_t)xcd_tile<2>(tile, gridDim.x) * T;
+  if (t < T / 128) {
     const uint64_t q = (a.j0 + off + 128u * t) >> 7;
     *reinterpret_cast<uint4*>(&sgn[4 * t]) = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, SIGN_STREAM, a.k0, a.k1);
   }
   float v[16];
   uint32_t at[16];
   int c = 0;
-  inv_lo_stages<L1, false, SB, EFM != 0>(a.lo, tile, vec, sm, [&](uint32_t o, float val) { v[c] = val; at[c] = o; ++c; });
+  inv_lo_stages<L1, false, SB, EFM != 0, N>(a.lo, off, vec, sm, [&](uint32_t o, float val) { v[c] = val; at[c] = o; ++c; });
   float* const out = static_cast<float*>(const_cast<void*>(a.out.p[vec])) + off;
   const char* const grad = EFM ? static_cast<const char*>(a.grad.p[vec]) + off * (EFM == 2 ? 2 : 4) : nullptr;
   const uint64_t left = a.lo.d - off;
   auto bit = [&](uint32_t o) { return (sgn[o >> 5] >> (o & 31)) & 1u; };
-  if (L1 == LOG_TILE || left >= TILE) {
+  if (!PART || left >= T) {
     finish_values<EFM>(v, a.c, out, grad, [&](int i) { return at[i]; }, [&](int i) { return bit(at[i]); });
   } else {           // the last tile of a vector of short blocks
 #pragma unroll

@@ -145,7 +145,7 @@ __device__ __forceinline__ void pipe_publish(uint32_t* unit_sync, uint32_t phase
 constexpr size_t pipe_smem_bytes() {
   size_t m = sizeof(SmemLo);
   if (sizeof(SmemQuant<7>) > m) m = sizeof(SmemQuant<7>);
-  if (sizeof(SmemInvLo) > m) m = sizeof(SmemInvLo);
+  if (sizeof(SmemInvLo<>) > m) m = sizeof(SmemInvLo<>);
   if (sizeof(SmemInvHi) > m) m = sizeof(SmemInvHi);
   if (sizeof(SmemRange<8>) > m) m = sizeof(SmemRange<8>);
   return m;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
       // X_i from the indices, inverse first pass into the slot the quantizer has finished with
       if (!pipe_wait<true>(us + (1 * SYNC_PHASE + NXCD) * SYNC_STRIDE, NXCD, P.status, &flag)) return;
       const InvLoView a{P.packed, P.range_M, nullptr, P.d, P.L, P.b, 1u, P.g, P.lo_tm, P.table};
-      inv_lo_tile<true, 0, 1>(a, gt, w, vec, *reinterpret_cast<SmemInvLo*>(raw));
+      inv_lo_tile<true, 0, 1>(a, gt, w, vec, *reinterpret_cast<SmemInvLo<>*>(raw));
       pipe_publish(us, 2, Tu >> 3);
     } else {
       // e <- (grad + e) - RHT^-1(X_i)

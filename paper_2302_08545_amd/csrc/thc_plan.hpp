@@ -185,6 +185,17 @@ inline Whole whole_route(const Plan& pl, uint64_t tiles, uint32_t W, bool ef, bo
   return even || wg >= 4096 ? Whole::NORMS : Whole::NO;
 }
 
+// Blocks of 2^14, inverse transform in one launch: a block to a workgroup of 1024 threads (k_inv_whole) or two blocks to
+// one of 512 (k_big_inv_whole).  With few blocks the first has half the work on each of twice the compute units: 8-bit sums
+// of 2 to 64 blocks 9.1 to 9.8 -> 6.2 to 6.6 us, 256 blocks 11.4 -> 8.7, 600 16.4 -> 14.6, 4096 67 -> 61, 16384 241 -> 223;
+// 16-bit sums of 1 to 16384 blocks 7.7 to 291 -> 6.1 to 268.  At 768 and 1024 blocks, where the second fills the chip
+// exactly, 16.4 -> 16.2 and 18.2 -> 19.8 (9-bit sums 17.4 -> 18.0 and 19.6 -> 21.9; 16-bit 20.6 -> 17.0, 22.4 -> 21.1).
+// With error feedback, which only the rotated uniform variant still has here, the second.
+inline bool inv_whole_14(uint64_t len, bool ef, uint32_t bits) {
+  const uint64_t K = len >> 14;
+  return !ef && (bits == 16 || K <= 704 || K > 1024);
+}
+
 // Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of
 // 2^15 coordinates (thc_big.hpp).  Blocks of 2^23 to 2^25: all (two passes instead of three: 1.16x at one block of one
 // vector, 1.5x at 16 of them).  2^22: both tile sizes take two passes, and the larger one pays once its few large tiles

@@ -239,3 +239,30 @@ def test_worker_side_block_by_block(log2_block, K, n, b, g, bf16, ef):
     assert_indices_match(A.packed[i].cpu().numpy(), pk, b)
     if ef:
         assert rel_l2(A.efs[i].cpu().numpy(), ne) <= 1e-5
+
+
+@pytest.mark.parametrize("K,agg_bits", [(1, 8), (3, 9), (704, 8), (705, 8), (705, 9), (705, 16), (1024, 9), (1025, 8)])
+def test_inverse_of_2_to_the_14_by_one_block_or_two_a_workgroup(K, agg_bits):
+    """Both kernels give the same bits: the whole vector against its slices of at most eight blocks, which lie on the other
+    side of the rule (705 to 1024 blocks) where the whole is inside it; block 0 and the last one against the oracle."""
+    block = 1 << 14
+    P, L = both_params(block * K, block, 1, agg_bits=agg_bits)
+    R = GpuRound(L)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    R.agg.copy_(torch.randint(0, 256, R.agg.shape, generator=gen, device=DEV, dtype=torch.uint8))
+    R.range_M.copy_(torch.rand(K, generator=gen, device=DEV) + 0.5)
+    R.decompress(11)
+    for k in range(0, K, max(8, K // 5)):
+        n = min(8, K - k)
+        _, S = both_params(block * n, block, 1, agg_bits=agg_bits)
+        S.first_block = k
+        Q = GpuRound(S)
+        Q.agg.copy_(R.agg[k * block // 8 * agg_bits:(k + n) * block // 8 * agg_bits])
+        Q.range_M.copy_(R.range_M[k:k + n])
+        Q.decompress(11)
+        assert torch.equal(Q.out, R.out[k * block:(k + n) * block])
+    Y, M, out = R.agg_numpy(), R.range_M.cpu().numpy(), R.out.cpu().numpy()
+    Pk = o.Params(d=block, block=block, n=1, b=P.b, g=P.g, t_p=P.t_p, seed=P.seed, table=P.table, agg_bits=agg_bits)
+    for k in {0, K - 1}:
+        ref = o.decompress(Pk, 11, Y[k * block:(k + 1) * block], M[k:k + 1], j0=k * block)
+        assert rel_l2(out[k * block:(k + 1) * block], ref) <= 1e-5
