@@ -160,7 +160,8 @@ inline bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {   // 8192-c
 //          more): blocks of up to 2^13 8.1 to 52.7 us -> 6.5 to 45 at 4 to 3104 workgroups (of 8192 coordinates), 2^14
 //          11.8 -> 8.7 at 128, 18.3 -> 17.0 at 1024, 53.5 -> 57.5 at 3104.  2 and 4 workers 10.4 to 11.0 -> 7.6 to 9.4 at up
 //          to 128, 13.9 to 15.8 (NORMS) -> 11.7 to 13.6 at 512, 21 -> 26 at 1024 (8 workers: 10.4 to 12.5 -> 10.2 to 12.1 at
-//          up to 256, so no longer a gain); 2^14 with 4 workers 10.3 to 11.3 -> 11.1: a launch less, but not faster.
+//          up to 256, so no longer a gain); 2^14 with 4 workers 10.3 to 11.3 -> 11.1, and
+//          a launch less, which is what bounds such a round on the host: two blocks, 22 -> 19.7 us.
 //   NORMS  a pass that keeps the sums only, the range, the blocks: three launches instead of two or three, 8.5 bytes a
 //          coordinate instead of 12.5.  Up to 2^13: 11.5 to 12.5 -> 12.0 to 13.1 at 256, 18.5 to 20.0 -> 13.0 to 15.8 at
 //          512 (16 and 32 workers, whose range is found by the quantizer otherwise, 14.2 to 15.8 -> 14.1 to 16.5),
@@ -179,7 +180,7 @@ inline Whole whole_route(const Plan& pl, uint64_t tiles, uint32_t W, bool ef, bo
   const uint64_t wg = tiles * W;
   if (ef) return pl.L <= 13 || wg <= 512 || wg >= 4096 ? Whole::NORMS : Whole::NO;
   if (W == 1 && (pl.L <= 13 || wg <= 1024)) return Whole::FIND;
-  if (W <= (pl.L <= 13 ? WHOLE_FIND_WORKERS : 2u) && wg <= 512) return Whole::FIND;
+  if (W <= WHOLE_FIND_WORKERS && wg <= 512) return Whole::FIND;
   if (pl.L <= 13) return wg >= (W > 8 ? 640u : 512u) ? Whole::NORMS : Whole::NO;
   const bool even = (wg > 448 && wg <= 512 && W <= 8) || (wg > 896 && wg <= 1024 && W <= 16);
   return even || wg >= 4096 ? Whole::NORMS : Whole::NO;
