@@ -38,6 +38,12 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t wg, uint32_t ntiles) {
   return (wg | G) < ntiles ? (wg & ~G) | ((wg & 7u) << S) | ((wg >> 3) & ((1u << S) - 1u)) : wg;
 }
 
+// A pass that reads what the pass before it has just written, and more of it than the 256 MB memory-side cache holds, walks
+// the launch's tiles and vectors last one first (see last_first): what was written last is still there, where a walk in the
+// same order would find each line just dropped.
+__device__ __forceinline__ uint32_t walk_x(uint32_t last_first) { return last_first ? gridDim.x - 1 - blockIdx.x : blockIdx.x; }
+__device__ __forceinline__ uint32_t walk_y(uint32_t last_first) { return last_first ? gridDim.y - 1 - blockIdx.y : blockIdx.y; }
+
 __device__ __forceinline__ uint32_t tm_row(const TileMap& m, uint32_t r) {
   return ((r & ((1u << m.n0) - 1u)) << m.sh0) | ((r >> m.n0) << m.sh1);
 }

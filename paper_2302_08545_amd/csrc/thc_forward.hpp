@@ -507,6 +507,7 @@ struct QuantArgs {
   uint32_t b, g;
   uint32_t round, worker, k0, k1;   // worker: id of the launch's first worker (selects the rounding stream)
   float c;                 // 1/sqrt(B)
+  uint32_t last_first;     // order of the walk over the tiles
   uint32_t lut[256];       // per grid cell k: lo | wd << 8 | z0 << 16
   // only where the pass finds the range itself (FIND): what k_range would be given, and where M goes
   const double* partials;
@@ -751,12 +752,13 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
 template <int R, bool CFOLD, bool FIND>
 __global__ __launch_bounds__(NT, 8) void k_fwd_hi_quant(const QuantArgs a) {
   __shared__ SmemQuant<R> sm;
-  const float* const xw = a.x + (uint64_t)blockIdx.y * a.d;
+  const uint32_t tile = walk_x(a.last_first), vec = walk_y(a.last_first);
+  const float* const xw = a.x + (uint64_t)vec * a.d;
   if constexpr (FIND) {
     __shared__ FindSmem smr;
-    hi_quant_tile<R, CFOLD, true, true>(a, blockIdx.x, blockIdx.y, xw, sm, &smr);
+    hi_quant_tile<R, CFOLD, true, true>(a, tile, vec, xw, sm, &smr);
   } else {
-    hi_quant_tile<R, CFOLD, false, true>(a, blockIdx.x, blockIdx.y, xw, sm);
+    hi_quant_tile<R, CFOLD, false, true>(a, tile, vec, xw, sm);
   }
 }
 

@@ -246,6 +246,7 @@ struct InvHiArgs {
   uint32_t round, k0, k1;
   uint32_t mode, bf16;
   float c;
+  uint32_t last_first;
 };
 
 // scale by 1/sqrt(B) and apply the diagonal; mode 1: (x + e) - that
@@ -332,7 +333,8 @@ __device__ __forceinline__ void inv_hi_tile(const A& a, uint32_t tile, uint32_t 
 template <int R>
 __global__ __launch_bounds__(NT) void k_inv_hi(const InvHiArgs a) {
   __shared__ SmemInvHi sm;
-  inv_hi_tile<R>(a, blockIdx.x, blockIdx.y, a.x + (uint64_t)blockIdx.y * a.d, sm);
+  const uint32_t tile = walk_x(a.last_first), vec = walk_y(a.last_first);
+  inv_hi_tile<R>(a, tile, vec, a.x + (uint64_t)vec * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -216,6 +216,17 @@ inline bool big_inverse(const Plan& pl, uint64_t d, uint64_t len, uint32_t W) {
   return big_forward(pl, d, W) && (pl.L > 22 || W * (len >> LOG_BIG) >= BIG_RESIDENT);
 }
 
+// Whether the quantizer and, with error feedback, the inverse's last pass walk a launch's tiles last one first: where the
+// half-transformed vectors of the launch, with error feedback these and the vectors themselves, exceed the 256 MB
+// memory-side cache.  In order -> last first: rounds of 2^20-point blocks with error feedback, 25 x 4 vectors 733 -> 707 us,
+// 25 x 8 1430 -> 1407, 9 x 16 1042 -> 1017, 64 x 8 3633 -> 3612; 2^25 x 8 2154 -> 2094; the range pass of the rotated
+// uniform variant behind its first pass, 25 x 4 vectors, 221 -> 214.  Below that size it gives nothing (25 x 1 167 either
+// way, one block without error feedback 31.3 -> 31.6), tiles of 2^15 gain at 2^25 only (8 blocks of 2^22 x 8 743 -> 750),
+// and the decompression's two passes lose 3 %.
+inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool big) {
+  return W * len > (1ull << (ef ? 25 : 26)) && (!big || pl.L == 25);
+}
+
 // The groups of whole blocks, `gc` coordinates of each of W vectors, in which a call walks its d coordinates:
 // group(first coordinate, coordinates, whether the forward and the inverse launches take the larger tiles).
 template <class Group>

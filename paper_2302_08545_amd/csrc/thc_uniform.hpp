@@ -109,17 +109,19 @@ struct HiMinMaxArgs {
   TileMap tm;
   uint32_t L;
   float c;
+  uint32_t last_first;
 };
 
 template <int R>
 __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
   __shared__ __align__(16) float lds[R < 2 ? 4 : TILE];
   __shared__ float smin[16], smax[16];
+  const uint32_t tile = walk_x(a.last_first), vec = walk_y(a.last_first);
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  const HiGeom<R> g(blockIdx.x, a.tm);
-  const float* const x = a.x + (uint64_t)blockIdx.y * a.d;
-  float* const pmin = a.pmin + (uint64_t)blockIdx.y * a.pstride;
-  float* const pmax = a.pmax + (uint64_t)blockIdx.y * a.pstride;
+  const HiGeom<R> g(tile, a.tm);
+  const float* const x = a.x + (uint64_t)vec * a.d;
+  float* const pmin = a.pmin + (uint64_t)vec * a.pstride;
+  float* const pmax = a.pmax + (uint64_t)vec * a.pstride;
   if constexpr (R >= 2) {
     hi_front<R>(x, g, lds, t);
     int idx[2];
@@ -141,8 +143,8 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
     __syncthreads();
     if (t == 0) {   // the whole tile lies in one block: one partial per tile
       for (int w = 1; w < 8; ++w) { mn = __builtin_fminf(mn, smin[w]); mx = __builtin_fmaxf(mx, smax[w]); }
-      pmin[blockIdx.x] = mn;
-      pmax[blockIdx.x] = mx;
+      pmin[tile] = mn;
+      pmax[tile] = mx;
     }
   } else {
     float4 r[2][2];
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
         mn = __builtin_fminf(mn, smin[t * cpb + c]);
         mx = __builtin_fmaxf(mx, smax[t * cpb + c]);
       }
-      const uint64_t pidx = ((uint64_t)blockIdx.x << (LOG_TILE - L1)) + t;
+      const uint64_t pidx = ((uint64_t)tile << (LOG_TILE - L1)) + t;
       if (pidx < (a.d >> L1)) { pmin[pidx] = mn; pmax[pidx] = mx; }
     }
   }

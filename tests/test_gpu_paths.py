@@ -266,3 +266,32 @@ def test_inverse_of_2_to_the_14_by_one_block_or_two_a_workgroup(K, agg_bits):
     for k in {0, K - 1}:
         ref = o.decompress(Pk, 11, Y[k * block:(k + 1) * block], M[k:k + 1], j0=k * block)
         assert rel_l2(out[k * block:(k + 1) * block], ref) <= 1e-5
+
+
+@pytest.mark.parametrize("log2_block,K,n,ef,order", [(16, 512, 2, False, 1), (16, 513, 2, False, 0), (16, 1025, 1, False, 1),
+                                                     (18, 65, 2, True, 1), (20, 33, 1, True, 0), (25, 2, 1, True, 1)])
+def test_walk_from_the_last_tile(log2_block, K, n, ef, order):
+    """Launches above 2^26 worker-coordinates, 2^25 with error feedback, walk their tiles last one first: the whole against
+    its single blocks, which do not, bit for bit, at the first block, the last one and one between."""
+    block = 1 << log2_block
+    _, L = both_params(block * K, block, n, order=order)
+    R = GpuRound(L, ef=ef)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    x = [torch.randn(block * K, device=DEV, generator=gen) * 1e-3 for _ in range(n)]
+    old = []
+    for e in R.efs or []:
+        e.copy_(torch.randn(block * K, device=DEV, generator=gen) * 2e-4)
+        old.append(e.clone())
+    R.compress_all(4, x)
+    for k in {0, K // 2, K - 1}:
+        _, S = both_params(block, block, n, order=order, first_block=k)
+        Q = GpuRound(S, ef=ef)
+        at = slice(k * block, (k + 1) * block)
+        for q, e in zip(Q.efs or [], old):
+            q.copy_(e[at])
+        Q.compress_all(4, [v[at].clone() for v in x])
+        assert Q.range_M[0] == R.range_M[k]
+        for q, p in zip(Q.packed, R.packed):
+            assert torch.equal(q, p[k * block // 2:(k + 1) * block // 2])
+        for q, e in zip(Q.efs or [], R.efs or []):
+            assert torch.equal(q, e[at])
