@@ -389,9 +389,17 @@ void launch_big_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_
   const dim3 grid((unsigned)((a.lo.d + BIG - 1) >> LOG_BIG), W), blk(NT);
   const uint32_t bits = a.lo.src_bits;
   if (efm == 0) {
-    if (bits == 8) k_big_inv_whole<L, 8, 0><<<grid, blk, 0, s>>>(a);
-    else if (bits == 16) k_big_inv_whole<L, 16, 0><<<grid, blk, 0, s>>>(a);
-    else k_big_inv_whole<L, 0, 0><<<grid, blk, 0, s>>>(a);
+    if (bits == 8) {
+      k_big_inv_whole<L, 8, 0><<<grid, blk, 0, s>>>(a);
+      return;
+    }
+    if constexpr (L == 15) {               // 16-bit sums of 2^14-point blocks: k_inv_whole
+      if (bits == 16) {
+        k_big_inv_whole<L, 16, 0><<<grid, blk, 0, s>>>(a);
+        return;
+      }
+    }
+    k_big_inv_whole<L, 0, 0><<<grid, blk, 0, s>>>(a);
   } else if (efm == 1) {
     if (bits == 4) k_big_inv_whole<L, 4, 1><<<grid, blk, 0, s>>>(a);
     else k_big_inv_whole<L, 0, 1><<<grid, blk, 0, s>>>(a);
@@ -450,7 +458,8 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
   }
 }
 
-// Worker side of one round (Alg. 3) for W co-resident vectors, group by group:
+// Worker side of one round (Alg. 3) for W co-resident vectors.  Blocks of up to 2^14 go block by block where whole_route says
+// so; else the passes, group by group:
 //   first pass (x = grad + e, diagonal, 13 stages; with `range_out` also the norms) -> [range] -> middle passes ->
 //   last pass + quantizer -> [error feedback: indices -> inverse first pass -> middle passes -> inverse last pass].
 // Every kernel of a group covers all W vectors (grid.y), so a group costs the same number of launches for any W.

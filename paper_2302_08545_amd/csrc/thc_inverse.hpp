@@ -338,7 +338,7 @@ __global__ __launch_bounds__(NT) void k_inv_hi(const InvHiArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Blocks that fit one workgroup (2^10 to 2^13 here, 2^14 and 2^15 in thc_big.hpp): the whole inverse transform in one
+// Blocks that fit one workgroup (2^10 to 2^14 here, 2^14 and 2^15 in thc_big.hpp): the whole inverse transform in one
 // launch.  What bounds the two passes is bytes and, in small calls, launches: the intermediate's 8 bytes per
 // coordinate and one launch go.  Rounds of 8 workers with error feedback: 4096 blocks of 2^13 2031 -> 1505 us, 512 blocks
 // of 2^15 999 -> 764 us; one block of 2^14 without it 36 -> 25 us.  Calls back to back are faster at every size.  A call

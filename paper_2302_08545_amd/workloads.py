@@ -167,7 +167,7 @@ def moved_bytes_per_coord(w: Workload) -> float:
     reads and writes the vector once (rocprofv3's FETCH_SIZE / WRITE_SIZE read exactly this on the VGG16-shaped
     workload).  A transform of 2^L coordinates takes a first and a last pass, and above L = 25 one in between (8192-
     coordinate tiles do 13 bits, then up to 9, tiles of 2^15 do 15 and up to 10; above that 13 + 7 + 6 or 7).  Blocks of up
-    to 2^15 move less: their inverse is one pass."""
+    to 2^15 move less: their inverse is one pass, and up to 2^14 so is the worker side once the norms are known."""
     in_b = 4 if w.dtype == "f32" else 2
     L = w.block.bit_length() - 1
     mids = 1 if L > 25 else 0
