@@ -216,7 +216,7 @@ __global__ __launch_bounds__(NT, 8) void k_uniform_quant(const UQuantArgs a) {
   const int t = threadIdx.x, idx = 8 * t;
   const uint64_t off = (uint64_t)xcd_tile<4>(blockIdx.x, gridDim.x) << LOG_UTILE;
   const uint64_t j = off + idx;
-  const uint64_t from = j < a.d ? j : 0;   // past the end: read from the start, not used
+  const uint64_t from = j < a.d ? j : off;   // past the end: read from the tile's own start, not used
   const uint32_t ent = a.lut[t & 255];
   float4 x[2], e[2];
   __builtin_amdgcn_sched_barrier(0);

@@ -104,9 +104,9 @@ __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(c
   __builtin_amdgcn_sched_barrier(0);
   auto load = [&](uint32_t w, float4 (&x)[4]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {              // past the end: read from the start, not used
+    for (int i = 0; i < 4; ++i) {              // past the end: read from the tile's start, not used
       const uint64_t j = off + first + 4 * 512 * i;
-      x[i] = load_grad4<BF16>(a.grads.p[w], j < a.d ? j : 0);
+      x[i] = load_grad4<BF16>(a.grads.p[w], j < a.d ? j : off);
     }
   };
   float4 x[4];
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(c
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint64_t j = off + first + 4 * 512 * i;
-      own[i] = *reinterpret_cast<const float4*>(ef + (j < a.d ? j : 0));
+      own[i] = *reinterpret_cast<const float4*>(ef + (j < a.d ? j : off));
     }
   }
   __builtin_amdgcn_sched_barrier(0);
