@@ -1096,12 +1096,6 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
     dispatch_0_9<LaunchQuant>(pl.R, q, (pl.L & 1) == 0, tiles_of(p->d), 1, s);
   } else {
     UQuantArgs q{};
-    q.grad = grad;
-    q.ef = ef_inout;
-    q.range_M = range_M;
-    q.range_m = range_m;
-    q.packed = packed_out;
-    q.d = p->d;
     q.L = (uint32_t)pl.L;
     q.b = p->b;
     q.g = p->g;
@@ -1109,16 +1103,25 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
     q.worker = worker_id;
     q.k0 = k0;
     q.k1 = k1;
-    q.j0 = base_coord(p);
     fill_lut(p, q.lut);
-    const dim3 grid((unsigned)((p->d + UTILE - 1) >> LOG_UTILE)), blk(NT);
-    if (p->in_dtype == THC_DTYPE_BF16) {
-      if (ef_inout) k_uniform_quant<true, true><<<grid, blk, 0, s>>>(q);
-      else k_uniform_quant<true, false><<<grid, blk, 0, s>>>(q);
-    } else {
-      if (ef_inout) k_uniform_quant<false, true><<<grid, blk, 0, s>>>(q);
-      else k_uniform_quant<false, false><<<grid, blk, 0, s>>>(q);
-    }
+    const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
+    for_pieces(p->d, [&](uint64_t x0, uint64_t len) {
+      q.grad = static_cast<const char*>(grad) + x0 * (bf16 ? 2 : 4);
+      q.ef = ef_inout ? ef_inout + x0 : nullptr;
+      q.range_M = range_M + x0 / p->block;
+      q.range_m = range_m + x0 / p->block;
+      q.packed = packed_out + x0 / 8 * p->b;
+      q.d = len;
+      q.j0 = base_coord(p) + x0;
+      const dim3 grid((unsigned)((len + UTILE - 1) >> LOG_UTILE)), blk(NT);
+      if (bf16) {
+        if (ef_inout) k_uniform_quant<true, true><<<grid, blk, 0, s>>>(q);
+        else k_uniform_quant<true, false><<<grid, blk, 0, s>>>(q);
+      } else {
+        if (ef_inout) k_uniform_quant<false, true><<<grid, blk, 0, s>>>(q);
+        else k_uniform_quant<false, false><<<grid, blk, 0, s>>>(q);
+      }
+    });
   }
   if (rotate && ef_inout) {
     // e <- (grad + e) - RHT^-1(X_i): rebuild X_i from the indices, inverse transform, subtract

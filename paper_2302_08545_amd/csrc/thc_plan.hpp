@@ -227,6 +227,15 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
   return W * len > (1ull << (ef ? 25 : 26)) && (!big || pl.L == 25);
 }
 
+// Kernels that take a whole vector, one launch after another of at most LAUNCH_COORDS coordinates (whole blocks): a launch
+// holds fewer than 2^32 threads, which at eight coordinates a thread is 2^35, a bf16 vector of 64 GB.
+constexpr uint64_t LAUNCH_COORDS = 1ull << 34;
+
+template <class Piece>
+inline void for_pieces(uint64_t d, Piece&& piece) {
+  for (uint64_t x0 = 0; x0 < d; x0 += LAUNCH_COORDS) piece(x0, d - x0 < LAUNCH_COORDS ? d - x0 : LAUNCH_COORDS);
+}
+
 // The groups of whole blocks, `gc` coordinates of each of W vectors, in which a call walks its d coordinates:
 // group(first coordinate, coordinates, whether the forward and the inverse launches take the larger tiles).
 template <class Group>

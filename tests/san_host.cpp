@@ -102,6 +102,18 @@ static int check_groups(uint64_t block, uint64_t d, uint64_t gc, uint32_t W, boo
   return bad + (at != d);
 }
 
+// whole vectors in launches of whole blocks and fewer than 2^32 threads, at eight coordinates a thread or more
+static int check_pieces(uint64_t d, int want) {
+  uint64_t at = 0;
+  int bad = 0, n = 0;
+  for_pieces(d, [&](uint64_t x0, uint64_t len) {
+    bad += x0 != at || !len || x0 % (1ull << 27) || len / 8 >= (1ull << 32);
+    at += len;
+    ++n;
+  });
+  return bad + (at != d) + (n != want);
+}
+
 // The index of a coordinate above the range, for the largest rounding draw: what the quantizer's fast form, which does
 // not clamp, makes of M itself.
 static bool fast_form_ends_at_the_top(const QuantScalars& q, uint32_t g, uint32_t wd) {
@@ -154,6 +166,8 @@ int main() {
   bad += check_groups(2 * M22, 3 * M22 * 2, 2 * M22, 1, true, true, true, true);
   bad += check_groups(M22 / 2, 256 * M22, 128 * M22, 8, false, false, false, false);
   bad += check_groups(16 * M22, 32 * M22, 16 * M22, 8, false, false, false, false);
+  bad += check_pieces(1ull << 10, 1) + check_pieces(1ull << 34, 1) + check_pieces((1ull << 34) + 1024, 2);
+  bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
   // largest number of workgroups at which the quantizer finds the range itself
   const struct { int L; uint32_t W; uint64_t most; } find[] = {{10, 1, 2048}, {13, 2, 1024}, {14, 3, 1024}, {16, 4, 768},
                                                               {16, 8, 512}, {10, 32, 128}, {17, 1, 1280}, {20, 4, 320}};

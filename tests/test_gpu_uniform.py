@@ -102,3 +102,23 @@ def test_bf16_uniform_plain():
     api.thc_uniform_compress(L, 1, 0, dg[1], None, False, rm, rM, pk, None)
     ref, _ = o.uniform_compress(P, 1, 0, gn[1], None, m_ref, M_ref, False)
     assert_indices_match(pk.cpu().numpy(), ref, b)
+
+
+def test_uniform_compress_of_more_than_2_to_the_35_coordinates():
+    """A launch takes fewer than 2^32 threads, so the longest vectors go in several: blocks on either side of every seam
+    and the last one, each with a range of its own, against the oracle.  64 GB of bf16."""
+    block, K, b = 1 << 14, (1 << 21) + 1, 1
+    _, L = uparams(K * block, block, 2, b, 2, bf16=True)
+    v = make_grads(block, 1, seed=35, bf16=True)[0]
+    x = torch.empty(K * block, dtype=torch.bfloat16, device=DEV)
+    x.view(K, block).copy_(v.to(DEV).expand(K, block))
+    gen = torch.Generator(device=DEV).manual_seed(35)
+    rm = torch.rand(K, generator=gen, device=DEV) * -2e-3 - 1e-3
+    rM = torch.rand(K, generator=gen, device=DEV) * 2e-3 + 1e-3
+    packed = torch.zeros(K * block * b // 8, dtype=torch.uint8, device=DEV)
+    api.thc_uniform_compress(L, 1, 8, x, None, False, rm, rM, packed, None)
+    P, _ = uparams(block, block, 2, b, 2)
+    for k in (0, (1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21):
+        ref, _ = o.uniform_compress(P, 1, 8, to_np32(v), None, rm[k:k + 1].cpu().numpy(), rM[k:k + 1].cpu().numpy(), False,
+                                    k * block)
+        assert_indices_match(packed[k * block * b // 8:(k + 1) * block * b // 8].cpu().numpy(), ref, b, f"block {k}")
