@@ -566,37 +566,29 @@ void launch_whole(const WholeArgs& a, bool bf16, bool ef, bool find, uint32_t W,
   else launch_whole_k<L, false>(a, ef, find, grid, s);
 }
 
-// the norms of W vectors and their range (Alg. 3's preliminary stage)
-void run_norms(const thc_params* p, const Plan& pl, const void* const* grads, const float* const* ef, uint32_t W,
-               float* range_M, double* partials, hipStream_t s) {
+// the norms of `len` coordinates, from x0 on, of W vectors and their range (Alg. 3's preliminary stage)
+void run_norms(const thc_params* p, const Plan& pl, const void* const* grads, const float* const* ef, uint32_t W, uint64_t x0,
+               uint64_t len, float* range_M, double* partials, hipStream_t s) {
+  const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
   FwdLoArgs a{};
   for (uint32_t i = 0; i < W; ++i) {
-    a.grads.p[i] = grads[i];
-    if (ef) a.efs.p[i] = ef[i];
+    a.grads.p[i] = static_cast<const char*>(grads[i]) + x0 * (bf16 ? 2 : 4);
+    if (ef) a.efs.p[i] = ef[i] + x0;
   }
   a.partials = partials;
-  a.pstride = p->d >> pl.L1;
-  a.d = p->d;
-  a.tm = lo_tilemap(pl, p->d);
-  launch_fwd_lo(pl, a, p->in_dtype == THC_DTYPE_BF16, ef != nullptr, true, tiles_of(p->d), W, s);
-  launch_range(RangeArgs{partials, range_M, p->d >> pl.L1, p->d, W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p}, s);
+  a.pstride = len >> pl.L1;
+  a.d = len;
+  a.tm = lo_tilemap(pl, len);
+  launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(len), W, s);
+  launch_range(RangeArgs{partials, range_M + x0 / p->block, a.pstride, len, W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p}, s);
 }
 
 // Blocks of up to 2^14, block by block: nothing of the vectors goes through the workspace.
 void run_forward_whole(const Forward& f, const Plan& pl, Whole route) {
   const thc_params* p = f.p;
   const bool bf16 = p->in_dtype == THC_DTYPE_BF16, ef = f.efs != nullptr, find = route == Whole::FIND;
-  if (route == Whole::NORMS)
-    run_norms(p, pl, f.grads, f.efs, f.W, f.range_out, ws_layout(f.ws, p, pl, ef).partials, f.s);
+  float* const range_M = f.range_out ? f.range_out : const_cast<float*>(f.range_in);
   WholeArgs a{};
-  for (uint32_t i = 0; i < f.W; ++i) {
-    a.grads.p[i] = f.grads[i];
-    if (ef) a.efs.p[i] = f.efs[i];
-    a.packed.p[i] = f.packed[i];
-  }
-  a.range_M = f.range_out ? f.range_out : const_cast<float*>(f.range_in);
-  a.d = p->d;
-  a.j0 = base_coord(p);
   a.L = (uint32_t)pl.L;
   a.b = p->b;
   a.g = p->g;
@@ -609,13 +601,25 @@ void run_forward_whole(const Forward& f, const Plan& pl, Whole route) {
   a.t_p = p->t_p;
   fill_lut(p, a.lut);
   std::memcpy(a.table, p->table, 256);
-  switch (pl.L) {
-    case 10: launch_whole<10>(a, bf16, ef, find, f.W, f.s); break;
-    case 11: launch_whole<11>(a, bf16, ef, find, f.W, f.s); break;
-    case 12: launch_whole<12>(a, bf16, ef, find, f.W, f.s); break;
-    case 13: launch_whole<13>(a, bf16, ef, find, f.W, f.s); break;
-    default: launch_whole<14>(a, bf16, ef, find, f.W, f.s); break;
-  }
+  for_pieces(p->d, [&](uint64_t x0, uint64_t len) {
+    if (route == Whole::NORMS)
+      run_norms(p, pl, f.grads, f.efs, f.W, x0, len, range_M, ws_layout(f.ws, p, pl, ef).partials, f.s);
+    for (uint32_t i = 0; i < f.W; ++i) {
+      a.grads.p[i] = static_cast<const char*>(f.grads[i]) + x0 * (bf16 ? 2 : 4);
+      if (ef) a.efs.p[i] = f.efs[i] + x0;
+      a.packed.p[i] = f.packed[i] + x0 / 8 * p->b;
+    }
+    a.range_M = range_M + x0 / p->block;
+    a.d = len;
+    a.j0 = base_coord(p) + x0;
+    switch (pl.L) {
+      case 10: launch_whole<10>(a, bf16, ef, find, f.W, f.s); break;
+      case 11: launch_whole<11>(a, bf16, ef, find, f.W, f.s); break;
+      case 12: launch_whole<12>(a, bf16, ef, find, f.W, f.s); break;
+      case 13: launch_whole<13>(a, bf16, ef, find, f.W, f.s); break;
+      default: launch_whole<14>(a, bf16, ef, find, f.W, f.s); break;
+    }
+  });
 }
 
 void run_forward(const Forward& f) {
@@ -828,7 +832,7 @@ int thc_prepare_range(const thc_params* p, const void* const* grads, const float
   hipStream_t s = static_cast<hipStream_t>(stream);
   // The same partial sums, in the same order, as the first pass of thc_compress_all takes them group by group, on tiles
   // of either size and in the single launch: all give the same M bit for bit.
-  run_norms(p, pl, grads, ef, p->n, range_M, ws_layout(ws, p, pl, false).partials, s);
+  run_norms(p, pl, grads, ef, p->n, 0, p->d, range_M, ws_layout(ws, p, pl, false).partials, s);
   return check_launch();
 }
 

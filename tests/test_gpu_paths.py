@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from oracle import thc_oracle as o
+from paper_2302_08545_amd import api
 
 from .test_gpu_parity import DEV, GpuRound, assert_indices_match, both_params, make_grads, rel_l2, to_np32
 
@@ -239,6 +240,36 @@ def test_worker_side_block_by_block(log2_block, K, n, b, g, bf16, ef):
     assert_indices_match(A.packed[i].cpu().numpy(), pk, b)
     if ef:
         assert rel_l2(A.efs[i].cpu().numpy(), ne) <= 1e-5
+
+
+@pytest.mark.parametrize("every_call", [False, True], ids=["compress", "compress_all"])
+def test_worker_side_of_more_than_2_to_the_36_coordinates(every_call):
+    """A launch takes fewer than 2^32 threads, so the longest vectors go in several: blocks on either side of a seam and
+    the last one against the oracle, each at a scale of its own.  128 GB of bf16."""
+    block, K = 1 << 14, (1 << 22) + 1
+    P, L = both_params(block * K, block, 1, b=1, g=1, agg_bits=1, bf16=True, table=[0, 1])
+    v = make_grads(block, 1, seed=36, bf16=True)[0]
+    x = torch.empty(block * K, dtype=torch.bfloat16, device=DEV)
+    scale = 2.0 ** (torch.arange(K, device=DEV) % 5).to(torch.bfloat16)
+    torch.mul(v.to(DEV).expand(K, block), scale[:, None], out=x.view(K, block))
+    packed = torch.zeros(block * K // 8, dtype=torch.uint8, device=DEV)
+    ws = torch.empty(api.thc_workspace_bytes(L, False), dtype=torch.uint8, device=DEV)
+    M = torch.rand(K, device=DEV, generator=torch.Generator(device=DEV).manual_seed(36)) * 1e-3 + 1e-3
+    given = M.clone()
+    if every_call:
+        api.thc_compress_all(L, 8, [x], None, M, [packed], ws)
+    else:
+        api.thc_compress(L, 0, 8, x, None, M, packed, ws)
+    Pk = o.Params(d=block, block=block, n=1, b=1, g=1, t_p=P.t_p, seed=P.seed, table=P.table, agg_bits=1)
+    for k in (0, (1 << 20) - 1, 1 << 20, (1 << 22) - 1, 1 << 22):
+        gk, Mk = to_np32(x[k * block:(k + 1) * block]), M[k:k + 1].cpu().numpy()
+        if every_call:
+            want = o.prepare_range(Pk, [gk])
+            assert abs(Mk[0] - want[0]) <= want[0] * 2.0 ** -23
+        else:
+            assert Mk[0] == given[k].item()
+        ref = o.compress(Pk, 0, 8, gk, None, Mk, j0=k * block)[0]
+        assert_indices_match(packed[k * block // 8:(k + 1) * block // 8].cpu().numpy(), ref, 1, f"block {k}")
 
 
 @pytest.mark.parametrize("K,agg_bits", [(1, 8), (3, 9), (704, 8), (705, 8), (705, 9), (705, 16), (1024, 9), (1025, 8)])
