@@ -259,21 +259,21 @@ void launch_range(const RangeArgs& r, hipStream_t s) {
   else k_range<<<dim3((unsigned)K), dim3(RANGE_NT), 0, s>>>(r);
 }
 
-template <int SB, int TB>
+template <int SB, bool TABLE>
 void launch_inv_lo_k(const InvLoArgs& a, bool split, dim3 grid, hipStream_t s) {
-  if (split) k_inv_lo<true, SB, TB><<<grid, dim3(NT), 0, s>>>(a);
-  else k_inv_lo<false, SB, TB><<<grid, dim3(NT), 0, s>>>(a);
+  if (split) k_inv_lo<true, SB, TABLE><<<grid, dim3(NT), 0, s>>>(a);
+  else k_inv_lo<false, SB, TABLE><<<grid, dim3(NT), 0, s>>>(a);
 }
 
 void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)tiles, W);
   if (a.use_table) {
-    if (a.src_bits == 4) launch_inv_lo_k<4, 1>(a, pl.split, grid, s);
-    else launch_inv_lo_k<0, 1>(a, pl.split, grid, s);
+    if (a.src_bits == 4) launch_inv_lo_k<4, true>(a, pl.split, grid, s);
+    else launch_inv_lo_k<0, true>(a, pl.split, grid, s);
   } else {
-    if (a.src_bits == 8) launch_inv_lo_k<8, 0>(a, pl.split, grid, s);
-    else if (a.src_bits == 16) launch_inv_lo_k<16, 0>(a, pl.split, grid, s);
-    else launch_inv_lo_k<0, 0>(a, pl.split, grid, s);
+    if (a.src_bits == 8) launch_inv_lo_k<8, false>(a, pl.split, grid, s);
+    else if (a.src_bits == 16) launch_inv_lo_k<16, false>(a, pl.split, grid, s);
+    else launch_inv_lo_k<0, false>(a, pl.split, grid, s);
   }
 }
 
@@ -721,7 +721,6 @@ void run_forward(const Forward& f) {
       q.pstride = a.pstride;
       q.range_out = find ? f.range_out + x0 / p->block : nullptr;
       q.n = f.W;
-      q.L1 = (uint32_t)pl.L1;
       q.t_p = p->t_p;
       dispatch_0_9<LaunchQuant>(pl.R, q, (pl.L & 1) == 0, tiles, f.W, f.s);
     }

@@ -513,7 +513,7 @@ struct QuantArgs {
   const double* partials;
   uint64_t pstride;
   float* range_out;
-  uint32_t n, L1;
+  uint32_t n;
   float t_p;
 };
 

@@ -111,9 +111,9 @@ struct alignas(16) SmemInvLo {
 };
 
 // One tile of N threads: the one at coordinate `off` of the launch's vector `vec`; put(o, value) takes each result, o its
-// offset from the tile's first coordinate.  SB and TB are the width and the kind of the codes where the launch knows them (TB 1: table
-// indices, 0: sums, -1: a.use_table says); SB = 0: a.src_bits says.
-template <int L1, bool XO, int SB, int TB, int N = NT, class A, class Put>
+// offset from the tile's first coordinate.  TABLE: the codes are table indices, else sums.  SB is their width where the launch
+// knows it, or 0: a.src_bits says.
+template <int L1, bool XO, int SB, bool TABLE, int N = NT, class A, class Put>
 __device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t vec, SmemInvLo<N>& sm, Put&& put) {
   static_assert(!XO || (L1 == LOG_TILE && N == NT), "the row-split tile needs blocks of at least 2^16");
   constexpr bool GUARD = (1 << L1) < 16 * N;
@@ -128,11 +128,10 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t
   const bool ok = !GUARD || j < a.d;
   const uint8_t* const src = static_cast<const uint8_t*>(a.src.p[vec]);
   const uint32_t bits = SB ? SB : a.src_bits;
-  const bool use_table = TB < 0 ? a.use_table != 0 : TB != 0;
 
   // raw bits first, so the load is in flight while the block constants are prepared
   uint32_t entry = 0;
-  if (use_table && t < 256) entry = a.table[t];
+  if (TABLE && t < 256) entry = a.table[t];
   uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   uint32_t y[16];
   const bool staged = !codes_fast_width(bits);
@@ -158,9 +157,8 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t
     }
   }
 
-  // A tile inside one block looks up values on the block's range; one of several blocks, or whose kind is not known, looks
-  // up the table's own values.
-  constexpr bool SCALED = TB == 1 && !GUARD;
+  // A tile inside one block looks up values on the block's range; one of several blocks looks up the table's own values.
+  constexpr bool SCALED = TABLE && !GUARD;
   const int nblk = GUARD ? (16 * N) >> a.L : 1;
   if (SCALED ? t < (SB ? 1 << SB : 256) : t < nblk) {
     const uint64_t blk = (off >> a.L) + (SCALED ? 0 : t);
@@ -174,7 +172,7 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t
       sStep[t] = step;
     }
   }
-  if (!SCALED && use_table && t < 256) tabf[t] = (float)entry;
+  if (TABLE && !SCALED && t < 256) tabf[t] = (float)entry;
   __syncthreads();
 
   if (!staged) {
@@ -203,7 +201,7 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t
   float v[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    const float f = use_table ? tabf[y[e]] : (float)y[e];
+    const float f = TABLE ? tabf[y[e]] : (float)y[e];
     v[e] = SCALED ? f : ok ? f * step + lo : 0.f;
   }
   bfly<4>(v);
@@ -214,21 +212,21 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t
   lds_stages<4, L1, true, SWZ, N>(lds, t, [&](int base, int eoff, float val) { put(lo_map<XO>(base) + lo_map<XO>(eoff), val); });
 }
 
-template <bool XO, int SB, int TB, class A>
+template <bool XO, int SB, bool TABLE, class A>
 __device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t vec, float* dst_vec, SmemInvLo<>& sm) {
   const uint64_t off = tm_base(a.tm, tile);
   float* const dst = dst_vec + off;
-  inv_lo_stages<LOG_TILE, XO, SB, TB>(a, off, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
+  inv_lo_stages<LOG_TILE, XO, SB, TABLE>(a, off, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
 }
 
 // What bounds it: writing 4 bytes a coordinate (pure writes reach 5.7 TB/s here).  Decoding is a large part of its
 // instructions, so the widths and sources that rounds use have instantiations of their own: 2^28 coordinates from 8-bit
 // sums 251 -> 231 us, from 4-bit indices, whose values are looked up on the block's range, 268 -> 245 us; one block of
 // 2^20 from 4-bit indices 5.4 -> 4.3 us.
-template <bool XO, int SB, int TB>
+template <bool XO, int SB, bool TABLE>
 __global__ __launch_bounds__(NT, 8) void k_inv_lo(const InvLoArgs a) {
   __shared__ SmemInvLo<> sm;
-  inv_lo_tile<XO, SB, TB>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
+  inv_lo_tile<XO, SB, TABLE>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -83,7 +83,7 @@ struct InvLoView {
   const float* range_M;
   const float* range_m;
   uint64_t d;
-  uint32_t L, src_bits, use_table, divisor;
+  uint32_t L, src_bits, divisor;
   const TileMap& tm;
   const uint8_t* table;
 };
@@ -220,8 +220,8 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
     if (phase == 2) {
       // X_i from the indices, inverse first pass into the slot the quantizer has finished with
       if (!pipe_wait<true>(us + (1 * SYNC_PHASE + NXCD) * SYNC_STRIDE, NXCD, P.status, &flag)) return;
-      const InvLoView a{P.packed, P.range_M, nullptr, P.d, P.L, P.b, 1u, P.g, P.lo_tm, P.table};
-      inv_lo_tile<true, 0, 1>(a, gt, w, vec, *reinterpret_cast<SmemInvLo<>*>(raw));
+      const InvLoView a{P.packed, P.range_M, nullptr, P.d, P.L, P.b, P.g, P.lo_tm, P.table};
+      inv_lo_tile<true, 0, true>(a, gt, w, vec, *reinterpret_cast<SmemInvLo<>*>(raw));
       pipe_publish(us, 2, Tu >> 3);
     } else {
       // e <- (grad + e) - RHT^-1(X_i)
