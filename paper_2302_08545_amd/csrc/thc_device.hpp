@@ -28,16 +28,6 @@ __device__ __forceinline__ uint64_t tm_base(const TileMap& m, uint32_t tile) {
   return ((uint64_t)(tile >> m.nfixed) << m.L) | off;
 }
 
-// Kernels that walk a vector in consecutive 8192-coordinate tiles, one per workgroup: workgroup ids are dealt
-// round-robin to the 8 XCDs, and streaming is faster (measured 5.7 against 5.3 TB/s) when an XCD keeps to its own
-// value of byte-address bits 18..20 rather than 15..17.  Inside every whole group of 8 << S = 64 tiles the low three bits
-// of the workgroup id therefore select tile bits S..S+2 = 3..5.
-template <int S = 3>
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t wg, uint32_t ntiles) {
-  constexpr uint32_t G = (8u << S) - 1u;
-  return (wg | G) < ntiles ? (wg & ~G) | ((wg & 7u) << S) | ((wg >> 3) & ((1u << S) - 1u)) : wg;
-}
-
 // A pass that reads what the pass before it has just written, and more of it than the 256 MB memory-side cache holds, walks
 // the launch's tiles and vectors last one first (see last_first): what was written last is still there, where a walk in the
 // same order would find each line just dropped.

@@ -37,4 +37,14 @@ struct TileMap {
   uint32_t fpos[4];
 };
 
+// Kernels that walk a vector in consecutive 8192-coordinate tiles, one per workgroup: workgroup ids are dealt
+// round-robin to the 8 XCDs, and streaming is faster (measured 5.7 against 5.3 TB/s) when an XCD keeps to its own
+// value of byte-address bits 18..20 rather than 15..17.  Inside every whole group of 8 << S = 64 tiles the low three bits
+// of the workgroup id therefore select tile bits S..S+2 = 3..5.
+template <int S = 3>
+THC_HOST_DEVICE uint32_t xcd_tile(uint32_t wg, uint32_t ntiles) {
+  constexpr uint32_t G = (8u << S) - 1u;
+  return (wg | G) < ntiles ? (wg & ~G) | ((wg & 7u) << S) | ((wg >> 3) & ((1u << S) - 1u)) : wg;
+}
+
 }  // namespace thc

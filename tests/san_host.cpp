@@ -114,6 +114,83 @@ static int check_pieces(uint64_t d, int want) {
   return bad + (at != d) + (n != want);
 }
 
+// the order in which workgroups take consecutive tiles leaves none out and takes none twice
+template <int S>
+static int check_xcd_tile() {
+  int bad = 0;
+  for (uint32_t n : {1u, 7u, (8u << S) - 1, 8u << S, (8u << S) + 1, 3 * (8u << S) + 5, 4096u}) {
+    std::vector<unsigned char> seen(n, 0);
+    for (uint32_t wg = 0; wg < n; ++wg) {
+      const uint32_t t = xcd_tile<S>(wg, n);
+      if (t >= n || seen[t]) { ++bad; break; }
+      seen[t] = 1;
+    }
+    if (n >= 8u << S)
+      for (uint32_t x = 0; x < 8; ++x) bad += (xcd_tile<S>(x, n) >> S & 7u) != x;
+  }
+  return bad;
+}
+
+// Both sides of every limit of whole_route: vectors of `tiles` 8192-coordinate tiles, W of them.
+static int check_whole_route() {
+  const struct { int L; uint32_t W; bool ef; uint64_t tiles; Whole want; } at[] = {
+      // no error feedback, up to 2^13
+      {10, 1, false, 1, Whole::FIND}, {13, 1, false, 1ull << 20, Whole::FIND}, {13, 2, false, 256, Whole::FIND},
+      {13, 2, false, 257, Whole::NORMS}, {10, 4, false, 128, Whole::FIND}, {10, 4, false, 129, Whole::NORMS},
+      {12, 5, false, 1, Whole::NO}, {12, 5, false, 102, Whole::NO}, {12, 5, false, 103, Whole::NORMS},
+      {13, 8, false, 63, Whole::NO}, {13, 8, false, 64, Whole::NORMS}, {11, 16, false, 39, Whole::NO},
+      {11, 16, false, 40, Whole::NORMS}, {13, 10, false, 63, Whole::NO}, {13, 10, false, 64, Whole::NORMS},
+      // 2^14: where its two workgroups a compute unit fill the chip evenly, and in large calls
+      {14, 1, false, 1024, Whole::FIND}, {14, 1, false, 1026, Whole::NO}, {14, 4, false, 128, Whole::FIND},
+      {14, 4, false, 130, Whole::NO}, {14, 4, false, 224, Whole::NO}, {14, 4, false, 226, Whole::NORMS},
+      {14, 4, false, 256, Whole::NORMS}, {14, 4, false, 258, Whole::NO}, {14, 4, false, 1022, Whole::NO},
+      {14, 4, false, 1024, Whole::NORMS}, {14, 8, false, 56, Whole::NO}, {14, 5, false, 90, Whole::NORMS},
+      {14, 8, false, 64, Whole::NORMS}, {14, 8, false, 66, Whole::NO}, {14, 9, false, 56, Whole::NO},
+      {14, 16, false, 32, Whole::NO}, {14, 16, false, 56, Whole::NO}, {14, 16, false, 58, Whole::NORMS},
+      {14, 16, false, 64, Whole::NORMS}, {14, 16, false, 66, Whole::NO}, {14, 17, false, 60, Whole::NO},
+      {14, 32, false, 126, Whole::NO}, {14, 32, false, 128, Whole::NORMS},
+      // error feedback
+      {10, 1, true, 1, Whole::NORMS}, {13, 64, true, 1000, Whole::NORMS}, {14, 1, true, 512, Whole::NORMS},
+      {14, 1, true, 514, Whole::NO}, {14, 8, true, 64, Whole::NORMS}, {14, 8, true, 66, Whole::NO},
+      {14, 8, true, 510, Whole::NO}, {14, 8, true, 512, Whole::NORMS},
+      {15, 1, false, 4, Whole::NO}, {15, 1, true, 4, Whole::NO}, {20, 8, false, 1024, Whole::NO}};
+  int bad = 0;
+  for (const auto& c : at) {
+    const Plan pl = make_plan(1ull << c.L, THC_ORDER_SPLIT);
+    bad += whole_route(pl, c.tiles, c.W, c.ef, false) != c.want;
+    bad += whole_route(pl, c.tiles, 1, c.ef, true) != (c.L <= 14 ? Whole::GIVEN : Whole::NO);
+  }
+  return bad;
+}
+
+// ... of the kernel that takes the inverse transform of blocks of 2^14 ...
+static int check_inv_whole_14() {
+  auto one = [](uint64_t K, bool ef, uint32_t bits) { return inv_whole_14(K << 14, ef, bits); };
+  int bad = 0;
+  for (uint32_t bits : {1u, 4u, 8u, 9u, 15u}) {
+    bad += !one(1, false, bits) || !one(704, false, bits) || one(705, false, bits) || one(1024, false, bits) ||
+           !one(1025, false, bits);
+  }
+  for (uint64_t K : {1ull, 704ull, 705ull, 1024ull, 1025ull, 16384ull})
+    bad += !one(K, false, 16) || one(K, true, 4) || one(K, true, 8);
+  return bad;
+}
+
+// ... and of the walk from the last tile.
+static int check_last_first() {
+  int bad = 0;
+  for (int L : {14, 16, 20, 21, 25}) {
+    const Plan pl = make_plan(1ull << L, THC_ORDER_SPLIT);
+    const uint64_t B = 1ull << L, a = 1ull << 26, b = 1ull << 25;
+    bad += last_first(pl, a, 1, false, false) || !last_first(pl, a + B, 1, false, false);
+    bad += last_first(pl, b, 1, true, false) || !last_first(pl, b + B, 1, true, false);
+    bad += last_first(pl, b / 8 > B ? b / 8 : B, b / 8 > B ? 8 : b / B, true, false);
+    bad += !last_first(pl, b, 2, true, false) || last_first(pl, b, 2, false, false) || !last_first(pl, b, 3, false, false);
+    bad += last_first(pl, 4 * a, 8, true, true) != (L == 25);
+  }
+  return bad;
+}
+
 // The index of a coordinate above the range, for the largest rounding draw: what the quantizer's fast form, which does
 // not clamp, makes of M itself.
 static bool fast_form_ends_at_the_top(const QuantScalars& q, uint32_t g, uint32_t wd) {
@@ -168,9 +245,14 @@ int main() {
   bad += check_groups(16 * M22, 32 * M22, 16 * M22, 8, false, false, false, false);
   bad += check_pieces(1ull << 10, 1) + check_pieces(1ull << 34, 1) + check_pieces((1ull << 34) + 1024, 2);
   bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
-  // largest number of workgroups at which the quantizer finds the range itself
-  const struct { int L; uint32_t W; uint64_t most; } find[] = {{10, 1, 2048}, {13, 2, 1024}, {14, 3, 1024}, {16, 4, 768},
-                                                              {16, 8, 512}, {10, 32, 128}, {17, 1, 1280}, {20, 4, 320}};
+  bad += check_xcd_tile<2>() + check_xcd_tile<3>() + check_xcd_tile<4>() + check_xcd_tile<6>();
+  bad += check_whole_route() + check_inv_whole_14() + check_last_first();
+  // largest number of workgroups at which the quantizer finds the range itself (where whole_route leaves it to the passes:
+  // from 2^15 on, in 2^14, and up to 2^13 with more than four workers)
+  const struct { int L; uint32_t W; uint64_t most; } find[] = {
+      {10, 1, 2048},  {13, 2, 1024},  {14, 3, 1024}, {16, 4, 768},  {16, 8, 512},  {10, 32, 128}, {17, 1, 1280}, {20, 4, 320},
+      {15, 1, 2048},  {16, 2, 1024},  {15, 3, 1024}, {15, 4, 768},  {15, 5, 819},  {14, 2, 1024}, {14, 4, 768},  {14, 8, 512},
+      {16, 64, 64},   {18, 5, 204},   {20, 16, 64},  {17, 17, 30},  {20, 32, 16}};
   for (const auto& f : find) {
     const Plan pl = make_plan(1ull << f.L, THC_ORDER_ASCENDING);
     bad += !find_range(pl, f.most, f.W) || find_range(pl, f.most + 1, f.W);
