@@ -263,10 +263,11 @@ def test_error_feedback_rounds():
             R.efs[i].copy_(torch.from_numpy(efs_ref[i]))
 
 
-@pytest.mark.parametrize("L,K,n,bf16,order", [(12, 11, 2, False, 0), (16, 5, 2, True, 1), (18, 3, 1, False, 1),
+@pytest.mark.parametrize("L,K,n,bf16,order", [(12, 11, 2, False, 0), (15, 5, 2, False, 0), (16, 5, 2, True, 1), (18, 3, 1, False, 1),
                                                  (21, 2, 1, False, 1)])
 def test_piecewise_processing_matches_the_oracle(L, K, n, bf16, order):
-    """Every call walks long vectors in groups of whole blocks that share the workspace's slot.  With the group forced
+    """The passes walk long vectors in groups of whole blocks that share the workspace's slot (at 2^12 only those of the
+    decompression: the worker side goes block by block).  With the group forced
     down to 2^14 coordinates (or one block, if larger) these vectors take several groups, the last one shorter; packed
     bytes, error feedback and the output must not change."""
     block = 1 << L

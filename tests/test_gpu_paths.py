@@ -97,12 +97,14 @@ def test_tiles_of_2_to_the_15(log2_block, K, n, b, g, agg_bits, bf16, ef, order)
     (15, 1, 5, 3, 31, 1), (16, 2, 33, 2, 3, 1), (17, 3, 2, 3, 21, 1), (19, 1, 7, 1, 1, 0), (20, 1, 10, 3, 21, 1),
     (21, 1, 3, 4, 30, 0), (22, 1, 2, 3, 21, 1), (16, 16, 32, 4, 30, 1), (16, 17, 32, 4, 30, 1), (10, 16384, 1, 4, 30, 0),
     (10, 16385, 1, 4, 30, 0), (13, 1024, 3, 4, 30, 0), (13, 1025, 3, 4, 30, 0), (14, 7, 9, 8, 255, 0), (17, 8, 8, 4, 30, 1),
-    (17, 9, 8, 4, 30, 1), (17, 20, 4, 4, 30, 0), (17, 21, 4, 4, 30, 0), (18, 1, 17, 4, 30, 1), (20, 1, 33, 2, 3, 1)])
+    (17, 9, 8, 4, 30, 1), (17, 20, 4, 4, 30, 0), (17, 21, 4, 4, 30, 0), (18, 1, 17, 4, 30, 1), (20, 1, 33, 2, 3, 1),
+    (15, 512, 1, 4, 30, 0), (15, 513, 1, 4, 30, 0), (16, 128, 3, 4, 30, 1), (16, 129, 3, 4, 30, 1), (13, 63, 5, 4, 30, 0)])
 def test_range_found_by_the_last_pass(log2_block, K, n, b, g, order):
     """Small calls of blocks of up to 2^20: the quantizer adds the norms up itself.  The range is that of thc_prepare_range
-    and the streams are those of thc_compress, bit for bit, and both are the oracle's.  The pairs of rows that differ in one
-    block lie on either side of a limit of the rule (2^16: 4096 workgroups; 2^10: 2048; 2^13: 3072; 2^17: 1024 and 1280);
-    2^21 and 2^22 take the range kernel."""
+    and the streams are those of thc_compress, bit for bit, and both are the oracle's.  Pairs of rows of 2^15 to 2^17 that
+    differ in one block lie on either side of a limit of the rule (2^16 x 32 workers: 4096 workgroups; x 3: 3072; 2^15 x 1:
+    2048; 2^17: 1024 and 1280); 2^21 and 2^22 take the range kernel.  Blocks of up to 2^14 come to the quantizer here only
+    with more than four workers; the rows with fewer go block by block, as all of thc_compress does at these sizes."""
     block = 1 << log2_block
     table = list(range(256)) if b == 8 else None
     agg_bits = 8 if g * n < 256 else 16
@@ -147,7 +149,9 @@ def test_sums_of_any_width(b, g, n):
     (14, 2, 2, 3, 21, 16, True, True), (14, 5, 2, 4, 30, 8, True, True), (15, 1, 2, 2, 8, 5, False, True),
     (15, 3, 1, 4, 30, 16, True, True), (15, 2, 2, 4, 30, 8, False, False)])
 def test_whole_inverse_in_one_launch(log2_block, K, n, b, g, agg_bits, bf16, ef):
-    """Blocks of up to 2^15: odd numbers of blocks leave the last tile partly empty."""
+    """Rounds on blocks of up to 2^15, whose decompression is one launch; odd numbers of blocks leave the last tile partly
+    empty.  Error feedback takes the inverse in one launch here at 2^15; up to 2^14 it is part of the worker side's own
+    launch (the uniform variant takes the inverse at every size)."""
     block = 1 << log2_block
     P, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, bf16=bf16,
                        table=list(range(256)) if b == 8 else None)
@@ -205,10 +209,13 @@ def test_norms_are_added_up_in_one_order_whatever_the_tile(log2_block, K, n, bf1
     (10, 4097, 1, 4, 30, False, False), (14, 64, 4, 4, 30, False, False), (14, 65, 4, 4, 30, False, False),
     (14, 32, 8, 4, 30, False, False), (14, 28, 8, 4, 30, False, False), (14, 64, 8, 2, 3, True, False),
     (14, 512, 1, 4, 30, False, False), (14, 513, 1, 4, 30, False, False), (14, 64, 4, 4, 30, False, True),
-    (14, 65, 4, 4, 30, False, True)])
+    (14, 65, 4, 4, 30, False, True), (14, 65, 4, 3, 21, True, True), (14, 512, 4, 4, 30, False, False),
+    (14, 512, 4, 4, 30, True, True)])
 def test_worker_side_block_by_block(log2_block, K, n, b, g, bf16, ef):
     """Blocks of up to 2^14, whose worker side is one launch once the range is known: thc_compress_all gives what
-    thc_prepare_range and thc_compress give, bit for bit, whichever way its range comes about, and both are the oracle's."""
+    thc_prepare_range and thc_compress give, bit for bit, whichever way its range comes about, and both are the oracle's.
+    Without error feedback its first and its last blocks are also what the passes make of them, which a call of five and more
+    workers on a few blocks still takes; with it, 2^14 with 513 to 4095 workgroups takes the passes."""
     block = 1 << log2_block
     agg_bits = 8 if g * n < 256 else 16
     table = list(range(256)) if (b, g) == (8, 255) else [round(i * g / 255) for i in range(256)] if b == 8 else None
@@ -235,11 +242,22 @@ def test_worker_side_block_by_block(log2_block, K, n, b, g, bf16, ef):
     M, gn = A.range_M.cpu().numpy(), [to_np32(v) for v in x]
     M_ref = o.prepare_range(P, gn, before)
     assert np.all(np.abs(M - M_ref) <= np.abs(M_ref) * 2.0 ** -23)
-    i = n - 1
-    pk, ne = o.compress(P, i, 4, gn[i], before[i] if ef else None, M)
-    assert_indices_match(A.packed[i].cpu().numpy(), pk, b)
+    for i in range(n) if block * K * n <= 1 << 19 else (n - 1,):
+        pk, ne = o.compress(P, i, 4, gn[i], before[i] if ef else None, M)
+        assert_indices_match(A.packed[i].cpu().numpy(), pk, b)
+        if ef:
+            assert rel_l2(A.efs[i].cpu().numpy(), ne) <= 1e-5
     if ef:
-        assert rel_l2(A.efs[i].cpu().numpy(), ne) <= 1e-5
+        return
+    N, k = max(n, 5), min(K, 3)                  # the workers that are added repeat the first one: the range stays
+    for first in {0, K - k}:
+        at = slice(first * block, (first + k) * block)
+        _, S = both_params(block * k, block, N, b=b, g=g, agg_bits=16, bf16=bf16, table=table, first_block=first)
+        Q = GpuRound(S)
+        Q.compress_all(4, [v[at].clone() for v in dg] + [dg[0][at].clone()] * (N - n))
+        assert torch.equal(Q.range_M, A.range_M[first:first + k])
+        for p, q in zip(A.packed, Q.packed):
+            assert torch.equal(p[at.start // 8 * b:at.stop // 8 * b], q)
 
 
 @pytest.mark.parametrize("every_call", [False, True], ids=["compress", "compress_all"])

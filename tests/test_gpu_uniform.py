@@ -39,11 +39,27 @@ def test_uniform_round_on_large_rotated_blocks(log2_block, K, n, b, agg_bits, ef
     _uniform_round(1 << log2_block, K, n, b, agg_bits, ef, 0, True, order)
 
 
-def _uniform_round(block, K, n, b, agg_bits, ef, first_block, rotate, order=0):
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("b", [4, 3])
+@pytest.mark.parametrize("log2_block", [10, 11, 12, 13, 14, 15])
+def test_uniform_round_with_error_feedback_on_small_rotated_blocks(log2_block, b, bf16):
+    """The error-feedback inverse in one launch at every block size that takes it, from 4-bit and from other indices; the last
+    tile is partly empty where a tile holds several blocks."""
+    _uniform_round(1 << log2_block, 5 if log2_block < 14 else 3, 2, b, 8, True, 0, True, bf16=bf16)
+
+
+@pytest.mark.parametrize("block,K,b,bf16", [(1 << 10, 1, 4, True), (1 << 10, 5, 3, True), (1 << 11, 3, 4, False),
+                                            (1 << 13, 3, 4, True), (1 << 16, 2, 8, True)])
+def test_uniform_round_with_error_feedback_without_rotation(block, K, b, bf16):
+    """Tiles of 4096 coordinates, the last one partly empty in the first three rows."""
+    _uniform_round(block, K, 2, b, 16, True, 3, False, bf16=bf16)
+
+
+def _uniform_round(block, K, n, b, agg_bits, ef, first_block, rotate, order=0, bf16=False):
     d = block * K
     j0 = first_block * block            # the buffers hold a slice of a longer vector
-    P, L = uparams(d, block, n, b, agg_bits, first_block=first_block, order=order)
-    grads = make_grads(d, n, seed=block % 97 + b)
+    P, L = uparams(d, block, n, b, agg_bits, bf16=bf16, first_block=first_block, order=order)
+    grads = make_grads(d, n, seed=block % 97 + b, bf16=bf16)
     for i, g in enumerate(grads):
         g += 0.002 * (i - 1)                                      # asymmetric ranges: m != -M
     dg = [g.to(DEV) for g in grads]
@@ -76,6 +92,33 @@ def _uniform_round(block, K, n, b, agg_bits, ef, first_block, rotate, order=0):
     api.thc_uniform_decompress(L, rnd, agg, rotate, rm, rM, out, ws)
     ref = o.uniform_decompress(P, rnd, Y, m_ref, M_ref, rotate, j0)
     assert rel_l2(out.cpu().numpy(), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("log2_block,K,n", [(20, 33, 2), (14, 2049, 2), (12, 16385, 1)])
+def test_range_pass_of_the_rotated_variant_from_the_last_tile(log2_block, K, n):
+    """Above 2^26 worker-coordinates the range pass walks its tiles last one first: the range and the streams of the whole
+    against those of its single blocks, which do not."""
+    block, b = 1 << log2_block, 4
+
+    def compress(L, x):
+        k = L.d // block
+        ws = torch.empty(api.thc_uniform_workspace_bytes(L, True), dtype=torch.uint8, device=DEV)
+        rm, rM = torch.zeros(k, device=DEV), torch.zeros(k, device=DEV)
+        api.thc_uniform_prepare_range(L, 6, x, None, True, rm, rM, ws)
+        packed = [torch.zeros(L.d * b // 8, dtype=torch.uint8, device=DEV) for _ in x]
+        for i in range(n):
+            api.thc_uniform_compress(L, i, 6, x[i], None, True, rm, rM, packed[i], ws)
+        return rm, rM, packed
+
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    x = [torch.randn(block * K, device=DEV, generator=gen) * 1e-3 + 1e-3 * i for i in range(n)]
+    rm, rM, packed = compress(uparams(block * K, block, n, b, 16, order=1)[1], x)
+    for k in (0, K // 2, K - 1):
+        at = slice(k * block, (k + 1) * block)
+        m, M, one = compress(uparams(block, block, n, b, 16, order=1, first_block=k)[1], [v[at].clone() for v in x])
+        assert m[0] == rm[k] and M[0] == rM[k]
+        for p, q in zip(packed, one):
+            assert torch.equal(p[k * block // 2:(k + 1) * block // 2], q)
 
 
 def test_uniform_needs_the_identity_table():
