@@ -140,6 +140,10 @@ WsLayout ws_layout(void* ws, const thc_params* p, const Plan& pl, bool ef) {
 
 uint64_t tiles_of(uint64_t d) { return (d + TILE - 1) / TILE; }
 
+Walk walk_over(bool last_first, uint64_t tiles, uint32_t W) {
+  return last_first ? Walk{(uint32_t)tiles - 1u, W - 1u, ~0u} : Walk{};
+}
+
 // global coordinate of the buffers' first element
 uint64_t base_coord(const thc_params* p) { return (uint64_t)p->first_block * p->block; }
 
@@ -416,8 +420,9 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
     BigInvLoArgs a{lo.src, lo.range_M, lo.range_m, wsx, len, lo.L, lo.src_bits, lo.use_table, lo.divisor, {}};
     std::memcpy(a.table, lo.table, 256);
     launch_big_inv_lo(pl, a, W, s);
-    const BigInvHiArgs h{wsx, hi.out, hi.grad, len, hi.j0, hi.round, hi.k0, hi.k1,
-                         (float)(1.0 / std::sqrt((double)p->block)), hi.mode == 1 && last_first(pl, len, W, true, true)};
+    const BigInvHiArgs h{wsx, hi.out, hi.grad, len, hi.j0,
+                         walk_over(hi.mode == 1 && last_first(pl, len, W, true, true), len >> LOG_BIG, W), hi.round, hi.k0, hi.k1,
+                         (float)(1.0 / std::sqrt((double)p->block))};
     dispatch_big<LaunchBigInvHi>(pl.L - LOG_BIG, h, pl.split, hi.mode == 0 ? 0 : hi.bf16 ? 2 : 1, W, s);
     return;
   }
@@ -444,7 +449,7 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
   run_mids(pl, wsx, len, W, s);
   hi.x = wsx;
   hi.d = len;
-  hi.last_first = hi.mode == 1 && last_first(pl, len, W, true, false);
+  hi.walk = walk_over(hi.mode == 1 && last_first(pl, len, W, true, false), tiles_of(len), W);
   hi.tm = pl.hi;
   hi.c = (float)(1.0 / std::sqrt((double)p->block));
   switch (pl.R) {   // blocks of 2^16 and more: 3 bits at least
@@ -708,15 +713,16 @@ void run_forward(const Forward& f) {
       launch_range(r, f.s);
     }
     if (big) {
-      BigQuantArgs bq{slot, q.range_M, q.packed, len, q.j0, q.b, q.g, q.round, q.worker, q.k0, q.k1, q.c,
-                      last_first(pl, len, f.W, f.efs != nullptr, true), {}};
+      BigQuantArgs bq{slot, q.range_M, q.packed, len, q.j0,
+                      walk_over(last_first(pl, len, f.W, f.efs != nullptr, true), len >> LOG_BIG, f.W), q.b, q.g, q.round,
+                      q.worker, q.k0, q.k1, q.c, {}};
       std::memcpy(bq.lut, q.lut, sizeof q.lut);
       dispatch_big<LaunchBigQuant>(pl.L - LOG_BIG, bq, pl.split, f.W, f.s);
     } else {
       run_mids(pl, slot, len, f.W, f.s);
       q.x = slot;
       q.d = len;
-      q.last_first = last_first(pl, len, f.W, f.efs != nullptr, false);
+      q.walk = walk_over(last_first(pl, len, f.W, f.efs != nullptr, false), tiles, f.W);
       q.partials = find ? a.partials : nullptr;
       q.pstride = a.pstride;
       q.range_out = find ? f.range_out + x0 / p->block : nullptr;
@@ -1043,8 +1049,9 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.tm = lo_tilemap(pl, p->d);
     launch_fwd_lo(pl, a, bf16, ef != nullptr, false, tiles_of(p->d), p->n, s);
     run_mids(pl, static_cast<float*>(ws), p->d, p->n, s);
-    const HiMinMaxArgs h{static_cast<float*>(ws), pmin, pmax, p->d, p->d >> pl.L1, pl.hi, (uint32_t)pl.L,
-                        (float)(1.0 / std::sqrt((double)p->block)), last_first(pl, p->d, p->n, false, false)};
+    const HiMinMaxArgs h{static_cast<float*>(ws), pmin, pmax, p->d,
+                        walk_over(last_first(pl, p->d, p->n, false, false), tiles_of(p->d), p->n), pl.hi, (uint32_t)pl.L,
+                        (float)(1.0 / std::sqrt((double)p->block))};
     dispatch_0_9<LaunchHiMinMax>(pl.R, h, tiles_of(p->d), p->n, s);
   } else {
     MinMaxArgs a{};

@@ -263,8 +263,8 @@ __device__ __forceinline__ void slot_swap(float (&v)[8][8]) {
 // update of 2^22-point blocks in the split order: 2^29 worker-coordinates in bf16 1432 -> 1402 us, in binary32 729 -> 718.
 // Elsewhere no choice was better throughout (R = 9 gains 2 to 9 % with error feedback and loses 3 % without).
 template <int R, bool XO, bool EF>
-__device__ __forceinline__ uint32_t big_hi_tile(uint32_t last_first) {
-  return xcd_tile<R == 10 ? 6 : R == 7 && XO && EF ? 4 : 3>(walk_x(last_first), gridDim.x);
+__device__ __forceinline__ uint32_t big_hi_tile(const Walk& w) {
+  return xcd_tile<R == 10 ? 6 : R == 7 && XO && EF ? 4 : 3>(walk_x(w), gridDim.x);
 }
 
 template <int R, bool XO>
@@ -344,10 +344,10 @@ struct BigQuantArgs {
   PtrArr packed;
   uint64_t d;
   uint64_t j0;
+  Walk walk;
   uint32_t b, g;
   uint32_t round, worker, k0, k1;
   float c;
-  uint32_t last_first;
   uint32_t lut[256];
 };
 
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_quant(const BigQuantArgs a) {
   __shared__ SmemBigHi sm;
   uint4* const lut = reinterpret_cast<uint4*>(sm.lut);
   const int t = threadIdx.x;
-  const uint32_t vec = walk_y(a.last_first), tile = big_hi_tile<R, XO, false>(a.last_first);
+  const uint32_t vec = walk_y(a.walk), tile = big_hi_tile<R, XO, false>(a.walk);
   const uint64_t base = big_hi_base<R, XO>(tile);
   const uint32_t ent = a.lut[t & 255];   // requested before the tile, so that the table is made while that travels
   float v[8][8];
@@ -526,9 +526,9 @@ struct BigInvHiArgs {
   PtrArr grad;
   uint64_t d;
   uint64_t j0;
+  Walk walk;
   uint32_t round, k0, k1;
   float c;
-  uint32_t last_first;
 };
 
 struct alignas(16) SmemBigInvHi {
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
   using H = BigHi<R>;
   __shared__ SmemBigInvHi sm;
   const int t = threadIdx.x;
-  const uint32_t vec = walk_y(a.last_first), tile = big_hi_tile<R, XO, EFM != 0>(a.last_first);
+  const uint32_t vec = walk_y(a.walk), tile = big_hi_tile<R, XO, EFM != 0>(a.walk);
   const uint64_t base = big_hi_base<R, XO>(tile);
   float v[8][8];
   big_hi_load<R, XO>(a.x + (uint64_t)vec * a.d + base, t, v);

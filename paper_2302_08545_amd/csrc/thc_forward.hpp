@@ -502,12 +502,12 @@ struct QuantArgs {
   PtrArr packed;           // per worker of the launch: d*b/8 bytes, written
   uint64_t d;
   uint64_t j0;             // global coordinate of x[0] (a multiple of B): the random streams are indexed globally
+  Walk walk;
   TileMap tm;
   uint32_t L;              // log2 B
   uint32_t b, g;
   uint32_t round, worker, k0, k1;   // worker: id of the launch's first worker (selects the rounding stream)
   float c;                 // 1/sqrt(B)
-  uint32_t last_first;     // order of the walk over the tiles
   uint32_t lut[256];       // per grid cell k: lo | wd << 8 | z0 << 16
   // only where the pass finds the range itself (FIND): what k_range would be given, and where M goes
   const double* partials;
@@ -752,7 +752,8 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
 template <int R, bool CFOLD, bool FIND>
 __global__ __launch_bounds__(NT, 8) void k_fwd_hi_quant(const QuantArgs a) {
   __shared__ SmemQuant<R> sm;
-  const uint32_t tile = walk_x(a.last_first), vec = walk_y(a.last_first);
+  // a launch that finds the range is too small to be walked backwards
+  const uint32_t tile = FIND ? blockIdx.x : walk_x(a.walk), vec = FIND ? blockIdx.y : walk_y(a.walk);
   const float* const xw = a.x + (uint64_t)vec * a.d;
   if constexpr (FIND) {
     __shared__ FindSmem smr;

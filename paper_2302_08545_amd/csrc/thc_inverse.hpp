@@ -240,11 +240,11 @@ struct InvHiArgs {
   PtrArr grad;         // per vector, mode 1 only
   uint64_t d;
   uint64_t j0;         // global coordinate of x[0] (a multiple of B), for the diagonal's random stream
+  Walk walk;
   TileMap tm;
   uint32_t round, k0, k1;
   uint32_t mode, bf16;
   float c;
-  uint32_t last_first;
 };
 
 // scale by 1/sqrt(B) and apply the diagonal; mode 1: (x + e) - that
@@ -331,7 +331,7 @@ __device__ __forceinline__ void inv_hi_tile(const A& a, uint32_t tile, uint32_t 
 template <int R>
 __global__ __launch_bounds__(NT) void k_inv_hi(const InvHiArgs a) {
   __shared__ SmemInvHi sm;
-  const uint32_t tile = walk_x(a.last_first), vec = walk_y(a.last_first);
+  const uint32_t tile = walk_x(a.walk), vec = walk_y(a.walk);
   inv_hi_tile<R>(a, tile, vec, a.x + (uint64_t)vec * a.d, sm);
 }
 

@@ -103,25 +103,27 @@ __global__ __launch_bounds__(64) void k_minmax_final(const MinMaxFinalArgs a) {
 // would cost twice the bytes of reading the half-rotated one a second time.
 struct HiMinMaxArgs {
   const float* x;    // half-rotated vectors, d floats per worker of the launch (grid.y)
-  float* pmin;       // partial minima, `pstride` = d >> L1 floats per worker
+  float* pmin;       // partial minima, one per tile or smaller block: d >> min(L, 13) floats per worker
   float* pmax;
-  uint64_t d, pstride;
+  uint64_t d;
+  Walk walk;
   TileMap tm;
   uint32_t L;
   float c;
-  uint32_t last_first;
 };
+static_assert(sizeof(HiMinMaxArgs) <= 128, "a third cache line of arguments takes a small launch 0.2 us");
 
 template <int R>
 __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
   __shared__ __align__(16) float lds[R < 2 ? 4 : TILE];
   __shared__ float smin[16], smax[16];
-  const uint32_t tile = walk_x(a.last_first), vec = walk_y(a.last_first);
+  const uint32_t tile = walk_x(a.walk), vec = walk_y(a.walk);
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const HiGeom<R> g(tile, a.tm);
   const float* const x = a.x + (uint64_t)vec * a.d;
-  float* const pmin = a.pmin + (uint64_t)vec * a.pstride;
-  float* const pmax = a.pmax + (uint64_t)vec * a.pstride;
+  const uint64_t part = (uint64_t)vec * (a.d >> (a.L < LOG_TILE ? a.L : LOG_TILE));
+  float* const pmin = a.pmin + part;
+  float* const pmax = a.pmax + part;
   if constexpr (R >= 2) {
     hi_front<R>(x, g, lds, t);
     int idx[2];
