@@ -739,6 +739,19 @@ void run_forward(const Forward& f) {
   });
 }
 
+template <bool BF16, int G>
+void launch_uniform_quant_g(const UQuantArgs& q, bool ef, hipStream_t s) {
+  const dim3 grid((unsigned)((q.d + (G << LOG_UTILE) - 1) / (G << LOG_UTILE))), blk(NT);
+  if (ef) k_uniform_quant<BF16, true, G><<<grid, blk, 0, s>>>(q);
+  else k_uniform_quant<BF16, false, G><<<grid, blk, 0, s>>>(q);
+}
+
+template <bool BF16>
+void launch_uniform_quant(const UQuantArgs& q, bool ef, bool one_group, hipStream_t s) {
+  if (one_group) launch_uniform_quant_g<BF16, 1>(q, ef, s);
+  else launch_uniform_quant_g<BF16, 2>(q, ef, s);
+}
+
 // ---- scratch of the entry point that allocates nothing -------------------------------------------------------
 // One array per GPU the library's code object is loaded on, held until the process ends.  Its name is a host-side
 // stand-in: the device address comes from hipGetSymbolAddress, once per device, with that device current.
@@ -1114,7 +1127,7 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
     q.k0 = k0;
     q.k1 = k1;
     fill_lut(p, q.lut);
-    const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
+    const bool bf16 = p->in_dtype == THC_DTYPE_BF16, one = uniform_one_group(p->d, bf16, ef_inout != nullptr);
     for_pieces(p->d, [&](uint64_t x0, uint64_t len) {
       q.grad = static_cast<const char*>(grad) + x0 * (bf16 ? 2 : 4);
       q.ef = ef_inout ? ef_inout + x0 : nullptr;
@@ -1123,14 +1136,8 @@ int thc_uniform_compress(const thc_params* p, uint32_t worker_id, uint64_t round
       q.packed = packed_out + x0 / 8 * p->b;
       q.d = len;
       q.j0 = base_coord(p) + x0;
-      const dim3 grid((unsigned)((len + UTILE - 1) >> LOG_UTILE)), blk(NT);
-      if (bf16) {
-        if (ef_inout) k_uniform_quant<true, true><<<grid, blk, 0, s>>>(q);
-        else k_uniform_quant<true, false><<<grid, blk, 0, s>>>(q);
-      } else {
-        if (ef_inout) k_uniform_quant<false, true><<<grid, blk, 0, s>>>(q);
-        else k_uniform_quant<false, false><<<grid, blk, 0, s>>>(q);
-      }
+      if (bf16) launch_uniform_quant<true>(q, ef_inout != nullptr, one, s);
+      else launch_uniform_quant<false>(q, ef_inout != nullptr, one, s);
     });
   }
   if (rotate && ef_inout) {

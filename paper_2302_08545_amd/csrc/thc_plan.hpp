@@ -227,6 +227,20 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
   return W * len > (1ull << (ef ? 25 : 26)) && (!big || pl.L == 25);
 }
 
+// Uniform quantizer on a vector of d coordinates: one group of eight coordinates to a thread, 4096 to a workgroup, or two.
+// One group / two, us:
+//   error feedback, binary32: 2^18 4.0 / 4.3, 2^20 4.7 / 4.8, 2^21 6.2 / 5.8, 6 * 2^20 14.6 / 13.7, 2^24 33.1 / 32.0, 25 * 2^20
+//     48.5 / 48.5, 2^28 605 / 584 (2^25 to 40 * 2^20, called again and again on the same vector, 64 / 65 and 79 / 84);
+//   bf16: 2^20 4.7 / 4.9, 2^21 6.0 / 5.8, 6 * 2^20 13.0 / 10.8, 25 * 2^20 43.4 / 41.6, 2^28 512 / 496 (48 and 56 * 2^20, again and
+//     again, 81 / 85 and 99 / 106);
+//   without it, binary32: 2^20 3.3 / 3.9, 2^22 4.8 / 4.9, 6 * 2^20 6.2 / 5.8, 12 * 2^20 12.3 / 11.3, 2^24 14.9 / 14.6, 25 * 2^20
+//     20.5 / 20.7, 2^26 55.8 / 57.4, 2^28 214 / 221;
+//   bf16: 2^20 3.4 / 3.8, 12 * 2^20 10.4 / 9.9, 2^24 12.3 / 12.3, 2^28 181 / 189.
+inline bool uniform_one_group(uint64_t d, bool bf16, bool ef) {
+  if (ef) return d <= 1ull << 20;
+  return bf16 || d <= 1ull << 22 || d > 1ull << 24;
+}
+
 // Kernels that take a whole vector, one launch after another of at most LAUNCH_COORDS coordinates (whole blocks): a launch
 // holds fewer than 2^32 threads, which at eight coordinates a thread is 2^35, a bf16 vector of 64 GB.
 constexpr uint64_t LAUNCH_COORDS = 1ull << 34;

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
   }
 }
 
-// Uniform stochastic quantization of one worker's vector: 4096 consecutive coordinates per workgroup.
+// Uniform stochastic quantization of one worker's vector: 4096 or 8192 consecutive coordinates per workgroup.
 // Without rotation only, so that the error-feedback update e <- x - (m + z (M-m)/g) is done here.
 struct UQuantArgs {
   const void* grad;
@@ -202,34 +202,40 @@ struct UQuantArgs {
   uint32_t lut[256];
 };
 
-// What bounds it: bytes (12.5 a coordinate with error feedback), as long as a workgroup asks for them at once: the grid-cell
-// table first, then the thread's eight coordinates, and the range and the table are prepared while those travel.  One
-// group of eight to a thread is what fits 64 registers with error feedback, hence four workgroups a compute unit (with two
-// groups 10 registers spill and the round below takes 924 us).  Eight vectors of 25 * 2^20 with error feedback: 61.6 ->
-// 60.5 us each, 5.4 TB/s, the round 839 -> 833 us.
-constexpr int LOG_UTILE = 12, UTILE = 1 << LOG_UTILE;
+constexpr int LOG_UTILE = 12;   // coordinates of a workgroup, a group to a thread
 
-template <bool BF16, bool EF>
-__global__ __launch_bounds__(NT, 8) void k_uniform_quant(const UQuantArgs a) {
+// What bounds it: bytes (12.5 a coordinate with error feedback) and, in small calls, latency.  With one group of eight
+// coordinates to a thread (G = 1) the workgroup asks for all it needs at once, the grid-cell table first, and prepares range
+// and table while that travels; it fits 64 registers, hence four workgroups a compute unit.  With two groups (G = 2) tables
+// serve twice as many coordinates, and the groups go one after the other (both requested at once spill 10 registers: 924
+// us for eight vectors of 25 * 2^20 with error feedback, which take 61 us each, 5.3 TB/s).  Which call takes which:
+// uniform_one_group.
+template <bool BF16, bool EF, int G>
+__global__ __launch_bounds__(NT, G == 1 ? 8 : 1) void k_uniform_quant(const UQuantArgs a) {
+  constexpr int LOG = LOG_UTILE + G - 1, T = 1 << LOG;
   __shared__ uint4 lut[256];
-  __shared__ QuantScalars sQ[UTILE >> 10];
-  __shared__ int sCare[UTILE >> 10];
-  __shared__ float sStep[UTILE >> 10];
-  const int t = threadIdx.x, idx = 8 * t;
-  const uint64_t off = (uint64_t)xcd_tile<4>(blockIdx.x, gridDim.x) << LOG_UTILE;
-  const uint64_t j = off + idx;
-  const uint64_t from = j < a.d ? j : off;   // past the end: read from the tile's own start, not used
-  const uint32_t ent = a.lut[t & 255];
+  __shared__ QuantScalars sQ[T >> 10];
+  __shared__ int sCare[T >> 10];
+  __shared__ float sStep[T >> 10];
+  const int t = threadIdx.x;
+  const uint64_t off = (uint64_t)xcd_tile<5 - G>(blockIdx.x, gridDim.x) << LOG;
   float4 x[2], e[2];
-  __builtin_amdgcn_sched_barrier(0);
+  auto load = [&](uint64_t at) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    x[k] = load_grad4<BF16>(a.grad, from + 4 * k);
-    if constexpr (EF) e[k] = *reinterpret_cast<const float4*>(a.ef + from + 4 * k);
+    for (int k = 0; k < 2; ++k) {
+      x[k] = load_grad4<BF16>(a.grad, at + 4 * k);
+      if constexpr (EF) e[k] = *reinterpret_cast<const float4*>(a.ef + at + 4 * k);
+    }
+  };
+  const uint64_t j = off + 8 * t, from = j < a.d ? j : off;   // past the end: read from the tile's own start, not used
+  const uint32_t ent = a.lut[t & 255];
+  if constexpr (G == 1) {
+    __builtin_amdgcn_sched_barrier(0);
+    load(from);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  __builtin_amdgcn_sched_barrier(0);
   if (t < 256) lut[t] = quant_lut_entry(ent);
-  const int nblk = a.L < LOG_UTILE ? (UTILE >> a.L) : 1;
+  const int nblk = a.L < LOG ? (T >> a.L) : 1;
   if (t < nblk) {
     const uint64_t blk = (off >> a.L) + t;
     float M = 0.f, m = 0.f;
@@ -240,28 +246,41 @@ __global__ __launch_bounds__(NT, 8) void k_uniform_quant(const UQuantArgs a) {
     sStep[t] = (float)(((double)M - (double)m) / (double)a.g);
   }
   __syncthreads();
-  if (j >= a.d) return;
-  float hv[8];
+  auto group = [&](int idx, uint64_t j) {
+    float hv[8];
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    if constexpr (EF) { x[k].x += e[k].x; x[k].y += e[k].y; x[k].z += e[k].z; x[k].w += e[k].w; }
-    hv[4 * k] = x[k].x; hv[4 * k + 1] = x[k].y; hv[4 * k + 2] = x[k].z; hv[4 * k + 3] = x[k].w;
-  }
-  const int bt = a.L < LOG_UTILE ? (idx >> a.L) : 0;
-  const QuantScalars s = sQ[bt];
-  const uint64_t q = (a.j0 + j) >> 3;
-  const uint4 rnd = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, a.worker, a.k0, a.k1);
-  uint32_t z[8];
-  if (!sCare[bt]) quantize8<false>(hv, rnd, s, lut, z);   // no scaling: the values are final (c = 1)
-  else quantize8<false, true>(hv, rnd, s, lut, z);
-  store_packed8(a.packed, j, a.b, z);
-  if constexpr (EF) {
-    const float step = sStep[bt], lo = s.lo;
-    float r[8];
+    for (int k = 0; k < 2; ++k) {
+      if constexpr (EF) { x[k].x += e[k].x; x[k].y += e[k].y; x[k].z += e[k].z; x[k].w += e[k].w; }
+      hv[4 * k] = x[k].x; hv[4 * k + 1] = x[k].y; hv[4 * k + 2] = x[k].z; hv[4 * k + 3] = x[k].w;
+    }
+    const int bt = a.L < LOG ? (idx >> a.L) : 0;
+    const QuantScalars s = sQ[bt];
+    const uint64_t q = (a.j0 + j) >> 3;
+    const uint4 rnd = philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), a.round, a.worker, a.k0, a.k1);
+    uint32_t z[8];
+    if (!sCare[bt]) quantize8<false>(hv, rnd, s, lut, z);   // no scaling: the values are final (c = 1)
+    else quantize8<false, true>(hv, rnd, s, lut, z);
+    store_packed8(a.packed, j, a.b, z);
+    if constexpr (EF) {
+      const float step = sStep[bt], lo = s.lo;
+      float r[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] = hv[k] - ((float)z[k] * step + lo);   // identity table: T[z] = z
-    *reinterpret_cast<float4*>(a.ef + j) = make_float4(r[0], r[1], r[2], r[3]);
-    *reinterpret_cast<float4*>(a.ef + j + 4) = make_float4(r[4], r[5], r[6], r[7]);
+      for (int k = 0; k < 8; ++k) r[k] = hv[k] - ((float)z[k] * step + lo);   // identity table: T[z] = z
+      *reinterpret_cast<float4*>(a.ef + j) = make_float4(r[0], r[1], r[2], r[3]);
+      *reinterpret_cast<float4*>(a.ef + j + 4) = make_float4(r[4], r[5], r[6], r[7]);
+    }
+  };
+  if constexpr (G == 1) {
+    if (j >= a.d) return;
+    group(8 * t, j);
+  } else {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const int idx = 8 * (t + NT * h);
+      if (off + idx >= a.d) continue;
+      load(off + idx);
+      group(idx, off + idx);
+    }
   }
 }
 

@@ -247,6 +247,11 @@ int main() {
   bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
   bad += check_xcd_tile<2>() + check_xcd_tile<3>() + check_xcd_tile<4>() + check_xcd_tile<6>();
   bad += check_whole_route() + check_inv_whole_14() + check_last_first();
+  // the uniform quantizer's groups of coordinates: the limits, and that bf16 without error feedback has none
+  for (bool bf16 : {false, true}) bad += !uniform_one_group(1 << 20, bf16, true) || uniform_one_group((1 << 20) + 1024, bf16, true);
+  bad += !uniform_one_group(1 << 22, false, false) || uniform_one_group((1 << 22) + 1024, false, false);
+  bad += uniform_one_group(1 << 24, false, false) || !uniform_one_group((1 << 24) + 1024, false, false);
+  for (uint64_t d : {1ull << 10, 1ull << 23, 1ull << 34}) bad += !uniform_one_group(d, true, false);
   // largest number of workgroups at which the quantizer finds the range itself (where whole_route leaves it to the passes:
   // from 2^15 on, in 2^14, and up to 2^13 with more than four workers)
   const struct { int L; uint32_t W; uint64_t most; } find[] = {

@@ -51,8 +51,37 @@ def test_uniform_round_with_error_feedback_on_small_rotated_blocks(log2_block, b
 @pytest.mark.parametrize("block,K,b,bf16", [(1 << 10, 1, 4, True), (1 << 10, 5, 3, True), (1 << 11, 3, 4, False),
                                             (1 << 13, 3, 4, True), (1 << 16, 2, 8, True)])
 def test_uniform_round_with_error_feedback_without_rotation(block, K, b, bf16):
-    """Tiles of 4096 coordinates, the last one partly empty in the first three rows."""
+    """Small vectors: tiles of 4096 coordinates, the last one partly empty in the first three rows."""
     _uniform_round(block, K, 2, b, 16, True, 3, False, bf16=bf16)
+
+
+@pytest.mark.parametrize("K,bf16,ef", [(1024, False, True), (1025, False, True), (1025, True, True), (4096, False, False),
+                                       (4097, False, False), (16384, False, False), (16385, False, False)])
+def test_quantizer_of_one_group_of_coordinates_a_thread_or_two(K, bf16, ef):
+    """Either side of the limits of uniform_one_group: the whole vector against its slices of at most 21 blocks, which take
+    one group, bit for bit; both leave the last tile partly empty."""
+    block, b = 1 << 10, 3
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    x = torch.randn(K * block, device=DEV, generator=gen) * 1e-3
+    x = x.to(torch.bfloat16) if bf16 else x
+    e0 = torch.randn(K * block, device=DEV, generator=gen) * 2e-4 if ef else None
+    rm = torch.rand(K, generator=gen, device=DEV) * -2e-3 - 1e-3
+    rM = torch.rand(K, generator=gen, device=DEV) * 2e-3 + 1e-3
+
+    def compress(first, k):
+        at = slice(first * block, (first + k) * block)
+        packed = torch.zeros(k * block * b // 8, dtype=torch.uint8, device=DEV)
+        e = e0[at].clone() if ef else None
+        _, L = uparams(k * block, block, 2, b, 8, bf16=bf16, first_block=first)
+        api.thc_uniform_compress(L, 1, 5, x[at].clone(), e, False, rm[first:first + k].clone(), rM[first:first + k].clone(), packed,
+                                 None)
+        return packed, e
+
+    packed, e = compress(0, K)
+    for first, k in ((0, 16), (K // 2, 21), (K - 21, 21), (K - 1, 1)):
+        p, q = compress(first, k)
+        assert torch.equal(p, packed[first * block * b // 8:(first + k) * block * b // 8])
+        assert not ef or torch.equal(q, e[first * block:(first + k) * block])
 
 
 def _uniform_round(block, K, n, b, agg_bits, ef, first_block, rotate, order=0, bf16=False):
