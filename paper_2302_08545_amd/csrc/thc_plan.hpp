@@ -187,14 +187,25 @@ inline Whole whole_route(const Plan& pl, uint64_t tiles, uint32_t W, bool ef, bo
 }
 
 // Blocks of 2^14, inverse transform in one launch: a block to a workgroup of 1024 threads (k_inv_whole) or two blocks to
-// one of 512 (k_big_inv_whole).  With few blocks the first has half the work on each of twice the compute units: 8-bit sums
-// of 2 to 64 blocks 9.1 to 9.8 -> 6.2 to 6.6 us, 256 blocks 11.4 -> 8.7, 600 16.4 -> 14.6, 4096 67 -> 61, 16384 241 -> 223;
-// 16-bit sums of 1 to 16384 blocks 7.7 to 291 -> 6.1 to 268.  At 768 and 1024 blocks, where the second fills the chip
-// exactly, 16.4 -> 16.2 and 18.2 -> 19.8 (9-bit sums 17.4 -> 18.0 and 19.6 -> 21.9; 16-bit 20.6 -> 17.0, 22.4 -> 21.1).
-// With error feedback, which only the rotated uniform variant still has here, the second.
+// one of 512 (k_big_inv_whole).  With few blocks the first has half the work on each of twice the compute units; 512 of its
+// workgroups are on the chip at once, and 1024 of the other's, which is why neither is better throughout.  Time of the first
+// over that of the second, by the number of blocks:
+//   8-bit sums   0.63 to 0.95 up to 512, 0.96 at 704, 1.00 at 768, 1.08 at 1024, 0.90 to 0.99 from 1040 to 1792, 1.01 to 1.06 at
+//                2048, 2304, 2560, 3072 and 3584 (3328 0.95), 0.95 to 0.99 from 3840 to 6144, 1.02 to 1.04 from 8192 on
+//   4 bits       the same up to 1792, 1.00 to 1.04 from 2048 to 3584, 0.92 to 0.94 from 3840 on
+//   5, 9 and 12  0.61 to 0.96 up to 512, 0.99 to 1.01 at 640, 1.02 to 1.03 at 704, 1.09 to 1.13 at 1024, 0.89 to 0.95 from 1040 to
+//                1280, 1.01 to 1.04 to 1536, 0.97 to 1.00 at 1664 and 1792, 1.02 to 1.10 at 2048 to 2560, 0.97 to 1.08 at 3072
+//                and 0.90 to 1.06 at 3328, 0.92 to 1.00 from 3584 to 8192; beyond that 5 bits 0.93, 9 bits 0.99, 12 bits 1.00 to 1.02
+//   16 bits      the first always; the second has no form of its own for them
+// With error feedback the second: the rotated uniform variant, and thc_compress_all where whole_route leaves it to the passes.
 inline bool inv_whole_14(uint64_t len, bool ef, uint32_t bits) {
   const uint64_t K = len >> 14;
-  return !ef && (bits == 16 || K <= 704 || K > 1024);
+  if (ef) return false;
+  if (bits == 16) return true;
+  const bool even = bits == 4 || bits == 8;
+  if (K <= 1024) return K <= (even ? 704 : 640);
+  if (K <= 3584) return K <= (even ? 1792 : 1280);
+  return bits < 8 || K <= (bits == 8 ? 6144 : 12288);
 }
 
 // Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of

@@ -167,11 +167,15 @@ static int check_whole_route() {
 static int check_inv_whole_14() {
   auto one = [](uint64_t K, bool ef, uint32_t bits) { return inv_whole_14(K << 14, ef, bits); };
   int bad = 0;
-  for (uint32_t bits : {1u, 4u, 8u, 9u, 15u}) {
-    bad += !one(1, false, bits) || !one(704, false, bits) || one(705, false, bits) || one(1024, false, bits) ||
-           !one(1025, false, bits);
+  for (uint32_t bits : {1u, 4u, 5u, 8u, 9u, 15u}) {
+    const bool even = bits == 4 || bits == 8;
+    const uint64_t a = even ? 704 : 640, b = even ? 1792 : 1280;
+    bad += !one(1, false, bits) || !one(a, false, bits) || one(a + 1, false, bits) || one(1024, false, bits);
+    bad += !one(1025, false, bits) || !one(b, false, bits) || one(b + 1, false, bits) || one(3584, false, bits);
+    bad += !one(3585, false, bits) || !one(6144, false, bits) || one(6145, false, bits) != (bits != 8);
+    bad += one(12288, false, bits) != (bits != 8) || one(12289, false, bits) != (bits < 8);
   }
-  for (uint64_t K : {1ull, 704ull, 705ull, 1024ull, 1025ull, 16384ull})
+  for (uint64_t K : {1ull, 704ull, 705ull, 1024ull, 1025ull, 2048ull, 16384ull})
     bad += !one(K, false, 16) || one(K, true, 4) || one(K, true, 8);
   return bad;
 }

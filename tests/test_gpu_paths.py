@@ -290,12 +290,13 @@ def test_worker_side_of_more_than_2_to_the_36_coordinates(every_call):
         assert_indices_match(packed[k * block // 8:(k + 1) * block // 8].cpu().numpy(), ref, 1, f"block {k}")
 
 
-@pytest.mark.parametrize("K,agg_bits", [(1, 8), (3, 9), (704, 8), (705, 8), (705, 9), (705, 16), (1024, 9), (1025, 8)])
+@pytest.mark.parametrize("K,agg_bits", [(1, 8), (3, 9), (704, 8), (705, 8), (705, 9), (705, 16), (1024, 9), (1025, 8), (640, 5),
+                                        (641, 5), (1280, 9), (1281, 9), (1792, 4), (1793, 4), (3584, 12), (3585, 12), (6145, 8)])
 def test_inverse_of_2_to_the_14_by_one_block_or_two_a_workgroup(K, agg_bits):
-    """Both kernels give the same bits: the whole vector against its slices of at most eight blocks, which lie on the other
-    side of the rule (705 to 1024 blocks) where the whole is inside it; block 0 and the last one against the oracle."""
-    block = 1 << 14
-    P, L = both_params(block * K, block, 1, agg_bits=agg_bits)
+    """Both kernels give the same bits: the whole vector against its slices of at most eight blocks, which take one block a
+    workgroup, on either side of the rule's limits; block 0 and the last one against the oracle."""
+    block, g = 1 << 14, 15 if agg_bits < 5 else 30
+    P, L = both_params(block * K, block, 1, g=g, agg_bits=agg_bits)
     R = GpuRound(L)
     gen = torch.Generator(device=DEV).manual_seed(K)
     R.agg.copy_(torch.randint(0, 256, R.agg.shape, generator=gen, device=DEV, dtype=torch.uint8))
@@ -303,7 +304,7 @@ def test_inverse_of_2_to_the_14_by_one_block_or_two_a_workgroup(K, agg_bits):
     R.decompress(11)
     for k in range(0, K, max(8, K // 5)):
         n = min(8, K - k)
-        _, S = both_params(block * n, block, 1, agg_bits=agg_bits)
+        _, S = both_params(block * n, block, 1, g=g, agg_bits=agg_bits)
         S.first_block = k
         Q = GpuRound(S)
         Q.agg.copy_(R.agg[k * block // 8 * agg_bits:(k + n) * block // 8 * agg_bits])
