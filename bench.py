@@ -48,6 +48,20 @@ def profiled_kernel(workload_name, prefix):
     return m.group(1), int(m.group(2)) / int(rounds.group(1)), float(m.group(4))
 
 
+def forward_kernels(w, calls, single_launch):
+    """What thc_compress_all (or the calls in its place) runs for this workload: the text of the roofline object."""
+    L = w.block.bit_length() - 1
+    if calls != "all":
+        return "thc_prepare_range + n x thc_compress"
+    if single_launch and 17 <= L <= 22 and w.K >= 4:
+        return "k_pipe_forward (thc_compress_all, single launch)"
+    if L <= 14:
+        return "thc_compress_all: block by block (k_fwd_lo for the norms, k_range_small, k_whole)"
+    return ("thc_compress_all: forward passes (k_fwd_lo / k_big_lo, k_range, k_fwd_hi_quant / k_big_quant)"
+            + ("" if not w.ef else " and inverse passes (error feedback)" if L > 15 else " and one inverse pass (error feedback)")
+            + " per group of blocks")
+
+
 # ---------------------------------------------------------------------------------------------- oracle baseline
 def _oracle_block_round(task):
     """One full round of the oracle on one block of all n workers (blocks are independent THC instances)."""
@@ -300,14 +314,11 @@ def main():
         "effective_hbm_GBps": bpc * w.d / per_step / 1e9,
         "effective_hbm_frac": bpc * w.d / per_step / 1e9 / HBM_PEAK_GBPS,
         "compulsory_bytes_per_coord": bpc,
-        # what two-pass transforms move between the L2s and memory or its cache, over the same time
-        "moved_bytes_per_coord": wl.moved_bytes_per_coord(w),
-        "moved_GBps": wl.moved_bytes_per_coord(w) * w.d / per_step / 1e9,
+        # what the passes move between the L2s and memory or its cache, over the same time
+        "moved_bytes_per_coord": wl.moved_bytes_per_coord(w, args.calls),
+        "moved_GBps": wl.moved_bytes_per_coord(w, args.calls) * w.d / per_step / 1e9,
         "stage_ms": stage_ms,
-        "roofline": {"bound": "hbm", "kernel": ("k_pipe_forward (thc_compress_all, single launch)" if args.single_launch else
-                                "thc_compress_all: forward passes (k_fwd_lo / k_big_lo, k_range, k_fwd_hi_quant / k_big_quant)"
-                                + (" and inverse passes (error feedback)" if w.ef else "") + " per group of blocks")
-                     if args.calls == "all" else "thc_prepare_range + n x thc_compress", "achieved": achieved,
+        "roofline": {"bound": "hbm", "kernel": forward_kernels(w, args.calls, args.single_launch), "achieved": achieved,
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
                      "algorithmic_bytes": fwd_alg_bytes, "launch_ms": fwd_ms,
                      "traffic": measured_traffic(w.name) if default_config else None},

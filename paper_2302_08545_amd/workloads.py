@@ -162,17 +162,25 @@ def bytes_per_coord(w: Workload) -> float:
     return comp + agg + dec
 
 
-def moved_bytes_per_coord(w: Workload) -> float:
+def moved_bytes_per_coord(w: Workload, calls: str = "all") -> float:
     """HBM bytes per (padded) coordinate the kernels actually move in one full round: every pass of a transform
     reads and writes the vector once (rocprofv3's FETCH_SIZE / WRITE_SIZE read exactly this on the VGG16-shaped
     workload).  A transform of 2^L coordinates takes a first and a last pass, and above L = 25 one in between (8192-
     coordinate tiles do 13 bits, then up to 9, tiles of 2^15 do 15 and up to 10; above that 13 + 7 + 6 or 7).  Blocks of up
-    to 2^15 move less: their inverse is one pass, and up to 2^14 so is the worker side once the norms are known."""
+    to 2^15 take their inverse in one pass, and in calls that fill the GPU blocks of up to 2^14 take the worker side in one
+    pass behind one that only reads, for the norms.  calls = "each": thc_prepare_range reads the vectors for the norms at
+    any block size."""
     in_b = 4 if w.dtype == "f32" else 2
     L = w.block.bit_length() - 1
     mids = 1 if L > 25 else 0
-    fwd = (in_b + (4 if w.ef else 0) + 4) + 8 * mids + (4 + w.b / 8)
-    ef = (w.b / 8 + 4) + 8 * mids + (4 + in_b + 4 + 4) if w.ef else 0
+    x_b = in_b + (4 if w.ef else 0)                              # a vector, with its buffer
+    norms = x_b if L <= 14 or calls == "each" else 0
+    if L <= 14:
+        fwd = x_b + (4 if w.ef else 0) + w.b / 8
+        ef = 0
+    else:
+        fwd = (x_b + 4) + 8 * mids + (4 + w.b / 8)
+        ef = (w.b / 8 + x_b + 4 + (8 + 8 * mids if L > 15 else 0)) if w.ef else 0
     agg = w.n * w.b / 8 + w.agg_bits / 8
-    dec = (w.agg_bits / 8 + 4) + 8 * mids + (4 + 4)
-    return w.n * (fwd + ef) + agg + dec
+    dec = w.agg_bits / 8 + 4 + (8 + 8 * mids if L > 15 else 0)
+    return w.n * (norms + fwd + ef) + agg + dec

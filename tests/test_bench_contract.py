@@ -29,11 +29,28 @@ def test_compulsory_bytes_per_coordinate(w, want):
 @pytest.mark.parametrize("w,want", [(wl.C3, 8 * 12.5 + 5 + 13), (wl.C4_B4, 16 * 12.5 + 10 + 14),
                                     (wl.C2, 8 * (12 + 4.5 + 4.5 + 16) + 5 + 13),
                                     (wl.replace(wl.C2, block=1 << 26, d=1 << 26),
-                                     8 * (12 + 8 + 4.5 + 4.5 + 8 + 16) + 5 + (1 + 4 + 8 + 8))],
-                         ids=lambda x: getattr(x, "name", str(x)))
+                                     8 * (12 + 8 + 4.5 + 4.5 + 8 + 16) + 5 + (1 + 4 + 8 + 8)),
+                                    (wl.replace(wl.C3, block=1 << 13), 8 * (4 + 4.5) + 5 + 5),
+                                    (wl.replace(wl.C2, block=1 << 14), 8 * (8 + 12.5) + 5 + 5),
+                                    (wl.replace(wl.C3, block=1 << 15), 8 * 12.5 + 5 + 5),
+                                    (wl.replace(wl.C2, block=1 << 15), 8 * (12 + 4.5 + 12.5) + 5 + 5)],
+                         ids=lambda x: f"{x.name}-{x.block}" if isinstance(x, wl.Workload) else str(x))
 def test_moved_bytes_per_coordinate_of_the_pass_structure(w, want):
-    # two passes (three above 2^25), each reading and writing the vector once
+    # two passes (three above 2^25), each reading and writing the vector once; up to 2^15 one pass back, and up to 2^14 one
+    # pass forward behind one that reads for the norms
     assert wl.moved_bytes_per_coord(w) == want
+    again = 0 if w.block <= 1 << 14 else w.n * (4 + (4 if w.ef else 0))
+    assert wl.moved_bytes_per_coord(w, "each") == want + again
+
+
+def test_the_kernels_that_the_roofline_names_are_those_that_run():
+    small, ef15 = wl.replace(wl.C3, block=1 << 14), wl.replace(wl.C2, block=1 << 15)
+    assert "k_whole" in bench.forward_kernels(small, "all", False) and "k_fwd_hi_quant" not in bench.forward_kernels(small, "all", False)
+    assert "one inverse pass" in bench.forward_kernels(ef15, "all", False)
+    assert "inverse passes" in bench.forward_kernels(wl.C2, "all", False) and "inverse" not in bench.forward_kernels(wl.C3, "all", False)
+    assert "k_pipe_forward" in bench.forward_kernels(wl.C3, "all", True)
+    assert "k_whole" in bench.forward_kernels(small, "all", True)
+    assert bench.forward_kernels(wl.C3, "each", False) == "thc_prepare_range + n x thc_compress"
 
 
 def test_counted_traffic_of_the_default_workload_is_read_from_the_tracked_profile():
