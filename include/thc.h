@@ -11,8 +11,9 @@
  *   thc_decompress      worker side: m + (Y/n)(M-m)/g, then the inverse RHT
  *
  * and, for n workers whose buffers all live on one GPU, thc_compress_all does the work of thc_prepare_range and of
- * the n calls of thc_compress in one sweep that reads every gradient once (the paper runs the norm exchange and
- * the RHT side by side; here the norms come out of the transform's first pass).
+ * the n calls of thc_compress in one sweep.  For blocks of 2^15 and more it reads every gradient once (the paper runs the
+ * norm exchange and the RHT side by side; here the norms come out of the transform's first pass); blocks of up to 2^14 are
+ * mostly taken through the whole transform at once, with the norms read beforehand.
  *
  * Conventions
  *   - All data pointers are DEVICE pointers (hipMalloc'd, 16-byte aligned) unless a comment says "host".
@@ -89,9 +90,9 @@ typedef struct thc_params {
   uint8_t  table[256]; /* T[0 .. 2^b-1]; see thc_solve_table                                               */
   uint32_t stage_order;/* THC_ORDER_ASCENDING or THC_ORDER_SPLIT                                           */
   uint32_t first_block;/* index, in the whole vector, of the first block these buffers hold (0 for a whole vector) */
-  uint32_t group_log2; /* 0 = default (29).  The transform's passes walk a vector in groups of whole blocks of about
-                          2^group_log2 coordinates (over all vectors of the call), 10..40: it sizes the workspace
-                          (which therefore does not grow with d); never a result */
+  uint32_t group_log2; /* 0 = default (29).  Where a transform goes pass by pass, the passes walk a vector in groups of
+                          whole blocks of about 2^group_log2 coordinates (over all vectors of the call), 10..40: it
+                          sizes the workspace (which therefore does not grow with d); never a result */
   uint32_t single_launch; /* 0 or 1.  1: thc_compress and thc_compress_all run all passes of all blocks in ONE kernel
                           launch where they can (split stage order, blocks of 2^17 .. 2^22, at least four blocks,
                           group_log2 = 0), blocks following each other through a ring of a few block-sized slots: a
@@ -136,8 +137,11 @@ int thc_compress(const thc_params* p, uint32_t worker_id, uint64_t round, const 
                  float* ef_inout, const float* range_M, uint8_t* packed_out, void* ws, void* stream);
 
 /* All n workers of one GPU in one sweep: what thc_prepare_range followed by thc_compress(0 .. n-1) computes, bit for
- * bit, reading every gradient (and error-feedback buffer) once: block group by block group, the transform's first
- * pass of all workers (with the norms), the range, then the last pass and the quantizer of all workers.
+ * bit.  Blocks of 2^15 and more: block group by block group, the transform's first pass of all workers (with the norms),
+ * the range, then the last pass and the quantizer of all workers, every gradient (and error-feedback buffer) read once,
+ * and once more by the error-feedback update.  Blocks of up to 2^14: a pass that reads everything for the norms, then all
+ * the rest block by block; or, where that is faster, as above; or, in small calls of one or a few workers without error
+ * feedback, one launch in which every workgroup reads its blocks' gradients of all workers for the norms.
  *   grads       host array of n device pointers.         ef_inout    host array of n device pointers, or NULL.
  *   range_M     device, d/block floats, written.         packed_out  host array of n device pointers, written. */
 int thc_compress_all(const thc_params* p, uint64_t round, const void* const* grads /* host */,
@@ -205,8 +209,9 @@ int thc_uniform_decompress(const thc_params* p, uint64_t round, const void* agg,
 
 /* Introspection for tests and tools: how the Hadamard transform of these parameters is cut into passes over
  * HBM on tiles of 8192 coordinates, and how every pass tiles a block.  Blocks of 2^23 to 2^25, and of 2^22 in large
- * calls, run on tiles of 2^15 coordinates instead (the first 15 bits, then the rest, in the same stage order), and the
- * inverse transform of blocks of up to 2^15 in one pass; neither is described here, and neither changes a result, except
+ * calls, run on tiles of 2^15 coordinates instead (the first 15 bits, then the rest, in the same stage order), the
+ * inverse transform of blocks of up to 2^15 in one pass, and most calls on blocks of up to 2^14 block by block; none of
+ * these is described here, and none changes a result, except
  * that the rotated uniform variant's forward transform is always the one described.  Returns the number of passes
  * (2 or 3), or a negative status; with
  * out != NULL it also writes one record of THC_PLAN_RECORD_WORDS 32-bit words per pass (cap_records must be at

@@ -261,7 +261,8 @@ __device__ __forceinline__ void slot_swap(float (&v)[8][8]) {
 // bytes of each of their rows, and an XCD that takes 64 of them in a row fetches whole pages: 2^28 worker-coordinates with
 // error feedback 910 -> 867 us (ascending 928 -> 888), one vector 126 -> 117, the quantizer 287 -> 281.  The error-feedback
 // update of 2^22-point blocks in the split order: 2^29 worker-coordinates in bf16 1432 -> 1402 us, in binary32 729 -> 718.
-// Elsewhere no choice was better throughout (R = 9 gains 2 to 9 % with error feedback and loses 3 % without).
+// For the other widths the choice is that of the first pass.  (R = 9: tile bits further up gain 2 to 9 % with error feedback
+// and lose 3 % without; a choice by EF, as for R = 7, is not made there.)
 template <int R, bool XO, bool EF>
 __device__ __forceinline__ uint32_t big_hi_tile(const Walk& w) {
   return xcd_tile<R == 10 ? 6 : R == 7 && XO && EF ? 4 : 3>(walk_x(w), gridDim.x);

@@ -140,11 +140,12 @@ inline TileMap lo_tilemap(const Plan& pl, uint64_t len) {
 // 3 on the device.  Against that, every workgroup reads its block's partial sums over again, while its tile's loads travel.
 // Measured, first pass and quantizer with the range found there against a launch of its own (time of the first over the
 // second), by the workgroups of the launch:
-//   blocks of 2^17 to 2^20, up to 128 partial sums a worker: 1 to 4 workers 0.94 to 0.97 at 1024, 0.96 to 1.00 at 1280,
-//     0.98 to 1.01 at 1536, 1.04 to 1.08 at 4096; 8 and 16 workers 0.94 to 0.99 at 512 and 1024, 1.00 to 1.05 at 1280 to
-//     1536; 32 workers 0.97 at 512, 1.03 at 1024.
-//   blocks of up to 2^16, at most 8 partial sums a worker: 1 and 2 workers 0.90 to 0.98 at up to 2048, 0.97 to 1.01 at 3072
-//     and 4096; 4 workers 0.83 to 0.98 at up to 4096; 8 to 32 workers 0.38 to 0.98 at up to 4096.
+//   blocks of 2^17 to 2^20, up to 128 partial sums a worker: 1 to 4 workers 0.93 to 0.97 at 512 and 1024, 0.96 to 1.00 at 1280,
+//     0.98 to 1.02 at 1536; 8 workers 0.95 to 0.98 at 512 and 1024, 1.01 from 1280 on; 32 workers 0.96 at 512, 1.03 at 1024.
+//   blocks of up to 2^16, at most 8 partial sums a worker: 1 to 4 workers 0.88 to 0.95 at up to 1024, 0.96 to 0.98 at 2048,
+//     0.97 to 0.99 at 3072 and 3584, 0.98 to 1.01 at 4096; 8 workers 0.89 to 0.98 at up to 3072, 0.98 to 1.01 at 4096; 32
+//     workers 0.81 to 0.95 at up to 2048, 0.94 to 0.99 at 4096, 0.96 to 1.01 at 5120 and 6144.  With up to four workers
+//     another 1 to 3 % would be had up to 3584.
 // Blocks of 2^22 lose 2 % at 1024.
 inline bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {   // 8192-coordinate tiles of each of W vectors
   if (pl.L > 20) return false;
@@ -156,21 +157,24 @@ inline bool find_range(const Plan& pl, uint64_t tiles, uint32_t W) {   // 8192-c
 // and where the range comes from.
 //   GIVEN  range known (thc_compress): one launch instead of two, with error feedback three.  Faster at every size measured
 //          (2^15 to 2^28 worker-coordinates): 7.5 to 10.9 us -> 5.4 to 7.8 for small calls, 620 -> 290 for large ones.
-//   FIND   every workgroup adds up its block's squares of all workers: one launch, W times the reads.  One worker (no reads
-//          more): blocks of up to 2^13 8.1 to 52.7 us -> 6.5 to 45 at 4 to 3104 workgroups (of 8192 coordinates), 2^14
-//          11.8 -> 8.7 at 128, 18.3 -> 17.0 at 1024, 53.5 -> 57.5 at 3104.  2 and 4 workers 10.4 to 11.0 -> 7.6 to 9.4 at up
-//          to 128, 13.9 to 15.8 (NORMS) -> 11.7 to 13.6 at 512, 21 -> 26 at 1024 (8 workers: 10.4 to 12.5 -> 10.2 to 12.1 at
-//          up to 256, so no longer a gain); 2^14 with 4 workers 10.3 to 11.3 -> 11.1, and
-//          a launch less, which is what bounds such a round on the host: two blocks, 22 -> 19.7 us.
+//   FIND   every workgroup adds up its block's squares of all workers: one launch, W times the reads.  Time over that of the
+//          passes: one worker (no reads more) up to 2^13 0.80 to 0.85 at 4 to 3104 workgroups (of 8192 coordinates), 2^14 0.47
+//          to 0.79 at 512 to 1024, 1.00 at 1280.  2 and 4 workers up to 2^13 0.51 to 0.95 at up to 512; at 1024 0.70 to 0.91,
+//          with 4 workers behind NORMS; 8 workers no gain (10.4 to 12.5 -> 10.2 to 12.1 us at up to 256).  2^14 with 2 workers
+//          0.95 to 1.07 at up to 128, 0.50 to 0.76 at 256 to 512; with 3 and 4 1.08 to 1.22 at up to 192 (9.2 -> 11.2 us), and
+//          a launch less, which is what bounds such a round on the host: two blocks x 4 workers, rounds one after the other,
+//          21.7 -> 19.7 us.
 //   NORMS  a pass that keeps the sums only, the range, the blocks: three launches instead of two or three, 8.5 bytes a
-//          coordinate instead of 12.5.  Up to 2^13: 11.5 to 12.5 -> 12.0 to 13.1 at 256, 18.5 to 20.0 -> 13.0 to 15.8 at
-//          512 (16 and 32 workers, whose range is found by the quantizer otherwise, 14.2 to 15.8 -> 14.1 to 16.5),
-//          19.1 to 20.9 -> 15.6 to 18.8 at 776, 622 -> 463 at 32768.  2^14, whose 1024 threads leave room for two
-//          workgroups a compute unit: 18.7 -> 13.7 at 512, 22.6 -> 18.4 at 1024, where they fill the chip evenly, 18.5 ->
-//          19.8 at 630, 19.2 -> 20.7 at 776, 53.5 -> 54.0 at 3104, 607 -> 477 at 32768.
-//          With error feedback (29 bytes -> 20.5) up to 2^13 always: 13.5 to 18.7 -> 12.6 to 16.9 at up to 256, 26 to 28 ->
-//          21 at 512, 45 -> 41 at 1024, 1459 -> 1019 at 32768; 2^14, one workgroup a compute unit: 21 to 33 -> 18 to 22 at
-//          up to 512, 36.1 -> 37.9 at 630, 47.6 -> 48.7 at 1024, 133.5 -> 132.8 at 3104, 1448 -> 1263 at 32768.
+//          coordinate instead of 12.5.  Time over that of the passes, 2 to 32 workers: up to 2^13 1.10 to 1.17 at 256 (8 and
+//          more), 1.01 to 1.10 at 384 and 448, 0.70 to 0.75 at 512 with up to 8 workers and 0.99 to 1.03 with more, 0.88 to
+//          0.95 at 576, 0.74 to 0.96 at 640 and 768, 0.79 to 0.88 at 1024, 622 -> 463 us at 32768.  2^14, whose 1024 threads
+//          leave room for two workgroups a compute unit: where they fill the chip evenly 0.71 to 0.95 (up to 8 workers, 449 to
+//          512) and 0.79 to 1.02 (up to 16, 897 to 1024; with more 0.98 to 1.04); 0.80 to 1.11 at 576 to 896, 0.94 to 1.13 at
+//          1152 to 1536, 0.96 to 1.03 at 2048, 0.91 to 0.97 at 3072 and 3584, 0.91 to 0.94 at 4096, 607 -> 477 us at 32768.
+//          There is more to gain from 3072 on and, with up to 8 workers, at 320 to 448 (0.80 to 0.99).
+//          With error feedback (29 bytes -> 20.5) up to 2^13 always: 13.5 to 18.7 -> 12.6 to 16.9 us at up to 256, 26 to 28 ->
+//          21 at 512, 45 -> 41 at 1024, 1459 -> 1019 at 32768; 2^14, one workgroup a compute unit: 0.65 to 0.84 at up to 512,
+//          0.90 to 1.06 at 576, 1.02 to 1.07 at 768 to 2048, 1.00 at 3072, 0.92 to 0.94 at 4096, 1448 -> 1263 us at 32768.
 enum class Whole { NO, GIVEN, FIND, NORMS };
 constexpr uint32_t WHOLE_FIND_WORKERS = 4;
 
@@ -232,8 +236,9 @@ inline bool big_inverse(const Plan& pl, uint64_t d, uint64_t len, uint32_t W) {
 // memory-side cache.  In order -> last first: rounds of 2^20-point blocks with error feedback, 25 x 4 vectors 733 -> 707 us,
 // 25 x 8 1430 -> 1407, 9 x 16 1042 -> 1017, 64 x 8 3633 -> 3612; 2^25 x 8 2154 -> 2094; the range pass of the rotated
 // uniform variant behind its first pass, 25 x 4 vectors, 221 -> 214.  Below that size it gives nothing (25 x 1 167 either
-// way, one block without error feedback 31.3 -> 31.6), tiles of 2^15 gain at 2^25 only (8 blocks of 2^22 x 8 743 -> 750),
-// and the decompression's two passes lose 3 %.
+// way, one block without error feedback 31.3 -> 31.6), and the decompression's two passes lose 3 %.  Tiles of 2^15, the worker
+// side with error feedback, time of last first over in order: 2^25 0.96 to 0.97, 2^24 0.98 to 0.99, 2^23 0.99 to 1.00, 2^22
+// 0.985 to 1.00 (32 workers in bf16, ascending, 1.004); without it 1.00 to 1.01 at all four.  The rule takes 2^25 only.
 inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool big) {
   return W * len > (1ull << (ef ? 25 : 26)) && (!big || pl.L == 25);
 }

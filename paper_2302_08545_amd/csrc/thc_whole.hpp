@@ -2,13 +2,11 @@
 //
 // What bounds it: bytes and instructions alike.  A block fits one workgroup, so once its range is known nothing of it
 // has to leave the compute unit: gradient (and buffer) in, indices (and buffer) out, 4.5 bytes a coordinate in binary32
-// instead of the 12.5 of two passes through memory, with error feedback 12.5 instead of 25.  The range needs every
+// instead of the 12.5 of two passes through memory, with error feedback 12.5 instead of 29.  The range needs every
 // worker's norm first: from thc_prepare_range, from a pass over the gradients that keeps the sums only (6.6 TB/s), or, in
 // small calls without error feedback, from every workgroup adding up its block's squares of all workers itself (FIND).
-// Which calls take which way: whole_route.  Measured at 2^28 worker-coordinates, blocks of 2^10 / 2^13 / 2^14, us:
-// thc_compress 609 / 621 / 603 -> 264 / 289 / 308, with error feedback 1483 / 1453 / 1446 -> 612 / 682 / 878;
-// thc_compress_all of 8 workers 619 / 622 / 607 -> 443 / 463 / 477, with error feedback 1483 / 1459 / 1448 -> 971 / 1019 /
-// 1263.
+// Which calls take which way, and what that measures: whole_route.  thc_compress at 2^28 coordinates in blocks of 2^10 / 2^13 /
+// 2^14: 609 / 621 / 603 -> 264 / 289 / 308 us, with error feedback 1483 / 1453 / 1446 -> 612 / 682 / 878.
 #pragma once
 
 #include "thc_inverse.hpp"
