@@ -30,10 +30,12 @@ __device__ __forceinline__ uint64_t tm_base(const TileMap& m, uint32_t tile) {
 
 // A pass that reads what the pass before it has just written, and more of it than the 256 MB memory-side cache holds, walks
 // the launch's tiles and vectors last one first (see last_first): what was written last is still there, where a walk in the
-// same order would find each line just dropped.  Where the walk starts and its step come as arguments, in the cache lines
-// of the tiling: the grid's size lies behind all arguments, in a line that nothing else has asked for, and reading it there
+// same order would find each line just dropped.  Where the walk starts and its step come as arguments, next to others that are
+// read first: the grid's size lies behind all arguments, in a cache line that nothing else has asked for, and reading it there
 // took 0.2 to 0.3 us of every launch (the quantizer on 32 tiles of blocks of 2^10 4.27 -> 3.75 us, of 2^17 4.57 -> 4.30;
-// thc_compress_all on one block of 2^18 10.5 -> 10.2).
+// thc_compress_all on one block of 2^18 10.5 -> 10.2).  Each kernel's place for them is the one measured best: the quantizer
+// 0.25 us ahead of the tiling, the inverse's last pass behind everything (8 blocks of 2^20 29.5 -> 28.3 us, from the grid's
+// size 28.6).
 struct Walk {
   uint32_t tile = 0, vec = 0;   // of the launch's first workgroup
   uint32_t step = 1;            // 1, or 2^32 - 1: backwards

@@ -240,11 +240,11 @@ struct InvHiArgs {
   PtrArr grad;         // per vector, mode 1 only
   uint64_t d;
   uint64_t j0;         // global coordinate of x[0] (a multiple of B), for the diagonal's random stream
-  Walk walk;
   TileMap tm;
   uint32_t round, k0, k1;
   uint32_t mode, bf16;
   float c;
+  Walk walk;           // the last of the arguments: see there
 };
 
 // scale by 1/sqrt(B) and apply the diagonal; mode 1: (x + e) - that
