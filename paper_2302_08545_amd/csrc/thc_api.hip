@@ -264,20 +264,27 @@ void launch_range(const RangeArgs& r, hipStream_t s) {
 }
 
 template <int SB, bool TABLE>
-void launch_inv_lo_k(const InvLoArgs& a, bool split, dim3 grid, hipStream_t s) {
-  if (split) k_inv_lo<true, SB, TABLE><<<grid, dim3(NT), 0, s>>>(a);
-  else k_inv_lo<false, SB, TABLE><<<grid, dim3(NT), 0, s>>>(a);
+void launch_inv_lo_k(const InvLoArgs& a, bool split, bool through, dim3 grid, hipStream_t s) {
+  const dim3 blk(NT);
+  if (split) {
+    if (through) k_inv_lo<true, SB, TABLE, THROUGH><<<grid, blk, 0, s>>>(a);
+    else k_inv_lo<true, SB, TABLE, STREAM><<<grid, blk, 0, s>>>(a);
+  } else {
+    if (through) k_inv_lo<false, SB, TABLE, THROUGH><<<grid, blk, 0, s>>>(a);
+    else k_inv_lo<false, SB, TABLE, STREAM><<<grid, blk, 0, s>>>(a);
+  }
 }
 
 void launch_inv_lo(const Plan& pl, const InvLoArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)tiles, W);
+  const bool through = through_inverse(a.d, W);
   if (a.use_table) {
-    if (a.src_bits == 4) launch_inv_lo_k<4, true>(a, pl.split, grid, s);
-    else launch_inv_lo_k<0, true>(a, pl.split, grid, s);
+    if (a.src_bits == 4) launch_inv_lo_k<4, true>(a, pl.split, through, grid, s);
+    else launch_inv_lo_k<0, true>(a, pl.split, through, grid, s);
   } else {
-    if (a.src_bits == 8) launch_inv_lo_k<8, false>(a, pl.split, grid, s);
-    else if (a.src_bits == 16) launch_inv_lo_k<16, false>(a, pl.split, grid, s);
-    else launch_inv_lo_k<0, false>(a, pl.split, grid, s);
+    if (a.src_bits == 8) launch_inv_lo_k<8, false>(a, pl.split, through, grid, s);
+    else if (a.src_bits == 16) launch_inv_lo_k<16, false>(a, pl.split, through, grid, s);
+    else launch_inv_lo_k<0, false>(a, pl.split, through, grid, s);
   }
 }
 
@@ -584,6 +591,7 @@ void run_norms(const thc_params* p, const Plan& pl, const void* const* grads, co
   a.pstride = len >> pl.L1;
   a.d = len;
   a.tm = lo_tilemap(pl, len);
+  a.stream = stream_norms(len, W, bf16, ef != nullptr);
   launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(len), W, s);
   launch_range(RangeArgs{partials, range_M + x0 / p->block, a.pstride, len, W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p}, s);
 }
@@ -705,6 +713,7 @@ void run_forward(const Forward& f) {
       launch_big_lo(pl, bl, bf16, f.efs != nullptr, f.W, f.s);
     } else {
       a.tm = lo_tilemap(pl, len);
+      a.stream = stream_inputs(len, f.W, bf16, f.efs != nullptr);
       launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, tiles, f.W, f.s);
     }
     const bool find = f.range_out && !big && find_range(pl, tiles, f.W);
@@ -1060,6 +1069,7 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.k0 = (uint32_t)p->seed;
     a.k1 = (uint32_t)(p->seed >> 32);
     a.tm = lo_tilemap(pl, p->d);
+    a.stream = stream_inputs(p->d, p->n, bf16, ef != nullptr);
     launch_fwd_lo(pl, a, bf16, ef != nullptr, false, tiles_of(p->d), p->n, s);
     run_mids(pl, static_cast<float*>(ws), p->d, p->n, s);
     const HiMinMaxArgs h{static_cast<float*>(ws), pmin, pmax, p->d,

@@ -336,9 +336,6 @@ __device__ __forceinline__ void big_hi_stages(float4* lds, int t, float (&v)[8][
   }
 }
 
-template <bool V>
-struct Const { static constexpr bool value = V; };
-
 struct BigQuantArgs {
   const float* x;          // half-rotated vectors, d floats per vector of the launch (grid.y)
   const float* range_M;    // m = -M

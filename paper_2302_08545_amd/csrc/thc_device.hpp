@@ -43,6 +43,58 @@ struct Walk {
 __device__ __forceinline__ uint32_t walk_x(const Walk& w) { return w.tile + w.step * blockIdx.x; }
 __device__ __forceinline__ uint32_t walk_y(const Walk& w) { return w.vec + w.step * blockIdx.y; }
 
+// What an access leaves in the caches.
+//   KEEP     the default.
+//   STREAM   non-temporal: the line goes first.  Only for instructions that take whole 128-byte lines: where two instructions
+//            share a line, the second finds it gone (rows of 64 bytes, a pass over blocks of 2^22: 435 -> 455 us).
+//   THROUGH  a device-scope store: written through the XCD's L2 at once.  Plain stores fill the L2 with dirty lines, whose
+//            eviction competes with the loads and whose rest is written back at the end of the kernel, before the next one starts.
+enum Mem { KEEP, STREAM, THROUGH };
+
+template <auto V>
+struct Const { static constexpr auto value = V; };
+
+template <class T>
+using Vec4 = T __attribute__((ext_vector_type(4)));
+
+template <Mem M>
+__device__ __forceinline__ float4 load_f4(const float* p) {
+  if constexpr (M == STREAM) {
+    const Vec4<float> r = __builtin_nontemporal_load(reinterpret_cast<const Vec4<float>*>(p));
+    return make_float4(r.x, r.y, r.z, r.w);
+  } else {
+    return *reinterpret_cast<const float4*>(p);
+  }
+}
+
+template <Mem M>
+__device__ __forceinline__ uint4 load_u4(const void* p) {
+  if constexpr (M == STREAM) {
+    const Vec4<uint32_t> r = __builtin_nontemporal_load(static_cast<const Vec4<uint32_t>*>(p));
+    return make_uint4(r.x, r.y, r.z, r.w);
+  } else {
+    return *static_cast<const uint4*>(p);
+  }
+}
+
+template <Mem M>
+__device__ __forceinline__ void store_f(float* p, float v) {
+  if constexpr (M == STREAM) __builtin_nontemporal_store(v, p);
+  else if constexpr (M == THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
+
+template <Mem M>
+__device__ __forceinline__ void store_f4(float* p, float4 v) {
+  static_assert(M != THROUGH, "no such store of 16 bytes");
+  if constexpr (M == STREAM) {
+    const Vec4<float> r = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(r, reinterpret_cast<Vec4<float>*>(p));
+  } else {
+    *reinterpret_cast<float4*>(p) = v;
+  }
+}
+
 __device__ __forceinline__ uint32_t tm_row(const TileMap& m, uint32_t r) {
   return ((r & ((1u << m.n0) - 1u)) << m.sh0) | ((r >> m.n0) << m.sh1);
 }

@@ -21,6 +21,7 @@ struct FwdLoArgs {
   uint64_t j0;         // global coordinate of the vectors' first element (a multiple of B): indexes the diagonal
   uint32_t round, k0, k1;
   TileMap tm;          // where the bits of the tile index land; the tile shape is a template parameter
+  uint32_t stream;     // see stream_inputs
 };
 
 // Tile index -> offset inside the tile's span for the "lo" passes.  XO = false: 8192 consecutive
@@ -31,13 +32,14 @@ __device__ __forceinline__ uint32_t lo_map(uint32_t idx) {
   return XO ? ((idx & 1023u) | ((idx >> 10) << 13)) : idx;
 }
 
-template <bool BF16>
+template <bool BF16, Mem M = KEEP>
 __device__ __forceinline__ float4 load_grad4(const void* g, uint64_t j) {
   if constexpr (BF16) {
-    const ushort4 h = *reinterpret_cast<const ushort4*>(static_cast<const uint16_t*>(g) + j);
+    const Vec4<uint16_t>* const p = reinterpret_cast<const Vec4<uint16_t>*>(static_cast<const uint16_t*>(g) + j);
+    const Vec4<uint16_t> h = M == STREAM ? __builtin_nontemporal_load(p) : *p;
     return make_float4(bf16_to_f32(h.x), bf16_to_f32(h.y), bf16_to_f32(h.z), bf16_to_f32(h.w));
   } else {
-    return *reinterpret_cast<const float4*>(static_cast<const float*>(g) + j);
+    return load_f4<M>(static_cast<const float*>(g) + j);
   }
 }
 
@@ -73,17 +75,21 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
 
   // all loads of the tile are issued before anything waits on them
   float4 x[4], e[4];
+  auto load = [&](auto mem) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint64_t j = off + lo_map<XO>(4u * (uint32_t)(i * NT + t));
-    const bool ok = !GUARD || j < a.d;
-    x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    e[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (ok) {
-      x[i] = load_grad4<BF16>(grad, j);
-      if constexpr (EF) e[i] = *reinterpret_cast<const float4*>(ef + j);
+    for (int i = 0; i < 4; ++i) {
+      const uint64_t j = off + lo_map<XO>(4u * (uint32_t)(i * NT + t));
+      const bool ok = !GUARD || j < a.d;
+      x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      e[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (ok) {
+        x[i] = load_grad4<BF16, mem.value>(grad, j);
+        if constexpr (EF) e[i] = load_f4<mem.value>(ef + j);
+      }
     }
-  }
+  };
+  if (a.stream) load(Const<STREAM>{});
+  else load(Const<KEEP>{});
 
   if (!NORM_ONLY && t < 64) {   // the tile's 8192 diagonal entries: 64 Philox calls of 128 bits
     const uint64_t q = (a.j0 + off + lo_map<XO>(128u * t)) >> 7;
@@ -151,7 +157,7 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
   float* dst = dst_vec + off;
   const uint64_t left = a.d - off;   // coordinates of this tile that exist (tail tile of a short vector)
   lds_stages<2, L1, true, PAD>(lds, t, [&](int base, int eoff, float v) {
-    if (!GUARD || (uint64_t)(base + eoff) < left) dst[lo_map<XO>(base) + lo_map<XO>(eoff)] = v;
+    if (!GUARD || (uint64_t)(base + eoff) < left) store_f<THROUGH>(&dst[lo_map<XO>(base) + lo_map<XO>(eoff)], v);
   });
 }
 
@@ -332,6 +338,9 @@ struct HiGeom {
 // epilogue; two rounds and nothing left for R = 8 and 9 (rows of 128 and 64 bytes: blocks of 2^21 and 2^22
 // coordinates then need no pass in between).
 template <int R>
+constexpr Mem hi_mem() { return R <= 8 ? STREAM : KEEP; }   // a row of the tile is a whole line, and read once
+
+template <int R>
 struct HiSplit {
   static constexpr int LOGW = LOG_TILE - R;
   static constexpr int W = 1 << LOGW;
@@ -340,17 +349,17 @@ struct HiSplit {
   static_assert(R >= 2 && R <= 9 && NB2 <= 1, "strided pass handles 2..9 row bits");
 };
 
-template <int R>
+template <int R, Mem M>
 __device__ __forceinline__ void hi_issue_loads(const float* src, const HiGeom<R>& g, int t, float4 (&x)[4]) {
   using S = HiSplit<R>;
   const int cg = t & (S::W / 4 - 1), rho = t >> (S::LOGW - 2);
   const float* pb = src + g.base;
   const uint32_t o = tm_row(g.m, 4 * rho) + 4 * cg;
   const uint32_t p1 = tm_row(g.m, 1), p2 = tm_row(g.m, 2);   // rows 4 rho + {1, 2, 3}
-  x[0] = *reinterpret_cast<const float4*>(pb + o);
-  x[1] = *reinterpret_cast<const float4*>(pb + (o + p1));
-  x[2] = *reinterpret_cast<const float4*>(pb + (o + p2));
-  x[3] = *reinterpret_cast<const float4*>(pb + (o + p1 + p2));
+  x[0] = load_f4<M>(pb + o);
+  x[1] = load_f4<M>(pb + (o + p1));
+  x[2] = load_f4<M>(pb + (o + p2));
+  x[3] = load_f4<M>(pb + (o + p1 + p2));
 }
 
 // row bits 0 and 1 in registers, then the tile goes to LDS (row-major, no padding)
@@ -375,10 +384,10 @@ __device__ __forceinline__ void hi_round1(float* lds, int t) {
   __syncthreads();
 }
 
-template <int R>
+template <int R, Mem M>
 __device__ __forceinline__ void hi_front(const float* src, const HiGeom<R>& g, float* lds, int t) {
   float4 x[4];
-  hi_issue_loads<R>(src, g, t, x);
+  hi_issue_loads<R, M>(src, g, t, x);
   hi_r0_to_lds<R>(x, lds, t);
   hi_round1<R>(lds, t);
 }
@@ -386,22 +395,10 @@ __device__ __forceinline__ void hi_front(const float* src, const HiGeom<R>& g, f
 // Two groups of eight consecutive coordinates per thread, with the last row bit (if any) applied:
 // tile index of each group in idx[], values in v[][].
 template <int R>
-__device__ __forceinline__ void hi_back_index(int t, int (&idx)[2]) {
-  using S = HiSplit<R>;
-  if constexpr (S::NB2 == 1) {
-    const int oct = t & (S::W / 8 - 1), r = t >> (S::LOGW - 3);      // r < 2^(R-1)
-    idx[0] = r * S::W + 8 * oct;
-    idx[1] = idx[0] + (TILE >> 1);
-  } else {
-    idx[0] = 8 * t;
-    idx[1] = 8 * (t + NT);
-  }
-}
-
-template <int R>
 __device__ __forceinline__ void hi_back(const float* lds, int t, int (&idx)[2], float (&v)[2][8]) {
   using S = HiSplit<R>;
-  hi_back_index<R>(t, idx);
+  idx[0] = 8 * t;
+  idx[1] = 8 * (t + NT);
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const float4 p0 = *reinterpret_cast<const float4*>(&lds[idx[h]]);
@@ -417,6 +414,15 @@ __device__ __forceinline__ void hi_back(const float* lds, int t, int (&idx)[2], 
       v[1][e] = a - b;
     }
   }
+}
+
+// The same tile as four groups of four consecutive coordinates, group i at tile index 4 t + 4 NT i: a wave's access takes
+// whole lines, where groups of eight take every other 16 bytes.
+template <int R>
+__device__ __forceinline__ void hi_back4(const float* lds, int t, float4 (&v)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4*>(&lds[4 * (t + NT * i)]);
+  if constexpr (HiSplit<R>::NB2 == 1) { bf4(v[0], v[2]); bf4(v[1], v[3]); }
 }
 
 // R < 2: a thread's two groups of eight consecutive values (the two rows of the same columns where there are two) come
@@ -473,16 +479,11 @@ __global__ __launch_bounds__(NT) void k_mid(MidArgs a) {
   const int t = threadIdx.x;
   const HiGeom<R> g(blockIdx.x, a.tm);
   a.x += (uint64_t)blockIdx.y * a.d;
-  hi_front<R>(a.x, g, lds, t);
-  int idx[2];
-  float v[2][8];
-  hi_back<R>(lds, t, idx, v);
+  hi_front<R, KEEP>(a.x, g, lds, t);
+  float4 v[4];
+  hi_back4<R>(lds, t, v);
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    float* o = a.x + g.coord(idx[h]);
-    *reinterpret_cast<float4*>(o) = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
-    *reinterpret_cast<float4*>(o + 4) = make_float4(v[h][4], v[h][5], v[h][6], v[h][7]);
-  }
+  for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(a.x + g.coord(4 * (t + NT * i))) = v[i];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -644,19 +645,19 @@ __device__ __forceinline__ void hi_quant_tile(const A& a, uint32_t tile, uint32_
     if constexpr (FIND && R > 3) {
       found = block_range(a.partials, a.pstride, a.n, 1u << R, blk, a.t_p, a.L, *smr, [&] {
         __builtin_amdgcn_sched_barrier(0);
-        hi_issue_loads<R>(xw, g, t, x);
+        hi_issue_loads<R, hi_mem<R>()>(xw, g, t, x);
         __builtin_amdgcn_sched_barrier(0);
       });
     } else if constexpr (FIND) {
       SmallRange<1 << R> r;
       if (t < 64) r.request(a.partials, a.pstride, a.n, blk);
       __builtin_amdgcn_sched_barrier(0);
-      hi_issue_loads<R>(xw, g, t, x);
+      hi_issue_loads<R, hi_mem<R>()>(xw, g, t, x);
       __builtin_amdgcn_sched_barrier(0);
       if (t < 64) found = r.range(a.n, a.t_p, a.L);
     } else {
       __builtin_amdgcn_sched_barrier(0);
-      hi_issue_loads<R>(xw, g, t, x);
+      hi_issue_loads<R, hi_mem<R>()>(xw, g, t, x);
       __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (FIND) {

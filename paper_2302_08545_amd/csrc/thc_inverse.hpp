@@ -212,21 +212,21 @@ __device__ __forceinline__ void inv_lo_stages(const A& a, uint64_t off, uint32_t
   lds_stages<4, L1, true, SWZ, N>(lds, t, [&](int base, int eoff, float val) { put(lo_map<XO>(base) + lo_map<XO>(eoff), val); });
 }
 
-template <bool XO, int SB, bool TABLE, class A>
+template <bool XO, int SB, bool TABLE, Mem M, class A>
 __device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t vec, float* dst_vec, SmemInvLo<>& sm) {
   const uint64_t off = tm_base(a.tm, tile);
   float* const dst = dst_vec + off;
-  inv_lo_stages<LOG_TILE, XO, SB, TABLE>(a, off, vec, sm, [&](uint32_t o, float val) { dst[o] = val; });
+  inv_lo_stages<LOG_TILE, XO, SB, TABLE>(a, off, vec, sm, [&](uint32_t o, float val) { store_f<M>(&dst[o], val); });
 }
 
 // What bounds it: writing 4 bytes a coordinate (pure writes reach 5.7 TB/s here).  Decoding is a large part of its
 // instructions, so the widths and sources that rounds use have instantiations of their own: 2^28 coordinates from 8-bit
 // sums 251 -> 231 us, from 4-bit indices, whose values are looked up on the block's range, 268 -> 245 us; one block of
 // 2^20 from 4-bit indices 5.4 -> 4.3 us.
-template <bool XO, int SB, bool TABLE>
+template <bool XO, int SB, bool TABLE, Mem M>
 __global__ __launch_bounds__(NT, 8) void k_inv_lo(const InvLoArgs a) {
   __shared__ SmemInvLo<> sm;
-  inv_lo_tile<XO, SB, TABLE>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
+  inv_lo_tile<XO, SB, TABLE, M>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -279,7 +279,7 @@ __device__ __forceinline__ void inv_hi_tile(const A& a, uint32_t tile, uint32_t 
   const void* const grad = a.grad.p[vec];
 
   float4 x[4];
-  hi_issue_loads<R>(xv, g, t, x);
+  hi_issue_loads<R, hi_mem<R>()>(xv, g, t, x);
   // the diagonal's bits while the loads travel
   // 32 consecutive tile indices are 32 consecutive coordinates, or, with 16-wide rows, two aligned halves
   if (t < TILE / 32) {
@@ -294,37 +294,28 @@ __device__ __forceinline__ void inv_hi_tile(const A& a, uint32_t tile, uint32_t 
   }
   hi_r0_to_lds<R>(x, lds, t);
   hi_round1<R>(lds, t);
-  int idx[2];
-  hi_back_index<R>(t, idx);
-  // error-feedback update: the gradient and the buffer's old contents are requested for both halves before
-  // anything is stored (the stores go to that same buffer), and while the tile's last stage runs
-  float4 gx[2][2], ex[2][2];
+  // error-feedback update: the gradient and the buffer's old contents are all requested before anything is stored (the
+  // stores go to that same buffer), and while the tile's last stage runs
+  float4 gx[4], ex[4];
   if (a.mode == 1) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint64_t j = g.coord(idx[h]);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        gx[h][k] = a.bf16 ? load_grad4<true>(grad, j + 4 * k) : load_grad4<false>(grad, j + 4 * k);
-        ex[h][k] = *reinterpret_cast<const float4*>(out + j + 4 * k);
-      }
+    for (int i = 0; i < 4; ++i) {
+      const uint64_t j = g.coord(4 * (t + NT * i));
+      gx[i] = a.bf16 ? load_grad4<true>(grad, j) : load_grad4<false>(grad, j);
+      ex[i] = *reinterpret_cast<const float4*>(out + j);
     }
   } else {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      for (int k = 0; k < 2; ++k) gx[h][k] = ex[h][k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < 4; ++i) gx[i] = ex[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  float v[2][8];
-  hi_back<R>(lds, t, idx, v);
+  float4 v[4];
+  hi_back4<R>(lds, t, v);
   __syncthreads();
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const uint64_t j = g.coord(idx[h]);
-    const uint32_t bits = sgn[idx[h] >> 5] >> (idx[h] & 31);
-    const float4 o0 = inv_finish4(make_float4(v[h][0], v[h][1], v[h][2], v[h][3]), bits, a, gx[h][0], ex[h][0]);
-    const float4 o1 = inv_finish4(make_float4(v[h][4], v[h][5], v[h][6], v[h][7]), bits >> 4, a, gx[h][1], ex[h][1]);
-    *reinterpret_cast<float4*>(out + j) = o0;
-    *reinterpret_cast<float4*>(out + j + 4) = o1;
+  for (int i = 0; i < 4; ++i) {
+    const int idx = 4 * (t + NT * i);
+    const uint32_t bits = sgn[idx >> 5] >> (idx & 31);
+    store_f4<STREAM>(out + g.coord(idx), inv_finish4(v[i], bits, a, gx[i], ex[i]));
   }
 }
 

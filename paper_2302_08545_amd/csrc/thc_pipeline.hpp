@@ -67,6 +67,7 @@ struct LoView {
   uint64_t pstride, d, j0;
   uint32_t round, k0, k1;
   const TileMap& tm;
+  uint32_t stream;
 };
 struct QuantView {
   const float* range_M;
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
       const uint32_t* old = P.sync + (uint64_t)(u - P.slots) * SYNC_PER_UNIT + SYNC_DONE * SYNC_STRIDE;
       if (!pipe_wait<false>(old, Tu, P.status, &flag)) return;
     }
-    const LoView a{P.grads, P.efs, P.partials, P.pstride, P.d, P.j0, P.round, P.k0, P.k1, P.lo_tm};
+    const LoView a{P.grads, P.efs, P.partials, P.pstride, P.d, P.j0, P.round, P.k0, P.k1, P.lo_tm, !EF};
     fwd_lo_tile<LOG_TILE, BF16, EF, true, false>(a, gt, w, vec, *reinterpret_cast<SmemLo*>(raw));
     pipe_publish(us, 0, Tu >> 3);
   } else if (phase == 1) {
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
       // X_i from the indices, inverse first pass into the slot the quantizer has finished with
       if (!pipe_wait<true>(us + (1 * SYNC_PHASE + NXCD) * SYNC_STRIDE, NXCD, P.status, &flag)) return;
       const InvLoView a{P.packed, P.range_M, nullptr, P.d, P.L, P.b, P.g, P.lo_tm, P.table};
-      inv_lo_tile<true, 0, true>(a, gt, w, vec, *reinterpret_cast<SmemInvLo<>*>(raw));
+      inv_lo_tile<true, 0, true, THROUGH>(a, gt, w, vec, *reinterpret_cast<SmemInvLo<>*>(raw));
       pipe_publish(us, 2, Tu >> 3);
     } else {
       // e <- (grad + e) - RHT^-1(X_i)

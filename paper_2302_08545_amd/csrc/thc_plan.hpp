@@ -246,6 +246,26 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
   return W * len > (1ull << (ef ? 25 : 26)) && (!big || pl.L == 25);
 }
 
+// Cache hints (see Mem) that depend on the size of a launch: `len` coordinates of each of W vectors.  The memory-side cache
+// holds 256 MB, and what is read again before that much else has come by should be left in it.
+//
+// stream_inputs: the first pass reads its vectors non-temporally.  Without error feedback nothing of the call reads them again,
+// so that only small ones, which the caller has just written, are better left alone; with it the update does, at the end.  Time
+// of streamed over kept: one block of 2^20 x 4 vectors 1.01, x 10 1.04, 4 x 8 (128 MB) 0.99, 10 x 8 0.97, 41 x 16 0.96, 256 x 8
+// 0.96; with error feedback 3 x 4 vectors (96 MB) 1.04, 25 x 1 in bf16 (150 MB) 0.98, 25 x 8 0.96.
+// stream_norms: the pass that keeps the norms only.  Time of streamed over kept: 4 x 2^18 (8 MB) 1.03, 25 blocks of 2^20 in bf16
+// with error feedback (150 MB) 0.99, 100 blocks (400 MB) 0.93.
+// through_inverse: the inverse's first pass writes through the L2, or else non-temporally.  Through over non-temporal: 4 MB 0.98,
+// 100 MB 0.98, 128 MB 1.01, 400 MB 1.02, 800 MB 1.04, 1 GB 1.00.
+constexpr uint64_t MB = 1ull << 20;
+
+inline uint64_t input_bytes(uint64_t len, uint32_t W, bool bf16, bool ef) { return W * len * ((bf16 ? 2 : 4) + (ef ? 4 : 0)); }
+inline bool stream_inputs(uint64_t len, uint32_t W, bool bf16, bool ef) {
+  return input_bytes(len, W, bf16, ef) >= (ef ? 128 : 64) * MB;
+}
+inline bool stream_norms(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 64 * MB; }
+inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
+
 // Uniform quantizer on a vector of d coordinates: one group of eight coordinates to a thread, 4096 to a workgroup, or two.
 // One group / two, us:
 //   error feedback, binary32: 2^18 4.0 / 4.3, 2^20 4.7 / 4.8, 2^21 6.2 / 5.8, 6 * 2^20 14.6 / 13.7, 2^24 33.1 / 32.0, 25 * 2^20

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
   float* const pmin = a.pmin + part;
   float* const pmax = a.pmax + part;
   if constexpr (R >= 2) {
-    hi_front<R>(x, g, lds, t);
+    hi_front<R, hi_mem<R>()>(x, g, lds, t);
     int idx[2];
     float v[2][8];
     hi_back<R>(lds, t, idx, v);
