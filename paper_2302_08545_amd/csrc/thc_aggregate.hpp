@@ -6,6 +6,12 @@
 namespace thc {
 
 // ---------------------------------------------------------------------------------------------
+// What bounds it in large calls: reading n streams once.  There (stream_sums) M = STREAM: loads and stores non-temporal, the
+// sums as whole lines by way of LDS.  16 streams of 33 * 2^20 4-bit indices to 9-bit sums 65.7 -> 55.5 us (5.8 TB/s), of 100 *
+// 2^20 to 16-bit sums 200 -> 171 (6.1 TB/s), 8 of 40 * 2^20 to 8-bit sums 40.0 -> 36.2, 10 of 64 * 2^20 3-bit ones 64.4 -> 57.8.
+// In small calls M = KEEP: the streams have just been written and are in the cache, and latency counts, so four workers'
+// loads are in flight (16 streams of 4 * 2^20 to 16-bit sums 12.2 -> 9.4 us; in large calls the same takes 1 to 6 % more).
+//
 // Aggregation (Alg. 2: Y = sum_i T[Z_i]; the PS only looks up and adds).  Index widths without a kernel of their own
 // below, sums of any width.
 //
@@ -42,6 +48,7 @@ __device__ __forceinline__ uint32_t spread4(uint32_t x) {
 // Writes a thread's 32 sums, acc[m] = those of coordinates 2m (low half) and 2m + 1 (high half).  Widths other than 8
 // and 16 go through LDS, `stage` holding 256 * 16 dwords, so that the workgroup writes consecutive 16-byte vectors; all of its
 // threads take part, those with `own` false hold no coordinates.
+template <Mem M>
 __device__ __forceinline__ void store_sums32(const uint32_t (&acc)[16], uint32_t bits, uint8_t* out, uint64_t v0,
                                              uint64_t nvec, bool own, uint32_t* stage) {
   const uint32_t t = threadIdx.x;
@@ -78,10 +85,10 @@ __device__ __forceinline__ void store_sums32(const uint32_t (&acc)[16], uint32_t
   const uint64_t left = nvec - v0;
   const uint32_t nvec4 = (uint32_t)(left < 256 ? left : 256) * bits / 4;   // whole: nvec is a multiple of 32
   uint4* const dst = reinterpret_cast<uint4*>(out + v0 * 4 * bits);
-  for (uint32_t i = t; i < nvec4; i += 256) dst[i] = reinterpret_cast<const uint4*>(stage)[i];
+  for (uint32_t i = t; i < nvec4; i += 256) store_u4<M>(dst + i, reinterpret_cast<const uint4*>(stage)[i]);
 }
 
-template <int B>
+template <int B, Mem M>
 __global__ __launch_bounds__(256) void k_aggregate_any(const AggArgs a) {
   __shared__ __align__(16) uint32_t stage[256 * 16];
   __shared__ uint32_t tab[B > 3 ? 1 << B : 1];
@@ -131,7 +138,10 @@ __global__ __launch_bounds__(256) void k_aggregate_any(const AggArgs a) {
         const uint32_t i = i0 + u < a.n ? i0 + u : i0;          // past the end: a load that is not used
         const uint32_t* const p = static_cast<const uint32_t*>(a.packed.p[i]) + v * B;
 #pragma unroll
-        for (int k = 0; k < B; ++k) w[u][k] = p[k];
+        for (int k = 0; k < B; ++k) {
+          if constexpr (M == STREAM && B <= 3) w[u][k] = __builtin_nontemporal_load(p + k);   // wider ones share lines
+          else w[u][k] = p[k];
+        }
       }
 #pragma unroll
       for (uint32_t u = 0; u < 4; ++u)
@@ -139,7 +149,7 @@ __global__ __launch_bounds__(256) void k_aggregate_any(const AggArgs a) {
     }
     if constexpr (B <= 3) widen();
   }
-  store_sums32(acc, a.agg_bits, a.out, v0, a.nvec, own, stage);
+  store_sums32<M>(acc, a.agg_bits, a.out, v0, a.nvec, own, stage);
 }
 
 // 4-bit indices -> 8-bit sums, the paper's prototype widths (Sec. 3).  One thread owns 32 coordinates
@@ -162,11 +172,15 @@ __device__ __forceinline__ uint32_t lut16x4(uint32_t sel, const uint32_t (&tb)[4
   return (hi & m) | (lo & ~m);
 }
 
+template <Mem M>
 __global__ __launch_bounds__(256) void k_aggregate_b4w8(const AggB4Args a) {
-  const uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (v >= a.nvec) return;
+  __shared__ uint4 stage[M == STREAM ? 512 : 1];
+  const uint32_t t = threadIdx.x;
+  const uint64_t v0 = (uint64_t)blockIdx.x * 256, v = v0 + t;
+  if (M == KEEP && v >= a.nvec) return;
   const uint32_t tb[4] = {a.tb[0], a.tb[1], a.tb[2], a.tb[3]};
   uint32_t ev[4] = {0, 0, 0, 0}, od[4] = {0, 0, 0, 0};
+  auto load = [&](uint32_t i) { return load_u4<M>(static_cast<const uint4*>(a.packed.p[i]) + v); };
   auto add = [&](const uint4 r) {
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
@@ -175,66 +189,35 @@ __global__ __launch_bounds__(256) void k_aggregate_b4w8(const AggB4Args a) {
       od[k] += lut16x4((w[k] >> 4) & 0x0F0F0F0Fu, tb);   // coordinates 8k + 1, 3, 5, 7
     }
   };
-  uint32_t i = 0;
-  for (; i + 4 <= a.n; i += 4) {           // four loads in flight: a small call has few wavefronts to hide them
-    uint4 r[4];
+  if (v < a.nvec) {
+    uint32_t i = 0;
+    for (; i + 4 <= a.n; i += 4) {         // four loads in flight: a small call has few wavefronts to hide them
+      uint4 r[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) r[u] = reinterpret_cast<const uint4*>(a.packed.p[i + u])[v];
+      for (int u = 0; u < 4; ++u) r[u] = load(i + u);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) add(r[u]);
+      for (int u = 0; u < 4; ++u) add(r[u]);
+    }
+    for (; i < a.n; ++i) add(load(i));
   }
-  for (; i < a.n; ++i) add(reinterpret_cast<const uint4*>(a.packed.p[i])[v]);
   uint32_t o[8];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     o[2 * k] = __builtin_amdgcn_perm(od[k], ev[k], 0x05010400u);
     o[2 * k + 1] = __builtin_amdgcn_perm(od[k], ev[k], 0x07030602u);
   }
-  uint4* dst = reinterpret_cast<uint4*>(a.out + v * 32);
-  dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
-  dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
-}
-
-// 4-bit indices -> 16-bit sums (g*n above 255).  Same lookups; workers are taken in runs of `chunk` =
-// floor(255 / g), inside which the byte-wise sums cannot carry, and every run is then widened into 16-bit lanes.
-struct AggB4W16Args {
-  PtrArr packed;
-  uint8_t* out;
-  uint64_t nvec;    // d / 32
-  uint32_t n, chunk;
-  uint32_t tb[4];
-};
-
-__global__ __launch_bounds__(256) void k_aggregate_b4w16(const AggB4W16Args a) {
-  const uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (v >= a.nvec) return;
-  const uint32_t tb[4] = {a.tb[0], a.tb[1], a.tb[2], a.tb[3]};
-  uint32_t acc[16];   // acc[4k + m] = sums of coordinates 8k + 2m (low half) and 8k + 2m + 1 (high half)
+  uint4* const dst = reinterpret_cast<uint4*>(a.out + v0 * 32);
+  uint4* const mine = (M == STREAM ? stage : dst) + 2 * t;
+  mine[0] = make_uint4(o[0], o[1], o[2], o[3]);
+  mine[1] = make_uint4(o[4], o[5], o[6], o[7]);
+  if constexpr (M == STREAM) {             // a wave's stores as whole lines
+    __syncthreads();
+    const uint64_t left = a.nvec - v0;
+    const uint32_t nvec4 = 2 * (uint32_t)(left < 256 ? left : 256);
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0;
-  for (uint32_t i0 = 0; i0 < a.n; i0 += a.chunk) {
-    const uint32_t i1 = (i0 + a.chunk < a.n) ? i0 + a.chunk : a.n;
-    uint32_t ev[4] = {0, 0, 0, 0}, od[4] = {0, 0, 0, 0};
-    for (uint32_t i = i0; i < i1; ++i) {
-      const uint4 r = reinterpret_cast<const uint4*>(a.packed.p[i])[v];
-      const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        ev[k] += lut16x4(w[k] & 0x0F0F0F0Fu, tb);
-        od[k] += lut16x4((w[k] >> 4) & 0x0F0F0F0Fu, tb);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      acc[4 * k + 0] += __builtin_amdgcn_perm(od[k], ev[k], 0x0C040C00u);
-      acc[4 * k + 1] += __builtin_amdgcn_perm(od[k], ev[k], 0x0C050C01u);
-      acc[4 * k + 2] += __builtin_amdgcn_perm(od[k], ev[k], 0x0C060C02u);
-      acc[4 * k + 3] += __builtin_amdgcn_perm(od[k], ev[k], 0x0C070C03u);
-    }
+    for (uint32_t i = t; i < 512; i += 256)
+      if (i < nvec4) store_u4<STREAM>(dst + i, stage[i]);
   }
-  uint4* dst = reinterpret_cast<uint4*>(a.out + v * 64);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) dst[k] = make_uint4(acc[4 * k], acc[4 * k + 1], acc[4 * k + 2], acc[4 * k + 3]);
 }
 
 // 2-bit indices -> 8-bit sums.  One thread owns 64 coordinates (16 bytes of every stream); the four table
@@ -248,6 +231,7 @@ struct AggB2Args {
   uint32_t tb;      // table bytes 0..3, little endian
 };
 
+template <Mem M>
 __global__ __launch_bounds__(256) void k_aggregate_b2w8(const AggB2Args a) {
   const uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   if (v >= a.nvec) return;
@@ -257,7 +241,7 @@ __global__ __launch_bounds__(256) void k_aggregate_b2w8(const AggB2Args a) {
 #pragma unroll
     for (int f = 0; f < 4; ++f) acc[k][f] = 0;
   for (uint32_t i = 0; i < a.n; ++i) {
-    const uint4 r = reinterpret_cast<const uint4*>(a.packed.p[i])[v];
+    const uint4 r = load_u4<M>(static_cast<const uint4*>(a.packed.p[i]) + v);
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -276,11 +260,20 @@ __global__ __launch_bounds__(256) void k_aggregate_b2w8(const AggB2Args a) {
   }
 }
 
-// 4-bit indices -> sums of any other width W (the exact width ceil(log2(g n + 1)) of Sec. 8.4, say).  Sums are
-// formed as in k_aggregate_b4w16; a thread's 32 fields make exactly W dwords, which go through LDS so that the
+// 4-bit indices -> sums of any other width W: 16 bits (g*n above 255), or the exact width ceil(log2(g n + 1)) of Sec. 8.4,
+// say.  Same lookups; workers are taken in runs of `chunk` = floor(255 / g), inside which the byte-wise sums cannot carry, and
+// every run is then widened into 16-bit lanes.  A thread's 32 fields make exactly W dwords, which go through LDS so that the
 // workgroup writes its 1024 * W bytes as consecutive 16-byte vectors.
-template <int W>
-__global__ __launch_bounds__(256) void k_aggregate_b4wx(const AggB4W16Args a) {
+struct AggB4WxArgs {
+  PtrArr packed;
+  uint8_t* out;
+  uint64_t nvec;    // d / 32
+  uint32_t n, chunk;
+  uint32_t tb[4];
+};
+
+template <int W, Mem M>
+__global__ __launch_bounds__(256) void k_aggregate_b4wx(const AggB4WxArgs a) {
   __shared__ __align__(16) uint32_t stage[256 * W];
   const int t = threadIdx.x;
   const uint64_t v0 = (uint64_t)blockIdx.x * 256;
@@ -293,15 +286,26 @@ __global__ __launch_bounds__(256) void k_aggregate_b4wx(const AggB4W16Args a) {
     for (uint32_t i0 = 0; i0 < a.n; i0 += a.chunk) {
       const uint32_t i1 = (i0 + a.chunk < a.n) ? i0 + a.chunk : a.n;
       uint32_t ev[4] = {0, 0, 0, 0}, od[4] = {0, 0, 0, 0};
-      for (uint32_t i = i0; i < i1; ++i) {
-        const uint4 r = reinterpret_cast<const uint4*>(a.packed.p[i])[v];
+      auto load = [&](uint32_t i) { return load_u4<M>(static_cast<const uint4*>(a.packed.p[i]) + v); };
+      auto add = [&](const uint4 r) {
         const uint32_t w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           ev[k] += lut16x4(w[k] & 0x0F0F0F0Fu, tb);
           od[k] += lut16x4((w[k] >> 4) & 0x0F0F0F0Fu, tb);
         }
+      };
+      uint32_t i = i0;
+      if constexpr (M == KEEP) {           // a small call: four loads in flight
+        for (; i + 4 <= i1; i += 4) {
+          uint4 r[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) r[u] = load(i + u);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) add(r[u]);
+        }
       }
+      for (; i < i1; ++i) add(load(i));
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         acc[4 * k + 0] += __builtin_amdgcn_perm(od[k], ev[k], 0x0C040C00u);
@@ -329,7 +333,7 @@ __global__ __launch_bounds__(256) void k_aggregate_b4wx(const AggB4W16Args a) {
   const uint32_t nvec4 = (uint32_t)(left < 256 ? left : 256) * W / 4;   // a multiple of 8 W / 4: nvec is a multiple of 32
   uint4* dst = reinterpret_cast<uint4*>(a.out + v0 * 4 * W);
   const uint4* src = reinterpret_cast<const uint4*>(stage);
-  for (uint32_t i = t; i < nvec4; i += 256) dst[i] = src[i];
+  for (uint32_t i = t; i < nvec4; i += 256) store_u4<M>(dst + i, src[i]);
 }
 
 }  // namespace thc

@@ -786,6 +786,56 @@ int static_scratch(float** out) {
   return THC_OK;
 }
 
+// ---- aggregation ----------------------------------------------------------------------------------------------
+template <Mem M>
+int run_aggregate(const thc_params* p, const uint8_t* const* packed, uint8_t* out, hipStream_t s) {
+  const dim3 blk(256);
+  auto fill = [&](auto& a, uint32_t per_thread) {
+    for (uint32_t i = 0; i < p->n; ++i) a.packed.p[i] = packed[i];
+    a.out = out;
+    a.nvec = p->d / per_thread;
+    a.n = p->n;
+    return dim3((unsigned)((a.nvec + 255) / 256));
+  };
+  if (p->b == 4 && p->agg_bits == 8) {
+    AggB4Args a{};
+    const dim3 grid = fill(a, 32);
+    std::memcpy(a.tb, p->table, 16);
+    k_aggregate_b4w8<M><<<grid, blk, 0, s>>>(a);
+  } else if (p->b == 2 && p->agg_bits == 8) {
+    AggB2Args a{};
+    const dim3 grid = fill(a, 64);
+    std::memcpy(&a.tb, p->table, 4);
+    k_aggregate_b2w8<M><<<grid, blk, 0, s>>>(a);
+  } else if (p->b == 4) {
+    AggB4WxArgs a{};
+    const dim3 grid = fill(a, 32);
+    a.chunk = 255u / p->g;              // g <= 255, so at least one worker per run
+    std::memcpy(a.tb, p->table, 16);
+    switch (p->agg_bits) {
+#define THC_AGG_WX(W) case W: k_aggregate_b4wx<W, M><<<grid, blk, 0, s>>>(a); break;
+      THC_AGG_WX(4) THC_AGG_WX(5) THC_AGG_WX(6) THC_AGG_WX(7) THC_AGG_WX(9) THC_AGG_WX(10) THC_AGG_WX(11)
+      THC_AGG_WX(12) THC_AGG_WX(13) THC_AGG_WX(14) THC_AGG_WX(15) THC_AGG_WX(16)
+#undef THC_AGG_WX
+      default: return THC_EINVAL;       // 4-bit tables reach at least g = 15: the sums need 4 bits or more
+    }
+  } else {
+    AggArgs a{};
+    const dim3 grid = fill(a, 32);
+    a.agg_bits = p->agg_bits;
+    a.chunk = 255u / p->g;              // g <= 255, so at least one worker per run
+    std::memcpy(a.tb, p->table, 8);
+    std::memcpy(a.table, p->table, 256);
+    switch (p->b) {
+#define THC_AGG_ANY(B) case B: k_aggregate_any<B, M><<<grid, blk, 0, s>>>(a); break;
+      THC_AGG_ANY(1) THC_AGG_ANY(2) THC_AGG_ANY(3) THC_AGG_ANY(5) THC_AGG_ANY(6) THC_AGG_ANY(7) THC_AGG_ANY(8)
+#undef THC_AGG_ANY
+      default: return THC_EINVAL;       // 4-bit indices have kernels of their own
+    }
+  }
+  return check_launch();
+}
+
 const char* const kNames[] = {"THC_OK", "THC_EINVAL", "THC_ETABLE", "THC_EOVERFLOW", "THC_EUNSUPPORTED", "THC_ELAUNCH"};
 
 }  // namespace
@@ -898,58 +948,8 @@ int thc_aggregate(const thc_params* p, const uint8_t* const* packed, void* agg_o
   for (uint32_t i = 0; i < p->n; ++i)
     if (!packed[i] || !aligned16(packed[i])) return THC_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p->b == 4 && p->agg_bits == 8) {
-    AggB4Args a{};
-    for (uint32_t i = 0; i < p->n; ++i) a.packed.p[i] = packed[i];
-    a.out = static_cast<uint8_t*>(agg_out);
-    a.nvec = p->d / 32;
-    a.n = p->n;
-    std::memcpy(a.tb, p->table, 16);
-    k_aggregate_b4w8<<<dim3((unsigned)((a.nvec + 255) / 256)), dim3(256), 0, s>>>(a);
-  } else if (p->b == 2 && p->agg_bits == 8) {
-    AggB2Args a{};
-    for (uint32_t i = 0; i < p->n; ++i) a.packed.p[i] = packed[i];
-    a.out = static_cast<uint8_t*>(agg_out);
-    a.nvec = p->d / 64;
-    a.n = p->n;
-    std::memcpy(&a.tb, p->table, 4);
-    k_aggregate_b2w8<<<dim3((unsigned)((a.nvec + 255) / 256)), dim3(256), 0, s>>>(a);
-  } else if (p->b == 4) {
-    AggB4W16Args a{};
-    for (uint32_t i = 0; i < p->n; ++i) a.packed.p[i] = packed[i];
-    a.out = static_cast<uint8_t*>(agg_out);
-    a.nvec = p->d / 32;
-    a.n = p->n;
-    a.chunk = 255u / p->g;              // g <= 255, so at least one worker per run
-    std::memcpy(a.tb, p->table, 16);
-    const dim3 grid((unsigned)((a.nvec + 255) / 256)), blk(256);
-    switch (p->agg_bits) {
-      case 16: k_aggregate_b4w16<<<grid, blk, 0, s>>>(a); break;
-#define THC_AGG_WX(W) case W: k_aggregate_b4wx<W><<<grid, blk, 0, s>>>(a); break;
-      THC_AGG_WX(4) THC_AGG_WX(5) THC_AGG_WX(6) THC_AGG_WX(7) THC_AGG_WX(9) THC_AGG_WX(10) THC_AGG_WX(11)
-      THC_AGG_WX(12) THC_AGG_WX(13) THC_AGG_WX(14) THC_AGG_WX(15)
-#undef THC_AGG_WX
-      default: return THC_EINVAL;       // 4-bit tables reach at least g = 15: the sums need 4 bits or more
-    }
-  } else {
-    AggArgs a{};
-    for (uint32_t i = 0; i < p->n; ++i) a.packed.p[i] = packed[i];
-    a.out = static_cast<uint8_t*>(agg_out);
-    a.nvec = p->d / 32;
-    a.n = p->n;
-    a.agg_bits = p->agg_bits;
-    a.chunk = 255u / p->g;              // g <= 255, so at least one worker per run
-    std::memcpy(a.tb, p->table, 8);
-    std::memcpy(a.table, p->table, 256);
-    const dim3 grid((unsigned)((a.nvec + 255) / 256)), blk(256);
-    switch (p->b) {
-#define THC_AGG_ANY(B) case B: k_aggregate_any<B><<<grid, blk, 0, s>>>(a); break;
-      THC_AGG_ANY(1) THC_AGG_ANY(2) THC_AGG_ANY(3) THC_AGG_ANY(5) THC_AGG_ANY(6) THC_AGG_ANY(7) THC_AGG_ANY(8)
-#undef THC_AGG_ANY
-      default: return THC_EINVAL;       // 4-bit indices have kernels of their own
-    }
-  }
-  return check_launch();
+  if (stream_sums(p->d, p->n, p->b)) return run_aggregate<STREAM>(p, packed, static_cast<uint8_t*>(agg_out), s);
+  return run_aggregate<KEEP>(p, packed, static_cast<uint8_t*>(agg_out), s);
 }
 
 namespace {

@@ -78,6 +78,16 @@ __device__ __forceinline__ uint4 load_u4(const void* p) {
 }
 
 template <Mem M>
+__device__ __forceinline__ void store_u4(void* p, uint4 v) {
+  if constexpr (M == STREAM) {
+    const Vec4<uint32_t> r = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(r, static_cast<Vec4<uint32_t>*>(p));
+  } else {
+    *static_cast<uint4*>(p) = v;
+  }
+}
+
+template <Mem M>
 __device__ __forceinline__ void store_f(float* p, float v) {
   if constexpr (M == STREAM) __builtin_nontemporal_store(v, p);
   else if constexpr (M == THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -13,7 +13,7 @@
 //   thc_forward.hpp    k_fwd_lo, k_range, k_range_small, k_mid, k_fwd_hi_quant
 //   thc_inverse.hpp    k_inv_lo, k_inv_hi, k_inv_whole (blocks of up to 2^14 in one launch)
 //   thc_uniform.hpp    k_minmax, k_minmax_final, k_fwd_hi_minmax, k_uniform_quant, k_uniform_dequant
-//   thc_aggregate.hpp  k_aggregate_b4w8, k_aggregate_b4w16, k_aggregate_b4wx, k_aggregate_b2w8, k_aggregate_any
+//   thc_aggregate.hpp  k_aggregate_b4w8, k_aggregate_b4wx, k_aggregate_b2w8, k_aggregate_any
 //   thc_pipeline.hpp   k_pipe_forward: the forward passes of all blocks in one launch, block after block
 //   thc_big.hpp        the same passes on tiles of 2^15 coordinates: k_big_lo, k_big_quant, k_big_inv_lo, k_big_inv_hi,
 //                      k_big_inv_whole (blocks of 2^14 and 2^15); thc_bigmap.hpp has their coordinate maps

@@ -196,6 +196,26 @@ static int check_last_first() {
   return bad;
 }
 
+// ... and of the cache hints: a call just below each limit and one at it.
+static int check_hints() {
+  int bad = 0;
+  for (uint32_t W : {1u, 4u, 32u}) {
+    for (bool bf16 : {false, true}) {
+      const uint64_t plain = 64 * MB / (bf16 ? 2 : 4) / W, with_ef = 128 * MB / (bf16 ? 6 : 8) / W;
+      bad += stream_inputs(plain - 1024, W, bf16, false) || !stream_inputs(plain, W, bf16, false);
+      bad += stream_inputs(with_ef - 1024, W, bf16, true) || !stream_inputs(with_ef + 1024, W, bf16, true);
+      bad += stream_norms(plain - 1024, W, bf16, false) || !stream_norms(plain, W, bf16, false);
+      bad += stream_norms(with_ef / 2 - 1024, W, bf16, true) || !stream_norms(with_ef / 2 + 1024, W, bf16, true);
+    }
+    bad += !through_inverse(64 * MB / W, W) || through_inverse(64 * MB / W + 1024, W);
+    for (uint32_t b : {1u, 3u, 4u, 8u}) {
+      const uint64_t d = 64 * MB / W / b * 8;
+      bad += stream_sums(d - 1024, W, b) || !stream_sums(d + 1024, W, b);
+    }
+  }
+  return bad;
+}
+
 // The index of a coordinate above the range, for the largest rounding draw: what the quantizer's fast form, which does
 // not clamp, makes of M itself.
 static bool fast_form_ends_at_the_top(const QuantScalars& q, uint32_t g, uint32_t wd) {
@@ -251,7 +271,7 @@ int main() {
   bad += check_pieces(1ull << 10, 1) + check_pieces(1ull << 34, 1) + check_pieces((1ull << 34) + 1024, 2);
   bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
   bad += check_xcd_tile<2>() + check_xcd_tile<3>() + check_xcd_tile<4>() + check_xcd_tile<6>();
-  bad += check_whole_route() + check_inv_whole_14() + check_last_first();
+  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints();
   // the uniform quantizer's groups of coordinates: the limits, and that bf16 without error feedback has none
   for (bool bf16 : {false, true}) bad += !uniform_one_group(1 << 20, bf16, true) || uniform_one_group((1 << 20) + 1024, bf16, true);
   bad += !uniform_one_group(1 << 22, false, false) || uniform_one_group((1 << 22) + 1024, false, false);

@@ -143,6 +143,28 @@ def test_sums_of_any_width(b, g, n):
         assert np.array_equal(R.agg_numpy(), o.aggregate(P, list(pk)))
 
 
+@pytest.mark.parametrize("b,g,agg_bits,n", [(4, 30, 8, 8), (4, 15, 7, 8), (4, 30, 9, 9), (4, 100, 16, 8), (2, 8, 8, 16),
+                                            (2, 8, 16, 16), (3, 31, 9, 11), (1, 1, 6, 32), (5, 36, 8, 7), (8, 255, 16, 4)])
+def test_sums_of_streams_beyond_the_cache(b, g, agg_bits, n):
+    """Streams of 64 MB and more together go past the caches: the whole against slices of it, which do not, bit for bit; the
+    last workgroup is mostly empty."""
+    block, K = 1 << 10, (1 << 14) + 1
+    T = [round(i * g / ((1 << b) - 1)) for i in range(1 << b)]
+    assert n * block * K * b // 8 >= 1 << 26
+    _, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, table=T)
+    gen = torch.Generator(device=DEV).manual_seed(b * 64 + n)
+    packed = [torch.randint(0, 256, (block * K * b // 8,), dtype=torch.uint8, device=DEV, generator=gen) for _ in range(n)]
+    agg = torch.zeros(block * K * agg_bits // 8, dtype=torch.uint8, device=DEV)
+    api.thc_aggregate(L, packed, agg)
+    step = 1 << 12
+    for k in range(0, K, step):
+        m = min(step, K - k)
+        _, S = both_params(block * m, block, n, b=b, g=g, agg_bits=agg_bits, table=T)
+        part = torch.zeros(block * m * agg_bits // 8, dtype=torch.uint8, device=DEV)
+        api.thc_aggregate(S, [p[k * block * b // 8:(k + m) * block * b // 8].clone() for p in packed], part)
+        assert torch.equal(part, agg[k * block * agg_bits // 8:(k + m) * block * agg_bits // 8])
+
+
 @pytest.mark.parametrize("log2_block,K,n,b,g,agg_bits,bf16,ef", [
     (10, 1, 1, 4, 30, 8, False, True), (10, 19, 2, 3, 21, 6, True, True), (11, 5, 2, 4, 30, 16, False, True),
     (12, 3, 3, 8, 255, 10, True, True), (13, 2, 2, 4, 30, 8, True, True), (14, 1, 1, 4, 30, 5, False, True),
