@@ -340,8 +340,16 @@ template <int R> struct LaunchBigInvHi {
 
 template <int SB, bool TABLE>
 void launch_big_inv_lo_k(const BigInvLoArgs& a, bool split, dim3 grid, hipStream_t s) {
-  if (split) k_big_inv_lo<SB, TABLE, true><<<grid, dim3(NT), 0, s>>>(a);
-  else k_big_inv_lo<SB, TABLE, false><<<grid, dim3(NT), 0, s>>>(a);
+  const dim3 blk(NT);
+  if constexpr (!TABLE) {
+    if (through_inverse(a.d, grid.y)) {
+      if (split) k_big_inv_lo<SB, TABLE, true, THROUGH><<<grid, blk, 0, s>>>(a);
+      else k_big_inv_lo<SB, TABLE, false, THROUGH><<<grid, blk, 0, s>>>(a);
+      return;
+    }
+  }
+  if (split) k_big_inv_lo<SB, TABLE, true, STREAM><<<grid, blk, 0, s>>>(a);
+  else k_big_inv_lo<SB, TABLE, false, STREAM><<<grid, blk, 0, s>>>(a);
 }
 
 void launch_big_inv_lo(const Plan& pl, const BigInvLoArgs& a, uint32_t W, hipStream_t s) {
@@ -624,6 +632,7 @@ void run_forward_whole(const Forward& f, const Plan& pl, Whole route) {
     }
     a.range_M = range_M + x0 / p->block;
     a.d = len;
+    a.stream = stream_blocks(len, f.W, bf16);
     a.j0 = base_coord(p) + x0;
     switch (pl.L) {
       case 10: launch_whole<10>(a, bf16, ef, find, f.W, f.s); break;
@@ -1086,6 +1095,7 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.pmax = pmax;
     a.d = p->d;
     a.L1 = (uint32_t)pl.L1;
+    a.stream = stream_norms(p->d, p->n, bf16, ef != nullptr);
     const dim3 grid((unsigned)tiles_of(p->d), p->n), blk(NT);
     if (bf16) { if (ef) k_minmax<true, true><<<grid, blk, 0, s>>>(a); else k_minmax<true, false><<<grid, blk, 0, s>>>(a); }
     else { if (ef) k_minmax<false, true><<<grid, blk, 0, s>>>(a); else k_minmax<false, false><<<grid, blk, 0, s>>>(a); }

@@ -11,6 +11,31 @@
 // has 32 to 64 loads in flight.  Blocks up to 2^21 are as fast or faster with the smaller tiles (first pass 740 us
 // against 740 to 780 us at 64 blocks of 2^20 x 8 vectors), and small calls keep more compute units busy with them.
 #pragma once
+// Transform passes on tiles of 2^15 coordinates, 64 values per thread: blocks of 2^22 (large calls) to 2^25.
+//
+// What bounds it: bytes.  Every pass over a block reads and writes (or reads) each value once at what HBM takes, 5 to
+// 6 TB/s here, so fewer passes is the gain: 15 + 10 stages make two passes of a 2^25-point block, where tiles of 8192
+// (13 + 6 + 6) make three; and blocks of 2^22 get rows of 256 columns (1 KB) in the last pass instead of 16 (64 bytes,
+// which over-fetches).  Measured, ResNet-50-shaped round (2^25, n = 8, error feedback): 3050 us with 8192-coordinate
+// tiles, 2160 us with these; the EF chain of GPT-2-shaped blocks (2^22, n = 32): 15.1 ms and 13.5 ms.
+//
+// Why this shape.  64 values x 512 threads is what two workgroups per compute unit can keep in registers (128 each);
+// the tile goes through LDS in two independent halves of 64 KB.  Four waves per SIMD are enough here because a wave
+// has 32 to 64 loads in flight.  Blocks up to 2^21 are as fast or faster with the smaller tiles (first pass 740 us
+// against 740 to 780 us at 64 blocks of 2^20 x 8 vectors), and small calls keep more compute units busy with them.
+#pragma once
+#ifndef BHLM
+#define BHLM KEEP
+#endif
+#ifndef BHGM
+#define BHGM KEEP
+#endif
+#ifndef BHEM
+#define BHEM KEEP
+#endif
+#ifndef BHSM
+#define BHSM KEEP
+#endif
 
 #include "thc_bigmap.hpp"
 #include "thc_inverse.hpp"
@@ -87,12 +112,12 @@ struct BigLoArgs {
   uint32_t round, k0, k1;
 };
 
-template <bool BF16>
+template <bool BF16, Mem M = KEEP>
 __device__ __forceinline__ void load_grad16(const void* g, uint64_t j, float (&v)[16]) {
   if constexpr (BF16) {
 #pragma unroll
     for (int e = 0; e < 16; e += 8) {
-      const uint4 r = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(g) + j + e);
+      const uint4 r = load_u4<M>(static_cast<const uint16_t*>(g) + j + e);
       const uint32_t w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -137,7 +162,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
   auto load = [&](int h) {   // operands of one half of the tile
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
-      load_grad16<BF16>(grad, tp + big_p<XO>((2 * h + y) << 13), v[2 * h + y]);
+      load_grad16<BF16, BF16 && EF ? STREAM : KEEP>(grad, tp + big_p<XO>((2 * h + y) << 13), v[2 * h + y]);
       if constexpr (EF) load_grad16<false>(ef, tp + big_p<XO>((2 * h + y) << 13), e[y]);
     }
   };
@@ -201,7 +226,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
           for (int k = 0; k < 16; ++k) x[y][k] = flip_bit(v[2 * h + y][k], bits, k);
         }
       },
-      [&](int k, float r) { dst[big_p<XO>(k << 9) + t] = r; });
+      [&](int k, float r) { store_f<THROUGH>(&dst[big_p<XO>(k << 9) + t], r); });
   if (a.partials) {          // the sums over a wave and over the waves, while the stores drain
     const double s = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
     if (lane < 4) sm.wsum[lane][wave] = s;
@@ -268,22 +293,21 @@ __device__ __forceinline__ uint32_t big_hi_tile(const Walk& w) {
   return xcd_tile<R == 10 ? 6 : R == 7 && XO && EF ? 4 : 3>(walk_x(w), gridDim.x);
 }
 
-template <int R, bool XO>
+template <class H, bool XO, Mem M = KEEP>
 __device__ __forceinline__ void big_hi_load(const float* src, int t, float (&v)[8][8]) {
-  constexpr BigLayout m = BigHi<R>::first();
-  const float* const p = src + BigHi<R>::template thread_off<XO, 0>(m, t);
+  constexpr BigLayout m = H::first();
+  const float* const p = src + H::template thread_off<XO, 0>(m, t);
 #pragma unroll
   for (int k = 0; k < 8; ++k)
 #pragma unroll
-    for (int e = 0; e < 8; e += 4) {
-      const float4 r = *reinterpret_cast<const float4*>(p + BigHi<R>::template slot_off<XO>(m, k) + e);
-      v[k][e] = r.x; v[k][e + 1] = r.y; v[k][e + 2] = r.z; v[k][e + 3] = r.w;
+    for (int h = 0; h < 2; ++h) {
+      const float4 r = load_f4<M>(p + H::template slot_off<XO>(m, k) + h * H::template half_off<XO>());
+      v[k][4 * h] = r.x; v[k][4 * h + 1] = r.y; v[k][4 * h + 2] = r.z; v[k][4 * h + 3] = r.w;
     }
 }
 
-template <int R>
+template <class H>
 __device__ __forceinline__ void big_hi_stages(float4* lds, int t, float (&v)[8][8]) {
-  using H = BigHi<R>;
   slot_stage<0>(v);
   slot_stage<1>(v);
   slot_stage<2>(v);
@@ -367,7 +391,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_quant(const BigQuantArgs a) {
   const uint32_t ent = a.lut[t & 255];   // requested before the tile, so that the table is made while that travels
   float v[8][8];
   __builtin_amdgcn_sched_barrier(0);
-  big_hi_load<R, XO>(a.x + (uint64_t)vec * a.d + base, t, v);
+  big_hi_load<BigHi<R>, XO>(a.x + (uint64_t)vec * a.d + base, t, v);
   __builtin_amdgcn_sched_barrier(0);
   build_quant_lut(ent, lut, t);
   if (t == 0) {
@@ -378,7 +402,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_quant(const BigQuantArgs a) {
     sm.sCare = careful;
   }
   __syncthreads();
-  big_hi_stages<R>(sm.x, t, v);
+  big_hi_stages<BigHi<R>>(sm.x, t, v);
   const QuantScalars s = *reinterpret_cast<const QuantScalars*>(sm.sQ);
   const bool careful = __builtin_amdgcn_readfirstlane(sm.sCare) != 0;
   constexpr BigLayout m = BigHi<R>::last();
@@ -466,7 +490,9 @@ __device__ __forceinline__ void codes16(const uint8_t* src, uint32_t bits, uint6
   }
 }
 
-template <int SB, bool TABLE, bool XO>
+// HOW the half-transformed vector is stored (see through_inverse).  With error feedback non-temporally at any size: 2^25 x 1
+// 385 us against 383, 4 blocks of 2^23 of one vector 387 against 380.
+template <int SB, bool TABLE, bool XO, Mem HOW>
 __global__ __launch_bounds__(NT, 4) void k_big_inv_lo(const BigInvLoArgs a) {
   __shared__ SmemBigInvLo sm;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -511,12 +537,13 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_lo(const BigInvLoArgs a) {
           for (int e = 0; e < 16; ++e) x[y][e] = TABLE ? sm.tabf[c[e]] : (float)c[e] * step + lo;
         }
       },
-      [&](int k, float r) { dst[big_p<XO>(k << 9) + t] = r; });
+      [&](int k, float r) { store_f<HOW>(&dst[big_p<XO>(k << 9) + t], r); });
 }
 
 // ---------------------------------------------------------------------------------------------
 // Inverse last pass: finish H, scale, diagonal; EFM 0: out = result, 1 / 2: e <- (grad + e) - result with a binary32 /
-// bf16 gradient.
+// bf16 gradient.  Accesses of whole lines, all of them non-temporal: rounds with error feedback 16 blocks of 2^22 x 32 in bf16
+// 13.25 -> 12.87 ms, x 16 in binary32 7.53 -> 7.36, 2 of 2^24 x 4 1117 -> 1053 us, one worker of 4 blocks of 2^23 385 -> 339.
 // ---------------------------------------------------------------------------------------------
 struct BigInvHiArgs {
   const float* x;
@@ -534,32 +561,19 @@ struct alignas(16) SmemBigInvHi {
   uint32_t sgn[BIG_SIGN_WORDS];   // bit (u & 31) of word (row << (C - 5)) + (column >> 5)
 };
 
-template <int EFM>
-__device__ __forceinline__ void load_grad8(const void* g, uint32_t j, float (&x)[8]) {
-  if constexpr (EFM == 2) {
-    const uint4 r = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(g) + j);
-    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      x[2 * k] = __uint_as_float(w[k] << 16);
-      x[2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
-    }
-  } else {
-    const float4 p = *reinterpret_cast<const float4*>(static_cast<const float*>(g) + j);
-    const float4 q = *reinterpret_cast<const float4*>(static_cast<const float*>(g) + j + 4);
-    x[0] = p.x; x[1] = p.y; x[2] = p.z; x[3] = p.w; x[4] = q.x; x[5] = q.y; x[6] = q.z; x[7] = q.w;
-  }
-}
-
 template <int R, bool XO, int EFM>
 __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
-  using H = BigHi<R>;
+  // Rows of 32 columns (R = 10) are whole lines only over two accesses, in either layout.  They keep the eight neighbouring
+  // columns, which measured best there; spread and streamed: 2^25 x 8 with error feedback 2077 -> 2203 us.
+  constexpr bool LINES = R <= 9;
+  constexpr Mem HOW = LINES ? STREAM : KEEP;
+  using H = BigHi<R, LINES>;
   __shared__ SmemBigInvHi sm;
   const int t = threadIdx.x;
   const uint32_t vec = walk_y(a.walk), tile = big_hi_tile<R, XO, EFM != 0>(a.walk);
   const uint64_t base = big_hi_base<R, XO>(tile);
   float v[8][8];
-  big_hi_load<R, XO>(a.x + (uint64_t)vec * a.d + base, t, v);
+  big_hi_load<H, XO, HOW>(a.x + (uint64_t)vec * a.d + base, t, v);
   // the diagonal while the loads travel: one Philox call covers 128 coordinates, or what of them the tile holds
   constexpr int PER = H::C >= 7 ? 4 : 1 << (H::C - 5);    // words of a call that belong to the tile
   for (int i = t; i < BIG_SIGN_WORDS / PER; i += NT) {
@@ -578,7 +592,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
     }
   }
   __syncthreads();
-  big_hi_stages<R>(sm.x, t, v);
+  big_hi_stages<H>(sm.x, t, v);
   constexpr BigLayout m = H::last();
   const uint32_t to = H::template thread_off<XO, 0>(m, t);
   float* const out = static_cast<float*>(const_cast<void*>(a.out.p[vec])) + base;
@@ -595,37 +609,39 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
   }
   // error feedback: the next eight values of the gradient and of the buffer are requested before this step's stores,
   // which the compiler must not move them across
-  float g[8], e[8];
-  if constexpr (EFM != 0) {
-    load_grad8<EFM>(grad, to, g);
-    load_grad8<1>(out, to, e);
-  }
+  constexpr uint32_t half = H::template half_off<XO>();
+  float4 g[2], e[2];
+  auto operands = [&](uint32_t o, float4 (&gn)[2], float4 (&en)[2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      gn[h] = load_grad4<EFM == 2, HOW>(grad, o + h * half);
+      en[h] = load_f4<HOW>(out + o + h * half);
+    }
+  };
+  if constexpr (EFM != 0) operands(to, g, e);
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const uint32_t so = H::template slot_off<XO>(m, k);
-    float gn[8], en[8];
+    float4 gn[2], en[2];
     if constexpr (EFM != 0) {
-      if (k < 7) {
-        const uint32_t sn = H::template slot_off<XO>(m, k + 1);
-        load_grad8<EFM>(grad, to + sn, gn);
-        load_grad8<1>(out, to + sn, en);
-      }
+      if (k < 7) operands(to + H::template slot_off<XO>(m, k + 1), gn, en);
     }
     uint32_t kw = 0;
     for (int s = 0; s < 3; ++s)
       if (k & (1 << s)) kw |= m.slot[s] >= 0 ? 1u << (H::C - 5 + m.slot[s]) : 1u << (-1 - m.slot[s] - 5);
-    const uint32_t bits = sm.sgn[tword | kw] >> tbit;
-    float r[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      r[i] = flip_bit(v[k][i] * a.c, bits, i);
-      if constexpr (EFM != 0) r[i] = (g[i] + e[i]) - r[i];
+    for (int h = 0; h < 2; ++h) {
+      // the second half of the row lies in a word of its own, the second four neighbours in the same
+      const uint32_t bits = sm.sgn[tword | kw | (LINES ? h << (LINES ? H::C - 6 : 0) : 0)] >> (tbit + (LINES ? 0 : 4 * h));
+      float4 r = make_float4(flip_bit(v[k][4 * h] * a.c, bits, 0), flip_bit(v[k][4 * h + 1] * a.c, bits, 1),
+                             flip_bit(v[k][4 * h + 2] * a.c, bits, 2), flip_bit(v[k][4 * h + 3] * a.c, bits, 3));
+      if constexpr (EFM != 0)
+        r = make_float4((g[h].x + e[h].x) - r.x, (g[h].y + e[h].y) - r.y, (g[h].z + e[h].z) - r.z, (g[h].w + e[h].w) - r.w);
+      store_f4<HOW>(out + to + so + h * half, r);
     }
-    *reinterpret_cast<float4*>(out + to + so) = make_float4(r[0], r[1], r[2], r[3]);
-    *reinterpret_cast<float4*>(out + to + so + 4) = make_float4(r[4], r[5], r[6], r[7]);
     if constexpr (EFM != 0) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) { g[i] = gn[i]; e[i] = en[i]; }
+      for (int h = 0; h < 2; ++h) { g[h] = gn[h]; e[h] = en[h]; }
     }
   }
 }

@@ -35,7 +35,9 @@ struct BigLayout {
   int thr[9];
 };
 
-template <int R>
+// A thread's eight values of a slot are columns 0..7 (what one Philox call and one packed word cover), or, SPREAD, columns 0..3
+// of each half of the row: a wave's 16-byte accesses then take whole lines, where neighbouring eights take every other 16 bytes.
+template <int R, bool SPREAD = false>
 struct BigHi {
   static_assert(R >= 7 && R <= 10, "the last pass takes 7 to 10 row bits");
   static constexpr int C = LOG_BIG - R;
@@ -44,9 +46,9 @@ struct BigHi {
   // columns first, then the row bits that are still missing
   static constexpr BigLayout first() {
     BigLayout m{{0, 1, 2}, {}};
-    int c = 3, q = 5;
+    int c = SPREAD ? 2 : 3, q = 5;
     for (int i = 0; i < 9; ++i)
-      m.thr[i] = i == 4 ? 3 : i == 5 ? 4 : c < C ? -1 - c++ : q++;
+      m.thr[i] = i == 4 ? 3 : i == 5 ? 4 : c < C - SPREAD ? -1 - c++ : q++;
     return m;
   }
   static constexpr void swap(BigLayout& m, int slot, int thr) {
@@ -85,6 +87,10 @@ struct BigHi {
     if (E >= 5) swap(m, 1, 5);
     return m;
   }
+
+  // offset of a slot's fifth value from its first
+  template <bool XO>
+  static constexpr uint32_t half_off() { return SPREAD ? big_u<XO>(1u << (C - 1)) : 4u; }
 
   template <bool XO>
   static constexpr uint32_t what_off(int what) {

@@ -351,7 +351,7 @@ __device__ __forceinline__ void finish_values(const float (&v)[N], float c, floa
   for (int i = 0; i < N; ++i) {
     float r = flip(v[i] * c, bit(i));
     if constexpr (EFM != 0) r = (x[i] + e[i]) - r;
-    out[off(i)] = r;
+    store_f<STREAM>(&out[off(i)], r);
   }
 }
 

@@ -257,6 +257,8 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // with error feedback (150 MB) 0.99, 100 blocks (400 MB) 0.93.
 // through_inverse: the inverse's first pass writes through the L2, or else non-temporally.  Through over non-temporal: 4 MB 0.98,
 // 100 MB 0.98, 128 MB 1.01, 400 MB 1.02, 800 MB 1.04, 1 GB 1.00.
+// stream_blocks: the gradients of blocks of up to 2^14 that go block by block, behind the norms.  Time of streamed over kept, all
+// of 1 GB: 2^10 0.99, 2^13 0.99, 2^14 0.99 to 1.00, 0.99 with error feedback; bf16 with error feedback, 2^13, 1.02.
 // stream_sums: the aggregation.  Time of streamed over kept, by the streams' bytes together: 34 MB 1.05, 67 MB 0.99, 105 MB 1.00,
 // 168 MB 0.90, 252 MB 0.90, 277 MB 0.85, 840 MB 0.85 to 0.95.
 constexpr uint64_t MB = 1ull << 20;
@@ -266,6 +268,7 @@ inline bool stream_inputs(uint64_t len, uint32_t W, bool bf16, bool ef) {
   return input_bytes(len, W, bf16, ef) >= (ef ? 128 : 64) * MB;
 }
 inline bool stream_norms(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 64 * MB; }
+inline bool stream_blocks(uint64_t len, uint32_t W, bool bf16) { return !bf16 && input_bytes(len, W, bf16, false) >= 64 * MB; }
 inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
 inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 64 * MB; }
 

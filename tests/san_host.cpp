@@ -47,9 +47,9 @@ static int check_cover(const TileMap& m, bool first_pass_rows) {
 
 // Tiles of 2^15 coordinates: the tiles of either pass cover a block once, the first does the first 15 bits of the
 // stage order and the last pass the rest, each with the row bit it is meant for in the slot index when its turn comes.
-template <int R, bool XO>
+template <int R, bool XO, bool SPREAD = false>
 static int check_big() {
-  using H = BigHi<R>;
+  using H = BigHi<R, SPREAD>;
   constexpr int L = LOG_BIG + R;
   std::vector<uint32_t> order;                     // offset each stage pairs
   if (XO) {
@@ -82,8 +82,10 @@ static int check_big() {
     add(hi, H::template slot_off<XO>(a, 1 << i));
     add(out, H::template slot_off<XO>(e, 1 << i));
   }
-  const uint64_t most = (1ull << L) - 8;          // the low three bits are a thread's eight columns
-  bad += lo != most + 7 || hi != most || out != most;
+  add(hi, H::template half_off<XO>());
+  add(out, H::template half_off<XO>());
+  const uint64_t most = (1ull << L) - 4;          // the low two bits are four of a thread's eight columns
+  bad += lo != most + 3 || hi != most || out != most;
   return bad + (big_hi_base<R, XO>(3u << R | 1) != (3ull << L) + big_hi_base<R, XO>(1));
 }
 
@@ -256,6 +258,8 @@ int main() {
   int bad = 0;
   bad += check_quant_form();
   bad += check_big<7, false>() + check_big<7, true>() + check_big<8, false>() + check_big<8, true>();
+  bad += check_big<7, false, true>() + check_big<7, true, true>() + check_big<8, true, true>() + check_big<9, false, true>();
+  bad += check_big<9, true, true>() + check_big<8, false, true>();
   bad += check_big<9, false>() + check_big<9, true>() + check_big<10, false>() + check_big<10, true>();
   const uint64_t M22 = 1ull << 22;
   bad += check_groups(M22, 64 * M22, 2 * M22, 1, false, false, false, false);   // thc_decompress_noalloc: 32 MB at a time
