@@ -92,7 +92,8 @@ typedef struct thc_params {
   uint32_t first_block;/* index, in the whole vector, of the first block these buffers hold (0 for a whole vector) */
   uint32_t group_log2; /* 0 = default (29).  Where a transform goes pass by pass, the passes walk a vector in groups of
                           whole blocks of about 2^group_log2 coordinates (over all vectors of the call), 10..40: it
-                          sizes the workspace (which therefore does not grow with d); never a result */
+                          sizes the workspace (which therefore does not grow with d); never a result.  By default the
+                          groups are smaller than what the workspace holds where that is faster */
   uint32_t single_launch; /* 0 or 1.  1: thc_compress and thc_compress_all run all passes of all blocks in ONE kernel
                           launch where they can (split stage order, blocks of 2^17 .. 2^22, at least four blocks,
                           group_log2 = 0), blocks following each other through a ring of a few block-sized slots: a

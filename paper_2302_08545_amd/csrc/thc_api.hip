@@ -51,8 +51,8 @@ int validate(const thc_params* p) {
 // lut          device copy of the quantizer's grid-cell table, 256 words
 //
 // Launch-by-launch path: a group is a run of whole blocks of every vector in the call, sized so that the group's
-// intermediate (all vectors of the call together) is about 2^group_log2 coordinates; the workspace does not grow
-// with d.  Random streams are indexed by global coordinate, so the grouping never changes a result.
+// intermediate (all vectors of the call together) is about 2^group_log2 coordinates, or by default what measured best
+// (walk_coords); the workspace does not grow with d.  Random streams are indexed by global coordinate, so the grouping never changes a result.
 constexpr size_t WS_HEADER_BIG = 1u << 21, WS_HEADER_SMALL = 4096;
 constexpr uint32_t DEFAULT_GROUP_LOG2 = 29;
 constexpr uint32_t DEFAULT_GROUP_LOG2_SMALL = 25;   // with thc_params.single_launch: the caller is after a small workspace
@@ -68,6 +68,19 @@ uint64_t group_coords(const thc_params* p, uint32_t W) {
   if (gc < p->block) gc = p->block;
   if (gc > p->d) gc = p->d;
   return gc;
+}
+
+// Coordinates of each of W vectors that one group takes, by default; at most what the ring holds.  The smaller a group, the more
+// of what its first pass writes is still in the memory-side cache when the last one reads it; against that stand two or three
+// launches a group.  Blocks of up to 2^21, groups of 2^29 / 2^28 / 2^27 / 2^26 coordinates, us: 256 x 8 vectors of 2^20 (half of it
+// padding) 5070 / 4950 / 4813 / 4788, 321 x 16 12250 / 12090 / 12000 / 12160, 512 x 8 of 2^17 1259 / 1245 / 1231 / 1258, with error
+// feedback 64 x 4 1802 / 1799 / 1784 / 1847.  A walk in steps of exactly 2^27 took 3 % more where it left a short rest (20 x 8):
+// hence even shares.  The decompression, two launches a group: rounds of one worker, 200 blocks of 2^20, 997 us at 2^29, 990 at
+// 2^27, 968 at 2^26 (256 MB), 978 at 2^25, and 1005 where shares exceed 2^26 a little.  Blocks of 2^22 and more lose up to 7 % (8 x 8 of 2^23) and keep their groups.
+uint64_t walk_coords(const thc_params* p, uint32_t W, bool inverse) {
+  const uint64_t most = group_coords(p, W);
+  if (p->group_log2 || p->single_launch || p->block >= (1ull << 22)) return most;
+  return std::min(most, even_share(p->d, p->block, W, 1ull << (inverse ? 26 : 27), inverse));
 }
 
 // Shape of the single-launch sweep over W vectors (thc_pipeline.hpp), or ok = false where it does not apply:
@@ -663,7 +676,7 @@ void run_forward(const Forward& f) {
   }
   const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
   const size_t in_size = bf16 ? 2 : 4;
-  const uint64_t gc = group_coords(p, f.W);
+  const uint64_t gc = walk_coords(p, f.W, false);
   const WsLayout wl = ws_layout(f.ws, p, pl, f.efs != nullptr);
   float* const slot = wl.ring;
   double* const partials = wl.partials;
@@ -888,7 +901,7 @@ int thc_describe_plan(const thc_params* p, uint32_t* out, size_t cap_records) {
   };
   int first[16];
   for (int i = 0; i < pl.L1; ++i) first[i] = (pl.split && i >= 10) ? i + 3 : i;
-  put(0, pl.split ? 3u : 0u, first, pl.L1, lo_tilemap(pl, group_coords(p, p->n)));
+  put(0, pl.split ? 3u : 0u, first, pl.L1, lo_tilemap(pl, walk_coords(p, p->n, false)));
   for (int m = 0; m < pl.nmid; ++m) put(1 + m, 1u, pl.bits[m], pl.mid[m], pl.midmap[m]);
   put(npass - 1, 2u, pl.bits[pl.nmid], pl.R, pl.hi);
   return npass;
@@ -994,7 +1007,7 @@ int thc_decompress(const thc_params* p, uint64_t round, const void* agg, const f
   if (round >> 32 || !agg || !range_M || !out || !ws) return THC_EINVAL;
   if (!aligned16(agg) || !aligned16(out) || !aligned16(ws)) return THC_EINVAL;
   const Plan pl = make_plan(p->block, p->stage_order);
-  run_decompress(p, pl, round, agg, range_M, out, ws_layout(ws, p, pl, false).ring, group_coords(p, 1),
+  run_decompress(p, pl, round, agg, range_M, out, ws_layout(ws, p, pl, false).ring, walk_coords(p, 1, true),
                  static_cast<hipStream_t>(stream));
   return check_launch();
 }

@@ -295,6 +295,16 @@ inline void for_pieces(uint64_t d, Piece&& piece) {
   for (uint64_t x0 = 0; x0 < d; x0 += LAUNCH_COORDS) piece(x0, d - x0 < LAUNCH_COORDS ? d - x0 : LAUNCH_COORDS);
 }
 
+// Coordinates of each of W vectors in one step of a walk over d of them: even shares of whole blocks, and of whole 2^20
+// coordinates (the first pass's tiling wants 2^19, see lo_tilemap).  A step takes at least `target` coordinates of all vectors
+// together, or with `most` at most that, where the vector and the units allow it.
+inline uint64_t even_share(uint64_t d, uint64_t block, uint32_t W, uint64_t target, bool most) {
+  const uint64_t unit = block > (1ull << 20) ? block : 1ull << 20;
+  const uint64_t whole = (W * d + (most ? target - 1 : 0)) / target, steps = whole ? whole : 1;
+  const uint64_t share = ((d + steps - 1) / steps + unit - 1) / unit * unit;
+  return share < d ? share : d;
+}
+
 // The groups of whole blocks, `gc` coordinates of each of W vectors, in which a call walks its d coordinates:
 // group(first coordinate, coordinates, whether the forward and the inverse launches take the larger tiles).
 template <class Group>

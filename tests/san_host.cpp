@@ -198,6 +198,25 @@ static int check_last_first() {
   return bad;
 }
 
+// even shares cover the vector in whole blocks, at least (or at most) the target where that can be
+static int check_even_share() {
+  int bad = 0;
+  for (uint64_t block : {1ull << 15, 1ull << 20, 1ull << 21})
+    for (uint32_t W : {1u, 3u, 8u, 64u})
+      for (uint64_t K : {1ull, 2ull, 7ull, 41ull, 63ull, 64ull, 65ull, 321ull, 4097ull})
+        for (bool most : {false, true}) {
+          const uint64_t d = K * block, T = 1ull << 26, s = even_share(d, block, W, T, most);
+          const uint64_t unit = block > (1ull << 20) ? block : 1ull << 20;
+          bad += !s || s > d || s % block || (s < d && s % (1ull << 19));
+          bad += most ? s > unit && W * (s - unit) >= T : s < d && W * s < T;
+          bad += W * d < T && s != d;
+          bad += W * d >= 2 * T && d >= 4 * unit && s == d;
+        }
+  return bad + (even_share(20ull << 20, 1ull << 20, 8, 1ull << 27, false) != 20ull << 20) +
+         (even_share(41ull << 20, 1ull << 20, 16, 1ull << 27, false) != 9ull << 20) +
+         (even_share(100ull << 20, 1ull << 20, 1, 1ull << 26, true) != 50ull << 20);
+}
+
 // ... and of the cache hints: a call just below each limit and one at it.
 static int check_hints() {
   int bad = 0;
@@ -275,7 +294,7 @@ int main() {
   bad += check_pieces(1ull << 10, 1) + check_pieces(1ull << 34, 1) + check_pieces((1ull << 34) + 1024, 2);
   bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
   bad += check_xcd_tile<2>() + check_xcd_tile<3>() + check_xcd_tile<4>() + check_xcd_tile<6>();
-  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints();
+  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints() + check_even_share();
   // the uniform quantizer's groups of coordinates: the limits, and that bf16 without error feedback has none
   for (bool bf16 : {false, true}) bad += !uniform_one_group(1 << 20, bf16, true) || uniform_one_group((1 << 20) + 1024, bf16, true);
   bad += !uniform_one_group(1 << 22, false, false) || uniform_one_group((1 << 22) + 1024, false, false);
