@@ -323,8 +323,8 @@ __global__ __launch_bounds__(256) void k_uniform_dequant(const UDequantArgs a) {
       const uint64_t blk = j >> a.L;
       const float M = a.range_M[blk], m = lower_of(a.range_m, blk, M);
       const float step = (float)(((double)M - (double)m) / (double)a.divisor);
-      *reinterpret_cast<float4*>(a.out + j) =
-          make_float4((float)y[0] * step + m, (float)y[1] * step + m, (float)y[2] * step + m, (float)y[3] * step + m);
+      store_f4<STREAM>(a.out + j, make_float4((float)y[0] * step + m, (float)y[1] * step + m, (float)y[2] * step + m,
+                                              (float)y[3] * step + m));
     }
     return;
   }
