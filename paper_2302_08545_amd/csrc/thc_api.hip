@@ -593,8 +593,16 @@ void launch_whole_k(const WholeArgs& a, bool ef, bool find, dim3 grid, hipStream
 }
 
 template <int L>
-void launch_whole(const WholeArgs& a, bool bf16, bool ef, bool find, uint32_t W, hipStream_t s) {
+void launch_whole(const WholeArgs& a, bool bf16, bool ef, bool find, bool split, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)((a.d + (1ull << WholeTile<L>::LOG) - 1) >> WholeTile<L>::LOG), W);
+  if constexpr (L == 14) {
+    if (find && split) {
+      const dim3 twice(2 * grid.x, W), blk(WholeTile<L>::N);
+      if (bf16) k_whole<L, true, false, true, true><<<twice, blk, 0, s>>>(a);
+      else k_whole<L, false, false, true, true><<<twice, blk, 0, s>>>(a);
+      return;
+    }
+  }
   if (bf16) launch_whole_k<L, true>(a, ef, find, grid, s);
   else launch_whole_k<L, false>(a, ef, find, grid, s);
 }
@@ -646,13 +654,14 @@ void run_forward_whole(const Forward& f, const Plan& pl, Whole route) {
     a.range_M = range_M + x0 / p->block;
     a.d = len;
     a.stream = stream_blocks(len, f.W, bf16);
+    const bool split = whole_split(pl, tiles_of(len), f.W);
     a.j0 = base_coord(p) + x0;
     switch (pl.L) {
-      case 10: launch_whole<10>(a, bf16, ef, find, f.W, f.s); break;
-      case 11: launch_whole<11>(a, bf16, ef, find, f.W, f.s); break;
-      case 12: launch_whole<12>(a, bf16, ef, find, f.W, f.s); break;
-      case 13: launch_whole<13>(a, bf16, ef, find, f.W, f.s); break;
-      default: launch_whole<14>(a, bf16, ef, find, f.W, f.s); break;
+      case 10: launch_whole<10>(a, bf16, ef, find, split, f.W, f.s); break;
+      case 11: launch_whole<11>(a, bf16, ef, find, split, f.W, f.s); break;
+      case 12: launch_whole<12>(a, bf16, ef, find, split, f.W, f.s); break;
+      case 13: launch_whole<13>(a, bf16, ef, find, split, f.W, f.s); break;
+      default: launch_whole<14>(a, bf16, ef, find, split, f.W, f.s); break;
     }
   });
 }

@@ -190,6 +190,12 @@ inline Whole whole_route(const Plan& pl, uint64_t tiles, uint32_t W, bool ef, bo
   return even || wg >= 4096 ? Whole::NORMS : Whole::NO;
 }
 
+// FIND at 2^14: whether two workgroups share a block's quantization.  A call of a few blocks leaves most of the chip idle, and a
+// workgroup's chain is long: halving its longest part pays for a second transform.  Time of a round over that of one workgroup
+// a block, by workgroups before the split: 1 0.94, 4 0.97, 8 0.96 (19.6 -> 18.8 us), 32 0.96, 64 0.98, 128 1.02 to 1.03.  Four to a
+// block 0.96 at 8 and 32, 1.05 at 64; blocks of up to 2^13, 512 threads to a workgroup, 0.99 to 1.00 at any size.
+inline bool whole_split(const Plan& pl, uint64_t tiles, uint32_t W) { return pl.L == 14 && (tiles / 2) * W <= 64; }
+
 // Blocks of 2^14, inverse transform in one launch: a block to a workgroup of 1024 threads (k_inv_whole) or two blocks to
 // one of 512 (k_big_inv_whole).  With few blocks the first has half the work on each of twice the compute units; 512 of its
 // workgroups are on the chip at once, and 1024 of the other's, which is why neither is better throughout; and it is the faster

@@ -83,8 +83,10 @@ __device__ __forceinline__ double whole_block_sum(const double* wsum, int k) {
   }
 }
 
-template <int L, bool BF16, bool EF, bool FIND>
+// SPLIT: two workgroups to a tile, both of which transform all of it and quantize half (see whole_split).
+template <int L, bool BF16, bool EF, bool FIND, bool SPLIT = false>
 __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(const WholeArgs a) {
+  static_assert(!SPLIT || FIND, "small calls");
   static_assert(!(EF && FIND), "the buffers would be read by some workgroups while others write them");
   using T = WholeTile<L>;
   constexpr int N = T::N;
@@ -95,7 +97,8 @@ __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(c
   QuantScalars* const sQ = reinterpret_cast<QuantScalars*>(sm.sQ);
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const uint32_t vec = blockIdx.y;
-  const uint64_t off = (uint64_t)xcd_tile<L == 14 ? 2 : 3>(blockIdx.x, gridDim.x) << T::LOG;
+  const uint32_t part = SPLIT ? blockIdx.x & 1u : 0u, tile = blockIdx.x >> SPLIT;
+  const uint64_t off = (uint64_t)xcd_tile<L == 14 ? 2 : 3>(tile, gridDim.x >> SPLIT) << T::LOG;
   // the first pass's share of a thread, tile by tile of 8192
   const int first = (t >> 9) << 13 | 4 * (t & 511);
 
@@ -149,7 +152,7 @@ __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(c
       if constexpr (FIND) {
         const double s = (uint32_t)lane < a.n ? whole_block_sum<L>(sm.wsum[lane], bt) : 0.0;
         M = range_from_sum(wave_largest(s), a.t_p, L);
-        if (lane == 0 && vec == 0) a.range_M[blk] = M;
+        if (lane == 0 && vec == 0 && part == 0) a.range_M[blk] = M;
       } else {
         M = a.range_M[blk];
       }
@@ -185,8 +188,8 @@ __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(c
   lds_stages<2, L, false, PAD, N>(lds, t, [](int, int, float) {});
   __syncthreads();
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int idx = 8 * (t + N * h), k = T::BLOCKS > 1 ? idx >> L : 0;
+  for (int h = 0; h < (SPLIT ? 1 : 2); ++h) {
+    const int idx = 8 * (t + N * (SPLIT ? (int)part : h)), k = T::BLOCKS > 1 ? idx >> L : 0;
     const uint64_t j = off + idx;
     const float4 p0 = *reinterpret_cast<const float4*>(&lds[phys<PAD>(idx)]);
     const float4 p1 = *reinterpret_cast<const float4*>(&lds[phys<PAD>(idx + 4)]);

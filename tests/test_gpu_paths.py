@@ -232,7 +232,10 @@ def test_norms_are_added_up_in_one_order_whatever_the_tile(log2_block, K, n, bf1
     (14, 32, 8, 4, 30, False, False), (14, 28, 8, 4, 30, False, False), (14, 64, 8, 2, 3, True, False),
     (14, 512, 1, 4, 30, False, False), (14, 513, 1, 4, 30, False, False), (14, 64, 4, 4, 30, False, True),
     (14, 65, 4, 4, 30, False, True), (14, 65, 4, 3, 21, True, True), (14, 512, 4, 4, 30, False, False),
-    (14, 512, 4, 4, 30, True, True)])
+    (14, 512, 4, 4, 30, True, True),
+    # two workgroups to a block: the fewest, 64 of them before the split, one more
+    (14, 1, 1, 4, 30, False, False), (14, 16, 4, 3, 21, True, False), (14, 17, 4, 4, 30, False, False),
+    (14, 21, 3, 8, 255, False, False), (14, 64, 1, 2, 8, False, False), (14, 65, 1, 4, 30, True, False)])
 def test_worker_side_block_by_block(log2_block, K, n, b, g, bf16, ef):
     """Blocks of up to 2^14, whose worker side is one launch once the range is known: thc_compress_all gives what
     thc_prepare_range and thc_compress give, bit for bit, whichever way its range comes about, and both are the oracle's.
