@@ -4,38 +4,13 @@
 // 6 TB/s here, so fewer passes is the gain: 15 + 10 stages make two passes of a 2^25-point block, where tiles of 8192
 // (13 + 6 + 6) make three; and blocks of 2^22 get rows of 256 columns (1 KB) in the last pass instead of 16 (64 bytes,
 // which over-fetches).  Measured, ResNet-50-shaped round (2^25, n = 8, error feedback): 3050 us with 8192-coordinate
-// tiles, 2160 us with these; the EF chain of GPT-2-shaped blocks (2^22, n = 32): 15.1 ms and 13.5 ms.
+// tiles, 2072 us with these; the EF chain of GPT-2-shaped blocks (2^22, n = 32): 15.1 ms and 12.8 ms.
 //
 // Why this shape.  64 values x 512 threads is what two workgroups per compute unit can keep in registers (128 each);
 // the tile goes through LDS in two independent halves of 64 KB.  Four waves per SIMD are enough here because a wave
 // has 32 to 64 loads in flight.  Blocks up to 2^21 are as fast or faster with the smaller tiles (first pass 740 us
 // against 740 to 780 us at 64 blocks of 2^20 x 8 vectors), and small calls keep more compute units busy with them.
 #pragma once
-// Transform passes on tiles of 2^15 coordinates, 64 values per thread: blocks of 2^22 (large calls) to 2^25.
-//
-// What bounds it: bytes.  Every pass over a block reads and writes (or reads) each value once at what HBM takes, 5 to
-// 6 TB/s here, so fewer passes is the gain: 15 + 10 stages make two passes of a 2^25-point block, where tiles of 8192
-// (13 + 6 + 6) make three; and blocks of 2^22 get rows of 256 columns (1 KB) in the last pass instead of 16 (64 bytes,
-// which over-fetches).  Measured, ResNet-50-shaped round (2^25, n = 8, error feedback): 3050 us with 8192-coordinate
-// tiles, 2160 us with these; the EF chain of GPT-2-shaped blocks (2^22, n = 32): 15.1 ms and 13.5 ms.
-//
-// Why this shape.  64 values x 512 threads is what two workgroups per compute unit can keep in registers (128 each);
-// the tile goes through LDS in two independent halves of 64 KB.  Four waves per SIMD are enough here because a wave
-// has 32 to 64 loads in flight.  Blocks up to 2^21 are as fast or faster with the smaller tiles (first pass 740 us
-// against 740 to 780 us at 64 blocks of 2^20 x 8 vectors), and small calls keep more compute units busy with them.
-#pragma once
-#ifndef BHLM
-#define BHLM KEEP
-#endif
-#ifndef BHGM
-#define BHGM KEEP
-#endif
-#ifndef BHEM
-#define BHEM KEEP
-#endif
-#ifndef BHSM
-#define BHSM KEEP
-#endif
 
 #include "thc_bigmap.hpp"
 #include "thc_inverse.hpp"

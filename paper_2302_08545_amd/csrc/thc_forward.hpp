@@ -161,6 +161,8 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
   });
 }
 
+// What bounds it: bytes.  Stored through the L2, read non-temporally (see Mem, stream_inputs) and in groups of 2^27 coordinates it
+// moves 7.0 TB/s between the L2s and memory (9 blocks of 2^20 x 16 vectors, 1.2 GB, 171 us), 6.1 with plain accesses in groups of 2^29.
 // One workgroup per tile (grid = (tiles, n workers)): measured on MI355X this streams faster than a
 // persistent grid with software prefetch, the hardware dispatcher keeps four workgroups per CU in flight.
 // NORM_ONLY: stop after the partial sums of squares (the norm exchange of Alg. 3 on its own): same sums, same order.

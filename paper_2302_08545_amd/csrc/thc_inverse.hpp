@@ -219,7 +219,9 @@ __device__ __forceinline__ void inv_lo_tile(const A& a, uint32_t tile, uint32_t 
   inv_lo_stages<LOG_TILE, XO, SB, TABLE>(a, off, vec, sm, [&](uint32_t o, float val) { store_f<M>(&dst[o], val); });
 }
 
-// What bounds it: writing 4 bytes a coordinate (pure writes reach 5.7 TB/s here).  Decoding is a large part of its
+// What bounds it: writing 4 bytes a coordinate (plain writes to HBM reach 5.7 TB/s here).  M: how they are stored, see
+// through_inverse: 4 x 2^26 coordinates from 8-bit sums 210 us, where 2^28 in one launch with plain stores took 210 and left the next
+// pass 410 instead of 324.  Decoding is a large part of its
 // instructions, so the widths and sources that rounds use have instantiations of their own: 2^28 coordinates from 8-bit
 // sums 251 -> 231 us, from 4-bit indices, whose values are looked up on the block's range, 268 -> 245 us; one block of
 // 2^20 from 4-bit indices 5.4 -> 4.3 us.
