@@ -6,7 +6,7 @@
 namespace thc {
 
 // ---------------------------------------------------------------------------------------------
-// What bounds it in large calls: reading n streams once.  There (stream_sums) M = STREAM: loads and stores non-temporal, the
+// What bounds it in large calls: reading n streams once.  There (from 80 MB on, stream_sums) M = STREAM: loads and stores non-temporal, the
 // sums as whole lines by way of LDS.  16 streams of 33 * 2^20 4-bit indices to 9-bit sums 65.7 -> 55.5 us (5.8 TB/s), of 100 *
 // 2^20 to 16-bit sums 200 -> 171 (6.1 TB/s), 8 of 40 * 2^20 to 8-bit sums 40.0 -> 36.2, 10 of 64 * 2^20 3-bit ones 64.4 -> 57.8.
 // In small calls M = KEEP: the streams have just been written and are in the cache, and latency counts, so four workers'

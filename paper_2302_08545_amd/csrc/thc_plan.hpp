@@ -265,8 +265,9 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // 100 MB 0.98, 128 MB 1.01, 400 MB 1.02, 800 MB 1.04, 1 GB 1.00.
 // stream_blocks: the gradients of blocks of up to 2^14 that go block by block, behind the norms.  Time of streamed over kept, all
 // of 1 GB: 2^10 0.99, 2^13 0.99, 2^14 0.99 to 1.00, 0.99 with error feedback; bf16 with error feedback, 2^13, 1.02.
-// stream_sums: the aggregation.  Time of streamed over kept, by the streams' bytes together: 34 MB 1.05, 67 MB 0.99, 105 MB 1.00,
-// 168 MB 0.90, 252 MB 0.90, 277 MB 0.85, 840 MB 0.85 to 0.95.
+// stream_sums: the aggregation.  Time of streamed over kept, by the streams' bytes together, on three sets of them in turn: 34 MB
+// 1.05, 66 MB 1.02 to 1.19 (0.80 to 0.95 with 3-bit indices, 16-bit sums or 3 workers), 82 MB 0.80 to 0.93, 100 to 190 MB 0.76 to
+// 0.94, 840 MB 0.85 to 0.95; behind the quantizer of the same round 67 MB 0.99, 105 MB 1.00.
 constexpr uint64_t MB = 1ull << 20;
 
 inline uint64_t input_bytes(uint64_t len, uint32_t W, bool bf16, bool ef) { return W * len * ((bf16 ? 2 : 4) + (ef ? 4 : 0)); }
@@ -276,7 +277,7 @@ inline bool stream_inputs(uint64_t len, uint32_t W, bool bf16, bool ef) {
 inline bool stream_norms(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 64 * MB; }
 inline bool stream_blocks(uint64_t len, uint32_t W, bool bf16) { return !bf16 && input_bytes(len, W, bf16, false) >= 64 * MB; }
 inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
-inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 64 * MB; }
+inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB; }
 
 // Uniform quantizer on a vector of d coordinates: one group of eight coordinates to a thread, 4096 to a workgroup, or two.
 // One group / two, us:

@@ -237,7 +237,7 @@ static int check_hints() {
     }
     bad += !through_inverse(64 * MB / W, W) || through_inverse(64 * MB / W + 1024, W);
     for (uint32_t b : {1u, 3u, 4u, 8u}) {
-      const uint64_t d = 64 * MB / W / b * 8;
+      const uint64_t d = 80 * MB / W / b * 8;
       bad += stream_sums(d - 1024, W, b) || !stream_sums(d + 1024, W, b);
     }
   }

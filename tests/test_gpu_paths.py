@@ -146,11 +146,11 @@ def test_sums_of_any_width(b, g, n):
 @pytest.mark.parametrize("b,g,agg_bits,n", [(4, 30, 8, 8), (4, 15, 7, 8), (4, 30, 9, 9), (4, 100, 16, 8), (2, 8, 8, 16),
                                             (2, 8, 16, 16), (3, 31, 9, 11), (1, 1, 6, 32), (5, 36, 8, 7), (8, 255, 16, 4)])
 def test_sums_of_streams_beyond_the_cache(b, g, agg_bits, n):
-    """Streams of 64 MB and more together go past the caches: the whole against slices of it, which do not, bit for bit; the
+    """Streams of 80 MB and more together go past the caches: the whole against slices of it, which do not, bit for bit; the
     last workgroup is mostly empty."""
-    block, K = 1 << 10, (1 << 14) + 1
+    block, K = 1 << 10, (5 << 12) + 1
     T = [round(i * g / ((1 << b) - 1)) for i in range(1 << b)]
-    assert n * block * K * b // 8 >= 1 << 26
+    assert n * block * K * b // 8 >= 80 << 20
     _, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, table=T)
     gen = torch.Generator(device=DEV).manual_seed(b * 64 + n)
     packed = [torch.randint(0, 256, (block * K * b // 8,), dtype=torch.uint8, device=DEV, generator=gen) for _ in range(n)]
