@@ -79,7 +79,7 @@ uint64_t group_coords(const thc_params* p, uint32_t W) {
 // 2^27, 968 at 2^26 (256 MB), 978 at 2^25, and 1005 where shares exceed 2^26 a little.  Blocks of 2^22 and more lose up to 7 % (8 x 8 of 2^23) and keep their groups.
 uint64_t walk_coords(const thc_params* p, uint32_t W, bool inverse) {
   const uint64_t most = group_coords(p, W);
-  if (p->group_log2 || p->single_launch || p->block >= (1ull << 22)) return most;
+  if (p->group_log2 || p->single_launch || !walks_in_shares(p->block, inverse)) return most;
   return std::min(most, even_share(p->d, p->block, W, 1ull << (inverse ? 26 : 27), inverse));
 }
 

@@ -302,6 +302,14 @@ inline void for_pieces(uint64_t d, Piece&& piece) {
   for (uint64_t x0 = 0; x0 < d; x0 += LAUNCH_COORDS) piece(x0, d - x0 < LAUNCH_COORDS ? d - x0 : LAUNCH_COORDS);
 }
 
+// Whether a walk goes in shares smaller than the ring (even_share): where one pass leaves in memory what the next one reads.  A
+// decompression that takes the inverse in one launch leaves nothing, and each share costs a launch and its drain; walked in
+// shares of 2^26 coordinates / in one launch, us: 2^27 coordinates from 8-bit sums in blocks of 2^10 110 / 108, 2^14 129 / 112,
+// 2^15 116 / 109; 2^29 501 / 478, 542 / 467 and 506 / 472; 2^28 from 16-bit sums 283 / 268, 298 / 283, 305 / 285.
+inline bool walks_in_shares(uint64_t block, bool inverse) {
+  return block < (1ull << 22) && (!inverse || block > (1ull << LOG_BIG));
+}
+
 // Coordinates of each of W vectors in one step of a walk over d of them: even shares of whole blocks, and of whole 2^20
 // coordinates (the first pass's tiling wants 2^19, see lo_tilemap).  A step takes at least `target` coordinates of all vectors
 // together, or with `most` at most that, where the vector and the units allow it.

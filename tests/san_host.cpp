@@ -217,6 +217,14 @@ static int check_even_share() {
          (even_share(100ull << 20, 1ull << 20, 1, 1ull << 26, true) != 50ull << 20);
 }
 
+// a decompression whose blocks take the inverse in one launch has no intermediate to keep in the cache, and is not cut
+static int check_walks_in_shares() {
+  int bad = 0;
+  for (int L = 10; L <= 27; ++L)
+    bad += walks_in_shares(1ull << L, true) != (L >= 16 && L <= 21) || walks_in_shares(1ull << L, false) != (L <= 21);
+  return bad;
+}
+
 // ... of the two workgroups to a block of 2^14
 static int check_whole_split() {
   const Plan p14 = make_plan(1 << 14, THC_ORDER_ASCENDING), p13 = make_plan(1 << 13, THC_ORDER_ASCENDING);
@@ -301,7 +309,7 @@ int main() {
   bad += check_pieces(1ull << 10, 1) + check_pieces(1ull << 34, 1) + check_pieces((1ull << 34) + 1024, 2);
   bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
   bad += check_xcd_tile<2>() + check_xcd_tile<3>() + check_xcd_tile<4>() + check_xcd_tile<6>();
-  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints() + check_even_share() + check_whole_split();
+  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints() + check_even_share() + check_walks_in_shares() + check_whole_split();
   // the uniform quantizer's groups of coordinates: the limits, and that bf16 without error feedback has none
   for (bool bf16 : {false, true}) bad += !uniform_one_group(1 << 20, bf16, true) || uniform_one_group((1 << 20) + 1024, bf16, true);
   bad += !uniform_one_group(1 << 22, false, false) || uniform_one_group((1 << 22) + 1024, false, false);
