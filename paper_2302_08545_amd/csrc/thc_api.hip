@@ -70,6 +70,10 @@ uint64_t group_coords(const thc_params* p, uint32_t W) {
   return gc;
 }
 
+struct GroupWalk {
+  uint64_t most, unit;   // for_groups' `gc` and `unit`
+};
+
 // Coordinates of each of W vectors that one group takes, by default; at most what the ring holds.  The smaller a group, the more
 // of what its first pass writes is still in the memory-side cache when the last one reads it; against that stand two or three
 // launches a group.  Blocks of up to 2^21, groups of 2^29 / 2^28 / 2^27 / 2^26 coordinates, us: 256 x 8 vectors of 2^20 (half of it
@@ -77,10 +81,12 @@ uint64_t group_coords(const thc_params* p, uint32_t W) {
 // feedback 64 x 4 1802 / 1799 / 1784 / 1847.  A walk in steps of exactly 2^27 took 3 % more where it left a short rest (20 x 8):
 // hence even shares.  The decompression, two launches a group: rounds of one worker, 200 blocks of 2^20, 997 us at 2^29, 990 at
 // 2^27, 968 at 2^26 (256 MB), 978 at 2^25, and 1005 where shares exceed 2^26 a little.  Blocks of 2^22 and more lose up to 7 % (8 x 8 of 2^23) and keep their groups.
-uint64_t walk_coords(const thc_params* p, uint32_t W, bool inverse) {
+GroupWalk walk_coords(const thc_params* p, uint32_t W, bool inverse) {
   const uint64_t most = group_coords(p, W);
-  if (p->group_log2 || p->single_launch || !walks_in_shares(p->block, inverse)) return most;
-  return std::min(most, even_share(p->d, p->block, W, 1ull << (inverse ? 26 : 27), inverse));
+  if (p->group_log2 || p->single_launch || !walks_in_shares(p->block, inverse)) return {most, 0};
+  const uint64_t share = even_share(p->d, p->block, W, 1ull << (inverse ? 26 : 27), inverse);
+  if (share > most) return {most, 0};
+  return {share, share_unit(p->block)};
 }
 
 // Shape of the single-launch sweep over W vectors (thc_pipeline.hpp), or ok = false where it does not apply:
@@ -685,7 +691,7 @@ void run_forward(const Forward& f) {
   }
   const bool bf16 = p->in_dtype == THC_DTYPE_BF16;
   const size_t in_size = bf16 ? 2 : 4;
-  const uint64_t gc = walk_coords(p, f.W, false);
+  const GroupWalk walk = walk_coords(p, f.W, false);
   const WsLayout wl = ws_layout(f.ws, p, pl, f.efs != nullptr);
   float* const slot = wl.ring;
   double* const partials = wl.partials;
@@ -716,7 +722,7 @@ void run_forward(const Forward& f) {
     ihi.mode = 1;
     ihi.bf16 = bf16;
   }
-  for_groups(pl, p->d, gc, f.W, [&](uint64_t x0, uint64_t len, bool big, bool inv_big) {
+  for_groups(pl, p->d, walk.most, f.W, [&](uint64_t x0, uint64_t len, bool big, bool inv_big) {
     const uint64_t tiles = tiles_of(len);
     FwdLoArgs a{};
     for (uint32_t i = 0; i < f.W; ++i) {
@@ -776,7 +782,7 @@ void run_forward(const Forward& f) {
       ihi.j0 = a.j0;
       run_inverse(p, pl, ilo, slot, ihi, len, inv_big, f.W, f.s);
     }
-  });
+  }, walk.unit);
 }
 
 template <bool BF16, int G>
@@ -910,7 +916,7 @@ int thc_describe_plan(const thc_params* p, uint32_t* out, size_t cap_records) {
   };
   int first[16];
   for (int i = 0; i < pl.L1; ++i) first[i] = (pl.split && i >= 10) ? i + 3 : i;
-  put(0, pl.split ? 3u : 0u, first, pl.L1, lo_tilemap(pl, walk_coords(p, p->n, false)));
+  put(0, pl.split ? 3u : 0u, first, pl.L1, lo_tilemap(pl, walk_coords(p, p->n, false).most));
   for (int m = 0; m < pl.nmid; ++m) put(1 + m, 1u, pl.bits[m], pl.mid[m], pl.midmap[m]);
   put(npass - 1, 2u, pl.bits[pl.nmid], pl.R, pl.hi);
   return npass;
@@ -985,9 +991,9 @@ int thc_aggregate(const thc_params* p, const uint8_t* const* packed, void* agg_o
 
 namespace {
 
-// m + (Y/n)(M-m)/g and the inverse RHT, group by group through `slot` (room for `gc` coordinates, whole blocks)
+// m + (Y/n)(M-m)/g and the inverse RHT, group by group through `slot` (room for `walk.most` coordinates, whole blocks)
 void run_decompress(const thc_params* p, const Plan& pl, uint64_t round, const void* agg, const float* range_M,
-                    float* out, float* slot, uint64_t gc, hipStream_t s) {
+                    float* out, float* slot, GroupWalk walk, hipStream_t s) {
   InvLoArgs lo{};
   lo.L = (uint32_t)pl.L;
   lo.src_bits = p->agg_bits;
@@ -998,13 +1004,13 @@ void run_decompress(const thc_params* p, const Plan& pl, uint64_t round, const v
   hi.k0 = (uint32_t)p->seed;
   hi.k1 = (uint32_t)(p->seed >> 32);
   hi.mode = 0;
-  for_groups(pl, p->d, gc, 1, [&](uint64_t x0, uint64_t len, bool, bool big) {
+  for_groups(pl, p->d, walk.most, 1, [&](uint64_t x0, uint64_t len, bool, bool big) {
     lo.src.p[0] = static_cast<const uint8_t*>(agg) + x0 / 8 * p->agg_bits;
     lo.range_M = range_M + x0 / p->block;
     hi.out.p[0] = out + x0;
     hi.j0 = base_coord(p) + x0;
     run_inverse(p, pl, lo, slot, hi, len, big, 1, s);
-  });
+  }, walk.unit);
 }
 
 }  // namespace
@@ -1038,7 +1044,7 @@ int thc_decompress_noalloc(const thc_params* p, uint64_t round, const void* agg,
   const Plan pl = make_plan(p->block, p->stage_order);
   uint64_t gc = STATIC_SCRATCH_FLOATS / p->block * p->block;   // whole blocks that fit the scratch array
   if (gc > p->d) gc = p->d;
-  run_decompress(p, pl, round, agg, range_M, out, scratch, gc, static_cast<hipStream_t>(stream));
+  run_decompress(p, pl, round, agg, range_M, out, scratch, {gc, 0}, static_cast<hipStream_t>(stream));
   return check_launch();
 }
 

@@ -310,23 +310,29 @@ inline bool walks_in_shares(uint64_t block, bool inverse) {
   return block < (1ull << 22) && (!inverse || block > (1ull << LOG_BIG));
 }
 
-// Coordinates of each of W vectors in one step of a walk over d of them: even shares of whole blocks, and of whole 2^20
-// coordinates (the first pass's tiling wants 2^19, see lo_tilemap).  A step takes at least `target` coordinates of all vectors
-// together, or with `most` at most that, where the vector and the units allow it.
+// What a walk in even shares counts in: whole blocks, and whole 2^20 coordinates (the first pass's tiling wants 2^19, see
+// lo_tilemap).
+inline uint64_t share_unit(uint64_t block) { return block > (1ull << 20) ? block : 1ull << 20; }
+
+// Coordinates of each of W vectors in the largest step of a walk over d of them in even shares.  A step takes about `target`
+// coordinates of all vectors together, rounded to whole units, or with `most` at most that.
 inline uint64_t even_share(uint64_t d, uint64_t block, uint32_t W, uint64_t target, bool most) {
-  const uint64_t unit = block > (1ull << 20) ? block : 1ull << 20;
+  const uint64_t unit = share_unit(block);
   const uint64_t whole = (W * d + (most ? target - 1 : 0)) / target, steps = whole ? whole : 1;
   const uint64_t share = ((d + steps - 1) / steps + unit - 1) / unit * unit;
   return share < d ? share : d;
 }
 
-// The groups of whole blocks, `gc` coordinates of each of W vectors, in which a call walks its d coordinates:
-// group(first coordinate, coordinates, whether the forward and the inverse launches take the larger tiles).
+// The groups of whole blocks, at most `gc` coordinates of each of W vectors, in which a call walks its d coordinates:
+// group(first coordinate, coordinates, whether the forward and the inverse launches take the larger tiles).  Groups of gc and
+// a rest, or with `unit` (of which gc is a multiple, or all of d) as many groups that differ by at most one unit.
 template <class Group>
-inline void for_groups(const Plan& pl, uint64_t d, uint64_t gc, uint32_t W, Group&& group) {
-  for (uint64_t x0 = 0; x0 < d; x0 += gc) {
-    const uint64_t len = d - x0 < gc ? d - x0 : gc;
+inline void for_groups(const Plan& pl, uint64_t d, uint64_t gc, uint32_t W, Group&& group, uint64_t unit = 0) {
+  const uint64_t steps = (d + gc - 1) / gc, units = unit ? (d + unit - 1) / unit : 0;
+  for (uint64_t x0 = 0, i = 0; x0 < d; ++i) {
+    const uint64_t want = unit ? (units / steps + (i < units % steps ? 1 : 0)) * unit : gc, len = d - x0 < want ? d - x0 : want;
     group(x0, len, big_forward(pl, len, W), big_inverse(pl, d, len, W));
+    x0 += len;
   }
 }
 

@@ -217,6 +217,30 @@ static int check_even_share() {
          (even_share(100ull << 20, 1ull << 20, 1, 1ull << 26, true) != 50ull << 20);
 }
 
+// ... and the walk in them: whole vector, no step above the largest share, all of them within a unit of each other but for the
+// last one's rest of a unit
+static int check_even_walk() {
+  int bad = 0;
+  for (uint64_t block : {1ull << 16, 1ull << 20, 1ull << 21}) {
+    const Plan pl = make_plan(block, THC_ORDER_SPLIT);
+    for (uint32_t W : {1u, 3u, 8u, 16u, 24u, 64u})
+      for (uint64_t K : {1ull, 2ull, 7ull, 41ull, 43ull, 73ull, 273ull, 321ull, 4097ull})
+        for (bool most : {false, true}) {
+          const uint64_t d = K * block, unit = share_unit(block), s = even_share(d, block, W, 1ull << 27, most);
+          uint64_t at = 0, least = ~0ull, steps = 0;
+          for_groups(pl, d, s, W, [&](uint64_t x0, uint64_t len, bool, bool) {
+            bad += x0 != at || !len || len > s || len % block;
+            at += len;
+            const uint64_t units = (len + unit - 1) / unit;
+            least = units < least ? units : least;
+            ++steps;
+          }, unit);
+          bad += at != d || steps != (d + s - 1) / s || (s < d && least + 1 < s / unit);
+        }
+  }
+  return bad;
+}
+
 // a decompression whose blocks take the inverse in one launch has no intermediate to keep in the cache, and is not cut
 static int check_walks_in_shares() {
   int bad = 0;
@@ -309,7 +333,7 @@ int main() {
   bad += check_pieces(1ull << 10, 1) + check_pieces(1ull << 34, 1) + check_pieces((1ull << 34) + 1024, 2);
   bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
   bad += check_xcd_tile<2>() + check_xcd_tile<3>() + check_xcd_tile<4>() + check_xcd_tile<6>();
-  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints() + check_even_share() + check_walks_in_shares() + check_whole_split();
+  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints() + check_even_share() + check_even_walk() + check_walks_in_shares() + check_whole_split();
   // the uniform quantizer's groups of coordinates: the limits, and that bf16 without error feedback has none
   for (bool bf16 : {false, true}) bad += !uniform_one_group(1 << 20, bf16, true) || uniform_one_group((1 << 20) + 1024, bf16, true);
   bad += !uniform_one_group(1 << 22, false, false) || uniform_one_group((1 << 22) + 1024, false, false);
