@@ -1123,7 +1123,7 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.pmax = pmax;
     a.d = p->d;
     a.L1 = (uint32_t)pl.L1;
-    a.stream = stream_norms(p->d, p->n, bf16, ef != nullptr);
+    a.stream = stream_minmax(p->d, p->n, bf16, ef != nullptr);
     const dim3 grid((unsigned)tiles_of(p->d), p->n), blk(NT);
     if (bf16) { if (ef) k_minmax<true, true><<<grid, blk, 0, s>>>(a); else k_minmax<true, false><<<grid, blk, 0, s>>>(a); }
     else { if (ef) k_minmax<false, true><<<grid, blk, 0, s>>>(a); else k_minmax<false, false><<<grid, blk, 0, s>>>(a); }

@@ -261,6 +261,9 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // 0.96; with error feedback 3 x 4 vectors (96 MB) 1.04, 25 x 1 in bf16 (150 MB) 0.98, 25 x 8 0.96.
 // stream_norms: the pass that keeps the norms only.  Time of streamed over kept: 4 x 2^18 (8 MB) 1.03, 25 blocks of 2^20 in bf16
 // with error feedback (150 MB) 0.99, 100 blocks (400 MB) 0.93.
+// stream_minmax: the uniform variant's range pass without rotation; its quantizer reads the vectors again and finds what the
+// cache holds.  Streamed over kept, prepare and compress: 64 MB 0.97 to 1.07, 96 to 160 MB 0.99 to 1.08, 192 and 224 MB 0.98 to
+// 1.09, 255 and 256 MB 0.93 to 1.02, 320 MB and more 0.92 to 1.01.
 // through_inverse: the inverse's first pass writes through the L2, or else non-temporally.  Through over non-temporal: 4 MB 0.98,
 // 100 MB 0.98, 128 MB 1.01, 400 MB 1.02, 800 MB 1.04, 1 GB 1.00.
 // stream_blocks: the gradients of blocks of up to 2^14 that go block by block, behind the norms.  Time of streamed over kept, all
@@ -278,6 +281,8 @@ inline bool stream_norms(uint64_t len, uint32_t W, bool bf16, bool ef) { return 
 inline bool stream_blocks(uint64_t len, uint32_t W, bool bf16) { return !bf16 && input_bytes(len, W, bf16, false) >= 64 * MB; }
 inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
 inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB; }
+
+inline bool stream_minmax(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 240 * MB; }
 
 // Uniform quantizer on a vector of d coordinates: one group of eight coordinates to a thread, 4096 to a workgroup, or two.
 // One group / two, us:

@@ -29,7 +29,7 @@ struct MinMaxArgs {
   float* pmax;
   uint64_t d;
   uint32_t L1;       // log2 of min(B, 8192)
-  uint32_t stream;   // see stream_norms
+  uint32_t stream;   // see stream_minmax
 };
 
 template <bool BF16, bool EF>

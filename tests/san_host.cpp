@@ -267,6 +267,11 @@ static int check_hints() {
       bad += stream_norms(plain - 1024, W, bf16, false) || !stream_norms(plain, W, bf16, false);
       bad += stream_norms(with_ef / 2 - 1024, W, bf16, true) || !stream_norms(with_ef / 2 + 1024, W, bf16, true);
     }
+    for (bool bf16 : {false, true})
+      for (bool ef : {false, true}) {
+        const uint64_t d = 240 * MB / ((bf16 ? 2 : 4) + (ef ? 4 : 0)) / W;
+        bad += stream_minmax(d - 1024, W, bf16, ef) || !stream_minmax(d + 1024, W, bf16, ef);
+      }
     bad += !through_inverse(64 * MB / W, W) || through_inverse(64 * MB / W + 1024, W);
     for (uint32_t b : {1u, 3u, 4u, 8u}) {
       const uint64_t d = 80 * MB / W / b * 8;

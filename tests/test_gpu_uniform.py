@@ -55,6 +55,29 @@ def test_uniform_round_with_error_feedback_without_rotation(block, K, b, bf16):
     _uniform_round(block, K, 2, b, 16, True, 3, False, bf16=bf16)
 
 
+@pytest.mark.parametrize("bf16,ef", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("n", [1, 3])
+def test_range_of_vectors_beyond_the_cache(n, bf16, ef):
+    """Inputs this large together are read past the caches: minimum and maximum of every block, exactly; the last tile
+    holds one block of eight."""
+    block = 1 << 10
+    per = (2 if bf16 else 4) + (4 if ef else 0)
+    K = ((256 << 20) // per // n // block) // 8 * 8 + 9
+    assert n * K * block * per >= 256 << 20
+    _, L = uparams(K * block, block, n, 4, 8, bf16=bf16)
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    grads = [torch.randn(K * block, device=DEV, generator=gen).to(torch.bfloat16 if bf16 else torch.float32) for _ in range(n)]
+    efs = [torch.randn(K * block, device=DEV, generator=gen) for _ in range(n)] if ef else None
+    m, M = torch.zeros(K, device=DEV), torch.zeros(K, device=DEV)
+    ws = torch.empty(api.thc_uniform_workspace_bytes(L, False), dtype=torch.uint8, device=DEV)
+    api.thc_uniform_prepare_range(L, 0, grads, efs, False, m, M, ws)
+    lo, hi = torch.full((K,), float("inf"), device=DEV), torch.full((K,), float("-inf"), device=DEV)
+    for i in range(n):
+        x = grads[i].float() + (efs[i] if ef else 0.0)
+        lo, hi = torch.minimum(lo, x.view(K, block).amin(1)), torch.maximum(hi, x.view(K, block).amax(1))
+    assert torch.equal(m, lo) and torch.equal(M, hi)
+
+
 @pytest.mark.parametrize("K,bf16,ef", [(1024, False, True), (1025, False, True), (1025, True, True), (4096, False, False),
                                        (4097, False, False), (16384, False, False), (16385, False, False)])
 def test_quantizer_of_one_group_of_coordinates_a_thread_or_two(K, bf16, ef):
