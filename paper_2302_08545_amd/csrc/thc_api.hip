@@ -626,7 +626,7 @@ void run_norms(const thc_params* p, const Plan& pl, const void* const* grads, co
   a.pstride = len >> pl.L1;
   a.d = len;
   a.tm = lo_tilemap(pl, len);
-  a.stream = stream_norms(len, W, bf16, ef != nullptr);
+  a.stream = stream_norms(pl, len, W, bf16, ef != nullptr);
   launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(len), W, s);
   launch_range(RangeArgs{partials, range_M + x0 / p->block, a.pstride, len, W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p}, s);
 }

@@ -259,8 +259,10 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // so that only small ones, which the caller has just written, are better left alone; with it the update does, at the end.  Time
 // of streamed over kept: one block of 2^20 x 4 vectors 1.01, x 10 1.04, 4 x 8 (128 MB) 0.99, 10 x 8 0.97, 41 x 16 0.96, 256 x 8
 // 0.96; with error feedback 3 x 4 vectors (96 MB) 1.04, 25 x 1 in bf16 (150 MB) 0.98, 25 x 8 0.96.
-// stream_norms: the pass that keeps the norms only.  Time of streamed over kept: 4 x 2^18 (8 MB) 1.03, 25 blocks of 2^20 in bf16
-// with error feedback (150 MB) 0.99, 100 blocks (400 MB) 0.93.
+// stream_norms: the pass that keeps the norms only.  Time of streamed over kept, with the compression behind it, inputs that no
+// cache held before.  Blocks of 2^10 to 2^14, whose compression is one launch: 32 MB 1.08 to 1.18 in binary32, 64 MB 0.94 to 1.00,
+// 96 to 192 MB 0.92 to 1.00, 256 MB to 1 GB 0.88 to 1.00; in bf16 without error feedback 0.98 to 1.01 throughout.  Blocks of
+// 2^20: 64 MB 1.00 to 1.11, 96 and 128 MB 0.97 to 1.02, 160 and 192 MB 0.94 to 1.00, 256 MB and more 0.92 to 1.00.
 // stream_minmax: the uniform variant's range pass without rotation; its quantizer reads the vectors again and finds what the
 // cache holds.  Streamed over kept, prepare and compress: 64 MB 0.97 to 1.07, 96 to 160 MB 0.99 to 1.08, 192 and 224 MB 0.98 to
 // 1.09, 255 and 256 MB 0.93 to 1.02, 320 MB and more 0.92 to 1.01.
@@ -277,7 +279,9 @@ inline uint64_t input_bytes(uint64_t len, uint32_t W, bool bf16, bool ef) { retu
 inline bool stream_inputs(uint64_t len, uint32_t W, bool bf16, bool ef) {
   return input_bytes(len, W, bf16, ef) >= (ef ? 128 : 64) * MB;
 }
-inline bool stream_norms(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 64 * MB; }
+inline bool stream_norms(const Plan& pl, uint64_t len, uint32_t W, bool bf16, bool ef) {
+  return input_bytes(len, W, bf16, ef) >= (pl.L > 14 ? 128 : 64) * MB;
+}
 inline bool stream_blocks(uint64_t len, uint32_t W, bool bf16) { return !bf16 && input_bytes(len, W, bf16, false) >= 64 * MB; }
 inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
 inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB; }
