@@ -261,14 +261,15 @@ static int check_hints() {
   int bad = 0;
   for (uint32_t W : {1u, 4u, 32u}) {
     for (bool bf16 : {false, true}) {
-      const uint64_t plain = 64 * MB / (bf16 ? 2 : 4) / W, with_ef = 128 * MB / (bf16 ? 6 : 8) / W;
+      const uint64_t plain = 64 * MB / (bf16 ? 2 : 4) / W, with_ef = 240 * MB / (bf16 ? 6 : 8) / W;
+      const uint64_t norms_ef = 64 * MB / (bf16 ? 6 : 8) / W;
       bad += stream_inputs(plain - 1024, W, bf16, false) || !stream_inputs(plain, W, bf16, false);
       bad += stream_inputs(with_ef - 1024, W, bf16, true) || !stream_inputs(with_ef + 1024, W, bf16, true);
       for (int L : {10, 14, 15, 20}) {
         const Plan pl = make_plan(1ull << L, THC_ORDER_SPLIT);
         const uint64_t x = L > 14 ? 2 : 1;
         bad += stream_norms(pl, x * plain - 1024, W, bf16, false) || !stream_norms(pl, x * plain, W, bf16, false);
-        bad += stream_norms(pl, x * with_ef / 2 - 1024, W, bf16, true) || !stream_norms(pl, x * with_ef / 2 + 1024, W, bf16, true);
+        bad += stream_norms(pl, x * norms_ef - 1024, W, bf16, true) || !stream_norms(pl, x * norms_ef + 1024, W, bf16, true);
       }
     }
     for (bool bf16 : {false, true})
