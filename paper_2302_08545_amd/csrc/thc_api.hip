@@ -318,16 +318,17 @@ void dispatch_big(int r, A&&... args) {
   }
 }
 
-template <bool BF16, bool EF>
+template <bool BF16, bool EF, Mem LOAD = KEEP>
 void launch_big_lo_k(const BigLoArgs& a, bool split, dim3 grid, hipStream_t s) {
-  if (split) k_big_lo<BF16, EF, true><<<grid, dim3(NT), 0, s>>>(a);
-  else k_big_lo<BF16, EF, false><<<grid, dim3(NT), 0, s>>>(a);
+  if (split) k_big_lo<BF16, EF, true, LOAD><<<grid, dim3(NT), 0, s>>>(a);
+  else k_big_lo<BF16, EF, false, LOAD><<<grid, dim3(NT), 0, s>>>(a);
 }
 
 void launch_big_lo(const Plan& pl, const BigLoArgs& a, bool bf16, bool ef, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)(a.d >> LOG_BIG), W);
   if (bf16) {
-    if (ef) launch_big_lo_k<true, true>(a, pl.split, grid, s);
+    if (ef && stream_big_inputs(a.d, W)) launch_big_lo_k<true, true, STREAM>(a, pl.split, grid, s);
+    else if (ef) launch_big_lo_k<true, true>(a, pl.split, grid, s);
     else launch_big_lo_k<true, false>(a, pl.split, grid, s);
   } else {
     if (ef) launch_big_lo_k<false, true>(a, pl.split, grid, s);

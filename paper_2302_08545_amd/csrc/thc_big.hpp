@@ -122,7 +122,9 @@ __device__ __forceinline__ float flip_bit(float x, uint32_t bits, int k) {
 // half, before the half's first stages need the space; the sums over a wave wait until the tile's stores are under way.
 // What that costs against sums of 16 values in a row and one partial sum a tile: one block of 2^23, 2^24 or 2^25 34.1 us
 // (32.5), 50.7 (49.3) and 92.6 (92.4) a call, eight vectors of 2^25 with error feedback 2041 us (2036).
-template <bool BF16, bool EF, bool XO>
+//
+// LOAD: how gradients are read, STREAM with bf16 and error feedback only, see stream_big_inputs.
+template <bool BF16, bool EF, bool XO, Mem LOAD>
 __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
   __shared__ SmemBigLo sm;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_lo(const BigLoArgs a) {
   auto load = [&](int h) {   // operands of one half of the tile
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
-      load_grad16<BF16, BF16 && EF ? STREAM : KEEP>(grad, tp + big_p<XO>((2 * h + y) << 13), v[2 * h + y]);
+      load_grad16<BF16, LOAD>(grad, tp + big_p<XO>((2 * h + y) << 13), v[2 * h + y]);
       if constexpr (EF) load_grad16<false>(ef, tp + big_p<XO>((2 * h + y) << 13), e[y]);
     }
   };

@@ -260,6 +260,10 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // of streamed over kept: one block of 2^20 x 4 vectors 1.01, x 10 1.04, 4 x 8 (128 MB) 0.99, 10 x 8 0.97, 41 x 16 0.96, 256 x 8
 // 0.96.  With error feedback, inputs that no cache held before: 128 MB 0.99 to 1.04 and at 2^14 1.11, 160 MB 0.98 to 1.09, 192 MB
 // 1.00 to 1.09, 224 MB 0.98 to 1.09, 256 MB 0.96 to 1.02, 320 to 768 MB 0.92 to 0.98.
+// stream_big_inputs: the bf16 gradients of that pass on tiles of 2^15, with error feedback.  Two instructions of 16 bytes a lane share
+// their lines, and still it gains from a size on.  Streamed over kept, thc_compress_all, gradients and buffers together: 2^23 (48
+// MB) 1.01 to 1.02, 2 x 2^23 and 2^24 (96 MB) 1.01 to 1.02, 4 x 2^23 (192 MB) 0.98 to 0.99, 2^25 (192 MB) 0.99 to 1.00, 2 x 2^24 x 4
+// vectors 0.99 to 1.00, 4 x 2^23 x 8, 2^25 x 8 and 16 x 2^22 x 16 0.99.
 // stream_norms: the pass that keeps the norms only.  Time of streamed over kept, with the compression behind it, inputs that no
 // cache held before.  Blocks of 2^10 to 2^14, whose compression is one launch: 32 MB 1.08 to 1.18 in binary32, 64 MB 0.94 to 1.00,
 // 96 to 192 MB 0.92 to 1.00, 256 MB to 1 GB 0.88 to 1.00; in bf16 without error feedback 0.98 to 1.01 throughout.  Blocks of
@@ -280,6 +284,7 @@ inline uint64_t input_bytes(uint64_t len, uint32_t W, bool bf16, bool ef) { retu
 inline bool stream_inputs(uint64_t len, uint32_t W, bool bf16, bool ef) {
   return input_bytes(len, W, bf16, ef) >= (ef ? 240 : 64) * MB;
 }
+inline bool stream_big_inputs(uint64_t len, uint32_t W) { return input_bytes(len, W, true, true) >= 160 * MB; }
 inline bool stream_norms(const Plan& pl, uint64_t len, uint32_t W, bool bf16, bool ef) {
   return input_bytes(len, W, bf16, ef) >= (pl.L > 14 ? 128 : 64) * MB;
 }

@@ -370,3 +370,39 @@ def test_walk_from_the_last_tile(log2_block, K, n, ef, order):
             assert torch.equal(q, p[k * block // 2:(k + 1) * block // 2])
         for q, e in zip(Q.efs or [], R.efs or []):
             assert torch.equal(q, e[at])
+
+
+@pytest.mark.parametrize("log2_block,K,step,n,bf16,ef,order", [
+    # 2^26 coordinates and more of all vectors: the error-feedback inverse's first pass; bf16 gradients of more than 160 MB with
+    # their buffers on tiles of 2^15
+    (18, 132, 40, 2, False, True, 0), (18, 132, 40, 2, True, True, 1), (23, 5, 2, 1, True, True, 0), (23, 5, 2, 1, True, True, 1)])
+def test_a_large_call_gives_what_its_slices_give(log2_block, K, step, n, bf16, ef, order):
+    """Rules that look at the size of a launch choose how memory is read and written, never what is computed: a whole round on
+    large vectors, every output bit for bit that of rounds on slices which lie on the other side of those rules."""
+    B, rnd = 1 << log2_block, 5
+    gen = torch.Generator(device=DEV).manual_seed(log2_block * K)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    grads = [(torch.randn(B * K, device=DEV, generator=gen) * 1e-3).to(dt) for _ in range(n)]
+    efs = [torch.randn(B * K, device=DEV, generator=gen) * 1e-4 for _ in range(n)] if ef else None
+
+    def run(k, m):
+        _, L = both_params(B * m, B, n, bf16=bf16, order=order, first_block=k)
+        R = GpuRound(L, ef)
+        if ef:
+            for i in range(n):
+                R.efs[i].copy_(efs[i][k * B:(k + m) * B])
+        R.compress_all(rnd, [g[k * B:(k + m) * B].clone() for g in grads])
+        R.aggregate()
+        R.decompress(rnd)
+        return R
+
+    whole = run(0, K)
+    for k in range(0, K, step):
+        m = min(step, K - k)
+        part, at = run(k, m), slice(k * B, (k + m) * B)
+        assert torch.equal(part.range_M, whole.range_M[k:k + m])
+        assert torch.equal(part.out, whole.out[at])
+        for i in range(n):
+            assert torch.equal(part.packed[i], whole.packed[i][k * B // 2:(k + m) * B // 2])
+            if ef:
+                assert torch.equal(part.efs[i], whole.efs[i][at])
