@@ -231,7 +231,14 @@ template <int R> struct LaunchQuant {
 };
 template <int R> struct LaunchHiMinMax {
   static void run(const HiMinMaxArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
-    k_fwd_hi_minmax<R><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+    const dim3 grid((unsigned)tiles, W), blk(NT);
+    if constexpr (R >= 2 && hi_mem<R>() == STREAM) {
+      if (stream_rotated(a.d, W)) {
+        k_fwd_hi_minmax<R, STREAM><<<grid, blk, 0, s>>>(a);
+        return;
+      }
+    }
+    k_fwd_hi_minmax<R, KEEP><<<grid, blk, 0, s>>>(a);
   }
 };
 template <int R> struct LaunchInvHi {

@@ -340,7 +340,7 @@ struct HiGeom {
 // epilogue; two rounds and nothing left for R = 8 and 9 (rows of 128 and 64 bytes: blocks of 2^21 and 2^22
 // coordinates then need no pass in between).
 template <int R>
-constexpr Mem hi_mem() { return R <= 8 ? STREAM : KEEP; }   // a row of the tile is a whole line, and read once
+constexpr Mem hi_mem() { return R <= 8 ? STREAM : KEEP; }   // a row of the tile is a whole line; for its last reader
 
 template <int R>
 struct HiSplit {

@@ -271,6 +271,9 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // stream_minmax: the uniform variant's range pass without rotation; its quantizer reads the vectors again and finds what the
 // cache holds.  Streamed over kept, prepare and compress: 64 MB 0.97 to 1.07, 96 to 160 MB 0.99 to 1.08, 192 and 224 MB 0.98 to
 // 1.09, 255 and 256 MB 0.93 to 1.02, 320 MB and more 0.92 to 1.01.
+// stream_rotated: the half-rotated vectors in the uniform variant's range pass, which the quantizer reads once more.  Streamed over
+// kept, prepare and compress, rotated, blocks of 2^16 and 2^20: 16 MB 1.01 to 1.02, 64 MB 1.03 to 1.05, 128 MB 1.02 to 1.03, 192 MB
+// 1.03 to 1.04, 256 MB 1.01 to 1.02, 384 MB 0.95 to 0.97, 512 MB 0.90 to 0.93, 1.6 GB 0.94 to 0.96.
 // through_inverse: the inverse's first pass writes through the L2, or else non-temporally.  Through over non-temporal: 4 MB 0.98,
 // 100 MB 0.98, 128 MB 1.01, 400 MB 1.02, 800 MB 1.04, 1 GB 1.00.
 // stream_blocks: the gradients of blocks of up to 2^14 that go block by block, behind the norms.  Time of streamed over kept, all
@@ -289,6 +292,7 @@ inline bool stream_norms(const Plan& pl, uint64_t len, uint32_t W, bool bf16, bo
   return input_bytes(len, W, bf16, ef) >= (pl.L > 14 ? 128 : 64) * MB;
 }
 inline bool stream_blocks(uint64_t len, uint32_t W, bool bf16) { return !bf16 && input_bytes(len, W, bf16, false) >= 64 * MB; }
+inline bool stream_rotated(uint64_t len, uint32_t W) { return W * len * 4 > 256 * MB; }
 inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
 inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB; }
 

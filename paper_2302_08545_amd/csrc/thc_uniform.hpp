@@ -123,7 +123,8 @@ struct HiMinMaxArgs {
 };
 static_assert(sizeof(HiMinMaxArgs) <= 128, "a third cache line of arguments takes a small launch 0.2 us");
 
-template <int R>
+// LOAD: how they are read, see stream_rotated.
+template <int R, Mem LOAD>
 __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
   __shared__ __align__(16) float lds[R < 2 ? 4 : TILE];
   __shared__ float smin[16], smax[16];
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(NT) void k_fwd_hi_minmax(const HiMinMaxArgs a) {
   float* const pmin = a.pmin + part;
   float* const pmax = a.pmax + part;
   if constexpr (R >= 2) {
-    hi_front<R, hi_mem<R>()>(x, g, lds, t);
+    hi_front<R, LOAD>(x, g, lds, t);
     int idx[2];
     float v[2][8];
     hi_back<R>(lds, t, idx, v);

@@ -278,6 +278,7 @@ static int check_hints() {
         bad += stream_minmax(d - 1024, W, bf16, ef) || !stream_minmax(d + 1024, W, bf16, ef);
       }
     bad += stream_big_inputs(160 * MB / 6 / W - 1024, W) || !stream_big_inputs(160 * MB / 6 / W + 1024, W);
+    bad += stream_rotated(64 * MB / W, W) || !stream_rotated(64 * MB / W + 1024, W);
     bad += !through_inverse(64 * MB / W, W) || through_inverse(64 * MB / W + 1024, W);
     for (uint32_t b : {1u, 3u, 4u, 8u}) {
       const uint64_t d = 80 * MB / W / b * 8;

@@ -78,6 +78,33 @@ def test_range_of_vectors_beyond_the_cache(n, bf16, ef):
     assert torch.equal(m, lo) and torch.equal(M, hi)
 
 
+@pytest.mark.parametrize("log2_block,K,step,order", [(16, 530, 130, 1), (17, 260, 130, 0), (20, 33, 16, 1), (21, 17, 8, 0)])
+def test_range_of_rotated_vectors_beyond_the_cache(log2_block, K, step, order):
+    """Half-rotated vectors of more than 256 MB together are read past the caches: the range of each block, and the indices, are
+    those of slices that are not."""
+    B, n, rnd = 1 << log2_block, 2, 3
+    assert n * B * K * 4 > 256 << 20 and n * B * step * 4 <= 256 << 20
+    gen = torch.Generator(device=DEV).manual_seed(log2_block)
+    grads = [torch.randn(B * K, device=DEV, generator=gen) for _ in range(n)]
+
+    def run(k, c):
+        _, L = uparams(B * c, B, n, 4, 8, first_block=k, order=order)
+        g = [x[k * B:(k + c) * B].clone() for x in grads]
+        m, M = torch.zeros(c, device=DEV), torch.zeros(c, device=DEV)
+        ws = torch.empty(api.thc_uniform_workspace_bytes(L, True), dtype=torch.uint8, device=DEV)
+        packed = torch.zeros(B * c // 2, dtype=torch.uint8, device=DEV)
+        api.thc_uniform_prepare_range(L, rnd, g, None, True, m, M, ws)
+        api.thc_uniform_compress(L, 1, rnd, g[1], None, True, m, M, packed, ws)
+        return m, M, packed
+
+    m, M, packed = run(0, K)
+    for k in range(0, K, step):
+        c = min(step, K - k)
+        pm, pM, pp = run(k, c)
+        assert torch.equal(pm, m[k:k + c]) and torch.equal(pM, M[k:k + c])
+        assert torch.equal(pp, packed[k * B // 2:(k + c) * B // 2])
+
+
 @pytest.mark.parametrize("K,bf16,ef", [(1024, False, True), (1025, False, True), (1025, True, True), (4096, False, False),
                                        (4097, False, False), (16384, False, False), (16385, False, False)])
 def test_quantizer_of_one_group_of_coordinates_a_thread_or_two(K, bf16, ef):
