@@ -242,8 +242,10 @@ template <int R> struct LaunchHiMinMax {
   }
 };
 template <int R> struct LaunchInvHi {
-  static void run(const InvHiArgs& a, uint64_t tiles, uint32_t W, hipStream_t s) {
-    k_inv_hi<R><<<dim3((unsigned)tiles, W), dim3(NT), 0, s>>>(a);
+  static void run(const InvHiArgs& a, bool keep, uint64_t tiles, uint32_t W, hipStream_t s) {
+    const dim3 grid((unsigned)tiles, W), blk(NT);
+    if (keep) k_inv_hi<R, KEEP><<<grid, blk, 0, s>>>(a);
+    else k_inv_hi<R, STREAM><<<grid, blk, 0, s>>>(a);
   }
 };
 
@@ -353,15 +355,21 @@ template <int R> struct LaunchBigQuant {
 
 template <int R> struct LaunchBigInvHi {
   template <bool XO>
-  static void go(const BigInvHiArgs& a, int mode, dim3 grid, hipStream_t s) {
+  static void go(const BigInvHiArgs& a, int mode, bool keep, dim3 grid, hipStream_t s) {
+    if constexpr (R == 8 || R == 9) {   // R = 7: calls beyond keep_estimate's limit; R = 10 stores plainly
+      if (mode == 0 && keep) {
+        k_big_inv_hi<R, XO, 0, KEEP><<<grid, dim3(NT), 0, s>>>(a);
+        return;
+      }
+    }
     if (mode == 0) k_big_inv_hi<R, XO, 0><<<grid, dim3(NT), 0, s>>>(a);
     else if (mode == 1) k_big_inv_hi<R, XO, 1><<<grid, dim3(NT), 0, s>>>(a);
     else k_big_inv_hi<R, XO, 2><<<grid, dim3(NT), 0, s>>>(a);
   }
-  static void run(const BigInvHiArgs& a, bool split, int mode, uint32_t W, hipStream_t s) {
+  static void run(const BigInvHiArgs& a, bool split, int mode, bool keep, uint32_t W, hipStream_t s) {
     const dim3 grid((unsigned)(a.d >> LOG_BIG), W);
-    if (split) go<true>(a, mode, grid, s);
-    else go<false>(a, mode, grid, s);
+    if (split) go<true>(a, mode, keep, grid, s);
+    else go<false>(a, mode, keep, grid, s);
   }
 };
 
@@ -418,34 +426,46 @@ void launch_inv_whole_ef(const InvWholeArgs& a, int efm, dim3 grid, hipStream_t 
 
 // Blocks of up to 2^15 coordinates: the inverse transform in one launch.
 template <int L1>
-void launch_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_t s) {
+void launch_inv_whole(const InvWholeArgs& a, int efm, bool keep, uint32_t W, hipStream_t s) {
   constexpr int N = inv_whole_threads(L1);
   const dim3 grid((unsigned)((a.lo.d + 16 * N - 1) / (16 * N)), W), blk(N);
   const uint32_t bits = a.lo.src_bits;
   if (efm == 0) {
-    if (bits == 8) k_inv_whole<L1, 8, 0><<<grid, blk, 0, s>>>(a);
-    else k_inv_whole<L1, 0, 0><<<grid, blk, 0, s>>>(a);
+    if (bits == 8) {
+      if (keep) k_inv_whole<L1, 8, 0, KEEP><<<grid, blk, 0, s>>>(a);
+      else k_inv_whole<L1, 8, 0><<<grid, blk, 0, s>>>(a);
+    } else {
+      if (keep) k_inv_whole<L1, 0, 0, KEEP><<<grid, blk, 0, s>>>(a);
+      else k_inv_whole<L1, 0, 0><<<grid, blk, 0, s>>>(a);
+    }
     return;
   }
   if constexpr (L1 <= LOG_TILE) launch_inv_whole_ef<L1>(a, efm, grid, s);
 }
 
+template <int L, Mem OUT>
+void launch_big_inv_whole_sums(const InvWholeArgs& a, dim3 grid, hipStream_t s) {
+  const dim3 blk(NT);
+  if (a.lo.src_bits == 8) {
+    k_big_inv_whole<L, 8, 0, OUT><<<grid, blk, 0, s>>>(a);
+    return;
+  }
+  if constexpr (L == 15) {               // 16-bit sums of 2^14-point blocks: k_inv_whole
+    if (a.lo.src_bits == 16) {
+      k_big_inv_whole<L, 16, 0, OUT><<<grid, blk, 0, s>>>(a);
+      return;
+    }
+  }
+  k_big_inv_whole<L, 0, 0, OUT><<<grid, blk, 0, s>>>(a);
+}
+
 template <int L>
-void launch_big_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_t s) {
+void launch_big_inv_whole(const InvWholeArgs& a, int efm, bool keep, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)((a.lo.d + BIG - 1) >> LOG_BIG), W), blk(NT);
   const uint32_t bits = a.lo.src_bits;
   if (efm == 0) {
-    if (bits == 8) {
-      k_big_inv_whole<L, 8, 0><<<grid, blk, 0, s>>>(a);
-      return;
-    }
-    if constexpr (L == 15) {               // 16-bit sums of 2^14-point blocks: k_inv_whole
-      if (bits == 16) {
-        k_big_inv_whole<L, 16, 0><<<grid, blk, 0, s>>>(a);
-        return;
-      }
-    }
-    k_big_inv_whole<L, 0, 0><<<grid, blk, 0, s>>>(a);
+    if (keep) launch_big_inv_whole_sums<L, KEEP>(a, grid, s);
+    else launch_big_inv_whole_sums<L, STREAM>(a, grid, s);
   } else if (efm == 1) {
     if (bits == 4) k_big_inv_whole<L, 4, 1><<<grid, blk, 0, s>>>(a);
     else k_big_inv_whole<L, 0, 1><<<grid, blk, 0, s>>>(a);
@@ -458,6 +478,7 @@ void launch_big_inv_whole(const InvWholeArgs& a, int efm, uint32_t W, hipStream_
 // inverse transform of W vectors of `len` coordinates that the first pass is about to produce in `wsx`
 void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, InvHiArgs hi, uint64_t len, bool big,
                  uint32_t W, hipStream_t s) {
+  const bool keep = hi.mode == 0 && keep_estimate(p->d, pl.L);
   if (big) {
     BigInvLoArgs a{lo.src, lo.range_M, lo.range_m, wsx, len, lo.L, lo.src_bits, lo.use_table, lo.divisor, {}};
     std::memcpy(a.table, lo.table, 256);
@@ -465,7 +486,7 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
     const BigInvHiArgs h{wsx, hi.out, hi.grad, len, hi.j0,
                          walk_over(hi.mode == 1 && last_first(pl, len, W, true, true), len >> LOG_BIG, W), hi.round, hi.k0, hi.k1,
                          (float)(1.0 / std::sqrt((double)p->block))};
-    dispatch_big<LaunchBigInvHi>(pl.L - LOG_BIG, h, pl.split, hi.mode == 0 ? 0 : hi.bf16 ? 2 : 1, W, s);
+    dispatch_big<LaunchBigInvHi>(pl.L - LOG_BIG, h, pl.split, hi.mode == 0 ? 0 : hi.bf16 ? 2 : 1, keep, W, s);
     return;
   }
   lo.tm = lo_tilemap(pl, len);
@@ -475,15 +496,15 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
     const InvWholeArgs a{lo, hi.out, hi.grad, hi.j0, hi.round, hi.k0, hi.k1, (float)(1.0 / std::sqrt((double)p->block))};
     const int efm = hi.mode == 0 ? 0 : hi.bf16 ? 2 : 1;
     switch (pl.L) {
-      case 10: launch_inv_whole<10>(a, efm, W, s); break;
-      case 11: launch_inv_whole<11>(a, efm, W, s); break;
-      case 12: launch_inv_whole<12>(a, efm, W, s); break;
-      case 13: launch_inv_whole<13>(a, efm, W, s); break;
+      case 10: launch_inv_whole<10>(a, efm, keep, W, s); break;
+      case 11: launch_inv_whole<11>(a, efm, keep, W, s); break;
+      case 12: launch_inv_whole<12>(a, efm, keep, W, s); break;
+      case 13: launch_inv_whole<13>(a, efm, keep, W, s); break;
       case 14:
-        if (inv_whole_14(len, efm != 0, lo.src_bits)) launch_inv_whole<14>(a, efm, W, s);
-        else launch_big_inv_whole<14>(a, efm, W, s);
+        if (inv_whole_14(len, efm != 0, lo.src_bits)) launch_inv_whole<14>(a, efm, keep, W, s);
+        else launch_big_inv_whole<14>(a, efm, keep, W, s);
         break;
-      default: launch_big_inv_whole<15>(a, efm, W, s); break;
+      default: launch_big_inv_whole<15>(a, efm, keep, W, s); break;
     }
     return;
   }
@@ -495,13 +516,13 @@ void run_inverse(const thc_params* p, const Plan& pl, InvLoArgs lo, float* wsx, 
   hi.tm = pl.hi;
   hi.c = (float)(1.0 / std::sqrt((double)p->block));
   switch (pl.R) {   // blocks of 2^16 and more: 3 bits at least
-    case 3: LaunchInvHi<3>::run(hi, tiles_of(len), W, s); break;
-    case 4: LaunchInvHi<4>::run(hi, tiles_of(len), W, s); break;
-    case 5: LaunchInvHi<5>::run(hi, tiles_of(len), W, s); break;
-    case 6: LaunchInvHi<6>::run(hi, tiles_of(len), W, s); break;
-    case 7: LaunchInvHi<7>::run(hi, tiles_of(len), W, s); break;
-    case 8: LaunchInvHi<8>::run(hi, tiles_of(len), W, s); break;
-    default: LaunchInvHi<9>::run(hi, tiles_of(len), W, s); break;
+    case 3: LaunchInvHi<3>::run(hi, keep, tiles_of(len), W, s); break;
+    case 4: LaunchInvHi<4>::run(hi, keep, tiles_of(len), W, s); break;
+    case 5: LaunchInvHi<5>::run(hi, keep, tiles_of(len), W, s); break;
+    case 6: LaunchInvHi<6>::run(hi, keep, tiles_of(len), W, s); break;
+    case 7: LaunchInvHi<7>::run(hi, keep, tiles_of(len), W, s); break;
+    case 8: LaunchInvHi<8>::run(hi, keep, tiles_of(len), W, s); break;
+    default: LaunchInvHi<9>::run(hi, keep, tiles_of(len), W, s); break;
   }
 }
 
@@ -1234,7 +1255,9 @@ int thc_uniform_decompress(const thc_params* p, uint64_t round, const void* agg,
   if (!rotate) {
     UDequantArgs a{agg, range_M, range_m, out, p->d, (uint32_t)pl.L, p->agg_bits, p->g * p->n};
     const uint64_t threads = p->d / 16;
-    k_uniform_dequant<<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s>>>(a);
+    const dim3 grid((unsigned)((threads + 255) / 256)), blk(256);
+    if (keep_plain_estimate(p->d)) k_uniform_dequant<KEEP><<<grid, blk, 0, s>>>(a);
+    else k_uniform_dequant<STREAM><<<grid, blk, 0, s>>>(a);
     return check_launch();
   }
   float* wsx = static_cast<float*>(ws);

@@ -538,7 +538,7 @@ struct alignas(16) SmemBigInvHi {
   uint32_t sgn[BIG_SIGN_WORDS];   // bit (u & 31) of word (row << (C - 5)) + (column >> 5)
 };
 
-template <int R, bool XO, int EFM>
+template <int R, bool XO, int EFM, Mem OUT = R <= 9 ? STREAM : KEEP>
 __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
   // Rows of 32 columns (R = 10) are whole lines only over two accesses, in either layout.  They keep the eight neighbouring
   // columns, which measured best there; spread and streamed: 2^25 x 8 with error feedback 2077 -> 2203 us.
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_hi(const BigInvHiArgs a) {
                              flip_bit(v[k][4 * h + 2] * a.c, bits, 2), flip_bit(v[k][4 * h + 3] * a.c, bits, 3));
       if constexpr (EFM != 0)
         r = make_float4((g[h].x + e[h].x) - r.x, (g[h].y + e[h].y) - r.y, (g[h].z + e[h].z) - r.z, (g[h].w + e[h].w) - r.w);
-      store_f4<HOW>(out + to + so + h * half, r);
+      store_f4<OUT>(out + to + so + h * half, r);
     }
     if constexpr (EFM != 0) {
 #pragma unroll
@@ -632,7 +632,7 @@ struct alignas(16) SmemBigWhole {
   float tabf[2][256];
 };
 
-template <int L, int SB, int EFM>
+template <int L, int SB, int EFM, Mem OUT = STREAM>
 __global__ __launch_bounds__(NT, 4) void k_big_inv_whole(const InvWholeArgs a) {
   static_assert(L == 14 || L == 15, "one or two blocks to a tile");
   constexpr bool TABLE = EFM != 0;               // error feedback starts from indices, decompression from sums
@@ -697,7 +697,7 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_whole(const InvWholeArgs a) {
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     if (k >= 4 && !two) break;
-    finish_values<EFM>(v[k], a.c, out, grad, [&](int i) { return (uint32_t)(8 * k + i) << 9; },
+    finish_values<EFM, OUT>(v[k], a.c, out, grad, [&](int i) { return (uint32_t)(8 * k + i) << 9; },
                        [&](int i) { return (sm.sgn[(8 * k + i) << 4 | t >> 5] >> (t & 31)) & 1u; });
   }
 }

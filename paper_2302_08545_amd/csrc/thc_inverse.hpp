@@ -268,8 +268,9 @@ struct alignas(16) SmemInvHi {
   uint32_t sgn[TILE / 32];
 };
 
-// One tile: tile index `tile` of the launch's vector `vec`, whose half-rotated image starts at xv.
-template <int R, class A>
+// One tile: tile index `tile` of the launch's vector `vec`, whose half-rotated image starts at xv.  OUT: how results are stored, see
+// keep_estimate.
+template <int R, Mem OUT, class A>
 __device__ __forceinline__ void inv_hi_tile(const A& a, uint32_t tile, uint32_t vec, const float* xv,
                                             SmemInvHi& sm) {
   float* const lds = sm.lds;
@@ -317,15 +318,15 @@ __device__ __forceinline__ void inv_hi_tile(const A& a, uint32_t tile, uint32_t 
   for (int i = 0; i < 4; ++i) {
     const int idx = 4 * (t + NT * i);
     const uint32_t bits = sgn[idx >> 5] >> (idx & 31);
-    store_f4<STREAM>(out + g.coord(idx), inv_finish4(v[i], bits, a, gx[i], ex[i]));
+    store_f4<OUT>(out + g.coord(idx), inv_finish4(v[i], bits, a, gx[i], ex[i]));
   }
 }
 
-template <int R>
+template <int R, Mem OUT>
 __global__ __launch_bounds__(NT) void k_inv_hi(const InvHiArgs a) {
   __shared__ SmemInvHi sm;
   const uint32_t tile = walk_x(a.walk), vec = walk_y(a.walk);
-  inv_hi_tile<R>(a, tile, vec, a.x + (uint64_t)vec * a.d, sm);
+  inv_hi_tile<R, OUT>(a, tile, vec, a.x + (uint64_t)vec * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(NT) void k_inv_hi(const InvHiArgs a) {
 // ---------------------------------------------------------------------------------------------
 // `N` results of a thread: scale, diagonal, and with EFM 1 / 2 (binary32 / bf16 gradient) e <- (grad + e) - that.  All
 // operands are requested before the first store, which goes to the buffer some of them come from.
-template <int EFM, int N, class Off, class Bit>
+template <int EFM, Mem OUT, int N, class Off, class Bit>
 __device__ __forceinline__ void finish_values(const float (&v)[N], float c, float* out, const void* grad, Off&& off,
                                               Bit&& bit) {
   float x[N], e[N];
@@ -353,7 +354,7 @@ __device__ __forceinline__ void finish_values(const float (&v)[N], float c, floa
   for (int i = 0; i < N; ++i) {
     float r = flip(v[i] * c, bit(i));
     if constexpr (EFM != 0) r = (x[i] + e[i]) - r;
-    store_f<STREAM>(&out[off(i)], r);
+    store_f<OUT>(&out[off(i)], r);
   }
 }
 
@@ -369,7 +370,7 @@ struct InvWholeArgs {
 constexpr int inv_whole_threads(int L) { return L <= LOG_TILE ? NT : 1 << (L - 4); }
 
 // SB as for k_inv_lo: 2^28 coordinates in blocks of 2^13 from 8-bit sums 285 -> 260 us.
-template <int L1, int SB, int EFM>
+template <int L1, int SB, int EFM, Mem OUT = STREAM>
 __global__ __launch_bounds__(inv_whole_threads(L1), EFM == 0 ? 8 : 4) void k_inv_whole(const InvWholeArgs a) {
   constexpr int N = inv_whole_threads(L1), T = 16 * N;
   constexpr bool PART = (1 << L1) < T;     // several blocks to a tile: the vector's last one may be partly empty
@@ -391,13 +392,13 @@ __global__ __launch_bounds__(inv_whole_threads(L1), EFM == 0 ? 8 : 4) void k_inv
   const uint64_t left = a.lo.d - off;
   auto bit = [&](uint32_t o) { return (sgn[o >> 5] >> (o & 31)) & 1u; };
   if (!PART || left >= T) {
-    finish_values<EFM>(v, a.c, out, grad, [&](int i) { return at[i]; }, [&](int i) { return bit(at[i]); });
+    finish_values<EFM, OUT>(v, a.c, out, grad, [&](int i) { return at[i]; }, [&](int i) { return bit(at[i]); });
   } else {           // the last tile of a vector of short blocks
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       if (at[i] >= left) continue;
       const float one[1] = {v[i]};
-      finish_values<EFM>(one, a.c, out, grad, [&](int) { return at[i]; }, [&](int) { return bit(at[i]); });
+      finish_values<EFM, OUT>(one, a.c, out, grad, [&](int) { return at[i]; }, [&](int) { return bit(at[i]); });
     }
   }
 }

@@ -228,7 +228,7 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
       // e <- (grad + e) - RHT^-1(X_i)
       if (!pipe_wait<true>(us + (2 * SYNC_PHASE + NXCD) * SYNC_STRIDE, NXCD, P.status, &flag)) return;
       const InvHiView a{P.efs, P.grads, P.d, P.j0, P.hi_tm, P.round, P.k0, P.k1, 1u, P.bf16, P.c};
-      inv_hi_tile<R>(a, gt, w, vec, *reinterpret_cast<SmemInvHi*>(raw));
+      inv_hi_tile<R, STREAM>(a, gt, w, vec, *reinterpret_cast<SmemInvHi*>(raw));
       if (threadIdx.x == 0)
         __hip_atomic_fetch_add(us + SYNC_DONE * SYNC_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

@@ -281,6 +281,17 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // stream_sums: the aggregation.  Time of streamed over kept, by the streams' bytes together, on three sets of them in turn: 34 MB
 // 1.05, 66 MB 1.02 to 1.19 (0.80 to 0.95 with 3-bit indices, 16-bit sums or 3 workers), 82 MB 0.80 to 0.93, 100 to 190 MB 0.76 to
 // 0.94, 840 MB 0.85 to 0.95; behind the quantizer of the same round 67 MB 0.99, 105 MB 1.00.
+// keep_estimate: the estimate, which the caller reads next, is stored plainly, or else non-temporally.  Kept over streamed, the
+// decompression and a step that reads the estimate (w -= lr * out) together, by the size of the estimate:
+//                  4 to 12 MB     16 MB          24 and 32 MB   48 to 96 MB    128 MB   160 MB         176 and 192 MB  208 to 256 MB
+//   2^10 to 2^14   1.00 to 1.03   1.01 to 1.03   0.98 to 1.02   0.93 to 1.00   0.92     1.00           1.03 to 1.07    1.06 to 1.08
+//   2^15           1.00 to 1.02   1.04           0.96 to 0.98   0.94 to 0.97   0.93     0.98           1.00 to 1.03    1.01 to 1.02
+//   2^16 to 2^21   1.00 to 1.03   1.03 to 1.04   0.95 to 1.01   0.94 to 0.99   0.92     0.93 to 0.95   0.96 to 1.01    1.00 to 1.08
+//   2^22                          1.00           0.90 to 1.00   0.90 (48), 0.98 (64), 1.05 (96)  1.14  1.20   1.11 to 1.15   1.00 to 1.10
+//   2^23, 2^24                                   1.00           0.92 to 0.96   0.91 to 0.93  0.90 to 0.97  0.90 to 1.00  0.97 to 1.06
+//   no rotation    0.94 to 1.01   0.94           0.92 to 0.94   0.92 to 0.96   0.92     0.99           1.02 to 1.04    1.04
+// The decompression by itself gains by the hint at every size above 4 MB (2^10 x 2^15, 128 MB, 30 us against 37): what it gains
+// below 160 MB, the reader loses and more.
 constexpr uint64_t MB = 1ull << 20;
 
 inline uint64_t input_bytes(uint64_t len, uint32_t W, bool bf16, bool ef) { return W * len * ((bf16 ? 2 : 4) + (ef ? 4 : 0)); }
@@ -297,6 +308,9 @@ inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 25
 inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB; }
 
 inline bool stream_minmax(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 240 * MB; }
+
+inline bool keep_estimate(uint64_t d, int L) { return 4 * d > 16 * MB && 4 * d <= (L == 22 ? 80 : 160) * MB; }
+inline bool keep_plain_estimate(uint64_t d) { return 4 * d > 4 * MB && 4 * d <= 160 * MB; }   // uniform variant without rotation
 
 // Uniform quantizer on a vector of d coordinates: one group of eight coordinates to a thread, 4096 to a workgroup, or two.
 // One group / two, us:

@@ -305,6 +305,7 @@ struct UDequantArgs {
   uint32_t L, agg_bits, divisor;
 };
 
+template <Mem OUT>
 __global__ __launch_bounds__(256) void k_uniform_dequant(const UDequantArgs a) {
   if (a.agg_bits == 8 || a.agg_bits == 16) {
     // byte-aligned sums: four coordinates per thread and step, so that a wave writes 1 KB at a time
@@ -324,8 +325,8 @@ __global__ __launch_bounds__(256) void k_uniform_dequant(const UDequantArgs a) {
       const uint64_t blk = j >> a.L;
       const float M = a.range_M[blk], m = lower_of(a.range_m, blk, M);
       const float step = (float)(((double)M - (double)m) / (double)a.divisor);
-      store_f4<STREAM>(a.out + j, make_float4((float)y[0] * step + m, (float)y[1] * step + m, (float)y[2] * step + m,
-                                              (float)y[3] * step + m));
+      store_f4<OUT>(a.out + j, make_float4((float)y[0] * step + m, (float)y[1] * step + m, (float)y[2] * step + m,
+                                           (float)y[3] * step + m));
     }
     return;
   }

@@ -256,6 +256,17 @@ static int check_whole_split() {
          whole_split(p14, 130, 1) + whole_split(p13, 2, 1);
 }
 
+// ... of the estimate's stores
+static int check_keep_estimate() {
+  int bad = 0;
+  for (int L = 10; L <= 25; ++L) {
+    const uint64_t most = (L == 22 ? 80 : 160) * MB / 4;
+    bad += keep_estimate(4 * MB, L) || !keep_estimate(4 * MB + 1024, L) || !keep_estimate(most, L) || keep_estimate(most + 1024, L);
+  }
+  return bad + keep_plain_estimate(MB) + !keep_plain_estimate(MB + 1024) + !keep_plain_estimate(40 * MB) +
+         keep_plain_estimate(40 * MB + 1024);
+}
+
 // ... and of the cache hints: a call just below each limit and one at it.
 static int check_hints() {
   int bad = 0;
@@ -345,7 +356,7 @@ int main() {
   bad += check_pieces(1ull << 10, 1) + check_pieces(1ull << 34, 1) + check_pieces((1ull << 34) + 1024, 2);
   bad += check_pieces((1ull << 36) - 1024, 4) + check_pieces(5ull << 34, 5);
   bad += check_xcd_tile<2>() + check_xcd_tile<3>() + check_xcd_tile<4>() + check_xcd_tile<6>();
-  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints() + check_even_share() + check_even_walk() + check_walks_in_shares() + check_whole_split();
+  bad += check_whole_route() + check_inv_whole_14() + check_last_first() + check_hints() + check_keep_estimate() + check_even_share() + check_even_walk() + check_walks_in_shares() + check_whole_split();
   // the uniform quantizer's groups of coordinates: the limits, and that bf16 without error feedback has none
   for (bool bf16 : {false, true}) bad += !uniform_one_group(1 << 20, bf16, true) || uniform_one_group((1 << 20) + 1024, bf16, true);
   bad += !uniform_one_group(1 << 22, false, false) || uniform_one_group((1 << 22) + 1024, false, false);

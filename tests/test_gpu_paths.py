@@ -375,7 +375,11 @@ def test_walk_from_the_last_tile(log2_block, K, n, ef, order):
 @pytest.mark.parametrize("log2_block,K,step,n,bf16,ef,order", [
     # 2^26 coordinates and more of all vectors: the error-feedback inverse's first pass; bf16 gradients of more than 160 MB with
     # their buffers on tiles of 2^15
-    (18, 132, 40, 2, False, True, 0), (18, 132, 40, 2, True, True, 1), (23, 5, 2, 1, True, True, 0), (23, 5, 2, 1, True, True, 1)])
+    (18, 132, 40, 2, False, True, 0), (18, 132, 40, 2, True, True, 1), (23, 5, 2, 1, True, True, 0), (23, 5, 2, 1, True, True, 1),
+    # estimates of 40 to 192 MB by way of every kernel that writes them
+    (10, 10241, 4096, 1, False, False, 0), (13, 1281, 512, 1, False, False, 0), (14, 641, 256, 1, False, False, 0),
+    (14, 2560, 256, 1, False, False, 0), (15, 323, 128, 1, False, False, 0), (16, 160, 64, 1, False, False, 1),
+    (20, 11, 4, 1, False, False, 0), (22, 3, 1, 1, False, False, 1), (23, 6, 2, 1, False, False, 0), (24, 3, 1, 1, False, False, 1)])
 def test_a_large_call_gives_what_its_slices_give(log2_block, K, step, n, bf16, ef, order):
     """Rules that look at the size of a launch choose how memory is read and written, never what is computed: a whole round on
     large vectors, every output bit for bit that of rounds on slices which lie on the other side of those rules."""

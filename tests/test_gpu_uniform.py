@@ -55,6 +55,24 @@ def test_uniform_round_with_error_feedback_without_rotation(block, K, b, bf16):
     _uniform_round(block, K, 2, b, 16, True, 3, False, bf16=bf16)
 
 
+@pytest.mark.parametrize("agg_bits", [8, 16, 7])
+def test_estimate_without_rotation_by_its_size(agg_bits):
+    """An estimate of more than 4 MB is stored otherwise than its slices: the same values."""
+    block, K = 1 << 10, 1025
+    _, L = uparams(K * block, block, 3, 4, agg_bits)
+    gen = torch.Generator(device=DEV).manual_seed(agg_bits)
+    agg = torch.randint(0, 256, (K * block * agg_bits // 8,), dtype=torch.uint8, device=DEV, generator=gen)
+    m, M = -torch.rand(K, device=DEV, generator=gen), torch.rand(K, device=DEV, generator=gen)
+    out = torch.zeros(K * block, device=DEV)
+    api.thc_uniform_decompress(L, 0, agg, False, m, M, out, None)
+    for k in range(0, K, 400):
+        n = min(400, K - k)
+        _, S = uparams(n * block, block, 3, 4, agg_bits)
+        part, cut = torch.zeros(n * block, device=DEV), agg[k * block * agg_bits // 8:(k + n) * block * agg_bits // 8].clone()
+        api.thc_uniform_decompress(S, 0, cut, False, m[k:k + n].clone(), M[k:k + n].clone(), part, None)
+        assert torch.equal(part, out[k * block:(k + n) * block])
+
+
 @pytest.mark.parametrize("bf16,ef", [(False, False), (False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("n", [1, 3])
 def test_range_of_vectors_beyond_the_cache(n, bf16, ef):
