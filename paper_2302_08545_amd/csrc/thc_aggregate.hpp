@@ -272,7 +272,9 @@ struct AggB4WxArgs {
   uint32_t tb[4];
 };
 
-template <int W, Mem M>
+//
+// FOUR: four workers' loads in flight, see sums_four_loads.
+template <int W, Mem M, bool FOUR>
 __global__ __launch_bounds__(256) void k_aggregate_b4wx(const AggB4WxArgs a) {
   __shared__ __align__(16) uint32_t stage[256 * W];
   const int t = threadIdx.x;
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(256) void k_aggregate_b4wx(const AggB4WxArgs a) {
         }
       };
       uint32_t i = i0;
-      if constexpr (M == KEEP) {           // a small call: four loads in flight
+      if constexpr (FOUR) {
         for (; i + 4 <= i1; i += 4) {
           uint4 r[4];
 #pragma unroll

@@ -879,7 +879,11 @@ int run_aggregate(const thc_params* p, const uint8_t* const* packed, uint8_t* ou
     a.chunk = 255u / p->g;              // g <= 255, so at least one worker per run
     std::memcpy(a.tb, p->table, 16);
     switch (p->agg_bits) {
-#define THC_AGG_WX(W) case W: k_aggregate_b4wx<W, M><<<grid, blk, 0, s>>>(a); break;
+#define THC_AGG_WX(W)                                                                         \
+  case W:                                                                                     \
+    if (M == KEEP || sums_four_loads(p->d)) k_aggregate_b4wx<W, M, true><<<grid, blk, 0, s>>>(a); \
+    else k_aggregate_b4wx<W, M, M == KEEP><<<grid, blk, 0, s>>>(a);                           \
+    break;
       THC_AGG_WX(4) THC_AGG_WX(5) THC_AGG_WX(6) THC_AGG_WX(7) THC_AGG_WX(9) THC_AGG_WX(10) THC_AGG_WX(11)
       THC_AGG_WX(12) THC_AGG_WX(13) THC_AGG_WX(14) THC_AGG_WX(15) THC_AGG_WX(16)
 #undef THC_AGG_WX

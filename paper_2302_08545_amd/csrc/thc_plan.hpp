@@ -280,7 +280,12 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // of 1 GB: 2^10 0.99, 2^13 0.99, 2^14 0.99 to 1.00, 0.99 with error feedback; bf16 with error feedback, 2^13, 1.02.
 // stream_sums: the aggregation.  Time of streamed over kept, by the streams' bytes together, on three sets of them in turn: 34 MB
 // 1.05, 66 MB 1.02 to 1.19 (0.80 to 0.95 with 3-bit indices, 16-bit sums or 3 workers), 82 MB 0.80 to 0.93, 100 to 190 MB 0.76 to
-// 0.94, 840 MB 0.85 to 0.95; behind the quantizer of the same round 67 MB 0.99, 105 MB 1.00.
+// 0.94, 840 MB 0.85 to 0.95; behind the quantizer of the same round 67 MB 0.99, 105 MB 1.00.  A single stream of 3-bit indices, whose
+// three loads a thread share their lines, 1.12 to 1.15 from 100 MB on, of 2-bit ones 0.98 to 1.02: kept.
+// sums_four_loads: streamed sums of 4-bit indices at other widths than 8 with four workers' loads in flight, where a call has few
+// wavefronts to hide them.  Time over that of one, 16-bit sums: 32 workers of 5 * 2^20 coordinates 0.70, 6.25 * 2^20 0.77, 8 * 2^20
+// 0.86, 12 * 2^20 1.04, 16 * 2^20 1.13; 16 workers of 10 * 2^20 0.95, 12.5 * 2^20 1.00, 16 * 2^20 1.05, 24 * 2^20 1.03; 8 workers
+// of 20 * 2^20 0.95, 25 * 2^20 0.99, 32 * 2^20 1.02.
 // keep_estimate: the estimate, which the caller reads next, is stored plainly, or else non-temporally.  Kept over streamed, the
 // decompression and a step that reads the estimate (w -= lr * out) together, by the size of the estimate:
 //                  4 to 12 MB     16 MB          24 and 32 MB   48 to 96 MB    128 MB   160 MB         176 and 192 MB  208 to 256 MB
@@ -305,7 +310,8 @@ inline bool stream_norms(const Plan& pl, uint64_t len, uint32_t W, bool bf16, bo
 inline bool stream_blocks(uint64_t len, uint32_t W, bool bf16) { return !bf16 && input_bytes(len, W, bf16, false) >= 64 * MB; }
 inline bool stream_rotated(uint64_t len, uint32_t W) { return W * len * 4 > 256 * MB; }
 inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
-inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB; }
+inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB && (n > 1 || b == 1 || b > 3); }
+inline bool sums_four_loads(uint64_t d) { return d <= 10 * MB; }   // coordinates
 
 inline bool stream_minmax(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 240 * MB; }
 

@@ -293,10 +293,11 @@ static int check_hints() {
     bad += !through_inverse(64 * MB / W, W) || through_inverse(64 * MB / W + 1024, W);
     for (uint32_t b : {1u, 3u, 4u, 8u}) {
       const uint64_t d = 80 * MB / W / b * 8;
-      bad += stream_sums(d - 1024, W, b) || !stream_sums(d + 1024, W, b);
+      bad += stream_sums(d - 1024, W, b) || stream_sums(d + 1024, W, b) == (W == 1 && b == 3);
     }
   }
-  return bad;
+  return bad + stream_sums(80 * MB * 4 + 1024, 1, 2) + !stream_sums(40 * MB * 4 + 1024, 2, 2) + !sums_four_loads(10 * MB) +
+         sums_four_loads(10 * MB + 1024);
 }
 
 // The index of a coordinate above the range, for the largest rounding draw: what the quantizer's fast form, which does

@@ -144,11 +144,12 @@ def test_sums_of_any_width(b, g, n):
 
 
 @pytest.mark.parametrize("b,g,agg_bits,n", [(4, 30, 8, 8), (4, 15, 7, 8), (4, 30, 9, 9), (4, 100, 16, 8), (2, 8, 8, 16),
-                                            (2, 8, 16, 16), (3, 31, 9, 11), (1, 1, 6, 32), (5, 36, 8, 7), (8, 255, 16, 4)])
+                                            (2, 8, 16, 16), (3, 31, 9, 11), (1, 1, 6, 32), (5, 36, 8, 7), (8, 255, 16, 4),
+                                            (4, 30, 16, 32), (4, 15, 9, 31), (3, 7, 3, 1)])
 def test_sums_of_streams_beyond_the_cache(b, g, agg_bits, n):
     """Streams of 80 MB and more together go past the caches: the whole against slices of it, which do not, bit for bit; the
-    last workgroup is mostly empty."""
-    block, K = 1 << 10, (5 << 12) + 1
+    last workgroup is mostly empty.  Of 31 and 32 workers with four loads in flight; a single stream of 3-bit indices is kept."""
+    block, K = 1 << 10, ((5 << 12) if n < 30 or b != 4 else 9 << 10) * (12 if n == 1 else 1) + 1
     T = [round(i * g / ((1 << b) - 1)) for i in range(1 << b)]
     assert n * block * K * b // 8 >= 80 << 20
     _, L = both_params(block * K, block, n, b=b, g=g, agg_bits=agg_bits, table=T)
