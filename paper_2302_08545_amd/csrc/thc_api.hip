@@ -249,40 +249,47 @@ template <int R> struct LaunchInvHi {
   }
 };
 
-template <int L1, bool BF16, bool EF>
+template <int L1, bool BF16, bool EF, Mem LOAD>
 void launch_fwd_lo_k(const FwdLoArgs& a, bool split, bool norm_only, uint64_t tiles, uint32_t n, hipStream_t s) {
   const dim3 grid((unsigned)tiles, n);
   if constexpr (L1 == LOG_TILE) {
     if (split) {
-      if (norm_only) k_fwd_lo<L1, BF16, EF, true, true><<<grid, dim3(NT), 0, s>>>(a);
-      else k_fwd_lo<L1, BF16, EF, true, false><<<grid, dim3(NT), 0, s>>>(a);
+      if (norm_only) k_fwd_lo<L1, BF16, EF, true, true, LOAD><<<grid, dim3(NT), 0, s>>>(a);
+      else k_fwd_lo<L1, BF16, EF, true, false, LOAD><<<grid, dim3(NT), 0, s>>>(a);
       return;
     }
   }
-  if (norm_only) k_fwd_lo<L1, BF16, EF, false, true><<<grid, dim3(NT), 0, s>>>(a);
-  else k_fwd_lo<L1, BF16, EF, false, false><<<grid, dim3(NT), 0, s>>>(a);
+  if (norm_only) k_fwd_lo<L1, BF16, EF, false, true, LOAD><<<grid, dim3(NT), 0, s>>>(a);
+  else k_fwd_lo<L1, BF16, EF, false, false, LOAD><<<grid, dim3(NT), 0, s>>>(a);
 }
 
-template <int L1>
+template <int L1, Mem LOAD>
 void launch_fwd_lo_t(const FwdLoArgs& a, bool bf16, bool ef, bool split, bool norm_only, uint64_t tiles, uint32_t n,
                      hipStream_t s) {
   if (bf16) {
-    if (ef) launch_fwd_lo_k<L1, true, true>(a, split, norm_only, tiles, n, s);
-    else launch_fwd_lo_k<L1, true, false>(a, split, norm_only, tiles, n, s);
+    if (ef) launch_fwd_lo_k<L1, true, true, LOAD>(a, split, norm_only, tiles, n, s);
+    else launch_fwd_lo_k<L1, true, false, LOAD>(a, split, norm_only, tiles, n, s);
   } else {
-    if (ef) launch_fwd_lo_k<L1, false, true>(a, split, norm_only, tiles, n, s);
-    else launch_fwd_lo_k<L1, false, false>(a, split, norm_only, tiles, n, s);
+    if (ef) launch_fwd_lo_k<L1, false, true, LOAD>(a, split, norm_only, tiles, n, s);
+    else launch_fwd_lo_k<L1, false, false, LOAD>(a, split, norm_only, tiles, n, s);
   }
 }
 
-void launch_fwd_lo(const Plan& pl, const FwdLoArgs& a, bool bf16, bool ef, bool norm_only, uint64_t tiles, uint32_t n,
-                   hipStream_t s) {
+template <Mem LOAD>
+void launch_fwd_lo_m(const Plan& pl, const FwdLoArgs& a, bool bf16, bool ef, bool norm_only, uint64_t tiles, uint32_t n,
+                     hipStream_t s) {
   switch (pl.L1) {
-    case 10: launch_fwd_lo_t<10>(a, bf16, ef, false, norm_only, tiles, n, s); break;
-    case 11: launch_fwd_lo_t<11>(a, bf16, ef, false, norm_only, tiles, n, s); break;
-    case 12: launch_fwd_lo_t<12>(a, bf16, ef, false, norm_only, tiles, n, s); break;
-    default: launch_fwd_lo_t<13>(a, bf16, ef, pl.split, norm_only, tiles, n, s); break;
+    case 10: launch_fwd_lo_t<10, LOAD>(a, bf16, ef, false, norm_only, tiles, n, s); break;
+    case 11: launch_fwd_lo_t<11, LOAD>(a, bf16, ef, false, norm_only, tiles, n, s); break;
+    case 12: launch_fwd_lo_t<12, LOAD>(a, bf16, ef, false, norm_only, tiles, n, s); break;
+    default: launch_fwd_lo_t<13, LOAD>(a, bf16, ef, pl.split, norm_only, tiles, n, s); break;
   }
+}
+
+void launch_fwd_lo(const Plan& pl, const FwdLoArgs& a, bool bf16, bool ef, bool norm_only, bool stream, uint64_t tiles,
+                   uint32_t n, hipStream_t s) {
+  if (stream) launch_fwd_lo_m<STREAM>(pl, a, bf16, ef, norm_only, tiles, n, s);
+  else launch_fwd_lo_m<KEEP>(pl, a, bf16, ef, norm_only, tiles, n, s);
 }
 
 void launch_range(const RangeArgs& r, hipStream_t s) {
@@ -620,15 +627,22 @@ void run_forward_pipe(const Forward& f, const Plan& pl, const PipeShape& sh) {
 }
 
 template <int L, bool BF16>
-void launch_whole_k(const WholeArgs& a, bool ef, bool find, dim3 grid, hipStream_t s) {
+void launch_whole_k(const WholeArgs& a, bool ef, bool find, bool stream, dim3 grid, hipStream_t s) {
   const dim3 blk(WholeTile<L>::N);
+  if constexpr (!BF16) {
+    if (stream && !find) {
+      if (ef) k_whole<L, BF16, true, false, false, STREAM><<<grid, blk, 0, s>>>(a);
+      else k_whole<L, BF16, false, false, false, STREAM><<<grid, blk, 0, s>>>(a);
+      return;
+    }
+  }
   if (ef) k_whole<L, BF16, true, false><<<grid, blk, 0, s>>>(a);
   else if (find) k_whole<L, BF16, false, true><<<grid, blk, 0, s>>>(a);
   else k_whole<L, BF16, false, false><<<grid, blk, 0, s>>>(a);
 }
 
 template <int L>
-void launch_whole(const WholeArgs& a, bool bf16, bool ef, bool find, bool split, uint32_t W, hipStream_t s) {
+void launch_whole(const WholeArgs& a, bool bf16, bool ef, bool find, bool split, bool stream, uint32_t W, hipStream_t s) {
   const dim3 grid((unsigned)((a.d + (1ull << WholeTile<L>::LOG) - 1) >> WholeTile<L>::LOG), W);
   if constexpr (L == 14) {
     if (find && split) {
@@ -638,8 +652,8 @@ void launch_whole(const WholeArgs& a, bool bf16, bool ef, bool find, bool split,
       return;
     }
   }
-  if (bf16) launch_whole_k<L, true>(a, ef, find, grid, s);
-  else launch_whole_k<L, false>(a, ef, find, grid, s);
+  if (bf16) launch_whole_k<L, true>(a, ef, find, stream, grid, s);
+  else launch_whole_k<L, false>(a, ef, find, stream, grid, s);
 }
 
 // the norms of `len` coordinates, from x0 on, of W vectors and their range (Alg. 3's preliminary stage)
@@ -655,8 +669,7 @@ void run_norms(const thc_params* p, const Plan& pl, const void* const* grads, co
   a.pstride = len >> pl.L1;
   a.d = len;
   a.tm = lo_tilemap(pl, len);
-  a.stream = stream_norms(pl, len, W, bf16, ef != nullptr);
-  launch_fwd_lo(pl, a, bf16, ef != nullptr, true, tiles_of(len), W, s);
+  launch_fwd_lo(pl, a, bf16, ef != nullptr, true, stream_norms(pl, len, W, bf16, ef != nullptr), tiles_of(len), W, s);
   launch_range(RangeArgs{partials, range_M + x0 / p->block, a.pstride, len, W, (uint32_t)pl.L, (uint32_t)pl.L1, p->t_p}, s);
 }
 
@@ -688,15 +701,14 @@ void run_forward_whole(const Forward& f, const Plan& pl, Whole route) {
     }
     a.range_M = range_M + x0 / p->block;
     a.d = len;
-    a.stream = stream_blocks(len, f.W, bf16);
-    const bool split = whole_split(pl, tiles_of(len), f.W);
+    const bool stream = stream_blocks(len, f.W, bf16), split = whole_split(pl, tiles_of(len), f.W);
     a.j0 = base_coord(p) + x0;
     switch (pl.L) {
-      case 10: launch_whole<10>(a, bf16, ef, find, split, f.W, f.s); break;
-      case 11: launch_whole<11>(a, bf16, ef, find, split, f.W, f.s); break;
-      case 12: launch_whole<12>(a, bf16, ef, find, split, f.W, f.s); break;
-      case 13: launch_whole<13>(a, bf16, ef, find, split, f.W, f.s); break;
-      default: launch_whole<14>(a, bf16, ef, find, split, f.W, f.s); break;
+      case 10: launch_whole<10>(a, bf16, ef, find, split, stream, f.W, f.s); break;
+      case 11: launch_whole<11>(a, bf16, ef, find, split, stream, f.W, f.s); break;
+      case 12: launch_whole<12>(a, bf16, ef, find, split, stream, f.W, f.s); break;
+      case 13: launch_whole<13>(a, bf16, ef, find, split, stream, f.W, f.s); break;
+      default: launch_whole<14>(a, bf16, ef, find, split, stream, f.W, f.s); break;
     }
   });
 }
@@ -779,8 +791,7 @@ void run_forward(const Forward& f) {
       launch_big_lo(pl, bl, bf16, f.efs != nullptr, f.W, f.s);
     } else {
       a.tm = lo_tilemap(pl, len);
-      a.stream = stream_inputs(len, f.W, bf16, f.efs != nullptr);
-      launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, tiles, f.W, f.s);
+      launch_fwd_lo(pl, a, bf16, f.efs != nullptr, false, stream_inputs(len, f.W, bf16, f.efs != nullptr), tiles, f.W, f.s);
     }
     const bool find = f.range_out && !big && find_range(pl, tiles, f.W);
     if (f.range_out && !find) {
@@ -812,6 +823,18 @@ void run_forward(const Forward& f) {
       run_inverse(p, pl, ilo, slot, ihi, len, inv_big, f.W, f.s);
     }
   }, walk.unit);
+}
+
+template <Mem LOAD>
+void launch_minmax(const MinMaxArgs& a, bool bf16, bool ef, uint32_t W, hipStream_t s) {
+  const dim3 grid((unsigned)tiles_of(a.d), W), blk(NT);
+  if (bf16) {
+    if (ef) k_minmax<true, true, LOAD><<<grid, blk, 0, s>>>(a);
+    else k_minmax<true, false, LOAD><<<grid, blk, 0, s>>>(a);
+  } else {
+    if (ef) k_minmax<false, true, LOAD><<<grid, blk, 0, s>>>(a);
+    else k_minmax<false, false, LOAD><<<grid, blk, 0, s>>>(a);
+  }
 }
 
 template <bool BF16, int G>
@@ -1139,8 +1162,7 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.k0 = (uint32_t)p->seed;
     a.k1 = (uint32_t)(p->seed >> 32);
     a.tm = lo_tilemap(pl, p->d);
-    a.stream = stream_inputs(p->d, p->n, bf16, ef != nullptr);
-    launch_fwd_lo(pl, a, bf16, ef != nullptr, false, tiles_of(p->d), p->n, s);
+    launch_fwd_lo(pl, a, bf16, ef != nullptr, false, stream_inputs(p->d, p->n, bf16, ef != nullptr), tiles_of(p->d), p->n, s);
     run_mids(pl, static_cast<float*>(ws), p->d, p->n, s);
     const HiMinMaxArgs h{static_cast<float*>(ws), pmin, pmax, p->d,
                         walk_over(last_first(pl, p->d, p->n, false, false), tiles_of(p->d), p->n), pl.hi, (uint32_t)pl.L,
@@ -1156,10 +1178,8 @@ int thc_uniform_prepare_range(const thc_params* p, uint64_t round, const void* c
     a.pmax = pmax;
     a.d = p->d;
     a.L1 = (uint32_t)pl.L1;
-    a.stream = stream_minmax(p->d, p->n, bf16, ef != nullptr);
-    const dim3 grid((unsigned)tiles_of(p->d), p->n), blk(NT);
-    if (bf16) { if (ef) k_minmax<true, true><<<grid, blk, 0, s>>>(a); else k_minmax<true, false><<<grid, blk, 0, s>>>(a); }
-    else { if (ef) k_minmax<false, true><<<grid, blk, 0, s>>>(a); else k_minmax<false, false><<<grid, blk, 0, s>>>(a); }
+    if (stream_minmax(p->d, p->n, bf16, ef != nullptr)) launch_minmax<STREAM>(a, bf16, ef != nullptr, p->n, s);
+    else launch_minmax<KEEP>(a, bf16, ef != nullptr, p->n, s);
   }
   MinMaxFinalArgs f{pmin, pmax, range_m, range_M, p->d, p->n, (uint32_t)pl.L, (uint32_t)pl.L1};
   k_minmax_final<<<dim3((unsigned)(p->d / p->block)), dim3(64), 0, s>>>(f);

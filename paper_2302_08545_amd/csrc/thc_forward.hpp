@@ -21,7 +21,6 @@ struct FwdLoArgs {
   uint64_t j0;         // global coordinate of the vectors' first element (a multiple of B): indexes the diagonal
   uint32_t round, k0, k1;
   TileMap tm;          // where the bits of the tile index land; the tile shape is a template parameter
-  uint32_t stream;     // see stream_inputs
 };
 
 // Tile index -> offset inside the tile's span for the "lo" passes.  XO = false: 8192 consecutive
@@ -56,8 +55,9 @@ struct alignas(16) SmemLo {
 };
 
 // One tile of the pass: tile index `tile` of vector `worker`; `dst` is where coordinate 0 of that vector's
-// half-rotated image lives (the tile's results go to dst[offset in the vector]).
-template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY, class A>
+// half-rotated image lives (the tile's results go to dst[offset in the vector]).  LOAD: how the vectors are read (stream_inputs,
+// stream_norms); chosen by the launch, since a choice in the kernel took small calls with error feedback 2 to 4 % (13.0 us).
+template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY, Mem LOAD, class A>
 __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t worker, float* dst_vec,
                                             SmemLo& sm) {
   static_assert(!XO || L1 == LOG_TILE, "the row-split tile needs blocks of at least 2^16");
@@ -75,21 +75,17 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
 
   // all loads of the tile are issued before anything waits on them
   float4 x[4], e[4];
-  auto load = [&](auto mem) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint64_t j = off + lo_map<XO>(4u * (uint32_t)(i * NT + t));
-      const bool ok = !GUARD || j < a.d;
-      x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      e[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (ok) {
-        x[i] = load_grad4<BF16, mem.value>(grad, j);
-        if constexpr (EF) e[i] = load_f4<mem.value>(ef + j);
-      }
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t j = off + lo_map<XO>(4u * (uint32_t)(i * NT + t));
+    const bool ok = !GUARD || j < a.d;
+    x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    e[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (ok) {
+      x[i] = load_grad4<BF16, LOAD>(grad, j);
+      if constexpr (EF) e[i] = load_f4<LOAD>(ef + j);
     }
-  };
-  if (a.stream) load(Const<STREAM>{});
-  else load(Const<KEEP>{});
+  }
 
   if (!NORM_ONLY && t < 64) {   // the tile's 8192 diagonal entries: 64 Philox calls of 128 bits
     const uint64_t q = (a.j0 + off + lo_map<XO>(128u * t)) >> 7;
@@ -166,10 +162,10 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
 // One workgroup per tile (grid = (tiles, n workers)): measured on MI355X this streams faster than a
 // persistent grid with software prefetch, the hardware dispatcher keeps four workgroups per CU in flight.
 // NORM_ONLY: stop after the partial sums of squares (the norm exchange of Alg. 3 on its own): same sums, same order.
-template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY = false>
+template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY, Mem LOAD>
 __global__ __launch_bounds__(NT) void k_fwd_lo(const FwdLoArgs a) {
   __shared__ SmemLo sm;
-  fwd_lo_tile<L1, BF16, EF, XO, NORM_ONLY>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
+  fwd_lo_tile<L1, BF16, EF, XO, NORM_ONLY, LOAD>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------

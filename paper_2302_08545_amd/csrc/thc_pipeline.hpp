@@ -67,7 +67,6 @@ struct LoView {
   uint64_t pstride, d, j0;
   uint32_t round, k0, k1;
   const TileMap& tm;
-  uint32_t stream;
 };
 struct QuantView {
   const float* range_M;
@@ -203,8 +202,8 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
       const uint32_t* old = P.sync + (uint64_t)(u - P.slots) * SYNC_PER_UNIT + SYNC_DONE * SYNC_STRIDE;
       if (!pipe_wait<false>(old, Tu, P.status, &flag)) return;
     }
-    const LoView a{P.grads, P.efs, P.partials, P.pstride, P.d, P.j0, P.round, P.k0, P.k1, P.lo_tm, !EF};
-    fwd_lo_tile<LOG_TILE, BF16, EF, true, false>(a, gt, w, vec, *reinterpret_cast<SmemLo*>(raw));
+    const LoView a{P.grads, P.efs, P.partials, P.pstride, P.d, P.j0, P.round, P.k0, P.k1, P.lo_tm};
+    fwd_lo_tile<LOG_TILE, BF16, EF, true, false, EF ? KEEP : STREAM>(a, gt, w, vec, *reinterpret_cast<SmemLo*>(raw));
     pipe_publish(us, 0, Tu >> 3);
   } else if (phase == 1) {
     if (!pipe_wait<true>(us + SYNC_READY * SYNC_STRIDE, 1u, P.status, &flag)) return;

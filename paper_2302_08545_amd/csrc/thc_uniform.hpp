@@ -29,42 +29,38 @@ struct MinMaxArgs {
   float* pmax;
   uint64_t d;
   uint32_t L1;       // log2 of min(B, 8192)
-  uint32_t stream;   // see stream_minmax
 };
 
-template <bool BF16, bool EF>
+// LOAD: how the vectors are read, see stream_minmax.
+template <bool BF16, bool EF, Mem LOAD>
 __global__ __launch_bounds__(NT) void k_minmax(const MinMaxArgs a) {
   __shared__ float smin[32], smax[32];   // one per 256 consecutive coordinates of the tile
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const uint32_t worker = blockIdx.y;
   const uint64_t off = (uint64_t)xcd_tile(blockIdx.x, gridDim.x) << LOG_TILE;
   const float* ef = EF ? static_cast<const float*>(a.efs.p[worker]) : nullptr;
-  auto scan = [&](auto mem) {
-    // past the end: read from the tile's start, not used
-    auto at = [&](int i) { const uint64_t j = off + 4u * (uint32_t)(i * NT + t); return j < a.d ? j : off; };
-    float4 x[4];
+  // past the end: read from the tile's start, not used
+  auto at = [&](int i) { const uint64_t j = off + 4u * (uint32_t)(i * NT + t); return j < a.d ? j : off; };
+  float4 x[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (!EF) x[i] = load_grad4<BF16, mem.value>(a.grads.p[worker], at(i));
+  for (int i = 0; i < 4; ++i)
+    if (!EF) x[i] = load_grad4<BF16, LOAD>(a.grads.p[worker], at(i));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if constexpr (EF) {                  // twice the loads: all of them at once are slower (bf16 by 4 %)
-        x[i] = load_grad4<BF16, mem.value>(a.grads.p[worker], at(i));
-        const float4 e = load_f4<mem.value>(ef + at(i));
-        x[i].x += e.x; x[i].y += e.y; x[i].z += e.z; x[i].w += e.w;
-      }
-      float mn = __builtin_inff(), mx = -__builtin_inff();
-      if (off + 4u * (uint32_t)(i * NT + t) < a.d) {
-        mn = __builtin_fminf(__builtin_fminf(x[i].x, x[i].y), __builtin_fminf(x[i].z, x[i].w));
-        mx = __builtin_fmaxf(__builtin_fmaxf(x[i].x, x[i].y), __builtin_fmaxf(x[i].z, x[i].w));
-      }
-      mn = wave_min(mn);
-      mx = wave_max(mx);
-      if (lane == 0) { smin[i * 8 + wave] = mn; smax[i * 8 + wave] = mx; }
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (EF) {                    // twice the loads: all of them at once are slower (bf16 by 4 %)
+      x[i] = load_grad4<BF16, LOAD>(a.grads.p[worker], at(i));
+      const float4 e = load_f4<LOAD>(ef + at(i));
+      x[i].x += e.x; x[i].y += e.y; x[i].z += e.z; x[i].w += e.w;
     }
-  };
-  if (a.stream) scan(Const<STREAM>{});
-  else scan(Const<KEEP>{});
+    float mn = __builtin_inff(), mx = -__builtin_inff();
+    if (off + 4u * (uint32_t)(i * NT + t) < a.d) {
+      mn = __builtin_fminf(__builtin_fminf(x[i].x, x[i].y), __builtin_fminf(x[i].z, x[i].w));
+      mx = __builtin_fmaxf(__builtin_fmaxf(x[i].x, x[i].y), __builtin_fmaxf(x[i].z, x[i].w));
+    }
+    mn = wave_min(mn);
+    mx = wave_max(mx);
+    if (lane == 0) { smin[i * 8 + wave] = mn; smax[i * 8 + wave] = mx; }
+  }
   __syncthreads();
   const int nblk = TILE >> a.L1, cpb = 32 / nblk;   // chunks of 256 per block inside the tile
   if (t < nblk) {

@@ -23,7 +23,6 @@ struct WholeArgs {
   uint32_t L, b, g;
   uint32_t round, worker, k0, k1;
   uint32_t n;              // FIND: vectors of the launch
-  uint32_t stream;         // see stream_blocks
   float c, t_p;
   uint32_t lut[256];
   uint8_t table[256];
@@ -83,8 +82,9 @@ __device__ __forceinline__ double whole_block_sum(const double* wsum, int k) {
   }
 }
 
-// SPLIT: two workgroups to a tile, both of which transform all of it and quantize half (see whole_split).
-template <int L, bool BF16, bool EF, bool FIND, bool SPLIT = false>
+// SPLIT: two workgroups to a tile, both of which transform all of it and quantize half (see whole_split).  LOAD: how the gradients
+// are read (see stream_blocks).
+template <int L, bool BF16, bool EF, bool FIND, bool SPLIT = false, Mem LOAD = KEEP>
 __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(const WholeArgs a) {
   static_assert(!SPLIT || FIND, "small calls");
   static_assert(!(EF && FIND), "the buffers would be read by some workgroups while others write them");
@@ -104,23 +104,22 @@ __global__ __launch_bounds__(WholeTile<L>::N, FIND || EF ? 4 : 8) void k_whole(c
 
   const uint32_t ent = a.lut[t & 255], entry = a.table[t & 255];
   __builtin_amdgcn_sched_barrier(0);
-  auto load = [&](uint32_t w, float4 (&x)[4], auto mem) {
+  auto load = [&](uint32_t w, float4 (&x)[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {              // past the end: read from the tile's start, not used
       const uint64_t j = off + first + 4 * 512 * i;
-      x[i] = load_grad4<BF16, mem.value>(a.grads.p[w], j < a.d ? j : off);
+      x[i] = load_grad4<BF16, LOAD>(a.grads.p[w], j < a.d ? j : off);
     }
   };
   float4 x[4];
-  if (!FIND && a.stream) load(vec, x, Const<STREAM>{});
-  else load(vec, x, Const<KEEP>{});
+  load(vec, x);
   if constexpr (FIND) {                        // the other workers three at a time
     auto other = [&](uint32_t c) { return vec + c < a.n ? vec + c : vec + c - a.n; };
     for (uint32_t c = 1; c < a.n; c += 3) {
       float4 y[3][4];
 #pragma unroll
       for (uint32_t u = 0; u < 3; ++u)
-        if (c + u < a.n) load(other(c + u), y[u], Const<KEEP>{});
+        if (c + u < a.n) load(other(c + u), y[u]);
 #pragma unroll
       for (uint32_t u = 0; u < 3; ++u)
         if (c + u < a.n) whole_squares<L>(y[u], sm.wsum[other(c + u)], wave, lane);

@@ -377,6 +377,9 @@ def test_walk_from_the_last_tile(log2_block, K, n, ef, order):
     # 2^26 coordinates and more of all vectors: the error-feedback inverse's first pass; bf16 gradients of more than 160 MB with
     # their buffers on tiles of 2^15
     (18, 132, 40, 2, False, True, 0), (18, 132, 40, 2, True, True, 1), (23, 5, 2, 1, True, True, 0), (23, 5, 2, 1, True, True, 1),
+    # more than 64 MB of gradients and buffers in blocks of up to 2^13: the norms and the blocks
+    (10, 9001, 4000, 2, False, False, 0), (11, 4500, 2000, 2, False, True, 0), (12, 1400, 600, 2, True, True, 0),
+    (13, 1201, 500, 1, False, True, 0),
     # estimates of 40 to 192 MB by way of every kernel that writes them
     (10, 10241, 4096, 1, False, False, 0), (13, 1281, 512, 1, False, False, 0), (14, 641, 256, 1, False, False, 0),
     (14, 2560, 256, 1, False, False, 0), (15, 323, 128, 1, False, False, 0), (16, 160, 64, 1, False, False, 1),
