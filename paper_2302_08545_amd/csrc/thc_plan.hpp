@@ -198,27 +198,21 @@ inline bool whole_split(const Plan& pl, uint64_t tiles, uint32_t W) { return pl.
 
 // Blocks of 2^14, inverse transform in one launch: a block to a workgroup of 1024 threads (k_inv_whole) or two blocks to
 // one of 512 (k_big_inv_whole).  With few blocks the first has half the work on each of twice the compute units; 512 of its
-// workgroups are on the chip at once, and 1024 of the other's, which is why neither is better throughout; and it is the faster
-// one where codes and results no longer fit the 256 MB memory-side cache.  Time of the first over that of the second, by the
-// number of blocks:
-//   8-bit sums   0.63 to 0.95 up to 512, 0.96 at 704, 1.00 at 768, 1.08 at 1024, 0.90 to 0.99 from 1040 to 1792, 1.02 to 1.06 from
-//                1920 to 3136; beyond the cache (from 3277 on) 0.94 to 1.00 up to 7168 but for 1.01 to 1.04 at 3520 to 3648, 1.02
-//                to 1.04 from 8192 on
-//   4 bits       0.60 to 0.97 up to 704, 1.06 at 1024, 0.87 to 0.99 from 1040 to 1792, 1.00 to 1.06 from 1920 to 3520 (0.98 at 3136
-//                and 3392), 0.91 to 0.94 beyond the cache (3641)
-//   5, 9 and 12  0.61 to 0.96 up to 512, 0.99 to 1.01 at 640, 1.02 to 1.03 at 704, 1.09 to 1.13 at 1024, 0.89 to 0.95 from 1040 to
-//                1280, 1.01 to 1.04 to 1536, 0.96 to 1.00 from 1600 to 1792, 1.02 to 1.10 from 1920 on; beyond the cache (3543, 3197
-//                and 2979) 0.90 to 0.98 up to 8192, then 5 bits 0.93, 9 bits 0.99, 12 bits 1.00 to 1.02
-//   16 bits      the first always; the second has no form of its own for them
+// workgroups are on the chip at once, and 1024 of the other's, which is why neither is better throughout.  From 1025 blocks on it
+// is the faster one as long as the estimate is stored plainly (keep_estimate, 2560 blocks).  Time of the first over that of the
+// second, by the number of blocks, sums that no cache holds:
+//                  128 to 512     640            704 to 1024    1040 to 1280   1281 to 1792   1920 to 2560   2816 to 3600   from 4200 on
+//   8-bit sums     0.69 to 0.95   0.98           1.02 to 1.15   0.90 to 0.94   0.94 to 0.95   0.95 to 0.99   1.03 to 1.05   1.07 to 1.13
+//   4 bits         0.65 to 0.88   0.99           1.01 to 1.07   0.82 to 0.86   0.87 to 0.93   0.87 to 0.93   0.98 to 1.00   1.04 to 1.13
+//   5, 9 and 12    0.64 to 0.96   1.03 to 1.04   1.05 to 1.15   0.84 to 0.90   0.88 to 0.99   0.91 to 1.00   0.98 to 1.06   0.99 to 1.17
+//   16 bits        the first always; the second has no form of its own for them
 // With error feedback the second: the rotated uniform variant, and thc_compress_all where whole_route leaves it to the passes.
 inline bool inv_whole_14(uint64_t len, bool ef, uint32_t bits) {
   const uint64_t K = len >> 14;
   if (ef) return false;
   if (bits == 16) return true;
-  const bool even = bits == 4 || bits == 8;
-  if (K <= 1024) return K <= (even ? 704 : 640);
-  if (len / 8 * (32 + bits) <= 1ull << 28) return K <= 1792 && (even || K <= 1280 || K > 1536);
-  return bits < 8 || K <= (bits == 8 ? 7168 : 12288);
+  if (K <= 1024) return K <= (bits == 4 || bits == 8 ? 640 : 512);
+  return K <= 2560;
 }
 
 // Which passes of a call over W vectors of d coordinates, walked in launches of `len` coordinates of each, take tiles of

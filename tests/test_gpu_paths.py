@@ -317,7 +317,8 @@ def test_worker_side_of_more_than_2_to_the_36_coordinates(every_call):
 
 
 @pytest.mark.parametrize("K,agg_bits", [(1, 8), (3, 9), (704, 8), (705, 8), (705, 9), (705, 16), (1024, 9), (1025, 8), (640, 5),
-                                        (641, 5), (1280, 9), (1281, 9), (1537, 9), (1792, 4), (1793, 4), (2978, 12), (2979, 12), (7169, 8)])
+                                        (641, 5), (1280, 9), (1281, 9), (1537, 9), (1792, 4), (1793, 4), (2978, 12), (2979, 12), (7169, 8),
+                                        (512, 9), (513, 9), (640, 8), (641, 8), (2560, 5), (2561, 8)])
 def test_inverse_of_2_to_the_14_by_one_block_or_two_a_workgroup(K, agg_bits):
     """Both kernels give the same bits: the whole vector against its slices of at most eight blocks, which take one block a
     workgroup, on either side of the rule's limits; block 0 and the last one against the oracle."""
