@@ -6,8 +6,9 @@
 namespace thc {
 
 // ---------------------------------------------------------------------------------------------
-// What bounds it in large calls: reading n streams once.  There (from 80 MB on, stream_sums) M = STREAM: loads and stores non-temporal, the
-// sums as whole lines by way of LDS.  16 streams of 33 * 2^20 4-bit indices to 9-bit sums 65.7 -> 55.5 us (5.8 TB/s), of 100 *
+// What bounds it in large calls: reading n streams once.  There (from 80 MB on, stream_sums) M = STREAM: loads non-temporal (but for
+// indices of 5 bits and more, whose loads share lines), the sums of 4-bit indices and those of other widths than 8 and 16 bits
+// as whole lines by way of LDS and non-temporal as well; the others' are plain 16-byte stores.  16 streams of 33 * 2^20 4-bit indices to 9-bit sums 65.7 -> 55.5 us (5.8 TB/s), of 100 *
 // 2^20 to 16-bit sums 200 -> 171 (6.1 TB/s), 8 of 40 * 2^20 to 8-bit sums 40.0 -> 36.2, 10 of 64 * 2^20 3-bit ones 64.4 -> 57.8.
 // In small calls M = KEEP: the streams have just been written and are in the cache, and latency counts, so four workers'
 // loads are in flight (16 streams of 4 * 2^20 to 16-bit sums 12.2 -> 9.4 us; in large calls the same takes 1 to 6 % more).

@@ -519,7 +519,8 @@ __global__ __launch_bounds__(NT, 4) void k_big_inv_lo(const BigInvLoArgs a) {
 
 // ---------------------------------------------------------------------------------------------
 // Inverse last pass: finish H, scale, diagonal; EFM 0: out = result, 1 / 2: e <- (grad + e) - result with a binary32 /
-// bf16 gradient.  Accesses of whole lines, all of them non-temporal: rounds with error feedback 16 blocks of 2^22 x 32 in bf16
+// bf16 gradient.  Accesses of whole lines but for bf16 gradients at R = 9 (halves of 64 bytes; read plainly, 2 x 2^24 x 4 vectors
+// take 1.00 to 1.01 of the time, 4 x 8 1.01), all of them non-temporal: rounds with error feedback 16 blocks of 2^22 x 32 in bf16
 // 13.25 -> 12.87 ms, x 16 in binary32 7.53 -> 7.36, 2 of 2^24 x 4 1117 -> 1053 us, one worker of 4 blocks of 2^23 385 -> 339.
 // ---------------------------------------------------------------------------------------------
 struct BigInvHiArgs {

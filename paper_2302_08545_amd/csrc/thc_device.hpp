@@ -45,8 +45,9 @@ __device__ __forceinline__ uint32_t walk_y(const Walk& w) { return w.vec + w.ste
 
 // What an access leaves in the caches.
 //   KEEP     the default.
-//   STREAM   non-temporal: the line goes first.  Only for instructions that take whole 128-byte lines: where two instructions
-//            share a line, the second finds it gone (rows of 64 bytes, a pass over blocks of 2^22: 435 -> 455 us).
+//   STREAM   non-temporal: the line goes first.  For instructions that take whole 128-byte lines: where two instructions share a
+//            line, the second finds it gone (rows of 64 bytes, a pass over blocks of 2^22: 435 -> 455 us).  Where it is used
+//            all the same, the figures stand there.
 //   THROUGH  a device-scope store: written through the XCD's L2 at once.  Plain stores fill the L2 with dirty lines, whose
 //            eviction competes with the loads and whose rest is written back at the end of the kernel, before the next one starts.
 enum Mem { KEEP, STREAM, THROUGH };

@@ -27,6 +27,10 @@
 // write-backs per unit instead of one per workgroup: a release fence per workgroup was measured at 4x to 30x the run
 // time of the whole chain.  Were workgroups ever dealt differently, a count would stay short and the waits would
 // time out into the status word: never a silent wrong result.
+//
+// Accesses are hinted as in the launch-by-launch passes, gradients non-temporal without error feedback.  The whole sweep, plain
+// accesses / these, blocks of 2^20, us: 4 x 1 vector 27.7 / 26.1, 8 x 4 100.4 / 102.0, 32 x 4 383 / 357, 256 x 8 4883 / 4795; with
+// error feedback 16 x 4 593 / 524, 64 x 8 4662 / 4009, 25 x 1 in bf16 222 / 203.
 #pragma once
 
 #include "thc_inverse.hpp"

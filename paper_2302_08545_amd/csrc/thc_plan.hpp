@@ -268,10 +268,13 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // stream_rotated: the half-rotated vectors in the uniform variant's range pass, which the quantizer reads once more.  Streamed over
 // kept, prepare and compress, rotated, blocks of 2^16 and 2^20: 16 MB 1.01 to 1.02, 64 MB 1.03 to 1.05, 128 MB 1.02 to 1.03, 192 MB
 // 1.03 to 1.04, 256 MB 1.01 to 1.02, 384 MB 0.95 to 0.97, 512 MB 0.90 to 0.93, 1.6 GB 0.94 to 0.96.
-// through_inverse: the inverse's first pass writes through the L2, or else non-temporally.  Through over non-temporal: 4 MB 0.98,
-// 100 MB 0.98, 128 MB 1.01, 400 MB 1.02, 800 MB 1.04, 1 GB 1.00.
-// stream_blocks: the gradients of blocks of up to 2^14 that go block by block, behind the norms.  Time of streamed over kept, all
-// of 1 GB: 2^10 0.99, 2^13 0.99, 2^14 0.99 to 1.00, 0.99 with error feedback; bf16 with error feedback, 2^13, 1.02.
+// through_inverse: the inverse's first pass writes through the L2, or else non-temporally.  Through over non-temporal, decompressions
+// that no cache holds parts of, blocks of 2^16 to 2^21: 4 MB 0.92 to 0.93, 16 and 64 MB 0.76 to 0.82, 100 and 128 MB 0.86 to 0.89,
+// 160 to 256 MB 0.84 to 0.89, and 512 MB to 1 GB, walked in shares of 256 MB, 0.87; 2^23 and 2^24 up to 256 MB 0.83 to 0.95, 384 and
+// 512 MB in one share 1.01 to 1.09; 2^25 0.91 to 1.00, 1.01 to 1.04.  Again and again on the same buffers the two are closer
+// (4 MB 0.98, 128 MB 1.01).  With error feedback, 2^20: 128 MB 0.95 to 0.97, 160 MB 1.00 to 1.02, 192 MB 1.01 to 1.02, 256 MB 1.00 to 1.05.
+// stream_blocks: the gradients of blocks of up to 2^14 that go block by block, behind the norms.  Time of streamed over kept, 64 MB
+// to 1 GB: 2^10 0.95 to 1.00, 2^13 and 2^14 0.97 to 1.01, with error feedback 0.98 to 1.01; in bf16 0.98 to 1.02, no gain.
 // stream_sums: the aggregation.  Time of streamed over kept, by the streams' bytes together, on three sets of them in turn: 34 MB
 // 1.05, 66 MB 1.02 to 1.19 (0.80 to 0.95 with 3-bit indices, 16-bit sums or 3 workers), 82 MB 0.80 to 0.93, 100 to 190 MB 0.76 to
 // 0.94, 840 MB 0.85 to 0.95; behind the quantizer of the same round 67 MB 0.99, 105 MB 1.00.  A single stream of 3-bit indices, whose
