@@ -335,11 +335,12 @@ def main():
                                                 "source": f"profiles/all_kernels_{w.name}.txt"}
     if w.name == "c3_vgg16" and default_config:
         # Vector-ALU view of the same sweep: wave64 instructions it issues (rocprofv3 SQ_INSTS_VALU,
-        # profiles/sq_counters_c3_vgg16.txt) against what 1024 SIMDs issue at one instruction per 4 cycles, 2.35 GHz
+        # profiles/sq_counters_c3_vgg16.txt) against what 1024 SIMDs issue at 2.35 GHz and one instruction per 2 cycles, the
+        # rate of binary32 arithmetic on vector registers (profiles/issue_rates_mi355x.txt; most other kinds take 4)
         insts = 4 * (242089984 + 230921728)
         result["alu_roofline"] = {"bound": "alu", "kernel": result["roofline"]["kernel"], "unit": "wave64 instructions/s",
-                                  "achieved": insts / (fwd_ms * 1e-3), "peak": 1024 * 2.35e9 / 4,
-                                  "frac": insts / (fwd_ms * 1e-3) / (1024 * 2.35e9 / 4)}
+                                  "achieved": insts / (fwd_ms * 1e-3), "peak": 1024 * 2.35e9 / 2,
+                                  "frac": insts / (fwd_ms * 1e-3) / (1024 * 2.35e9 / 2)}
     if uniform:
         # Alg. 1 runs other kernels: the figures above that describe Alg. 3's passes do not apply
         for key in ("roofline", "moved_bytes_per_coord", "moved_GBps"):

@@ -63,5 +63,6 @@ def test_counted_traffic_of_the_default_workload_is_read_from_the_tracked_profil
 
 def test_the_largest_kernel_of_the_default_workload_is_read_from_the_tracked_profile():
     name, per_round, avg_us = bench.profiled_kernel("c3_vgg16", "k_fwd_lo")
-    assert name.startswith("k_fwd_lo<13") and per_round == 4 and 500 < avg_us < 1000
+    # the default walk takes groups of 2^27 worker-coordinates, 512 MB read and written each: 128 us at 8 TB/s, 300 at 3.6
+    assert name.startswith("k_fwd_lo<13") and per_round == 8 * 2 ** 28 // 2 ** 27 and 128 < avg_us < 300
     assert bench.profiled_kernel("no_such_workload", "k_fwd_lo") is None
