@@ -249,18 +249,31 @@ template <int R> struct LaunchInvHi {
   }
 };
 
-template <int L1, bool BF16, bool EF, Mem LOAD>
-void launch_fwd_lo_k(const FwdLoArgs& a, bool split, bool norm_only, uint64_t tiles, uint32_t n, hipStream_t s) {
-  const dim3 grid((unsigned)tiles, n);
-  if constexpr (L1 == LOG_TILE) {
-    if (split) {
-      if (norm_only) k_fwd_lo<L1, BF16, EF, true, true, LOAD><<<grid, dim3(NT), 0, s>>>(a);
-      else k_fwd_lo<L1, BF16, EF, true, false, LOAD><<<grid, dim3(NT), 0, s>>>(a);
+template <int L1, bool BF16, bool EF, bool XO, Mem LOAD>
+void launch_fwd_lo_x(const FwdLoArgs& a, bool norm_only, uint64_t tiles, uint32_t n, hipStream_t s) {
+  const dim3 grid((unsigned)tiles, n), blk(NT);
+  if (norm_only) {
+    k_fwd_lo<L1, BF16, EF, XO, true, LOAD, KEEP><<<grid, blk, 0, s>>>(a);
+    return;
+  }
+  if constexpr (LOAD == KEEP) {
+    if (plain_first_pass(tiles, n)) {
+      k_fwd_lo<L1, BF16, EF, XO, false, LOAD, KEEP><<<grid, blk, 0, s>>>(a);
       return;
     }
   }
-  if (norm_only) k_fwd_lo<L1, BF16, EF, false, true, LOAD><<<grid, dim3(NT), 0, s>>>(a);
-  else k_fwd_lo<L1, BF16, EF, false, false, LOAD><<<grid, dim3(NT), 0, s>>>(a);
+  k_fwd_lo<L1, BF16, EF, XO, false, LOAD, THROUGH><<<grid, blk, 0, s>>>(a);
+}
+
+template <int L1, bool BF16, bool EF, Mem LOAD>
+void launch_fwd_lo_k(const FwdLoArgs& a, bool split, bool norm_only, uint64_t tiles, uint32_t n, hipStream_t s) {
+  if constexpr (L1 == LOG_TILE) {
+    if (split) {
+      launch_fwd_lo_x<L1, BF16, EF, true, LOAD>(a, norm_only, tiles, n, s);
+      return;
+    }
+  }
+  launch_fwd_lo_x<L1, BF16, EF, false, LOAD>(a, norm_only, tiles, n, s);
 }
 
 template <int L1, Mem LOAD>

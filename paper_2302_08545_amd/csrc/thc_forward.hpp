@@ -56,8 +56,9 @@ struct alignas(16) SmemLo {
 
 // One tile of the pass: tile index `tile` of vector `worker`; `dst` is where coordinate 0 of that vector's
 // half-rotated image lives (the tile's results go to dst[offset in the vector]).  LOAD: how the vectors are read (stream_inputs,
-// stream_norms); chosen by the launch, since a choice in the kernel took small calls with error feedback 2 to 4 % (13.0 us).
-template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY, Mem LOAD, class A>
+// stream_norms), STORE: how the results are written (plain_first_pass); chosen by the launch, since a choice in the kernel took small
+// calls with error feedback 2 to 4 % (13.0 us).
+template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY, Mem LOAD, Mem STORE, class A>
 __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t worker, float* dst_vec,
                                             SmemLo& sm) {
   static_assert(!XO || L1 == LOG_TILE, "the row-split tile needs blocks of at least 2^16");
@@ -153,7 +154,7 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
   float* dst = dst_vec + off;
   const uint64_t left = a.d - off;   // coordinates of this tile that exist (tail tile of a short vector)
   lds_stages<2, L1, true, PAD>(lds, t, [&](int base, int eoff, float v) {
-    if (!GUARD || (uint64_t)(base + eoff) < left) store_f<THROUGH>(&dst[lo_map<XO>(base) + lo_map<XO>(eoff)], v);
+    if (!GUARD || (uint64_t)(base + eoff) < left) store_f<STORE>(&dst[lo_map<XO>(base) + lo_map<XO>(eoff)], v);
   });
 }
 
@@ -162,10 +163,10 @@ __device__ __forceinline__ void fwd_lo_tile(const A& a, uint32_t tile, uint32_t 
 // One workgroup per tile (grid = (tiles, n workers)): measured on MI355X this streams faster than a
 // persistent grid with software prefetch, the hardware dispatcher keeps four workgroups per CU in flight.
 // NORM_ONLY: stop after the partial sums of squares (the norm exchange of Alg. 3 on its own): same sums, same order.
-template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY, Mem LOAD>
+template <int L1, bool BF16, bool EF, bool XO, bool NORM_ONLY, Mem LOAD, Mem STORE>
 __global__ __launch_bounds__(NT) void k_fwd_lo(const FwdLoArgs a) {
   __shared__ SmemLo sm;
-  fwd_lo_tile<L1, BF16, EF, XO, NORM_ONLY, LOAD>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
+  fwd_lo_tile<L1, BF16, EF, XO, NORM_ONLY, LOAD, STORE>(a, blockIdx.x, blockIdx.y, a.ws_x + (uint64_t)blockIdx.y * a.d, sm);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(NT, 8) void k_pipe_forward(const PipeArgs P) {
       if (!pipe_wait<false>(old, Tu, P.status, &flag)) return;
     }
     const LoView a{P.grads, P.efs, P.partials, P.pstride, P.d, P.j0, P.round, P.k0, P.k1, P.lo_tm};
-    fwd_lo_tile<LOG_TILE, BF16, EF, true, false, EF ? KEEP : STREAM>(a, gt, w, vec, *reinterpret_cast<SmemLo*>(raw));
+    fwd_lo_tile<LOG_TILE, BF16, EF, true, false, EF ? KEEP : STREAM, THROUGH>(a, gt, w, vec, *reinterpret_cast<SmemLo*>(raw));
     pipe_publish(us, 0, Tu >> 3);
   } else if (phase == 1) {
     if (!pipe_wait<true>(us + SYNC_READY * SYNC_STRIDE, 1u, P.status, &flag)) return;

@@ -268,6 +268,9 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 // stream_rotated: the half-rotated vectors in the uniform variant's range pass, which the quantizer reads once more.  Streamed over
 // kept, prepare and compress, rotated, blocks of 2^16 and 2^20: 16 MB 1.01 to 1.02, 64 MB 1.03 to 1.05, 128 MB 1.02 to 1.03, 192 MB
 // 1.03 to 1.04, 256 MB 1.01 to 1.02, 384 MB 0.95 to 0.97, 512 MB 0.90 to 0.93, 1.6 GB 0.94 to 0.96.
+// plain_first_pass: the forward first pass stores plainly, or else through the L2.  Where a few workgroups write, there is no
+// eviction to spare, and a launch ends later.  Through over plain, thc_compress_all, by workgroups of 8192 coordinates: 4 1.00 to
+// 1.01, 16 to 24 1.01 to 1.03, 64 0.99, 84 1.00 to 1.02, 128 0.93 to 1.00, 512 0.92 to 0.94.
 // through_inverse: the inverse's first pass writes through the L2, or else non-temporally.  Through over non-temporal, decompressions
 // that no cache holds parts of, blocks of 2^16 to 2^21: 4 MB 0.92 to 0.93, 16 and 64 MB 0.76 to 0.82, 100 and 128 MB 0.86 to 0.89,
 // 160 to 256 MB 0.84 to 0.89, and 512 MB to 1 GB, walked in shares of 256 MB, 0.87; 2^23 and 2^24 up to 256 MB 0.83 to 0.95, 384 and
@@ -292,6 +295,7 @@ inline bool last_first(const Plan& pl, uint64_t len, uint32_t W, bool ef, bool b
 //   2^22                          1.00           0.90 to 1.00   0.90 (48), 0.98 (64), 1.05 (96)  1.14  1.20   1.11 to 1.15   1.00 to 1.10
 //   2^23, 2^24                                   1.00           0.92 to 0.96   0.91 to 0.93  0.90 to 0.97  0.90 to 1.00  0.97 to 1.06
 //   no rotation    0.94 to 1.01   0.94           0.92 to 0.94   0.92 to 0.96   0.92     0.99           1.02 to 1.04    1.04
+// Blocks of 2^15, whose one workgroup a block writes all of an estimate of 0.1 to 1 MB, 0.98 to 0.99; 2^10 to 2^14 0.99 to 1.01.
 // The decompression by itself gains by the hint at every size above 4 MB (2^10 x 2^15, 128 MB, 30 us against 37): what it gains
 // below 160 MB, the reader loses and more.
 constexpr uint64_t MB = 1ull << 20;
@@ -305,6 +309,7 @@ inline bool stream_norms(const Plan& pl, uint64_t len, uint32_t W, bool bf16, bo
   return input_bytes(len, W, bf16, ef) >= (pl.L > 14 ? 128 : 64) * MB;
 }
 inline bool stream_blocks(uint64_t len, uint32_t W, bool bf16) { return !bf16 && input_bytes(len, W, bf16, false) >= 64 * MB; }
+inline bool plain_first_pass(uint64_t tiles, uint32_t W) { return tiles * W < 64; }
 inline bool stream_rotated(uint64_t len, uint32_t W) { return W * len * 4 > 256 * MB; }
 inline bool through_inverse(uint64_t len, uint32_t W) { return W * len * 4 <= 256 * MB; }
 inline bool stream_sums(uint64_t d, uint32_t n, uint32_t b) { return n * (d / 8) * b >= 80 * MB && (n > 1 || b == 1 || b > 3); }
@@ -312,7 +317,9 @@ inline bool sums_four_loads(uint64_t d) { return d <= 10 * MB; }   // coordinate
 
 inline bool stream_minmax(uint64_t len, uint32_t W, bool bf16, bool ef) { return input_bytes(len, W, bf16, ef) >= 240 * MB; }
 
-inline bool keep_estimate(uint64_t d, int L) { return 4 * d > 16 * MB && 4 * d <= (L == 22 ? 80 : 160) * MB; }
+inline bool keep_estimate(uint64_t d, int L) {
+  return (L == 15 && 4 * d <= MB) || (4 * d > 16 * MB && 4 * d <= (L == 22 ? 80 : 160) * MB);
+}
 inline bool keep_plain_estimate(uint64_t d) { return 4 * d > 4 * MB && 4 * d <= 160 * MB; }   // uniform variant without rotation
 
 // Uniform quantizer on a vector of d coordinates: one group of eight coordinates to a thread, 4096 to a workgroup, or two.

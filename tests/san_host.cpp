@@ -257,6 +257,7 @@ static int check_keep_estimate() {
   int bad = 0;
   for (int L = 10; L <= 25; ++L) {
     const uint64_t most = (L == 22 ? 80 : 160) * MB / 4;
+    bad += keep_estimate(MB / 4, L) != (L == 15) || keep_estimate(MB / 4 + 1024, L);
     bad += keep_estimate(4 * MB, L) || !keep_estimate(4 * MB + 1024, L) || !keep_estimate(most, L) || keep_estimate(most + 1024, L);
   }
   return bad + keep_plain_estimate(MB) + !keep_plain_estimate(MB + 1024) + !keep_plain_estimate(40 * MB) +
@@ -292,6 +293,7 @@ static int check_hints() {
       bad += stream_sums(d - 1024, W, b) || stream_sums(d + 1024, W, b) == (W == 1 && b == 3);
     }
   }
+  bad += !plain_first_pass(63, 1) + plain_first_pass(64, 1) + !plain_first_pass(7, 9) + plain_first_pass(8, 8);
   return bad + stream_sums(80 * MB * 4 + 1024, 1, 2) + !stream_sums(40 * MB * 4 + 1024, 2, 2) + !sums_four_loads(10 * MB) +
          sums_four_loads(10 * MB + 1024);
 }
